@@ -26,6 +26,7 @@ SOURCES = [
     "attention_splitk.hip",
     "merge_states.hip",
     "rmsnorm_gemm.hip",
+    "rmsnorm_gemm_rows.hip",
     "diag.hip",
 ]
 

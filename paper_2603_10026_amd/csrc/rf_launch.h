@@ -52,6 +52,12 @@ hipError_t launch_rmsnorm_gemm_bf16(const void* x, const void* g, const void* w,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy,
                                     float eps, hipStream_t s);
 
+// The same for few rows, 16-byte aligned rows of y, w within 4 GiB (the launcher above chooses).
+bool rmsnorm_gemm_rows_fits(int K, int64_t ldw);
+hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w, void* y, int M,
+                                    int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
+                                    hipStream_t s);
+
 // Rows of length n (pitch in elements); mean, var: one float per row.
 hipError_t launch_variance(const void* x, bool is_bf16, float* mean, float* var, int64_t rows,
                            int64_t n, int64_t x_pitch, bool vec_ok, hipStream_t s);

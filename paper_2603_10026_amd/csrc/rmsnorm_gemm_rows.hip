@@ -1,0 +1,238 @@
+// RMSNorm + linear for few rows (the tokens of a decode step): the "sum + sum" cascade of
+// rmsnorm_gemm.hip, cut for launches whose time is the trip of w from memory.
+//
+// A 128 x 512 tile of the large kernel leaves all but N / 512 compute units idle here.  This
+// kernel cuts the output into 16 MT x 16 C tiles (C columns of w per lane) and gives every
+// workgroup the whole contraction axis, split over its 4 wavefronts by interleaved 64-k steps:
+// no LDS, no barrier and no shared state until the wavefronts' sums are added at the end.
+//
+//   Y^T = W^T X^T      A = W^T, B = X^T (16x16x32 bf16 MFMA)
+//
+// A lane loads C neighbouring columns of 8 rows of w, which after pairing rows in registers is
+// the A operand of C MFMAs; the row of x is the B operand as it lies in memory.  g is applied
+// on the w side (round(w g) instead of round(x g), one bf16 rounding either way): a workgroup
+// holds 16 C columns of w but may hold more rows of x, and the w values are unpacked for the
+// pairing anyway.  ss is the diagonal of X X^T, taken by the matrix pipe from the operand that
+// is in registers already.
+//
+// What bounds it: the 128-byte lines a compute unit can have on their way.  A read of w alone in
+// this pattern takes 15.9 us (4096 x 4096 from HBM, C = 2, 128 workgroups), 17.7 us with whole
+// lines and half the workgroups (C = 4), and cache-policy bits change nothing; the last 50 GB/s
+// per compute unit are its 32 KB of L1 lines in flight over the memory latency.  Two steps in
+// flight and 4 wavefronts are therefore faster than 8 wavefronts with more (which evict each
+// other's lines): 48 x 4096 x 4096 takes 17.3 us against 20.1, and 90.8 us in 128 x 512 tiles.
+#include <math.h>
+
+#include "rf_device.h"
+#include "rf_launch.h"
+
+namespace rf {
+
+namespace {
+constexpr int kRWaves = 4;
+constexpr int kRThreads = kRWaves * kWave;
+}  // namespace
+
+// P: steps of 32 k in flight per wavefront
+template <int MT, int C, int P>
+__global__ __launch_bounds__(kRThreads) void rmsnorm_gemm_rows_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ g, const bf16_t* __restrict__ w,
+    bf16_t* __restrict__ y, int M, int K, int N, int64_t ldx, int64_t ldw, int64_t ldy,
+    float inv_k, float eps, int n_mtiles) {
+  constexpr int CD = C / 2;  // 32-bit words of w per lane and k-row
+  __shared__ f32x4 s_acc[kRWaves][C * MT][kWave];
+  __shared__ float s_ss[kRWaves][16 * MT];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15;
+  const int g4 = lane >> 4;
+
+  // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  The row tiles of a
+  // column tile, and the column tiles that share the 128-byte lines of w, go to one XCD; these
+  // groups are dealt round-robin, so that every XCD reads all over a row of w.
+  constexpr int GC = C >= 4 ? 1 : 4 / C;  // column tiles per 128-byte line
+  const int unit = GC * n_mtiles;
+  const int j = blockIdx.x >> 3;
+  const int mt = __builtin_amdgcn_readfirstlane(j % unit % n_mtiles);
+  const int nt = __builtin_amdgcn_readfirstlane((j / unit * 8 + (blockIdx.x & 7)) * GC + j % unit / n_mtiles);
+  const int m0 = mt * 16 * MT, n0 = nt * 16 * C;
+  if (n0 >= N) return;
+
+  const int mine = 2 * ((K / 64 - wave + kRWaves - 1) / kRWaves);  // 32-k steps of this wavefront, in pairs
+
+  // Buffer loads: a scalar byte offset per (step, row) and one loop-invariant lane offset, so the
+  // loop has no vector address arithmetic.  Columns past N re-read the last ones and are not stored.
+  const auto wrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(w), 0, 0xffffffffu, 0x00020000);
+  const auto xrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(x + (int64_t)m0 * ldx), 0, 0xffffffffu, 0x00020000);
+  const auto grs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(g), 0, 0xffffffffu, 0x00020000);
+  const uint32_t ldw2 = (uint32_t)ldw * 2;
+  const uint32_t w_lane = 8 * g4 * ldw2 + min(n0 + C * i16, N - C) * 2;
+  uint32_t x_lane[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+    x_lane[t] = (uint32_t)(min(m0 + 16 * t + i16, M - 1) - m0) * (uint32_t)(ldx * 2) + 16 * g4;
+
+  uint32_t wr[P][8][CD];
+  u32x4 xr[P][MT], gr[P];
+  auto load = [&](int p, int i) {
+    const int ii = min(i, mine - 1);
+    const uint32_t k0 = (wave + kRWaves * (ii >> 1)) * 64 + (ii & 1) * 32;
+    const uint32_t wo = k0 * ldw2;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (CD == 1) {
+        wr[p][e][0] = __builtin_amdgcn_raw_buffer_load_b32(wrs, w_lane, wo + e * ldw2, 0);
+      } else {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(wrs, w_lane, wo + e * ldw2, 0);
+#pragma unroll
+        for (int d = 0; d < CD; ++d) wr[p][e][d] = v[d];
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t) xr[p][t] = __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane[t], k0 * 2, 0);
+    gr[p] = __builtin_amdgcn_raw_buffer_load_b128(grs, 16 * g4, k0 * 2, 0);
+  };
+
+  f32x4 acc[C][MT], sq[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    sq[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  auto step = [&](int p) {
+    u32x4 af[C];
+#pragma unroll
+    for (int e2 = 0; e2 < 4; ++e2) {
+      const float g0 = bf16_lo(gr[p][e2]), g1 = bf16_hi(gr[p][e2]);
+#pragma unroll
+      for (int d = 0; d < CD; ++d) {
+        const uint32_t r0 = wr[p][2 * e2][d], r1 = wr[p][2 * e2 + 1][d];
+        af[2 * d][e2] = pack_bf16(bf16_lo(r0) * g0, bf16_lo(r1) * g1);
+        af[2 * d + 1][e2] = pack_bf16(bf16_hi(r0) * g0, bf16_hi(r1) * g1);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const bf16x8 b = __builtin_bit_cast(bf16x8, xr[p][t]);
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[c]), b, acc[c][t], 0, 0, 0);
+      sq[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, b, sq[t], 0, 0, 0);
+    }
+  };
+
+  if (mine > 0) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      load(p, p);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    int i = 0;
+    for (; i + P <= mine; i += P) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        step(p);
+        load(p, i + P + p);
+        __builtin_amdgcn_sched_barrier(0);  // (keeps the requests in the order they are waited for)
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      if (i + p < mine) step(p);
+  }
+
+  // ---- add the wavefronts' sums ----
+  // acc[c][t] of lane (i16, g4), element r: row m0 + 16 t + i16, column n0 + C (4 g4 + r) + c
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) s_acc[wave][c * MT + t][lane] = acc[c][t];
+  if ((i16 >> 2) == g4) {  // this lane holds the diagonal element of row i16
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const f32x4 s = sq[t];
+      const int r = i16 & 3;
+      s_ss[wave][16 * t + i16] = r == 0 ? s[0] : r == 1 ? s[1] : r == 2 ? s[2] : s[3];
+    }
+  }
+  __syncthreads();
+  for (int idx = tid; idx < MT * kWave; idx += kRThreads) {
+    const int t = idx >> 6, l = idx & 63;
+    float ss = 0.f;
+#pragma unroll
+    for (int wv = 0; wv < kRWaves; ++wv) ss += s_ss[wv][16 * t + (l & 15)];
+    const float rs = 1.0f / sqrtf(ss * inv_k + eps);
+    const int m = m0 + 16 * t + (l & 15);
+    const int n = n0 + 4 * C * (l >> 4);
+    float out[4][C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      f32x4 v = s_acc[0][c * MT + t][l];
+#pragma unroll
+      for (int wv = 1; wv < kRWaves; ++wv) v += s_acc[wv][c * MT + t][l];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) out[r][c] = v[r] * rs;
+    }
+    if (m < M) {
+#pragma unroll
+      for (int h = 0; h < C / 2; ++h) {  // 8 columns at a time (N is a multiple of 8)
+        u32x4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int q = 8 * h + 2 * j;
+          o[j] = pack_bf16(out[q / C][q % C], out[(q + 1) / C][(q + 1) % C]);
+        }
+        if (n + 8 * h < N) *reinterpret_cast<u32x4*>(y + (int64_t)m * ldy + n + 8 * h) = o;
+      }
+    }
+  }
+}
+
+namespace {
+struct RowsShape { int mt, c; };
+constexpr RowsShape kRowsShapes[] = {{1, 2}, {2, 2}, {1, 4}, {2, 4}, {4, 4}};
+inline int64_t rows_tiles(const RowsShape& r, int64_t M, int64_t N) {
+  return ((M + 16 * r.mt - 1) / (16 * r.mt)) * ((N + 16 * r.c - 1) / (16 * r.c));
+}
+// What a tile shape costs, in cache-line bytes per k and compute unit: a workgroup takes 128
+// bytes of w (half of each line unused at C = 2) and 2 bytes per row of x through its L1, whose
+// 32 KB bound what it has in flight; a launch of more than 256 workgroups takes turns, one of
+// fewer leaves compute units idle, which costs less than in proportion because the rest then
+// share the memory.  Orders the measured times of all five shapes on 4096 x 4096 (1 to 128 rows)
+// and 8192 x 8192 (7 and 100 rows) right to within 5 %.
+inline double rows_cost(const RowsShape& r, int64_t M, int64_t N) {
+  const double wg = (double)rows_tiles(r, M, N);
+  const double idle = wg < 256 ? 1.0 + 0.1 * log2(256.0 / wg) : wg / 256.0;
+  return idle * (128 + 32 * r.mt);
+}
+}  // namespace
+
+// (the buffer loads take 32-bit byte offsets inside w)
+bool rmsnorm_gemm_rows_fits(int K, int64_t ldw) { return (int64_t)K * ldw * 2 < ((int64_t)1 << 32); }
+
+hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w, void* y, int M,
+                                    int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
+                                    hipStream_t s) {
+  if (!rmsnorm_gemm_rows_fits(K, ldw)) return hipErrorInvalidValue;
+  RowsShape best = kRowsShapes[0];
+  for (const RowsShape& r : kRowsShapes)
+    if (rows_cost(r, M, N) < rows_cost(best, M, N)) best = r;
+  const int n_mt = (M + 16 * best.mt - 1) / (16 * best.mt);
+  const int group_cols = 64;  // columns of one 128-byte line: one tile at C = 4, two at C = 2
+  const int64_t groups = ((int64_t)N + group_cols - 1) / group_cols;
+  const int64_t grid = (groups + 7) / 8 * 8 * (group_cols / (16 * best.c)) * n_mt;
+  if (grid > INT32_MAX) return hipErrorInvalidValue;
+#define RF_ROWS(MT, C, P)                                                                            \
+  if (best.mt == MT && best.c == C)                                                                  \
+    hipLaunchKernelGGL((rmsnorm_gemm_rows_kernel<MT, C, P>), dim3((unsigned)grid), dim3(kRThreads), 0, s, \
+                       (const bf16_t*)x, (const bf16_t*)g, (const bf16_t*)w, (bf16_t*)y, M, K, N, ldx, ldw, \
+                       ldy, 1.0f / (float)K, eps, n_mt);
+  RF_ROWS(1, 2, 4) RF_ROWS(2, 2, 2) RF_ROWS(1, 4, 2) RF_ROWS(2, 4, 2) RF_ROWS(4, 4, 2)
+#undef RF_ROWS
+  return hipGetLastError();
+}
+
+}  // namespace rf

@@ -1,0 +1,32 @@
+"""RMSNorm + linear at few rows: the tiles of rmsnorm_gemm_rows.hip against the fp64 oracle at the
+edges of its row tiles (16, 32, 64), of its column tiles (32, 64, groups of 64 columns over 8 XCDs),
+at contraction axes that leave some of the 4 wavefronts without a step, and at the row count where
+the large tiles take over."""
+import sys
+
+import pytest
+import torch
+
+from oracle import rf_oracle as O
+from paper_2603_10026_amd import inputs as I
+
+sys.path.insert(0, __file__.rsplit("/", 1)[0])
+from test_gpu_parity import DEV, check, rf, say  # noqa: E402,F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,K,N", [
+    (1, 64, 8), (1, 64, 520), (2, 128, 32), (15, 192, 40), (16, 256, 64), (17, 320, 72), (31, 448, 1032), (33, 576, 4096),
+    (47, 64 * 9, 8 * 67), (64, 512, 2048), (65, 512, 2056), (100, 1088, 4096), (128, 256, 8200), (129, 640, 4104),
+    (256, 192, 1000), (257, 192, 1000),
+])
+def test_rmsnorm_gemm_few_rows(rf, M, K, N):  # noqa: F811
+    say(f"rmsnorm_gemm few rows M{M} K{K} N{N}")
+    x, g, w = I.rmsnorm_gemm_inputs(I.SEED_BASE + 50 + M, M, K, N)
+    tx, tg, tw = (I.to_torch(a, "bf16", DEV) for a in (x, g, w))
+    y = torch.full((M, N + 16), float("nan"), dtype=torch.bfloat16, device=DEV)
+    rf.rf_rmsnorm_gemm(tx, tg, tw, eps=1e-6, y=y[:, 8:N + 8])
+    torch.cuda.synchronize()
+    check(y[:, 8:N + 8], O.rmsnorm_gemm(x, g, w, 1e-6), "bf16", "rmsnorm_gemm few rows")
+    assert bool(torch.isnan(y[:, :8]).all()) and bool(torch.isnan(y[:, N + 8:]).all())
