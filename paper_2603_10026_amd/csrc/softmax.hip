@@ -7,7 +7,10 @@
 // DPP; the normalised row is written once with 128-bit stores.  HBM traffic is
 // the algorithmic minimum (one read + one write).
 //
-// Kernel 2 (any row length / alignment): one workgroup streams a row, every
+// Rows that start at any element or hold no whole number of vectors take the same kernels with
+// unaligned vectors (below).
+//
+// Kernel 2 (rows too long for the registers of a workgroup): one workgroup streams a row, every
 // lane carrying the level-1 incremental state (m, l) (Appendix A.2,
 // incremental form), corrected once per 128-bit vector; lane states are merged
 // with the level-k fused expression (Section 3.2 Eq. (11)) across the wavefront
@@ -22,6 +25,54 @@ namespace rf {
 
 constexpr int kSoftmaxWavesPerWg = 4;
 
+namespace {
+
+// Rows that start anywhere (natural element alignment) and hold any number n >= V of elements,
+// in 16-byte vectors all the same: vector idx covers elements idx V .. idx V + V - 1, and the one
+// that would reach past the end is moved back to the last V elements, where it repeats up to V - 1
+// elements of its neighbour.  A repeated element does not change a maximum and is stored twice
+// with the same value; only the sum has to leave it out.  Vectors past the end sit in the same
+// place and contribute nothing.  (The hardware takes 16-byte accesses at any address; a wavefront's
+// 1 KB then touches nine 128-byte lines instead of eight.)  256 rows of 50001 fp32 values take
+// 22 us where element-wise accesses and two sweeps took 136; 4096 rows of 4095 bf16 values 13.6
+// where they took 36.5 (4096 rows of 4096: 12.0).
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+template <typename T>
+__device__ __forceinline__ u32x4 ragged_load(const T* row, int idx, int n) {
+  constexpr int V = Elem<T>::kPerVec;
+  return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(row + min(idx * V, n - V)));
+}
+template <typename T>
+__device__ __forceinline__ void ragged_store(T* row, int idx, int n, const u32x4& v) {
+  constexpr int V = Elem<T>::kPerVec;
+  __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any*>(row + min(idx * V, n - V)));
+}
+// Exponentials of a vector, in place; returns s + their sum.
+template <int V>
+__device__ __forceinline__ float exp_sum(float s, float* e, float mb) {
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    e[i] = fast_exp2(fmaf(e[i], kLog2e, mb));
+    s += e[i];
+  }
+  return s;
+}
+// whole: wave-uniform, no lane's vector reaches past the end
+template <int V>
+__device__ __forceinline__ float ragged_exp_sum(float s, float* e, float mb, int idx, int n, bool whole) {
+  if (whole) return exp_sum<V>(s, e, mb);
+  const int first = idx * V - min(idx * V, n - V);  // elements below it are the neighbour's (V or more: none is ours)
+#pragma unroll
+  for (int i = 0; i < V; ++i) {
+    e[i] = fast_exp2(fmaf(e[i], kLog2e, mb));
+    s += i >= first ? e[i] : 0.f;
+  }
+  return s;
+}
+
+}  // namespace
+
 // One wavefront per row; NCH 128-bit chunks per lane; n % kPerVec == 0.
 // LANE_LEVEL = false (the shipped path): the two reductions are fused at wavefront level,
 // the row max is known before the sum starts, nothing is ever corrected.
@@ -35,7 +86,7 @@ constexpr int softmax_waves_per_simd(int floats_per_lane) {
   return floats_per_lane <= 32 ? 8 : floats_per_lane <= 64 ? 4 : 2;
 }
 
-template <typename T, int NCH, bool LANE_LEVEL = false>
+template <typename T, int NCH, bool RAGGED, bool LANE_LEVEL = false>
 __global__ __launch_bounds__(kSoftmaxWavesPerWg * kWave,
                              softmax_waves_per_simd(NCH * Elem<T>::kPerVec) * 4 / kSoftmaxWavesPerWg)
 void softmax_row_in_regs_kernel(
@@ -47,7 +98,7 @@ void softmax_row_in_regs_kernel(
   if (row >= rows) return;
   const u32x4* xr = reinterpret_cast<const u32x4*>(x + row * x_pitch);
   u32x4* yr = reinterpret_cast<u32x4*>(y + row * y_pitch);
-  const int nvec = n / V;
+  const int nvec = RAGGED ? (n + V - 1) / V : n / V;
 
   // Straight-line code: vectors past the end of the row are loaded from the last valid
   // vector and replaced by -inf (the identity of the max stage; exp gives 0 for the sum
@@ -62,6 +113,10 @@ void softmax_row_in_regs_kernel(
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int idx = c * kWave + lane;
+    if constexpr (RAGGED) {
+      Elem<T>::unpack(ragged_load(x + row * x_pitch, idx, n), e[c]);
+      continue;
+    }
     const bool full = (c + 1) * kWave <= nvec;  // wave-uniform
     u32x4 r = __builtin_nontemporal_load(full ? xl + c * kWave : xt);
     const bool ok = idx < nvec;
@@ -103,11 +158,8 @@ void softmax_row_in_regs_kernel(
     const float mb = -m * kLog2e;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-#pragma unroll
-      for (int i = 0; i < V; ++i) {
-        e[c][i] = fast_exp2(fmaf(e[c][i], kLog2e, mb));
-        l += e[c][i];
-      }
+      if constexpr (RAGGED) l = ragged_exp_sum<V>(l, e[c], mb, c * kWave + lane, n, (c + 1) * kWave * V <= n);
+      else l = exp_sum<V>(l, e[c], mb);
       __builtin_amdgcn_sched_barrier(0);  // one vector at a time: no extra live temporaries
     }
     l = wave_sum(l);
@@ -120,7 +172,8 @@ void softmax_row_in_regs_kernel(
       float f[V];
 #pragma unroll
       for (int i = 0; i < V; ++i) f[i] = e[c][i] * inv;
-      __builtin_nontemporal_store(Elem<T>::pack(f), yr + idx);
+      if constexpr (RAGGED) ragged_store(y + row * y_pitch, idx, n, Elem<T>::pack(f));
+      else __builtin_nontemporal_store(Elem<T>::pack(f), yr + idx);
     }
   }
 }
@@ -128,7 +181,7 @@ void softmax_row_in_regs_kernel(
 // Short rows (at most LPR vectors of 16 bytes): 64 / LPR rows per wavefront, one vector per
 // lane, the two reductions over the LPR lanes of a row by butterfly shuffles.  A wavefront per
 // row would leave most lanes (and most of every 128-byte line fetched) idle.
-template <typename T, int LPR>
+template <typename T, int LPR, bool RAGGED>
 __global__ __launch_bounds__(kSoftmaxWavesPerWg * kWave) void softmax_short_rows_kernel(
     const T* __restrict__ x, T* __restrict__ y, int64_t rows, int n, int64_t x_pitch,
     int64_t y_pitch) {
@@ -138,13 +191,18 @@ __global__ __launch_bounds__(kSoftmaxWavesPerWg * kWave) void softmax_short_rows
   const int lane = threadIdx.x & (kWave - 1);
   const int sub = lane % LPR;       // vector index inside the row
   const int64_t row = ((int64_t)blockIdx.x * kSoftmaxWavesPerWg + (threadIdx.x >> 6)) * RPW + lane / LPR;
-  const int nvec = n / V;
+  const int nvec = RAGGED ? (n + V - 1) / V : n / V;
   const bool ok = row < rows && sub < nvec;
-  // lanes without a vector read a valid address (their own row's first vector, or row 0's)
-  const u32x4* src = reinterpret_cast<const u32x4*>(x + (row < rows ? row : 0) * x_pitch) + (sub < nvec ? sub : 0);
-  u32x4 r = __builtin_nontemporal_load(src);
+  u32x4 r;
+  if constexpr (RAGGED) {
+    r = ragged_load(x + (row < rows ? row : 0) * x_pitch, sub, n);
+  } else {
+    // lanes without a vector read a valid address (their own row's first vector, or row 0's)
+    const u32x4* src = reinterpret_cast<const u32x4*>(x + (row < rows ? row : 0) * x_pitch) + (sub < nvec ? sub : 0);
+    r = __builtin_nontemporal_load(src);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) r[j] = ok ? r[j] : kNegInf;
+    for (int j = 0; j < 4; ++j) r[j] = ok ? r[j] : kNegInf;
+  }
   float e[V];
   Elem<T>::unpack(r, e);
   float m = e[0];
@@ -153,24 +211,22 @@ __global__ __launch_bounds__(kSoftmaxWavesPerWg * kWave) void softmax_short_rows
 #pragma unroll
   for (int off = LPR / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
   const float mb = -m * kLog2e;
-  float l = 0.f;
-#pragma unroll
-  for (int i = 0; i < V; ++i) {
-    e[i] = fast_exp2(fmaf(e[i], kLog2e, mb));
-    l += e[i];
-  }
+  float l = RAGGED ? ragged_exp_sum<V>(0.f, e, mb, sub, n, false) : exp_sum<V>(0.f, e, mb);
 #pragma unroll
   for (int off = LPR / 2; off > 0; off >>= 1) l += __shfl_xor(l, off, kWave);
   const float inv = 1.0f / l;
 #pragma unroll
   for (int i = 0; i < V; ++i) e[i] *= inv;
-  if (ok) __builtin_nontemporal_store(Elem<T>::pack(e), reinterpret_cast<u32x4*>(y + row * y_pitch) + sub);
+  if (ok) {
+    if constexpr (RAGGED) ragged_store(y + row * y_pitch, sub, n, Elem<T>::pack(e));
+    else __builtin_nontemporal_store(Elem<T>::pack(e), reinterpret_cast<u32x4*>(y + row * y_pitch) + sub);
+  }
 }
 
 // Long rows that still fit the registers of one workgroup (up to WAVES * 64 lanes * 64 values):
 // one workgroup per row, the row read once and kept as fp32; the two reductions go through
 // the wavefronts' DPP reductions and one LDS exchange each.
-template <typename T, int NCH, int WAVES>
+template <typename T, int NCH, int WAVES, bool RAGGED>
 __global__ __launch_bounds__(WAVES * kWave) void softmax_row_in_regs_wg_kernel(
     const T* __restrict__ x, T* __restrict__ y, int64_t rows, int n, int64_t x_pitch,
     int64_t y_pitch) {
@@ -182,11 +238,15 @@ __global__ __launch_bounds__(WAVES * kWave) void softmax_row_in_regs_wg_kernel(
   const int64_t row = blockIdx.x;
   const u32x4* xr = reinterpret_cast<const u32x4*>(x + row * x_pitch);
   u32x4* yr = reinterpret_cast<u32x4*>(y + row * y_pitch);
-  const int nvec = n / V;
+  const int nvec = RAGGED ? (n + V - 1) / V : n / V;
   float e[NCH][V];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int idx = c * TH + tid;
+    if constexpr (RAGGED) {
+      Elem<T>::unpack(ragged_load(x + row * x_pitch, idx, n), e[c]);
+      continue;
+    }
     u32x4 r = __builtin_nontemporal_load(xr + min(idx, nvec - 1));
     const bool ok = idx < nvec;
 #pragma unroll
@@ -209,11 +269,8 @@ __global__ __launch_bounds__(WAVES * kWave) void softmax_row_in_regs_wg_kernel(
   float l = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      e[c][i] = fast_exp2(fmaf(e[c][i], kLog2e, mb));
-      l += e[c][i];
-    }
+    if constexpr (RAGGED) l = ragged_exp_sum<V>(l, e[c], mb, c * TH + tid, n, (c + 1) * TH * V <= n);
+    else l = exp_sum<V>(l, e[c], mb);
   }
   l = wave_sum(l);
   if ((tid & (kWave - 1)) == 0) s_sum[tid >> 6] = l;
@@ -229,17 +286,18 @@ __global__ __launch_bounds__(WAVES * kWave) void softmax_row_in_regs_wg_kernel(
       float f[V];
 #pragma unroll
       for (int i = 0; i < V; ++i) f[i] = e[c][i] * inv;
-      __builtin_nontemporal_store(Elem<T>::pack(f), yr + idx);
+      if constexpr (RAGGED) ragged_store(y + row * y_pitch, idx, n, Elem<T>::pack(f));
+      else __builtin_nontemporal_store(Elem<T>::pack(f), yr + idx);
     }
   }
 }
 
 // One workgroup per row, any n; two sweeps over the row (the second one is served by the
-// L2 for rows of a few hundred KB).  VEC: rows are 16-byte aligned, so both sweeps use
-// 128-bit accesses and the incremental state is corrected once per vector; otherwise
-// scalar accesses, one correction per element.
+// L2 for rows of a few hundred KB).  Both sweeps use 128-bit accesses, at any alignment, and the
+// incremental state is corrected once per vector; what is left of the row after the last whole
+// vector is taken element by element.
 constexpr int kStreamThreads = 256;
-template <typename T, bool VEC>
+template <typename T>
 __global__ __launch_bounds__(kStreamThreads) void softmax_row_streaming_kernel(
     const T* __restrict__ x, T* __restrict__ y, int64_t rows, int64_t n, int64_t x_pitch,
     int64_t y_pitch) {
@@ -250,11 +308,11 @@ __global__ __launch_bounds__(kStreamThreads) void softmax_row_streaming_kernel(
   if (row >= rows) return;
   const T* xr = x + row * x_pitch;
   T* yr = y + row * y_pitch;
-  const int64_t nvec = VEC ? n / V : 0;   // full vectors; the rest is handled element-wise
+  const int64_t nvec = n / V;   // full vectors; the rest is handled element-wise
   // level-1 incremental state per lane
   float m = -INFINITY, l = 0.f;
-  if constexpr (VEC) {
-    const u32x4* xv = reinterpret_cast<const u32x4*>(xr);
+  {
+    const u32x4_any* xv = reinterpret_cast<const u32x4_any*>(xr);
     for (int64_t j = threadIdx.x; j < nvec; j += kStreamThreads) {
       float f[V];
       Elem<T>::unpack(xv[j], f);
@@ -292,9 +350,9 @@ __global__ __launch_bounds__(kStreamThreads) void softmax_row_streaming_kernel(
     lg += (sm[w] == -INFINITY) ? 0.f : sl[w] * fast_exp2((sm[w] - mg) * kLog2e);
   const float inv = 1.0f / lg;
   const float mb = -mg * kLog2e;
-  if constexpr (VEC) {
-    const u32x4* xv = reinterpret_cast<const u32x4*>(xr);
-    u32x4* yv = reinterpret_cast<u32x4*>(yr);
+  {
+    const u32x4_any* xv = reinterpret_cast<const u32x4_any*>(xr);
+    u32x4_any* yv = reinterpret_cast<u32x4_any*>(yr);
     for (int64_t j = threadIdx.x; j < nvec; j += kStreamThreads) {
       float f[V];
       Elem<T>::unpack(xv[j], f);
@@ -309,57 +367,65 @@ __global__ __launch_bounds__(kStreamThreads) void softmax_row_streaming_kernel(
   }
 }
 
-template <typename T>
+// RAGGED: rows that do not start on 16 bytes or do not hold a whole number of vectors.
+template <typename T, bool RAGGED>
 static hipError_t launch_softmax_t(const T* x, T* y, int64_t rows, int64_t n, int64_t x_pitch,
-                                   int64_t y_pitch, bool vec_ok, hipStream_t s) {
+                                   int64_t y_pitch, hipStream_t s) {
   constexpr int V = Elem<T>::kPerVec;
   const int64_t per_chunk = (int64_t)V * kWave;
-  if (vec_ok && n % V == 0 && n > 0 && n <= 32 * V) {
+  if (n >= V && n <= 32 * V) {
     // short rows: 2, 4, 8 or 16 rows per wavefront
-    const int nvec = (int)(n / V);
+    const int nvec = (int)((n + V - 1) / V);
     const int lpr = nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : 32;
     const int64_t rows_per_wg = (int64_t)kSoftmaxWavesPerWg * (kWave / lpr);
     const unsigned grid = (unsigned)((rows + rows_per_wg - 1) / rows_per_wg);
     const dim3 block(kSoftmaxWavesPerWg * kWave);
 #define RF_SOFTMAX_SHORT(L)                                                               \
-  hipLaunchKernelGGL((softmax_short_rows_kernel<T, L>), dim3(grid), block, 0, s, x, y, rows, \
+  hipLaunchKernelGGL((softmax_short_rows_kernel<T, L, RAGGED>), dim3(grid), block, 0, s, x, y, rows, \
                      (int)n, x_pitch, y_pitch)
     if (lpr == 4) RF_SOFTMAX_SHORT(4);
     else if (lpr == 8) RF_SOFTMAX_SHORT(8);
     else if (lpr == 16) RF_SOFTMAX_SHORT(16);
     else RF_SOFTMAX_SHORT(32);
 #undef RF_SOFTMAX_SHORT
-  } else if (vec_ok && n % V == 0 && n <= (64 / V) * per_chunk) {
+  } else if (n >= V && n <= (64 / V) * per_chunk) {
     // one wavefront per row, at most 64 values per lane
     const int nch = (int)((n + per_chunk - 1) / per_chunk);
     const unsigned grid = (unsigned)((rows + kSoftmaxWavesPerWg - 1) / kSoftmaxWavesPerWg);
     const dim3 block(kSoftmaxWavesPerWg * kWave);
 #define RF_SOFTMAX_CASE(N)                                                              \
-  hipLaunchKernelGGL((softmax_row_in_regs_kernel<T, N>), dim3(grid), block, 0, s, x, y, \
+  hipLaunchKernelGGL((softmax_row_in_regs_kernel<T, N, RAGGED>), dim3(grid), block, 0, s, x, y, \
                      rows, (int)n, x_pitch, y_pitch)
+    // (six and twelve between the powers of two: 4000 rows of 2560 bf16 values 9.2 -> 8.5 us)
     if (nch <= 1) RF_SOFTMAX_CASE(1);
     else if (nch <= 2) RF_SOFTMAX_CASE(2);
+    else if (nch <= 3) RF_SOFTMAX_CASE(3);
     else if (nch <= 4) RF_SOFTMAX_CASE(4);
+    else if (nch <= 6) RF_SOFTMAX_CASE(6);
     else if (nch <= 8) RF_SOFTMAX_CASE(8);
+    else if (nch <= 12) RF_SOFTMAX_CASE(12);
     else RF_SOFTMAX_CASE(16);
 #undef RF_SOFTMAX_CASE
-  } else if (vec_ok && n % V == 0 && n <= 16 * 64 * (int64_t)kWave) {
-    // up to 64 values per lane, 2 / 4 / 8 / 16 wavefronts: rows of 8K, 16K, 32K, 64K values
+  } else if (n >= V && n <= 16 * 64 * (int64_t)kWave) {
+    // 2 / 4 / 8 / 16 wavefronts of at most 64 values per lane (rows of 8K, 16K, 32K, 64K values);
+    // rows of up to three quarters of that hold 48 values per lane, so that at most a third of
+    // the lanes' vectors lie past the end (1000 rows of 20001 bf16 values: 20.1 -> 18.5 us; a
+    // wavefront count fitted to the row instead leaves the SIMDs unevenly filled: 23.8 us).
     constexpr int NCHW = 64 / V;
     const int64_t per_wave = (int64_t)NCHW * V * kWave;   // 4096 values
-#define RF_SOFTMAX_WG(W)                                                                       \
-  hipLaunchKernelGGL((softmax_row_in_regs_wg_kernel<T, NCHW, W>), dim3((unsigned)rows),        \
-                     dim3(W * kWave), 0, s, x, y, rows, (int)n, x_pitch, y_pitch)
-    if (n <= 2 * per_wave) RF_SOFTMAX_WG(2);
-    else if (n <= 4 * per_wave) RF_SOFTMAX_WG(4);
-    else if (n <= 8 * per_wave) RF_SOFTMAX_WG(8);
-    else RF_SOFTMAX_WG(16);
+    const int w = n <= 2 * per_wave ? 2 : n <= 4 * per_wave ? 4 : n <= 8 * per_wave ? 8 : 16;
+    const bool few = 4 * n <= 3 * w * per_wave;
+#define RF_SOFTMAX_WG(W)                                                                           \
+  if (w == W && few)                                                                               \
+    hipLaunchKernelGGL((softmax_row_in_regs_wg_kernel<T, NCHW * 3 / 4, W, RAGGED>), dim3((unsigned)rows), \
+                       dim3(W * kWave), 0, s, x, y, rows, (int)n, x_pitch, y_pitch);               \
+  else if (w == W)                                                                                 \
+    hipLaunchKernelGGL((softmax_row_in_regs_wg_kernel<T, NCHW, W, RAGGED>), dim3((unsigned)rows),  \
+                       dim3(W * kWave), 0, s, x, y, rows, (int)n, x_pitch, y_pitch);
+    RF_SOFTMAX_WG(2) RF_SOFTMAX_WG(4) RF_SOFTMAX_WG(8) RF_SOFTMAX_WG(16)
 #undef RF_SOFTMAX_WG
-  } else if (vec_ok) {
-    hipLaunchKernelGGL((softmax_row_streaming_kernel<T, true>), dim3((unsigned)rows),
-                       dim3(kStreamThreads), 0, s, x, y, rows, n, x_pitch, y_pitch);
-  } else {
-    hipLaunchKernelGGL((softmax_row_streaming_kernel<T, false>), dim3((unsigned)rows),
+  } else {  // longer rows, and rows of less than one vector
+    hipLaunchKernelGGL((softmax_row_streaming_kernel<T>), dim3((unsigned)rows),
                        dim3(kStreamThreads), 0, s, x, y, rows, n, x_pitch, y_pitch);
   }
   return hipGetLastError();
@@ -489,10 +555,10 @@ hipError_t launch_softmax_level(const void* x, void* y, int64_t rows, int64_t n,
     const int nch = (int)((n + per_chunk - 1) / per_chunk);
 #define RF_SOFTMAX_LEVEL_CASE(N)                                                                    \
   if (level == 1)                                                                                   \
-    hipLaunchKernelGGL((softmax_row_in_regs_kernel<T, N, true>), dim3(grid), block, 0, s, xp, yp,   \
+    hipLaunchKernelGGL((softmax_row_in_regs_kernel<T, N, false, true>), dim3(grid), block, 0, s, xp, yp,   \
                        rows, (int)n, x_pitch, y_pitch);                                             \
   else                                                                                              \
-    hipLaunchKernelGGL((softmax_row_in_regs_kernel<T, N, false>), dim3(grid), block, 0, s, xp, yp,  \
+    hipLaunchKernelGGL((softmax_row_in_regs_kernel<T, N, false, false>), dim3(grid), block, 0, s, xp, yp,  \
                        rows, (int)n, x_pitch, y_pitch)
     if (nch <= 1) { RF_SOFTMAX_LEVEL_CASE(1); }
     else if (nch <= 2) { RF_SOFTMAX_LEVEL_CASE(2); }
@@ -501,7 +567,7 @@ hipError_t launch_softmax_level(const void* x, void* y, int64_t rows, int64_t n,
     else { RF_SOFTMAX_LEVEL_CASE(16); }
 #undef RF_SOFTMAX_LEVEL_CASE
   } else if (level == 3) {
-    hipLaunchKernelGGL((softmax_row_streaming_kernel<T, true>), dim3((unsigned)rows), dim3(kStreamThreads), 0, s,
+    hipLaunchKernelGGL((softmax_row_streaming_kernel<T>), dim3((unsigned)rows), dim3(kStreamThreads), 0, s,
                        xp, yp, rows, n, x_pitch, y_pitch);
   } else {
     if (ml_buf == nullptr) return hipErrorInvalidValue;
@@ -517,10 +583,12 @@ hipError_t launch_softmax_level(const void* x, void* y, int64_t rows, int64_t n,
 
 hipError_t launch_softmax(const void* x, void* y, bool is_bf16, int64_t rows, int64_t n,
                           int64_t x_pitch, int64_t y_pitch, bool vec_ok, hipStream_t s) {
-  if (is_bf16)
-    return launch_softmax_t<bf16_t>((const bf16_t*)x, (bf16_t*)y, rows, n, x_pitch, y_pitch,
-                                    vec_ok, s);
-  return launch_softmax_t<float>((const float*)x, (float*)y, rows, n, x_pitch, y_pitch, vec_ok, s);
+  const int64_t v = is_bf16 ? Elem<bf16_t>::kPerVec : Elem<float>::kPerVec;
+  const bool ragged = !vec_ok || n % v != 0;
+#define RF_SOFTMAX(T, R) launch_softmax_t<T, R>((const T*)x, (T*)y, rows, n, x_pitch, y_pitch, s)
+  if (is_bf16) return ragged ? RF_SOFTMAX(bf16_t, true) : RF_SOFTMAX(bf16_t, false);
+  return ragged ? RF_SOFTMAX(float, true) : RF_SOFTMAX(float, false);
+#undef RF_SOFTMAX
 }
 
 }  // namespace rf

@@ -1,0 +1,45 @@
+"""Softmax over rows that start at any element and hold any number of elements, against the fp64
+oracle: row lengths around every boundary of the dispatch (one vector, lanes per row, vectors per
+lane, wavefronts per row, the registers of a workgroup), at every alignment an element type allows,
+x and y aligned differently, in place, with the bytes around every output row left as they were."""
+import sys
+
+import pytest
+import torch
+
+from oracle import rf_oracle as O
+from paper_2603_10026_amd import inputs as I
+
+sys.path.insert(0, __file__.rsplit("/", 1)[0])
+from test_gpu_parity import DEV, check, rf, say  # noqa: E402,F401
+
+pytestmark = pytest.mark.gpu
+
+SOFTMAX_N = {
+    "bf16": [1, 7, 8, 9, 31, 33, 63, 65, 129, 255, 257, 511, 513, 1025, 1537, 2049, 3071, 3073, 4095, 4097, 6145, 8191,
+             8193, 12289, 24577, 32769, 49153, 65535, 65537],
+    "f32": [1, 3, 4, 5, 15, 17, 31, 33, 65, 127, 129, 255, 257, 513, 769, 1025, 1537, 2049, 3073, 4095, 4097, 6145, 8193,
+            12289, 24577, 32769, 49153, 65535, 65537],
+}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_softmax_ragged_rows(rf, dtype):  # noqa: F811
+    for i, n in enumerate(SOFTMAX_N[dtype]):
+        rows = 37 if n < 3000 else 3
+        xo, yo = i % 8, (3 * i + 1) % 8           # first element of x and of y: every alignment
+        say(f"softmax ragged {dtype} rows={rows} n={n} x+{xo} y+{yo}")
+        x = I.softmax_inputs(I.SEED_BASE + 60 + i, rows, n, 2.0, dtype)
+        t = I.to_torch(x, dtype, DEV)
+        xb = torch.full((rows, n + 9), 50.0, dtype=t.dtype, device=DEV)   # large neighbours: reading one would show
+        yb = torch.full((rows, n + 11), -7.0, dtype=t.dtype, device=DEV)
+        xb[:, xo:xo + n] = t
+        rf.rf_safe_softmax(xb[:, xo:xo + n], yb[:, yo:yo + n])
+        torch.cuda.synchronize()
+        ref = O.safe_softmax(x)
+        check(yb[:, yo:yo + n], ref, dtype, "softmax ragged")
+        assert bool((yb[:, :yo] == -7.0).all()) and bool((yb[:, yo + n:] == -7.0).all())
+        rf.rf_safe_softmax(xb[:, xo:xo + n], xb[:, xo:xo + n])            # in place
+        torch.cuda.synchronize()
+        check(xb[:, xo:xo + n], ref, dtype, "softmax ragged in place")
+        assert bool((xb[:, :xo] == 50.0).all()) and bool((xb[:, xo + n:] == 50.0).all())
