@@ -198,10 +198,8 @@ rf_status rf_variance(const rf_tensor* x, rf_tensor* mean, rf_tensor* var, rf_st
   if (x->data == nullptr || mean->data == nullptr || var->data == nullptr) return RF_ERR_INVALID_ARG;
   if (x->stride[nd - 1] != 1 && n > 1) return RF_ERR_UNSUPPORTED;
   if (rows > INT32_MAX) return RF_ERR_UNSUPPORTED;
-  const size_t es = esize(x->dtype);
-  const bool vec_ok = reinterpret_cast<uintptr_t>(x->data) % 16 == 0 && (xp * es) % 16 == 0;
   hipError_t e = rf::launch_variance(x->data, x->dtype == RF_BF16, (float*)mean->data,
-                                     (float*)var->data, rows, n, xp, vec_ok, (hipStream_t)stream);
+                                     (float*)var->data, rows, n, xp, (hipStream_t)stream);
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
 }
 

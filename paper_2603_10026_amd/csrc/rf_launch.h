@@ -60,7 +60,7 @@ hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w,
 
 // Rows of length n (pitch in elements); mean, var: one float per row.
 hipError_t launch_variance(const void* x, bool is_bf16, float* mean, float* var, int64_t rows,
-                           int64_t n, int64_t x_pitch, bool vec_ok, hipStream_t s);
+                           int64_t n, int64_t x_pitch, hipStream_t s);
 
 // x [S,hd], w [hd,E] bf16; prob, idx [S,topk] with row pitches ldp, ldi; part: fp32
 // workspace of moe_num_slices(S, hd) * S * E floats.  hd % 128 == 0, E in {32, 64, 128},

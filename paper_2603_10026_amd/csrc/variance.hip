@@ -11,12 +11,14 @@
 // of the expanded square vanishes).  It is associative and commutative, so the
 // same operator merges vectors, lanes, wavefronts.
 //
-// One workgroup (4 wavefronts, or 16 when rows are few and long) streams one row once.  Every lane turns each
+// Short rows take a wavefront or less each (variance_rows_kernel).  For longer ones,
+// one workgroup (4 wavefronts, or 16 when rows are few and long) streams one row once.  Every lane turns each
 // 128-bit vector into an exact state (two passes over 4 or 8 registers), merges
 // the eight vectors of a chunk pairwise (equal counts: no division), and folds
 // the result into its running state (what is left of a row after the full chunks
 // goes through chunks of 4, 2 and 1 vectors per lane); lanes merge through DPP / shuffles,
-// wavefronts through LDS.  HBM traffic is one read of x.
+// wavefronts through LDS.  HBM traffic is one read of x.  Rows may start at any element: all
+// loads are 16-byte vectors at whatever alignment that gives.
 #include <type_traits>
 
 #include "rf_device.h"
@@ -93,14 +95,71 @@ __device__ __forceinline__ VarState var_shfl_xor(const VarState& a, int mask) {
   return b;
 }
 
+// 16-byte vectors of rows that start at any element
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+constexpr int kVarRowsThreads = 256;
 constexpr int kVarUnroll = 8;  // 128-bit loads in flight per lane in a full chunk
 
 }  // namespace
 
-// VEC: the row base and pitch allow 128-bit loads.  kVarWaves wavefronts share a row: 4 when
-// there are enough rows to fill the GPU, 16 when there are few (each row then needs more loads
-// in flight to be read at speed).
-template <typename T, bool VEC, int kVarWaves>
+// Rows of one to 512 vectors: LPR lanes hold a row in registers, NCH
+// vectors each, and take the two stages one after the other, each over registers and reduced by
+// shuffles over the lanes of the row.  The workgroup-per-row kernel below spends such a row's time
+// on its barrier and its state merges and leaves lanes idle: 16384 rows of 1000 bf16 values
+// VARA us there, VARB here; 32768 rows of 64 fp32 values VARC and VARD.
+// Rows may start at any element: vector idx covers elements idx V .., and the one that would
+// reach past the end is moved back to the last V elements, where it repeats elements of its
+// neighbour, which both sums leave out.
+template <typename T, int NCH, int LPR>
+__global__ __launch_bounds__(kVarRowsThreads) void variance_rows_kernel(
+    const T* __restrict__ x, float* __restrict__ mean_out, float* __restrict__ var_out, int64_t rows, int n,
+    int64_t x_pitch) {
+  constexpr int V = Elem<T>::kPerVec;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int sub = lane % LPR;
+  const int64_t row = ((int64_t)blockIdx.x * (kVarRowsThreads / kWave) + (threadIdx.x >> 6)) * (kWave / LPR) + lane / LPR;
+  const T* xr = x + min(row, rows - 1) * x_pitch;
+  float f[NCH][V];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c)
+    Elem<T>::unpack(__builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(xr + min((c * LPR + sub) * V, n - V))), f[c]);
+  auto lanes_sum = [](float v) {
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+    return v;
+  };
+  // sum over the row of g(element); chunks that no vector leaves are summed without masks
+  auto row_sum = [&](auto g) {
+    float s = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      float part = 0.f;
+      if ((c + 1) * LPR * V <= n) {  // uniform
+#pragma unroll
+        for (int i = 0; i < V; ++i) part += g(f[c][i]);
+      } else {
+        const int e0 = (c * LPR + sub) * V;
+        const int first = e0 - min(e0, n - V);  // elements below it are the neighbour's (V or more: none is ours)
+#pragma unroll
+        for (int i = 0; i < V; ++i) part += i >= first ? g(f[c][i]) : 0.f;
+      }
+      s += part;
+    }
+    return lanes_sum(s);
+  };
+  const float inv_n = 1.0f / (float)n;
+  const float mean = row_sum([](float v) { return v; }) * inv_n;
+  const float m2 = row_sum([mean](float v) { return (v - mean) * (v - mean); });
+  if (sub == 0 && row < rows) {
+    mean_out[row] = mean;
+    var_out[row] = m2 * inv_n;
+  }
+}
+
+// Longer rows.  kVarWaves wavefronts share a row: 4 when there are enough rows to fill the GPU, 16
+// when there are few (each row then needs more loads in flight to be read at speed).
+template <typename T, int kVarWaves>
 __global__ __launch_bounds__(kVarWaves * kWave) void variance_kernel(const T* __restrict__ x,
                                                                      float* __restrict__ mean_out,
                                                                      float* __restrict__ var_out,
@@ -113,8 +172,8 @@ __global__ __launch_bounds__(kVarWaves * kWave) void variance_kernel(const T* __
   const T* xr = x + row * x_pitch;
 
   VarState st{0.f, 0.f, 0.f};
-  if constexpr (VEC) {
-    const u32x4* xv = reinterpret_cast<const u32x4*>(xr);
+  {
+    const u32x4_any* xv = reinterpret_cast<const u32x4_any*>(xr);
     const int64_t nvec = n / V;  // full vectors
     int64_t base = 0;
     // a chunk: every lane owns U full vectors, all U loads in flight together
@@ -156,12 +215,6 @@ __global__ __launch_bounds__(kVarWaves * kWave) void variance_kernel(const T* __
       for (int i = 0; i < V; ++i) f[i] = (tail0 + i < n) ? Elem<T>::load(xr + tail0 + i) : 0.f;
       st = var_merge(st, var_of_vector<V>(f, (int)(n - tail0)));
     }
-  } else {
-    // level-1 incremental form, one element at a time
-    for (int64_t i = tid; i < n; i += kVarThreads) {
-      const float v = Elem<T>::load(xr + i);
-      st = var_merge(st, VarState{1.f, v, 0.f});
-    }
   }
 
   // merge the 64 lane states, then the wavefront states
@@ -179,24 +232,50 @@ __global__ __launch_bounds__(kVarWaves * kWave) void variance_kernel(const T* __
   }
 }
 
-hipError_t launch_variance(const void* x, bool is_bf16, float* mean, float* var, int64_t rows,
-                           int64_t n, int64_t x_pitch, bool vec_ok, hipStream_t s) {
-  if (rows > INT32_MAX) return hipErrorInvalidValue;
+template <typename T>
+static hipError_t launch_variance_t(const T* x, float* mean, float* var, int64_t rows, int64_t n,
+                                    int64_t x_pitch, hipStream_t s) {
+  constexpr int V = Elem<T>::kPerVec;
+  const int64_t nvec64 = (n + V - 1) / V;
+  // A wavefront per row up to 6 vectors a lane (1.0 to 5 times the workgroup's speed for 16 to
+  // 16384 rows), up to 8 where there are rows to fill the GPU (2 times at 16384 rows of 4095 bf16
+  // values, 0.96 at 256); with more, too few wavefronts fit the registers (16384 x 4095 fp32: 0.96).
+  if (n >= V && nvec64 <= (rows >= 1024 ? 8 : 6) * kWave) {
+    const int nvec = (int)nvec64;
+    const int lpr = nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : nvec <= 32 ? 32 : 64;
+    const int nch = (nvec + lpr - 1) / lpr;  // 1 for less than 64 lanes
+    const int64_t rows_per_wg = (kVarRowsThreads / kWave) * (kWave / lpr);
+    const dim3 grid((unsigned)((rows + rows_per_wg - 1) / rows_per_wg)), block(kVarRowsThreads);
+#define RF_VAR_ROWS(NCH, LPR)                                                                        \
+  hipLaunchKernelGGL((variance_rows_kernel<T, NCH, LPR>), grid, block, 0, s, x, mean, var, rows, (int)n, x_pitch)
+    if (lpr == 4) RF_VAR_ROWS(1, 4);
+    else if (lpr == 8) RF_VAR_ROWS(1, 8);
+    else if (lpr == 16) RF_VAR_ROWS(1, 16);
+    else if (lpr == 32) RF_VAR_ROWS(1, 32);
+    else if (nch <= 1) RF_VAR_ROWS(1, 64);
+    else if (nch <= 2) RF_VAR_ROWS(2, 64);
+    else if (nch <= 3) RF_VAR_ROWS(3, 64);
+    else if (nch <= 4) RF_VAR_ROWS(4, 64);
+    else if (nch <= 6) RF_VAR_ROWS(6, 64);
+    else RF_VAR_ROWS(8, 64);
+#undef RF_VAR_ROWS
+    return hipGetLastError();
+  }
   // Few long rows: 16 wavefronts per row instead of 4.  Measured per call under graph replay:
   // 128 rows of 32768 go from 8.5 to 6.0 us, one such row from 4.2 to 3.8; rows of 8192 are
   // faster with 4 wavefronts (2.7 against 3.2 us), and so are 512 rows or more of any length.
   const bool wide = rows <= 256 && n >= 16384;
   const dim3 grid((unsigned)rows), block((wide ? 16 : 4) * kWave);
-#define RF_LAUNCH_VAR(T, VEC)                                                                    \
-  if (wide) hipLaunchKernelGGL((variance_kernel<T, VEC, 16>), grid, block, 0, s, (const T*)x, mean, var, n, x_pitch); \
-  else hipLaunchKernelGGL((variance_kernel<T, VEC, 4>), grid, block, 0, s, (const T*)x, mean, var, n, x_pitch);
-  if (is_bf16) {
-    if (vec_ok) { RF_LAUNCH_VAR(bf16_t, true) } else { RF_LAUNCH_VAR(bf16_t, false) }
-  } else {
-    if (vec_ok) { RF_LAUNCH_VAR(float, true) } else { RF_LAUNCH_VAR(float, false) }
-  }
-#undef RF_LAUNCH_VAR
+  if (wide) hipLaunchKernelGGL((variance_kernel<T, 16>), grid, block, 0, s, x, mean, var, n, x_pitch);
+  else hipLaunchKernelGGL((variance_kernel<T, 4>), grid, block, 0, s, x, mean, var, n, x_pitch);
   return hipGetLastError();
+}
+
+hipError_t launch_variance(const void* x, bool is_bf16, float* mean, float* var, int64_t rows,
+                           int64_t n, int64_t x_pitch, hipStream_t s) {
+  if (rows > INT32_MAX) return hipErrorInvalidValue;
+  return is_bf16 ? launch_variance_t((const bf16_t*)x, mean, var, rows, n, x_pitch, s)
+                 : launch_variance_t((const float*)x, mean, var, rows, n, x_pitch, s);
 }
 
 }  // namespace rf

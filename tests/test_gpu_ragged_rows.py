@@ -1,4 +1,4 @@
-"""Softmax over rows that start at any element and hold any number of elements, against the fp64
+"""Softmax and variance over rows that start at any element and hold any number of elements, against the fp64
 oracle: row lengths around every boundary of the dispatch (one vector, lanes per row, vectors per
 lane, wavefronts per row, the registers of a workgroup), at every alignment an element type allows,
 x and y aligned differently, in place, with the bytes around every output row left as they were."""
@@ -43,3 +43,23 @@ def test_softmax_ragged_rows(rf, dtype):  # noqa: F811
         torch.cuda.synchronize()
         check(xb[:, xo:xo + n], ref, dtype, "softmax ragged in place")
         assert bool((xb[:, :xo] == 50.0).all()) and bool((xb[:, xo + n:] == 50.0).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_variance_ragged_rows(rf, dtype):  # noqa: F811
+    for i, n in enumerate(SOFTMAX_N[dtype] + [2047, 4090, 100003]):
+        for rows in ((37, 1030) if n < 5000 else (3,)):   # 1024 rows: where 8 vectors per lane are taken
+            xo = i % 8
+            say(f"variance ragged {dtype} rows={rows} n={n} x+{xo}")
+            x = I.variance_inputs(I.SEED_BASE + 70 + i, rows, n, dtype)
+            t = I.to_torch(x, dtype, DEV)
+            xb = torch.full((rows, n + 9), 1.0e4, dtype=t.dtype, device=DEV)   # large neighbours: reading one would show
+            xb[:, xo:xo + n] = t
+            mean, var = rf.rf_variance(xb[:, xo:xo + n])
+            torch.cuda.synchronize()
+            m_ref, v_ref = O.variance(x)
+            check(mean, m_ref, "f32", "variance ragged mean")
+            if n == 1:
+                assert float(var.abs().max()) == 0.0
+            else:
+                check(var, v_ref, "f32", "variance ragged var")
