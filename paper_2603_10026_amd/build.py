@@ -20,6 +20,7 @@ SOURCES = [
     "variance.hip",
     "moe_routing.hip",
     "fp8_quant_gemm.hip",
+    "fp8_quant_gemm_rows.hip",
     "attention_f32.hip",
     "attention_bf16.hip",
     "attention_bf16_wide.hip",

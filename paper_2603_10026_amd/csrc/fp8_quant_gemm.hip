@@ -528,6 +528,8 @@ __global__ __launch_bounds__(kQThreads, 1) void fp8_quant_gemm_kernel(
 
 hipError_t launch_fp8_quant_gemm(const void* a, const void* w, void* c, int M, int K, int N,
                                  int64_t lda, int64_t ldw, int64_t ldc, hipStream_t s) {
+  if (fp8_quant_gemm_rows_wins(M, K, N, c, ldc))
+    return launch_fp8_quant_gemm_rows(a, w, c, M, K, N, lda, ldw, ldc, s);
   const int n_mtiles = (M + kQM - 1) / kQM;
   // The 512-wide N tile does the most work per byte staged.  When the 256-wide tiling still
   // fits the chip in one round of workgroups (one per compute unit), it is taken instead: it

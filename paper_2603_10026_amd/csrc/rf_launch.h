@@ -82,6 +82,11 @@ hipError_t launch_moe_routing_static(const void* x, const void* w, int S, int hd
 hipError_t launch_fp8_quant_gemm(const void* a, const void* w, void* c, int M, int K, int N,
                                  int64_t lda, int64_t ldw, int64_t ldc, hipStream_t s);
 
+// The same for few tokens, 8-byte aligned rows of c (the launcher above chooses).
+bool fp8_quant_gemm_rows_wins(int M, int K, int N, const void* c, int64_t ldc);
+hipError_t launch_fp8_quant_gemm_rows(const void* a, const void* w, void* c, int M, int K, int N,
+                                      int64_t lda, int64_t ldw, int64_t ldc, hipStream_t s);
+
 // Fusion-level study of the softmax cascade (bf16 rows, n % 8 == 0, n <= 8192): level 0 =
 // unfused (three kernels; ml_buf holds 2 * rows floats), 1 = fused per lane, 2 = per
 // wavefront (the shipped kernel), 3 = per workgroup, 4 = across workgroups (two kernels;
