@@ -25,6 +25,7 @@ SOURCES = [
     "attention_bf16.hip",
     "attention_bf16_wide.hip",
     "attention_splitk.hip",
+    "attention_fewrows.hip",
     "merge_states.hip",
     "rmsnorm_gemm.hip",
     "rmsnorm_gemm_rows.hip",

@@ -507,6 +507,7 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
   // so that all workgroups do the same work: with 256-query tiles if that still leaves one
   // workgroup per compute unit, else with 128-query tiles if that leaves two.  Smaller causal
   // launches keep one 128-query tile per workgroup, heaviest tiles first.
+  if (attention_fewrows_wins(a, sk, sv)) return launch_attention_fewrows(q, k, v, o, sq, sk, sv, so, a, s);
   const int64_t n_bh = (int64_t)a.B * a.Hq;
   auto tiles = [&](int bq) { return (a.Lq + bq - 1) / bq; };
   int nw = a.Lq <= 128 ? 4 : 8;

@@ -30,6 +30,14 @@ hipError_t launch_attention_f32(const float* q, const float* k, const float* v, 
 hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, void* o,
                                  Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                  const AttnShape& a, hipStream_t s);
+// The same for few query rows; the launchers of the tiled and of the split kernel choose them.
+bool attention_fewrows_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv);
+hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v, void* o, Strides4 sq,
+                                    Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, hipStream_t s);
+bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv);
+hipError_t launch_attention_fewrows_splitk(const void* q, const void* k, const void* v, Strides4 sq, Strides4 sk,
+                                           Strides4 sv, int num_splits, float* part_m, float* part_l,
+                                           float* part_acc, const AttnShape& a, hipStream_t s);
 // measured variant: 64 query rows per wavefront, one wavefront per SIMD; no mask, head
 // dimension 128, Lk >= 64, K/V row pitches below 2^24 (other shapes: hipErrorInvalidValue)
 hipError_t launch_attention_bf16_wide(const void* q, const void* k, const void* v, void* o,
