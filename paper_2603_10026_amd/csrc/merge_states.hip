@@ -22,49 +22,59 @@ __global__ __launch_bounds__(kMergeThreads) void merge_states_kernel(
   __shared__ float s_red2[kMergeThreads / kWave];
   __shared__ f32x4 s_part[kMergeThreads];
 
-  const int64_t row = blockIdx.x;
-  const int i = (int)(row % Lq);
-  const int h = (int)((row / Lq) % Hq);
-  const int b = (int)(row / ((int64_t)Lq * Hq));
+  // (32-bit index arithmetic: a 64-bit division costs some hundred instructions)
+  const uint32_t row32 = blockIdx.x;
+  const int i = (int)(row32 % (uint32_t)Lq);
+  const int h = (int)(row32 / (uint32_t)Lq % (uint32_t)Hq);
+  const int b = (int)(row32 / (uint32_t)Lq / (uint32_t)Hq);
+  const int64_t row = row32;
   const float* pm = part_m + row * S;
   const float* pl = part_l + row * S;
   const float* pa = part_acc + row * (int64_t)S * d;
   const int tid = threadIdx.x;
 
-  // The acc loads do not depend on the weights: when a thread has at most kPre
-  // chunks, issue them all now so that the whole kernel pays one memory latency.
+  float m, l, wgt = 0.f;
   f32x4 pre[kPre];
   if (PREFETCHED) {
+    // At most 64 chunks and kPre per thread: everything is requested at once, so the whole kernel
+    // pays one memory latency, and every wavefront forms m, l and the chunks' weights by itself,
+    // a chunk per lane: no barrier and no second trip for them.
+    const int lane = tid & 63;
+    const float mc = lane < S ? pm[lane] : -INFINITY;
+    const float lc = lane < S ? pl[lane] : 0.f;
     const int G0 = kMergeThreads / ncol_p2;
     const int c0 = tid % ncol_p2, sg0 = tid / ncol_p2;
-    if (c0 < d / 4) {
 #pragma unroll
-      for (int i = 0; i < kPre; ++i) {
-        const int s = sg0 + i * G0;
-        pre[i] = (s < S) ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(pa + (int64_t)s * d + 4 * c0))
-                         : f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+    for (int i = 0; i < kPre; ++i) {
+      const int s = sg0 + i * G0;
+      pre[i] = (s < S && c0 < d / 4) ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(pa + (int64_t)s * d + 4 * c0))
+                                     : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    m = wave_max(mc);
+    const float m_use = (m == -INFINITY) ? 0.f : m;
+    wgt = (mc == -INFINITY) ? -1.f : fast_exp2((mc - m_use) * kLog2e);  // -1: an empty chunk
+    l = wave_sum((mc == -INFINITY) ? 0.f : lc * wgt);
+  } else {
+    // m = max over chunks
+    m = -INFINITY;
+    for (int s = tid; s < S; s += kMergeThreads) m = fmaxf(m, pm[s]);
+    m = wave_max(m);
+    if ((tid & 63) == 0) s_red[tid >> 6] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
+    const float m_use = (m == -INFINITY) ? 0.f : m;
+    // l = sum over chunks of l_c exp(m_c - m)
+    l = 0.f;
+    for (int s = tid; s < S; s += kMergeThreads) {
+      const float mc = pm[s];
+      if (mc != -INFINITY) l += pl[s] * fast_exp2((mc - m_use) * kLog2e);
+    }
+    l = wave_sum(l);
+    if ((tid & 63) == 0) s_red2[tid >> 6] = l;
+    __syncthreads();
+    l = (s_red2[0] + s_red2[1]) + (s_red2[2] + s_red2[3]);
   }
-
-  // m = max over chunks
-  float m = -INFINITY;
-  for (int s = tid; s < S; s += kMergeThreads) m = fmaxf(m, pm[s]);
-  m = wave_max(m);
-  if ((tid & 63) == 0) s_red[tid >> 6] = m;
-  __syncthreads();
-  m = fmaxf(fmaxf(s_red[0], s_red[1]), fmaxf(s_red[2], s_red[3]));
   const float m_use = (m == -INFINITY) ? 0.f : m;
-  // l = sum over chunks of l_c exp(m_c - m)
-  float l = 0.f;
-  for (int s = tid; s < S; s += kMergeThreads) {
-    const float mc = pm[s];
-    if (mc != -INFINITY) l += pl[s] * fast_exp2((mc - m_use) * kLog2e);
-  }
-  l = wave_sum(l);
-  if ((tid & 63) == 0) s_red2[tid >> 6] = l;
-  __syncthreads();
-  l = (s_red2[0] + s_red2[1]) + (s_red2[2] + s_red2[3]);
   const float inv = l > 0.f ? 1.0f / l : 0.f;
 
   // O = sum over chunks of acc_c exp(m_c - m) / l
@@ -73,26 +83,21 @@ __global__ __launch_bounds__(kMergeThreads) void merge_states_kernel(
   const int c = tid % ncol_p2;
   const int sg = tid / ncol_p2;
   f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (c < ncol) {
-    if (PREFETCHED) {
-      // (the kPre loads of this thread were issued at kernel entry)
+  if (PREFETCHED) {
+    // (the kPre loads of this thread were issued at kernel entry)
 #pragma unroll
-      for (int i = 0; i < kPre; ++i) {
-        const int s = sg + i * G;
-        if (s < S) {
-          const float mc = pm[s];
-          const float w = (mc == -INFINITY) ? 0.f : fast_exp2((mc - m_use) * kLog2e);
-          sum += ((mc == -INFINITY) ? f32x4{0.f, 0.f, 0.f, 0.f} : pre[i]) * w;
-        }
-      }
-    } else {
-      for (int s = sg; s < S; s += G) {
-        const float mc = pm[s];
-        if (mc == -INFINITY) continue;
-        const float w = fast_exp2((mc - m_use) * kLog2e);
-        const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(pa + (int64_t)s * d + 4 * c));
-        sum += a * w;
-      }
+    for (int i = 0; i < kPre; ++i) {
+      const int s = sg + i * G;
+      const float w = __shfl(wgt, s & 63, 64);  // (all lanes: the weight of chunk s is in lane s)
+      if (s < S && !(w < 0.f)) sum += pre[i] * w;
+    }
+  } else if (c < ncol) {
+    for (int s = sg; s < S; s += G) {
+      const float mc = pm[s];
+      if (mc == -INFINITY) continue;
+      const float w = fast_exp2((mc - m_use) * kLog2e);
+      const f32x4 a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(pa + (int64_t)s * d + 4 * c));
+      sum += a * w;
     }
   }
   s_part[tid] = sum;
@@ -121,7 +126,7 @@ hipError_t launch_merge_states(const float* part_m, const float* part_l, const f
   int p2 = 1;
   while (p2 < ncol) p2 <<= 1;
   if (p2 > kMergeThreads) return hipErrorInvalidValue;
-  const bool pre = S <= kPre * (kMergeThreads / p2);
+  const bool pre = S <= kWave && S <= kPre * (kMergeThreads / p2);
 #define RF_MERGE_LAUNCH(B16, PRE)                                                                  \
   hipLaunchKernelGGL((merge_states_kernel<B16, PRE>), dim3((unsigned)rows), dim3(kMergeThreads), 0, \
                      s, part_m, part_l, part_acc, o, Hq, Lq, S, d, p2, so)
