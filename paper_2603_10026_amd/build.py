@@ -22,6 +22,7 @@ SOURCES = [
     "fp8_quant_gemm.hip",
     "fp8_quant_gemm_rows.hip",
     "attention_f32.hip",
+    "attention_f32_few.hip",
     "attention_bf16.hip",
     "attention_bf16_wide.hip",
     "attention_splitk.hip",

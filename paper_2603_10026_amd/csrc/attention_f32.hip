@@ -17,15 +17,17 @@
 
 namespace rf {
 
-template <int D, int NW>
+// QT: tiles of 16 query rows per workgroup; a wavefront multiplies every K/V fragment it has
+// fetched by all of them.
+template <int D, int NW, int QT>
 __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     float* __restrict__ o, Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so, int Hq, int Hkv,
     int Lq, int Lk, float scale_log2e, int causal, int n_qtiles) {
   constexpr int DJ = D / 16;  // 16-wide slices of the head dim
-  __shared__ float s_m[NW][16];
-  __shared__ float s_l[NW][16];
-  __shared__ float s_acc[NW][16][D + 4];
+  __shared__ float s_m[NW][16 * QT];
+  __shared__ float s_l[NW][16 * QT];
+  __shared__ float s_acc[NW][16 * QT][D + 4];
 
   // (every argument is named here so that the compiler fetches the whole argument block with its
   // first scalar loads and waits for it once: fetched where first used, the block came in three
@@ -53,7 +55,7 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
   const int h = __builtin_amdgcn_readfirstlane(bh % Hq);
   const int b = __builtin_amdgcn_readfirstlane(bh / Hq);
   const int hk = __builtin_amdgcn_readfirstlane(h / (Hq / Hkv));
-  const int q0 = qt * 16;
+  const int q0 = qt * 16 * QT;
 
   const float* qb = q + (int64_t)b * sq.b + (int64_t)h * sq.h;
   const float* kb = k + (int64_t)b * sk.b + (int64_t)hk * sk.h;
@@ -67,35 +69,42 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
 
   // Q^T fragments.  Contraction slot (g, e) of step j stands for head-dim index
   // 16j + 4g + e on both operands.
-  f32x4 qf[DJ];
-  {
+  f32x4 qf[QT][DJ];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
     // (rows past the end repeat the last query: their results are computed and never stored)
-    const int qi = min(q0 + i16, Lq - 1);
+    const int qi = min(q0 + 16 * t + i16, Lq - 1);
 #pragma unroll
     for (int j = 0; j < DJ; ++j)
-      qf[j] = *reinterpret_cast<const f32x4*>(qb + (int64_t)qi * sq.l + 16 * j + 4 * g);
+      qf[t][j] = *reinterpret_cast<const f32x4*>(qb + (int64_t)qi * sq.l + 16 * j + 4 * g);
   }
 
   // last visible key of this lane's query, and of the whole query tile
   const int shift = Lk - Lq;
-  const int my_q = q0 + i16;
-  const int my_last = causal ? min(Lk - 1, my_q + shift) : Lk - 1;
-  const int tile_last = causal ? min(Lk - 1, min(Lq - 1, q0 + 15) + shift) : Lk - 1;
+  int my_last[QT];
+#pragma unroll
+  for (int t = 0; t < QT; ++t) my_last[t] = causal ? min(Lk - 1, q0 + 16 * t + i16 + shift) : Lk - 1;
+  const int tile_last = causal ? min(Lk - 1, min(Lq - 1, q0 + 16 * QT - 1) + shift) : Lk - 1;
   const int n_ktiles = tile_last >= 0 ? tile_last / 16 + 1 : 0;
 
-  float m2 = -INFINITY;  // running max, in log2 units (score * scale * log2 e)
-  float l = 0.f;         // running sum, this lane's keys only
+  float m2[QT];  // running max, in log2 units (score * scale * log2 e)
+  float l[QT];   // running sum, this lane's keys only
   // Row i of the t-th O^T tile stands for head-dim index DJ * i + t (not 16 t + i): the DJ
   // A-operand values a lane needs for one key are then DJ consecutive floats of the V row,
   // fetched with 128-bit loads, and one load instruction reads whole 64 DJ-byte row pieces.
-  f32x4 acc[DJ];         // acc[t][r] = O^T[head-dim DJ * (4g + r) + t][query i16]
+  f32x4 acc[QT][DJ];  // acc[.][t][r] = O^T[head-dim DJ * (4g + r) + t][query i16]
 #pragma unroll
-  for (int t = 0; t < DJ; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int qq = 0; qq < QT; ++qq) {
+    m2[qq] = -INFINITY;
+    l[qq] = 0.f;
+#pragma unroll
+    for (int t = 0; t < DJ; ++t) acc[qq][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
   // A wavefront's tiles are taken TG at a time: all K and V fragments of the group are
   // requested before the first product, so memory latency is paid once per group, not twice
   // per tile (at the small sizes this kernel serves, that latency is most of the run time).
-  constexpr int TG = (D == 64 && NW <= 8) ? 4 : 2;
+  constexpr int TG = ((D == 64 && NW <= 8) ? 4 : 2) / QT;
   const bool small_pitch = sk.l < (1 << 26) && sv.l < (1 << 26);  // 32-bit byte offsets inside a 16-key tile
   const uint32_t k_lane = (uint32_t)(((int64_t)i16 * sk.l + 4 * g) * 4);
   const uint32_t v_lane = (uint32_t)(((int64_t)(4 * g) * sv.l + DJ * i16) * 4);
@@ -137,66 +146,72 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
       const int kt = kt0 + NW * jj;
       if (kt >= n_ktiles) break;  // uniform per wavefront
       const int key0 = kt * 16;
-      // ---- S^T tile = K_tile Q^T (fp32 MFMA), as two independent accumulation chains ----
-      f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, s_b = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < DJ; j += 2) {
+      for (int qq = 0; qq < QT; ++qq) {
+        // ---- S^T tile = K_tile Q^T (fp32 MFMA), as two independent accumulation chains ----
+        f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, s_b = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[jj][j][e], qf[j][e], s, 0, 0, 0);
-          s_b = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[jj][j + 1][e], qf[j + 1][e], s_b, 0, 0, 0);
+        for (int j = 0; j < DJ; j += 2) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[jj][j][e], qf[qq][j][e], s, 0, 0, 0);
+            s_b = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[jj][j + 1][e], qf[qq][j + 1][e], s_b, 0, 0, 0);
+          }
         }
-      }
-      s += s_b;
-      // s[r] = score(key key0 + 4g + r, query i16); mask, then stage 1: running max
-      float tmax = -INFINITY;
+        s += s_b;
+        // s[r] = score(key key0 + 4g + r, query i16); mask, then stage 1: running max
+        float tmax = -INFINITY;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int key = key0 + 4 * g + r;
-        s[r] = (key <= my_last) ? s[r] * scale_log2e : -INFINITY;
-        tmax = fmaxf(tmax, s[r]);
-      }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      const float m_new = fmaxf(m2, tmax);
-      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;  // identity repair
-      const float corr = fast_exp2(m2 - m_use);                // 0 when m2 == -inf
-      m2 = m_new;
-      // stage 2: running sum of exponentials
-      float p[4];
-      float psum = 0.f;
+        for (int r = 0; r < 4; ++r) {
+          const int key = key0 + 4 * g + r;
+          s[r] = (key <= my_last[qq]) ? s[r] * scale_log2e : -INFINITY;
+          tmax = fmaxf(tmax, s[r]);
+        }
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+        const float m_new = fmaxf(m2[qq], tmax);
+        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;  // identity repair
+        const float corr = fast_exp2(m2[qq] - m_use);            // 0 when m2 == -inf
+        m2[qq] = m_new;
+        // stage 2: running sum of exponentials
+        float p[4];
+        float psum = 0.f;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        p[r] = fast_exp2(s[r] - m_use);
-        psum += p[r];
-      }
-      l = l * corr + psum;
-      // stage 3: rescale acc, then acc += V^T P^T
+        for (int r = 0; r < 4; ++r) {
+          p[r] = fast_exp2(s[r] - m_use);
+          psum += p[r];
+        }
+        l[qq] = l[qq] * corr + psum;
+        // stage 3: rescale acc, then acc += V^T P^T
 #pragma unroll
-      for (int t = 0; t < DJ; ++t) {
+        for (int t = 0; t < DJ; ++t) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[t][r] *= corr;
-      }
+          for (int r = 0; r < 4; ++r) acc[qq][t][r] *= corr;
+        }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < 4; ++u) {
 #pragma unroll
-        for (int t = 0; t < DJ; ++t)
-          acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[jj][u][t / 4][t % 4], p[u], acc[t], 0, 0, 0);
+          for (int t = 0; t < DJ; ++t)
+            acc[qq][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[jj][u][t / 4][t % 4], p[u], acc[qq][t], 0, 0, 0);
+        }
       }
     }
   }
 
   // ---- merge the NW wavefront states (level-k fused expression) ----
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
-  if (g == 0) { s_m[wave][i16] = m2; s_l[wave][i16] = l; }
 #pragma unroll
-  for (int t = 0; t < DJ; ++t) {
+  for (int qq = 0; qq < QT; ++qq) {
+    l[qq] += __shfl_xor(l[qq], 16, 64);
+    l[qq] += __shfl_xor(l[qq], 32, 64);
+    if (g == 0) { s_m[wave][16 * qq + i16] = m2[qq]; s_l[wave][16 * qq + i16] = l[qq]; }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) s_acc[wave][i16][DJ * (4 * g + r) + t] = acc[t][r];
+    for (int t = 0; t < DJ; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_acc[wave][16 * qq + i16][DJ * (4 * g + r) + t] = acc[qq][t][r];
+    }
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < 16 * (D / 4); idx += NW * kWave) {
+  for (int idx = threadIdx.x; idx < 16 * QT * (D / 4); idx += NW * kWave) {
     const int qi = idx / (D / 4);
     const int c4 = idx % (D / 4);
     float mg = -INFINITY;
@@ -223,24 +238,37 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
 hipError_t launch_attention_f32(const float* q, const float* k, const float* v, float* o,
                                 Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                 const AttnShape& a, hipStream_t s) {
-  const int n_qtiles = (a.Lq + 15) / 16;
-  const int64_t grid = (int64_t)n_qtiles * a.B * a.Hq;
+  if (attention_f32_few_wins(a, sk, sv)) return launch_attention_f32_few(q, k, v, o, sq, sk, sv, so, a, s);
+  const int64_t wg16 = (int64_t)((a.Lq + 15) / 16) * a.B * a.Hq, wg32 = (int64_t)((a.Lq + 31) / 32) * a.B * a.Hq;
+  // One or two tiles of 16 rows per workgroup.  A compute unit holds one workgroup at a time, and
+  // one with two tiles takes 1.4 times as long (K and V cross the L2 once for both): two tiles as
+  // soon as they save enough turns.  us with one / two tiles, d = 64: 512 heads of 128 x 512
+  // 148 / 111, 32 heads x 32 rows x 600 23.3 / 18.3, 288 workgroups of one tile x 1520 keys, causal,
+  // 39.7 / 35.1; 256 workgroups x 512 keys 10.2 / 15.0.  d = 128 the same with 8 wavefronts: 512
+  // workgroups x 1000 keys 61.9 / 50.3; on shorter key axes one tile and 4 wavefronts, two workgroups
+  // to a compute unit, do better (512 x 256 keys 18.5 / 19.3), and 8 wavefronts where there is a unit
+  // for each workgroup (160 x 1546 keys 52.1 with 4, 45.2 with 8).
+  const double turns1 = (double)((wg16 + 255) / 256), turns2 = 1.42 * (double)((wg32 + 255) / 256);
+  const bool long_axis = a.d == 64 || a.Lk >= 512;
+  const bool two = long_axis && turns2 < turns1;
+  const int n_qtiles = two ? (a.Lq + 31) / 32 : (a.Lq + 15) / 16;
+  const int64_t grid = two ? wg32 : wg16;
   if (grid > INT32_MAX) return hipErrorInvalidValue;
   const float sl2 = a.scale * kLog2e;
-  if (a.d == 64 && grid < 256 && a.Lk > 128) {
+#define RF_LAUNCH_F32(DD, NW, QT)                                                                       \
+  hipLaunchKernelGGL((attention_f32_kernel<DD, NW, QT>), dim3((unsigned)grid), dim3(NW * kWave), 0, s, q, k, v, o, \
+                     sq, sk, sv, so, a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal, n_qtiles)
+  if (a.d == 64) {
+    if (two) RF_LAUNCH_F32(64, 8, 2);
     // few workgroups and many keys: 16 wavefronts share the key axis of a query tile
-    hipLaunchKernelGGL((attention_f32_kernel<64, 16>), dim3((unsigned)grid), dim3(16 * kWave), 0, s,
-                       q, k, v, o, sq, sk, sv, so, a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal,
-                       n_qtiles);
-  } else if (a.d == 64) {
-    hipLaunchKernelGGL((attention_f32_kernel<64, 8>), dim3((unsigned)grid), dim3(8 * kWave), 0, s,
-                       q, k, v, o, sq, sk, sv, so, a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal,
-                       n_qtiles);
+    else if (grid < 256 && a.Lk > 128) RF_LAUNCH_F32(64, 16, 1);
+    else RF_LAUNCH_F32(64, 8, 1);
   } else {
-    hipLaunchKernelGGL((attention_f32_kernel<128, 4>), dim3((unsigned)grid), dim3(4 * kWave), 0, s,
-                       q, k, v, o, sq, sk, sv, so, a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal,
-                       n_qtiles);
+    if (two) RF_LAUNCH_F32(128, 8, 2);
+    else if (long_axis && grid <= 256) RF_LAUNCH_F32(128, 8, 1);
+    else RF_LAUNCH_F32(128, 4, 1);
   }
+#undef RF_LAUNCH_F32
   return hipGetLastError();
 }
 

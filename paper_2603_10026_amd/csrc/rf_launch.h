@@ -27,6 +27,11 @@ hipError_t launch_attention_f32(const float* q, const float* k, const float* v, 
                                 Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                 const AttnShape& a, hipStream_t s);
 
+// The same in tiles of 4 query rows, for launches with few of them (the launcher above chooses).
+bool attention_f32_few_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv);
+hipError_t launch_attention_f32_few(const float* q, const float* k, const float* v, float* o, Strides4 sq,
+                                    Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, hipStream_t s);
+
 hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, void* o,
                                  Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                  const AttnShape& a, hipStream_t s);

@@ -1,5 +1,5 @@
-"""Attention with few query rows against the fp64 oracle: the tiles of attention_fewrows.hip
-at their edges and on both sides of the rules that choose them."""
+"""Attention with few query rows against the fp64 oracle: the tiles of attention_fewrows.hip and
+attention_f32_few.hip at their edges and on both sides of the rules that choose them."""
 import sys
 
 import numpy as np
@@ -23,6 +23,11 @@ FEW_ATTENTION = [
     ("bf16", 8, 8, 8, 40, 100, 64, True),
     # the tiled kernel from here on: many query tiles
     ("bf16", 8, 32, 32, 200, 130, 64, False), ("bf16", 8, 32, 8, 130, 193, 128, True), ("bf16", 8, 32, 32, 300, 330, 64, True),
+    ("f32", 1, 1, 1, 1, 129, 64, False), ("f32", 2, 6, 2, 3, 130, 128, True), ("f32", 1, 4, 1, 5, 511, 64, True),
+    ("f32", 1, 2, 2, 7, 513, 128, False), ("f32", 1, 1, 1, 200, 150, 64, True), ("f32", 1, 4, 4, 64, 1100, 64, False),
+    # tiles of 16 rows, and of two of them, from here on
+    ("f32", 2, 16, 4, 40, 140, 64, True), ("f32", 4, 16, 16, 33, 200, 128, True), ("f32", 4, 32, 32, 50, 140, 64, False),
+    ("f32", 8, 32, 32, 65, 100, 64, True), ("f32", 4, 32, 8, 161, 140, 128, True),
 ]
 
 
