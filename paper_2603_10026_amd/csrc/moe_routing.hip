@@ -10,15 +10,17 @@
 //
 // Kernel 1 (scores): workgroup (row block of 64 tokens, k slice).  x and w tiles
 //   of 128 k go HBM -> LDS with direct-to-LDS 128-bit loads two tiles ahead of their
-//   use (three LDS stages), one barrier per tile.  The product is computed
+//   use (three LDS stages, all requested up front), one barrier per tile.  The product is computed
 //   transposed, P^T = W^T X^T, with 32x32x16 bf16 MFMAs: W^T fragments come from 64-bit LDS transpose reads, X
 //   fragments from 128-bit reads.  The four wavefronts split the eight 16-wide
 //   contraction steps of a tile, so every LDS byte is read exactly once; their
 //   accumulators are summed through LDS in a fixed order and the fp32 partial
 //   scores of the slice are written to the caller's workspace.
-// Kernel 2 (cascade): 16 lanes per token add the slices' partial scores in slice
-//   order, then run the cascade: each lane reduces its experts, lanes merge
-//   (max; sum with the exp rescale; TopK of the union) with DPP lane exchanges.
+// Kernel 2 (cascade): a wavefront per token adds the slices' partial scores in slice
+//   order, then runs the cascade over its lanes.  (16 lanes per token with up to 8 experts
+//   each kept a longer chain of compares per TopK round and a quarter of the wavefronts:
+//   with it 2048 x 4096 x 128 experts, top 8, took 18.5 us in all, 64 x 4096 x 128 19.2 and
+//   100 x 8192 x 128, 64 slices, 26.8; now 15.7, 9.8 and 12.0.)
 #include <atomic>
 
 #include "rf_device.h"
@@ -46,24 +48,212 @@ typedef __attribute__((address_space(1))) const void global_cvoid_m;
 __device__ __forceinline__ int fXm(int row) { return row & 15; }
 template <int PPR>
 __device__ __forceinline__ int fWm(int krow) { return ((krow & 3) << 2) & (PPR - 1); }
+constexpr int kMoeFusedWaves = 8;
+
+// Maximum / sum over all 64 lanes, every lane gets the result; vector-ALU lane swaps only.
+__device__ __forceinline__ float wave_max_valu(float v) {
+  v = row16_max(v);
+  auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+  s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float wave_sum_valu(float v) {
+  v = row16_sum(v);
+  auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+// low halves / high halves of two packed bf16 pairs
+__device__ __forceinline__ uint32_t pair_lo(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100u); }
+__device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); }
 
 }  // namespace
 
+// The cascade of one token, a wavefront per token: p[i] of a lane is the score of expert
+// 64 i + lane (-inf past the last expert).  The chain of the TopK rounds is what this costs; a
+// round is one maximum over the lanes (vector-ALU swaps), after which the scalar unit finds the
+// lowest expert that holds it in the comparison masks.
 template <int EPL>
-__device__ __forceinline__ void moe_cascade_token(const float (&p)[EPL], int q, int row, bool live,
-                                                  int topk, float* __restrict__ prob,
-                                                  int32_t* __restrict__ idx, int64_t ldp, int64_t ldi);
+__device__ __forceinline__ void moe_cascade_token(float (&p)[EPL], int E, int lane, int row, int topk,
+                                                  float* __restrict__ prob, int32_t* __restrict__ idx,
+                                                  int64_t ldp, int64_t ldi) {
+  // stage 1: max;  stage 2: sum of exponentials
+  float m = p[0];
+#pragma unroll
+  for (int i = 1; i < EPL; ++i) m = fmaxf(m, p[i]);
+  m = wave_max_valu(m);
+  float t = 0.f;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) t += 64 * i + lane < E ? fast_exp2((p[i] - m) * kLog2e) : 0.f;
+  t = wave_sum_valu(t);
+  const float inv_t = 1.0f / t;
+  // stage 3: TopK.  Each round takes the largest remaining score of the token (ties: the lowest
+  // expert index).
+  float my_prob = 0.f;
+  int my_idx = 0;
+  for (int j = 0; j < topk; ++j) {
+    float bv = p[0];
+#pragma unroll
+    for (int i = 1; i < EPL; ++i) bv = fmaxf(bv, p[i]);
+    bv = wave_max_valu(bv);
+    int bi = E;  // no candidate
+    if (__builtin_amdgcn_readfirstlane(__float_as_uint(bv)) != 0xff800000u) {
+#pragma unroll
+      for (int i = EPL - 1; i >= 0; --i) {
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(p[i] == bv);
+        if (mask != 0) bi = 64 * i + __builtin_ctzll(mask);
+      }
+    }
+    bv = bi == E ? -INFINITY : bv;
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) p[i] = bi == 64 * i + lane ? -INFINITY : p[i];
+    if (lane == j) {
+      my_prob = fast_exp2((bv - m) * kLog2e) * inv_t;
+      my_idx = bi;
+    }
+  }
+  if (lane < topk) {
+    prob[(int64_t)row * ldp + lane] = my_prob;
+    idx[(int64_t)row * ldi + lane] = my_idx;
+  }
+}
 
-// NT = E / 32.  part[ks][row][e] = sum over the k slice of x[row,k] w[k,e].
-// FUSED (single-segment strategy, Section 4.3: the whole contraction axis in one workgroup, grid
-// y = 1): the scores never leave the chip; the workgroup runs the cascade on them itself and
-// writes prob / idx.  Chosen when the contraction axis is short enough that splitting it only
-// buys a second launch.
-template <int NT, bool FUSED>
+// Single-segment strategy (Section 4.3): 16 tokens and the whole contraction axis per workgroup,
+// the scores never leave the chip and the workgroup runs the cascade on them itself.  Chosen where
+// the contraction axis is short enough that splitting it only buys a second launch.
+//
+// What bounds it is latency: the wavefronts split the 32-k steps among themselves and take x and w
+// straight from memory into the operands, w as whole rows whose pairs are joined in registers, with
+// no LDS and no barrier before their sums are added.  2048 x 1024 x 128 experts 9.2 us, 22.3 with x
+// and w through LDS in tiles of 128 k and 64 tokens; 16 x 896 x 128 8.8 and 21.2.
+template <int E>
+__global__ __launch_bounds__(kMoeFusedWaves * kWave, 2) void moe_fused_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, int S, int n_steps, int64_t ldx,
+    int64_t ldw, int topk, float* __restrict__ prob, int32_t* __restrict__ idx, int64_t ldp,
+    int64_t ldi) {
+  constexpr int NW = kMoeFusedWaves;
+  constexpr int P = 4;         // steps in flight per wavefront
+  constexpr int C = E / 16;    // experts per lane of a row of w
+  constexpr int CD = C / 2;    // 32-bit words of it
+  constexpr int kPitch = E + 4;
+  __shared__ __attribute__((aligned(16))) float s_p[NW][16][kPitch];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15;
+  const int g4 = lane >> 4;
+  const int row0 = blockIdx.x * 16;
+  // this wavefront's run of 32-k steps
+  const int a0 = n_steps * wave / NW;
+  const int mine = n_steps * (wave + 1) / NW - a0;
+
+  // Slot (g4, e) of a 32-k step stands for k = 8 g4 + e on both operands.  (Rows past the end
+  // repeat the last token; their scores are not stored.)
+  const uint32_t x_lane = (uint32_t)(((int64_t)min(row0 + i16, S - 1) * ldx + 8 * g4) * 2);
+  const uint32_t ldw2 = (uint32_t)ldw * 2;
+  const uint32_t w_lane = 8 * g4 * ldw2 + 2 * C * i16;
+  uint32_t wr[P][8][CD];
+  u32x4 xr[P];
+  auto load = [&](int p, int i) {
+    const int n = a0 + min(i, mine - 1);
+    const char* xt = reinterpret_cast<const char*>(x) + (int64_t)n * 64;
+    const char* wt = reinterpret_cast<const char*>(w) + (int64_t)n * 32 * ldw * 2;
+    xr[p] = *reinterpret_cast<const u32x4*>(xt + x_lane);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const char* src = wt + (int64_t)e * ldw * 2 + w_lane;
+      if constexpr (CD == 4) {
+        const u32x4 v = *reinterpret_cast<const u32x4*>(src);
+#pragma unroll
+        for (int d = 0; d < CD; ++d) wr[p][e][d] = v[d];
+      } else if constexpr (CD == 2) {
+        const u32x2 v = *reinterpret_cast<const u32x2*>(src);
+#pragma unroll
+        for (int d = 0; d < CD; ++d) wr[p][e][d] = v[d];
+      } else {
+        wr[p][e][0] = *reinterpret_cast<const uint32_t*>(src);
+      }
+    }
+  };
+  f32x4 acc[C];  // acc[c][r]: P[token i16][expert C (4 g4 + r) + c]
+#pragma unroll
+  for (int c = 0; c < C; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto step = [&](int p) {
+    const bf16x8 bx = __builtin_bit_cast(bf16x8, xr[p]);
+#pragma unroll
+    for (int d = 0; d < CD; ++d) {
+      u32x4 lo, hi;
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) {
+        lo[e2] = pair_lo(wr[p][2 * e2][d], wr[p][2 * e2 + 1][d]);
+        hi[e2] = pair_hi(wr[p][2 * e2][d], wr[p][2 * e2 + 1][d]);
+      }
+      acc[2 * d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lo), bx, acc[2 * d], 0, 0, 0);
+      acc[2 * d + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hi), bx, acc[2 * d + 1], 0, 0, 0);
+    }
+  };
+  if (mine > 0) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      load(p, p);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    int i = 0;
+    for (; i + P < mine; i += P) {
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        step(p);
+        load(p, i + P + p);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      if (i + p < mine) step(p);
+  }
+
+  // ---- add the wavefronts' sums, in a fixed order ----
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float* dst = &s_p[wave][i16][C * (4 * g4 + r)];
+    if constexpr (C >= 4) {
+#pragma unroll
+      for (int c = 0; c < C; c += 4)
+        *reinterpret_cast<f32x4*>(dst + c) = f32x4{acc[c][r], acc[c + 1][r], acc[c + 2][r], acc[c + 3][r]};
+    } else {
+#pragma unroll
+      for (int c = 0; c < C; ++c) dst[c] = acc[c][r];
+    }
+  }
+  __syncthreads();
+  constexpr int EPL = E > 64 ? E / 64 : 1;
+  for (int tok = wave; tok < 16 && row0 + tok < S; tok += NW) {
+    float p[EPL];
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const int e = 64 * i + lane;
+      p[i] = -INFINITY;
+      if (e < E) {
+        p[i] = s_p[0][tok][e];
+#pragma unroll
+        for (int u = 1; u < NW; ++u) p[i] += s_p[u][tok][e];
+      }
+    }
+    moe_cascade_token<EPL>(p, E, lane, row0 + tok, topk, prob, idx, ldp, ldi);
+  }
+}
+
+// Multi-segment strategy: NT = E / 32.  part[ks][row][e] = sum over the k slice of x[row,k] w[k,e].
+// (Taking x and w straight into the operands, as the single-segment kernel does, was measured here
+// too: never faster, and up to 2 us slower from 64 tokens on.)
+template <int NT>
 __global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, float* __restrict__ part, int S,
-    int n_kblocks, int64_t ldx, int64_t ldw, int topk, float* __restrict__ prob,
-    int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
+    int n_kblocks, int64_t ldx, int64_t ldw) {
   constexpr int E = 32 * NT;
   constexpr int PPR = E / 8;               // 16-byte pieces per W row
   constexpr int kWTileB = kMoeKB * E * 2;  // [k][e]
@@ -163,17 +353,20 @@ __global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
 
   if (b0 < b1) issue_tile(b0, 0);
   if (b0 + 1 < b1) issue_tile(b0 + 1, 1);
+  if (b0 + 2 < b1) issue_tile(b0 + 2, 2);
   int stage = 0;
   for (int blk = b0; blk < b1; ++blk) {
     // This wavefront's loads of the tile have landed (loads retire in order; only the
-    // next tile's may still be in flight); then everyone's have, and everyone is done
-    // reading the stage that the tile after next goes to.
-    if (blk + 1 < b1)
+    // next tile's, at first the next two tiles', may still be in flight); then everyone's have,
+    // and everyone is done reading the stage that the tile after next goes to.
+    if (blk == b0 && blk + 2 < b1)
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(2 * kLoadsPerTile) : "memory");
+    else if (blk + 1 < b1)
       asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(kLoadsPerTile) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
-    if (blk + 2 < b1) issue_tile(blk + 2, stage == 0 ? 2 : stage - 1);
+    if (blk > b0 && blk + 2 < b1) issue_tile(blk + 2, stage == 0 ? 2 : stage - 1);
     const uint32_t soff = stage * kStageB;
     stage = stage == 2 ? 0 : stage + 1;
     // Fragment reads are raw instructions with a hand-placed wait: through the compiler's
@@ -241,147 +434,43 @@ __global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
         }
   }
   __syncthreads();
-  if constexpr (!FUSED) {
-    float* prow = part + ((int64_t)ks * S) * E;
+  float* prow = part + ((int64_t)ks * S) * E;
 #pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      const int c = wave * CPW + cc;
-      f32x4 v = red[c * 64 + lane];
+  for (int cc = 0; cc < CPW; ++cc) {
+    const int c = wave * CPW + cc;
+    f32x4 v = red[c * 64 + lane];
 #pragma unroll
-      for (int r = 1; r < 4; ++r) v += red[r * (kChunks * 64) + c * 64 + lane];
-      const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
-      const int m = row0 + 32 * mi + i32;
-      if (m < S) *reinterpret_cast<f32x4*>(prow + (int64_t)m * E + 32 * ni + 8 * r4 + 4 * hh) = v;
-    }
-  } else {
-    // sums in the same fixed order, kept in registers until every wavefront has read the four
-    // copies, then laid out [token][expert] at the start of LDS
-    f32x4 sum[CPW];
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      const int c = wave * CPW + cc;
-      sum[cc] = red[c * 64 + lane];
-#pragma unroll
-      for (int r = 1; r < 4; ++r) sum[cc] += red[r * (kChunks * 64) + c * 64 + lane];
-    }
-    __syncthreads();
-    float* sc = reinterpret_cast<float*>(lds);  // [kMoeRows][E + 4] (padded rows)
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      const int c = wave * CPW + cc;
-      const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
-      *reinterpret_cast<f32x4*>(sc + (32 * mi + i32) * (E + 4) + 32 * ni + 8 * r4 + 4 * hh) = sum[cc];
-    }
-    __syncthreads();
-    // the cascade: 16 lanes per token, 16 tokens per pass
-    constexpr int EPL = E / 16;
-    const int q = tid & 15;
-#pragma unroll 1
-    for (int pass = 0; pass < kMoeRows / 16; ++pass) {
-      const int tl = 16 * pass + (tid >> 4);
-      const int row = row0 + tl;
-      float p[EPL];
-#pragma unroll
-      for (int i = 0; i < EPL; i += 2) {
-        const float2 v2 = *reinterpret_cast<const float2*>(sc + tl * (E + 4) + q * EPL + i);
-        p[i] = v2.x;
-        p[i + 1] = v2.y;
-      }
-      moe_cascade_token<EPL>(p, q, row, row < S, topk, prob, idx, ldp, ldi);
-    }
+    for (int r = 1; r < 4; ++r) v += red[r * (kChunks * 64) + c * 64 + lane];
+    const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
+    const int m = row0 + 32 * mi + i32;
+    if (m < S) *reinterpret_cast<f32x4*>(prow + (int64_t)m * E + 32 * ni + 8 * r4 + 4 * hh) = v;
   }
 }
 
-// 16 lanes per token; lane q owns experts [q EPL, (q+1) EPL).
-constexpr int kCascadeThreads = 64;  // one wavefront = 4 tokens per workgroup
+constexpr int kCascadeThreads = 256;  // 4 tokens per workgroup
 
-// The cascade of one token on the scores p[EPL] its 16 lanes hold (lane q: experts q EPL ..).
-template <int EPL>
-__device__ __forceinline__ void moe_cascade_token(const float (&p)[EPL], int q, int row, bool live,
-                                                  int topk, float* __restrict__ prob,
-                                                  int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
-  constexpr int E = 16 * EPL;
-  // stage 1: max;  stage 2: sum of exponentials (lane-level fused form, merged across
-  // the 16 lanes with the level-k expression)
-  float m = p[0];
-#pragma unroll
-  for (int i = 1; i < EPL; ++i) m = fmaxf(m, p[i]);
-  float t = 0.f;
-#pragma unroll
-  for (int i = 0; i < EPL; ++i) t += fast_exp2((p[i] - m) * kLog2e);
-  // (four DPP exchange patterns whose composition reaches all 16 lanes of a row)
-#define RF_MERGE_MT(CTRL)                                                          \
-  {                                                                                \
-    const float m_o = dpp_f32<CTRL>(m), t_o = dpp_f32<CTRL>(t);                    \
-    const float m_n = fmaxf(m, m_o);                                               \
-    t = t * fast_exp2((m - m_n) * kLog2e) + t_o * fast_exp2((m_o - m_n) * kLog2e); \
-    m = m_n;                                                                       \
-  }
-  RF_MERGE_MT(kDppQuadXor1) RF_MERGE_MT(kDppQuadXor2) RF_MERGE_MT(kDppRowHalfMirror) RF_MERGE_MT(kDppRowMirror)
-#undef RF_MERGE_MT
-  const float inv_t = 1.0f / t;
-  // stage 3: TopK.  Each round takes the largest remaining score of the token (ties: the
-  // lowest expert index): lane-local best, then a 16-lane merge of (score, index) pairs.
-  uint32_t taken = 0;
-  float my_prob = 0.f;
-  int my_idx = 0;
-  for (int j = 0; j < topk; ++j) {
-    float bv = -INFINITY;
-    int bi = E;  // no candidate
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      const bool ok = !((taken >> i) & 1u) && (p[i] > bv);  // strict: keeps the lowest index
-      bv = ok ? p[i] : bv;
-      bi = ok ? q * EPL + i : bi;
-    }
-#define RF_MERGE_TOP(CTRL)                                         \
-  {                                                                \
-    const float ov = dpp_f32<CTRL>(bv);                            \
-    const int oi = dpp_i32<CTRL>(bi);                              \
-    const bool take = (ov > bv) || (ov == bv && oi < bi);          \
-    bv = take ? ov : bv;                                           \
-    bi = take ? oi : bi;                                           \
-  }
-    RF_MERGE_TOP(kDppQuadXor1) RF_MERGE_TOP(kDppQuadXor2) RF_MERGE_TOP(kDppRowHalfMirror) RF_MERGE_TOP(kDppRowMirror)
-#undef RF_MERGE_TOP
-    if (bi / EPL == q && bi < E) taken |= 1u << (bi % EPL);
-    if ((j & 15) == q) {
-      my_prob = fast_exp2((bv - m) * kLog2e) * inv_t;
-      my_idx = bi;
-    }
-  }
-  if (live && q < topk) {
-    prob[(int64_t)row * ldp + q] = my_prob;
-    idx[(int64_t)row * ldi + q] = my_idx;
-  }
-}
-
-template <int EPL>
+template <int E>
 __global__ __launch_bounds__(kCascadeThreads) void moe_cascade_kernel(
     const float* __restrict__ part, int KS, int S, int topk, float* __restrict__ prob,
     int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
-  constexpr int E = 16 * EPL;
-  const int tid = threadIdx.x;
-  const int q = tid & 15;
-  const int row = blockIdx.x * (kCascadeThreads / 16) + (tid >> 4);
-  const bool live = row < S;
-  const int rrow = live ? row : S - 1;  // dead groups repeat the last token, store nothing
-
+  constexpr int EPL = E > 64 ? E / 64 : 1;
+  const int lane = threadIdx.x & 63;
+  const int row = __builtin_amdgcn_readfirstlane(blockIdx.x * (kCascadeThreads / kWave) + (threadIdx.x >> 6));
+  if (row >= S) return;
   // scores: slices added in slice order
   float p[EPL];
 #pragma unroll
   for (int i = 0; i < EPL; ++i) p[i] = 0.f;
+  const float* src = part + (int64_t)row * E + (E < 64 ? min(lane, E - 1) : lane);
+  const int64_t slice = (int64_t)S * E;
 #pragma unroll 8
   for (int s = 0; s < KS; ++s) {
-    const float* src = part + ((int64_t)s * S + rrow) * E + q * EPL;
 #pragma unroll
-    for (int i = 0; i < EPL; i += 2) {
-      const float2 v = *reinterpret_cast<const float2*>(src + i);
-      p[i] += v.x;
-      p[i + 1] += v.y;
-    }
+    for (int i = 0; i < EPL; ++i) p[i] += src[64 * i];
+    src += slice;
   }
-  moe_cascade_token<EPL>(p, q, row, live, topk, prob, idx, ldp, ldi);
+  if (E < 64 && lane >= E) p[0] = -INFINITY;
+  moe_cascade_token<EPL>(p, E, lane, row, topk, prob, idx, ldp, ldi);
 }
 
 // Device address of `scratch` on the current device, resolved once per device (with that
@@ -412,9 +501,9 @@ hipError_t launch_moe_routing_static(const void* x, const void* w, int S, int hd
 }
 
 // Contraction axes of at most this length are not split: one launch, scores stay on chip.
-// Measured on 2048 tokens: with only S/64 workgroups, each streaming all of w, the single
-// segment wins at hd = 768 and 1024 (by half a microsecond per call under graph replay) and
-// loses from hd = 2048 on (18 us against 11 us for 64 experts, 29 against 17.5 for 128).
+// Every workgroup streams all of w, at the 60 GB/s a compute unit's loads reach: 9.2 us at 1024
+// for 2048 tokens and 128 experts, 8.8 at 896 for 16 tokens, growing with hd; the two launches take
+// 13.7 and 7.9 us at 2048.
 constexpr int kMoeSingleSegmentMaxHd = 1024;
 
 int moe_num_slices(int S, int hd) {
@@ -431,38 +520,42 @@ int moe_num_slices(int S, int hd) {
 hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E, int topk,
                               int64_t ldx, int64_t ldw, float* prob, int32_t* idx, int64_t ldp,
                               int64_t ldi, float* part, hipStream_t s) {
-  const int n_rb = (S + kMoeRows - 1) / kMoeRows;
   const int n_kblocks = hd / kMoeKB;
   const int KS = moe_num_slices(S, hd);
   // 32-bit lane offsets inside x and inside one 128-row tile of w
   if ((int64_t)S * ldx * 2 >= ((int64_t)1 << 32) || (int64_t)kMoeKB * ldw * 2 >= ((int64_t)1 << 32))
     return hipErrorInvalidValue;
-  const dim3 grid1((unsigned)n_rb, (unsigned)KS), block(kMoeThreads);
   const bf16_t* xb = (const bf16_t*)x;
   const bf16_t* wb = (const bf16_t*)w;
   if (hd <= kMoeSingleSegmentMaxHd) {
     // single-segment strategy: scores GEMM and cascade in one kernel
+#define RF_MOE_FUSED(EE)                                                                                   \
+  hipLaunchKernelGGL((moe_fused_kernel<EE>), dim3((unsigned)((S + 15) / 16)), dim3(kMoeFusedWaves * kWave), 0, s, xb, \
+                     wb, S, hd / 32, ldx, ldw, topk, prob, idx, ldp, ldi)
     switch (E) {
-      case 32: hipLaunchKernelGGL((moe_scores_kernel<1, true>), grid1, block, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi); break;
-      case 64: hipLaunchKernelGGL((moe_scores_kernel<2, true>), grid1, block, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi); break;
-      case 128: hipLaunchKernelGGL((moe_scores_kernel<4, true>), grid1, block, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi); break;
+      case 32: RF_MOE_FUSED(32); break;
+      case 64: RF_MOE_FUSED(64); break;
+      case 128: RF_MOE_FUSED(128); break;
       default: return hipErrorInvalidValue;
     }
+#undef RF_MOE_FUSED
     return hipGetLastError();
   }
+  const dim3 grid1((unsigned)((S + kMoeRows - 1) / kMoeRows), (unsigned)KS), block1(kMoeThreads);
   switch (E) {
-    case 32: hipLaunchKernelGGL((moe_scores_kernel<1, false>), grid1, block, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi); break;
-    case 64: hipLaunchKernelGGL((moe_scores_kernel<2, false>), grid1, block, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi); break;
-    case 128: hipLaunchKernelGGL((moe_scores_kernel<4, false>), grid1, block, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi); break;
+    case 32: hipLaunchKernelGGL((moe_scores_kernel<1>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw); break;
+    case 64: hipLaunchKernelGGL((moe_scores_kernel<2>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw); break;
+    case 128: hipLaunchKernelGGL((moe_scores_kernel<4>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw); break;
     default: return hipErrorInvalidValue;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const dim3 grid2((unsigned)((S + kCascadeThreads / 16 - 1) / (kCascadeThreads / 16))), block2(kCascadeThreads);
+  constexpr int kTokens = kCascadeThreads / kWave;
+  const dim3 grid2((unsigned)((S + kTokens - 1) / kTokens)), block2(kCascadeThreads);
   switch (E) {
-    case 32: hipLaunchKernelGGL((moe_cascade_kernel<2>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
-    case 64: hipLaunchKernelGGL((moe_cascade_kernel<4>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
-    case 128: hipLaunchKernelGGL((moe_cascade_kernel<8>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
+    case 32: hipLaunchKernelGGL((moe_cascade_kernel<32>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
+    case 64: hipLaunchKernelGGL((moe_cascade_kernel<64>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
+    case 128: hipLaunchKernelGGL((moe_cascade_kernel<128>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
