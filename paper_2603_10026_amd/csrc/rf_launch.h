@@ -66,7 +66,7 @@ hipError_t launch_rmsnorm_gemm_bf16(const void* x, const void* g, const void* w,
                                     float eps, hipStream_t s);
 
 // The same for few rows, 16-byte aligned rows of y, w within 4 GiB (the launcher above chooses).
-bool rmsnorm_gemm_rows_fits(int K, int64_t ldw);
+bool rmsnorm_gemm_rows_wins(int M, int K, int N, int64_t ldw, const void* y, int64_t ldy);
 hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w, void* y, int M,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
                                     hipStream_t s);

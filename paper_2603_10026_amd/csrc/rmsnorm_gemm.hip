@@ -433,8 +433,7 @@ hipError_t launch_rmsnorm_gemm_bf16(const void* x, const void* g, const void* w,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
                                     hipStream_t s) {
   // Few rows: 128 x 512 tiles would leave most compute units idle.
-  if (M <= 256 && rmsnorm_gemm_rows_fits(K, ldw) && (ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0)
-    return launch_rmsnorm_gemm_rows(x, g, w, y, M, K, N, ldx, ldw, ldy, eps, s);
+  if (rmsnorm_gemm_rows_wins(M, K, N, ldw, y, ldy)) return launch_rmsnorm_gemm_rows(x, g, w, y, M, K, N, ldx, ldw, ldy, eps, s);
   const int n_mtiles = (M + kBM - 1) / kBM;
   const int n_ntiles = (N + kBN - 1) / kBN;
   const int64_t grid = (int64_t)n_mtiles * n_ntiles;

@@ -20,7 +20,9 @@
 // lines and half the workgroups (C = 4), and cache-policy bits change nothing; the last 50 GB/s
 // per compute unit are its 32 KB of L1 lines in flight over the memory latency.  Two steps in
 // flight and 4 wavefronts are therefore faster than 8 wavefronts with more (which evict each
-// other's lines): 48 x 4096 x 4096 takes 17.3 us against 20.1, and 90.8 us in 128 x 512 tiles.
+// other's lines): 48 x 4096 x 4096 takes 15.8 us, and 87 us in 128 x 512 tiles.  A few hundred rows
+// are bound by the same lines in either kernel, and 64 x 128 tiles move fewest of them per compute
+// unit in use: 1024 x 8192 x 2048 takes 63 us against 171.
 #include <math.h>
 
 #include "rf_device.h"
@@ -82,7 +84,11 @@ __global__ __launch_bounds__(kRThreads) void rmsnorm_gemm_rows_kernel(
     const uint32_t wo = k0 * ldw2;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      if constexpr (CD == 1) {
+      if constexpr (CD == 4) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(wrs, w_lane, wo + e * ldw2, 0);
+#pragma unroll
+        for (int d = 0; d < CD; ++d) wr[p][e][d] = v[d];
+      } else if constexpr (CD == 1) {
         wr[p][e][0] = __builtin_amdgcn_raw_buffer_load_b32(wrs, w_lane, wo + e * ldw2, 0);
       } else {
         const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(wrs, w_lane, wo + e * ldw2, 0);
@@ -192,38 +198,49 @@ __global__ __launch_bounds__(kRThreads) void rmsnorm_gemm_rows_kernel(
 }
 
 namespace {
-struct RowsShape { int mt, c; };
-constexpr RowsShape kRowsShapes[] = {{1, 2}, {2, 2}, {1, 4}, {2, 4}, {4, 4}};
-inline int64_t rows_tiles(const RowsShape& r, int64_t M, int64_t N) {
-  return ((M + 16 * r.mt - 1) / (16 * r.mt)) * ((N + 16 * r.c - 1) / (16 * r.c));
+// Tile shapes and what a workgroup of each takes: us for the launch and the sums, us per 1024 k.
+// The latter is its lines' way through the compute unit, 46 GB/s of w and x at C <= 4 and 62-67 at
+// C = 8, where a lane's load of w is 16 bytes: bigger tiles win as soon as there are enough of them.
+struct RowsShape { int mt, c; double us, us_per_k; };
+constexpr RowsShape kRowsShapes[] = {{1, 2, 2.9, 2.6}, {2, 2, 3.2, 3.0}, {1, 4, 3.3, 3.05}, {2, 4, 3.7, 4.05},
+                                     {4, 4, 4.6, 5.5}, {2, 8, 4.4, 4.6}, {4, 8, 6.0, 6.3}};
+// Columns of whole 128-byte lines: two tiles at C = 2, else one.
+inline int group_cols(int c) { return c > 4 ? 16 * c : 64; }
+// More workgroups than the 32 compute units of an XCD take turns (the column groups are dealt to the
+// 8 XCDs, so some may get one more).  Within 10 % of the measured times of all shapes
+// for 512 to 8192 k, 512 to 8192 columns and 1 to 2048 rows.
+inline double rows_us(const RowsShape& r, int M, int K, int N) {
+  const int group = group_cols(r.c), n_groups = (N + group - 1) / group;
+  const double wg_xcd = (double)((M + 16 * r.mt - 1) / (16 * r.mt)) * ((n_groups + 7) / 8) * (group / (16 * r.c));
+  return 2.0 + (r.us + r.us_per_k * (K / 1024.0) - 2.0) * ceil(wg_xcd / 32);
 }
-// What a tile shape costs, in cache-line bytes per k and compute unit: a workgroup takes 128
-// bytes of w (half of each line unused at C = 2) and 2 bytes per row of x through its L1, whose
-// 32 KB bound what it has in flight; a launch of more than 256 workgroups takes turns, one of
-// fewer leaves compute units idle, which costs less than in proportion because the rest then
-// share the memory.  Orders the measured times of all five shapes on 4096 x 4096 (1 to 128 rows)
-// and 8192 x 8192 (7 and 100 rows) right to within 5 %.
-inline double rows_cost(const RowsShape& r, int64_t M, int64_t N) {
-  const double wg = (double)rows_tiles(r, M, N);
-  const double idle = wg < 256 ? 1.0 + 0.1 * log2(256.0 / wg) : wg / 256.0;
-  return idle * (128 + 32 * r.mt);
+const RowsShape& best_shape(int M, int K, int N) {
+  const RowsShape* best = kRowsShapes;
+  for (const RowsShape& r : kRowsShapes)
+    if (rows_us(r, M, K, N) < rows_us(*best, M, K, N)) best = &r;
+  return *best;
 }
 }  // namespace
 
-// (the buffer loads take 32-bit byte offsets inside w)
-bool rmsnorm_gemm_rows_fits(int K, int64_t ldw) { return (int64_t)K * ldw * 2 < ((int64_t)1 << 32); }
+// The 128 x 512 tiles take 5 us and 20.5 for every 1024 k up to 64 of them, 29 at 256, whatever the
+// row count.  Both sides at the line (us here / there): 1024 x 4096 x 4096 66 / 89, 1500 rows 97 / 90;
+// 768 x 8192 x 8192 170 / 174, 1024 rows 241 / 176; 2048 x 8192 x 2048 123 / 171.
+// (the buffer loads take 32-bit byte offsets inside w; rows of y are stored 16 bytes at a time)
+bool rmsnorm_gemm_rows_wins(int M, int K, int N, int64_t ldw, const void* y, int64_t ldy) {
+  if ((int64_t)K * ldw * 2 >= ((int64_t)1 << 32) || (ldy & 7) != 0 || (reinterpret_cast<uintptr_t>(y) & 15) != 0) return false;
+  const double wg = (double)((M + 127) / 128) * ((N + 511) / 512);
+  const double large = 5.0 + (K / 1024.0) * (20.5 + 8.5 * fmin(fmax((wg - 64) / 192, 0.0), 1.0)) * ceil(wg / 256);
+  return 1.15 * rows_us(best_shape(M, K, N), M, K, N) < large;
+}
 
 hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w, void* y, int M,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
                                     hipStream_t s) {
-  if (!rmsnorm_gemm_rows_fits(K, ldw)) return hipErrorInvalidValue;
-  RowsShape best = kRowsShapes[0];
-  for (const RowsShape& r : kRowsShapes)
-    if (rows_cost(r, M, N) < rows_cost(best, M, N)) best = r;
+  const RowsShape& best = best_shape(M, K, N);
   const int n_mt = (M + 16 * best.mt - 1) / (16 * best.mt);
-  const int group_cols = 64;  // columns of one 128-byte line: one tile at C = 4, two at C = 2
-  const int64_t groups = ((int64_t)N + group_cols - 1) / group_cols;
-  const int64_t grid = (groups + 7) / 8 * 8 * (group_cols / (16 * best.c)) * n_mt;
+  const int group = group_cols(best.c);
+  const int64_t groups = ((int64_t)N + group - 1) / group;
+  const int64_t grid = (groups + 7) / 8 * 8 * (group / (16 * best.c)) * n_mt;
   if (grid > INT32_MAX) return hipErrorInvalidValue;
 #define RF_ROWS(MT, C, P)                                                                            \
   if (best.mt == MT && best.c == C)                                                                  \
@@ -231,6 +248,7 @@ hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w,
                        (const bf16_t*)x, (const bf16_t*)g, (const bf16_t*)w, (bf16_t*)y, M, K, N, ldx, ldw, \
                        ldy, 1.0f / (float)K, eps, n_mt);
   RF_ROWS(1, 2, 4) RF_ROWS(2, 2, 2) RF_ROWS(1, 4, 2) RF_ROWS(2, 4, 2) RF_ROWS(4, 4, 2)
+  RF_ROWS(2, 8, 2) RF_ROWS(4, 8, 2)
 #undef RF_ROWS
   return hipGetLastError();
 }

@@ -1,7 +1,7 @@
 """RMSNorm + linear at few rows: the tiles of rmsnorm_gemm_rows.hip against the fp64 oracle at the
-edges of its row tiles (16, 32, 64), of its column tiles (32, 64, groups of 64 columns over 8 XCDs),
-at contraction axes that leave some of the 4 wavefronts without a step, and at the row count where
-the large tiles take over."""
+edges of its row tiles (16, 32, 64), of its column tiles (32, 64, 128, groups of 64 columns over 8
+XCDs), at contraction axes that leave some of the 4 wavefronts without a step, and on both sides of
+the rule that hands over to the large tiles."""
 import sys
 
 import pytest
@@ -20,6 +20,9 @@ pytestmark = pytest.mark.gpu
     (1, 64, 8), (1, 64, 520), (2, 128, 32), (15, 192, 40), (16, 256, 64), (17, 320, 72), (31, 448, 1032), (33, 576, 4096),
     (47, 64 * 9, 8 * 67), (64, 512, 2048), (65, 512, 2056), (100, 1088, 4096), (128, 256, 8200), (129, 640, 4104),
     (256, 192, 1000), (257, 192, 1000),
+    # tiles of 32 and 64 rows x 128 columns, ragged in both directions; then the large tiles
+    (100, 512, 8200), (256, 576, 4104), (500, 320, 4096), (1000, 1024, 1000), (2047, 192, 1032), (1500, 128, 4104),
+    (3000, 256, 2056),
 ])
 def test_rmsnorm_gemm_few_rows(rf, M, K, N):  # noqa: F811
     say(f"rmsnorm_gemm few rows M{M} K{K} N{N}")
