@@ -28,6 +28,8 @@
 // reference gives the same O = acc / l, exponentials stay below 2^kTau, and
 // the rescale of acc (the correction step of the incremental form) is skipped
 // on almost every tile.
+#include <math.h>
+
 #include <type_traits>
 
 #include "rf_device.h"
@@ -62,7 +64,10 @@ __device__ __forceinline__ void wait_vmem_all() {
 
 }  // namespace
 
-template <int D, int NW, bool PAIRED>
+// KG = 2: two groups of NW / 2 wavefronts each, with K/V buffers of their own, take the key tiles in
+// turn for the same NW / 2 * 32 query rows; their states are merged through LDS at the end.  For
+// launches that leave compute units idle: twice the workgroups, half the key tiles in each.
+template <int D, int NW, bool PAIRED, int KG = 1>
 __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     bf16_t* __restrict__ o, Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so, int Hq, int Hkv,
@@ -74,18 +79,25 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   constexpr int ROWB = D * 2;                // bytes per K/V row
   constexpr int TILEB = kBK * ROWB;          // bytes per K or V tile
   constexpr int ROWS_PER_LD = 1024 / ROWB;   // rows covered by one wavefront load
-  constexpr int kWaves = NW;
-  constexpr int kBQ = 32 * NW;               // query rows per workgroup
+  constexpr int kWaves = NW / KG;            // wavefronts that share a key tile
+  constexpr int kBQ = 32 * kWaves;           // query rows per workgroup
+  static_assert(KG == 1 || (KG == 2 && !PAIRED), "two key groups, one query tile");
   constexpr int LD_PER_WAVE = kBK / ROWS_PER_LD / kWaves;
 
   // Two K/V slots.  Layout: the K slots, then the V slots; the K address registers point at the
   // first K slot, the V registers at the first V slot.
   constexpr int NS = 2;
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * NS * TILEB];  // [K,V][slot]
+  // [key group][K,V][slot].  (Two groups: sized at the launch.  One workgroup then fills a compute
+  // unit, and a compiler that knows plans for a wavefront per SIMD and moves accumulators between
+  // vector and accumulation registers all along.)
+  __shared__ __attribute__((aligned(1024))) unsigned char lds_one[KG == 1 ? 2 * NS * TILEB : 1024];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds_two[];
+  unsigned char* const lds = KG == 1 ? lds_one : lds_two;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = KG == 1 ? tid >> 6 : (tid >> 6) % kWaves;  // within the key group
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((tid >> 6) / kWaves);
   const int i32 = lane & 31;
   const int hh = lane >> 5;
 
@@ -151,7 +163,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   // One direct-to-LDS load of this wavefront's share of the tile at key0: load e of K
   // (is_v = 0) or of V (is_v = 1) into buffer buf.
   const uint32_t lds_base =
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds + (KG == 1 ? 0 : kg * (2 * NS * TILEB));
   // LDS address of this wavefront's first load in K slot 0, on the scalar unit
   const uint32_t dma_base = __builtin_amdgcn_readfirstlane(lds_base + wave * LD_PER_WAVE * 1024);
   auto issue_one = [&](int key0, int buf, int e, int is_v) {
@@ -196,7 +208,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   {
     const int last_row0 = min(Lq - 1, qt * kBQ + kBQ - 1);
     const int wg_last0 = causal ? min(Lk - 1, last_row0 + (Lk - Lq)) : Lk - 1;
-    if (wg_last0 >= 0) issue_loads(0, 0);
+    if (wg_last0 >= kg * kBK) issue_loads(kg * kBK, 0);
   }
 
   // ---- LDS read offsets (loop invariant) ----
@@ -294,9 +306,9 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
     const int key0 = kt * kBK;
     wait_vmem_all();   // this wavefront's share of tile kt has landed
     __syncthreads();   // everyone's share has landed; everyone is done reading the other slot
-    const bool more = kt + 1 < n_ktiles;
+    const bool more = kt + KG < n_ktiles;
     if (key0 > wave_last) {  // nothing visible for this wavefront (uniform): only fetch its share
-      if (more) issue_loads(key0 + kBK, FILL);
+      if (more) issue_loads(key0 + KG * kBK, FILL);
       return;
     }
     u32x4 kq[KS][2];
@@ -312,8 +324,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
     // The loads of the next tile are issued one at a time between the MFMAs.  Issued in a
     // burst right after the barrier, the eight wavefronts of a CU queue up behind each
     // other in the vector-memory unit and every one of them idles for the whole burst.
-    constexpr int kIssueEvery = KS / (2 * LD_PER_WAVE);  // contraction steps per load
-    static_assert(kIssueEvery * 2 * LD_PER_WAVE == KS, "loads spread evenly over the contraction steps");
+    constexpr int kLoads = 2 * LD_PER_WAVE;
+    constexpr int kIssueEvery = kLoads < KS ? KS / kLoads : 1;  // contraction steps per load
+    constexpr int kPerIssue = kLoads < KS ? 1 : kLoads / KS;    // or loads per step
+    static_assert(kLoads * kIssueEvery == KS * kPerIssue, "loads spread evenly over the contraction steps");
     static_assert(2 * (KS - 1) <= 15, "the wait counts below fit the LDS counter");
     auto st_step = [&](auto kk_tag) {
       constexpr int kk = decltype(kk_tag)::value;
@@ -325,8 +339,13 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
                                                      __builtin_bit_cast(bf16x8, qf[kk]), s[0], 0, 0, 0);
       s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k1),
                                                      __builtin_bit_cast(bf16x8, qf[kk]), s[1], 0, 0, 0);
-      if (more && kk % kIssueEvery == 0)
-        issue_one(key0 + kBK, FILL, (kk / kIssueEvery) >> 1, (kk / kIssueEvery) & 1);
+      if (more && kk % kIssueEvery == 0) {
+#pragma unroll
+        for (int j = 0; j < kPerIssue; ++j) {
+          const int e = kk / kIssueEvery * kPerIssue + j;
+          issue_one(key0 + KG * kBK, FILL, e >> 1, e & 1);
+        }
+      }
       __builtin_amdgcn_sched_barrier(0);
     };
     st_step(std::integral_constant<int, 0>{});
@@ -450,9 +469,10 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   };
 
   if (pass && n_ktiles > 0) issue_loads(0, 0);   // (first pass: requested during the set-up)
-  for (int kt = 0; kt < n_ktiles; kt += 2) {
-    tile_step(kt, std::integral_constant<int, 0>{});
-    if (kt + 1 < n_ktiles) tile_step(kt + 1, std::integral_constant<int, 1>{});
+  // (every key group takes as many turns, for the barriers in them: a tile past the end is skipped)
+  for (int kt = 0; kt < n_ktiles; kt += 2 * KG) {
+    tile_step(kt + kg, std::integral_constant<int, 0>{});
+    if (kt + KG < n_ktiles) tile_step(kt + KG + kg, std::integral_constant<int, 1>{});
   }
 
   // ---- epilogue: O = acc / l ----
@@ -463,8 +483,41 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   // (or 8) lanes.  A wavefront stages and stores its own 32 rows, so no barrier is needed in
   // between.
   l += __shfl_xor(l, 32, 64);
+  if constexpr (KG == 2) {
+    // Level-k merge of the two groups' states: the second group parks its own in its K/V buffers, a
+    // lane's values for the same lane of the same wavefront of the first.
+    float (*s_ml)[2][kWave] = reinterpret_cast<float (*)[2][kWave]>(lds_one);
+    static_assert(kWaves * 2 * kWave * 4 <= 1024, "the groups' m and l");
+    __syncthreads();  // every wavefront is done with the last tiles
+    f32x4* park = reinterpret_cast<f32x4*>(lds + 2 * NS * TILEB) + wave * (DT * 4 * kWave) + lane;
+    static_assert(kWaves * DT * 16 * kWave * 4 <= 2 * NS * TILEB, "a group's accumulators fit its K/V buffers");
+    if (kg == 1) {
+      s_ml[wave][0][lane] = m_ref;
+      s_ml[wave][1][lane] = l;
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          park[(t * 4 + r4) * kWave] = f32x4{acc[t][4 * r4], acc[t][4 * r4 + 1], acc[t][4 * r4 + 2], acc[t][4 * r4 + 3]};
+    }
+    __syncthreads();
+    if (kg == 1) return;
+    const float m1 = s_ml[wave][0][lane];
+    const float m = fmaxf(m_ref, m1);
+    const float m_use = (m == -INFINITY) ? 0.f : m;
+    const float w0 = fast_exp2(m_ref - m_use), w1 = fast_exp2(m1 - m_use);  // 0 for an empty state
+    l = l * w0 + s_ml[wave][1][lane] * w1;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 o1 = park[(t * 4 + r4) * kWave];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[t][4 * r4 + j] = acc[t][4 * r4 + j] * w0 + o1[j] * w1;
+      }
+  }
   const float inv = l > 0.f ? 1.0f / l : 0.f;
-  __syncthreads();
+  if constexpr (KG == 1) __syncthreads();
   {
     unsigned char* stage = lds + (wave * 32) * ROWB;
     // (opaque copies: the addresses below are the same in both passes of a paired launch, and
@@ -507,7 +560,6 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
   // so that all workgroups do the same work: with 256-query tiles if that still leaves one
   // workgroup per compute unit, else with 128-query tiles if that leaves two.  Smaller causal
   // launches keep one 128-query tile per workgroup, heaviest tiles first.
-  if (attention_fewrows_wins(a, sk, sv)) return launch_attention_fewrows(q, k, v, o, sq, sk, sv, so, a, s);
   const int64_t n_bh = (int64_t)a.B * a.Hq;
   auto tiles = [&](int bq) { return (a.Lq + bq - 1) / bq; };
   int nw = a.Lq <= 128 ? 4 : 8;
@@ -520,21 +572,43 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
       paired = (tiles(128) % 2 == 0 && (tiles(128) / 2) * n_bh >= 512) ? 1 : 0;
     }
   }
-  const int n_qtiles = tiles(32 * nw);
+  // Launches that leave the chip idle: 64 query rows per workgroup with the keys split over two
+  // groups of wavefronts, or 16 rows (attention_fewrows.hip), by expected us.  All walk the keys in
+  // steps that overlap little until there is a workgroup per compute unit, and share the units
+  // beyond.  A tile of 64 keys takes 1.28 us with 128 rows alone on a unit (d = 64: 0.95), and 1.05
+  // (0.65) of the unit's time; a step of the two groups, 128 keys, 1.72 (1.05), and 2.0 (1.4).
+  // Measured, tiled / two groups / 16 rows: 16 heads of 512 x 2048, d = 128, 54.5 / 32.1 / 41.6;
+  // 3 x 2 heads of 2249 x 4040, causal, 86.1 / 59.4 / 94; 32 heads of 512 x 512, d = 64,
+  // 12.7 / 8.6 / 12; one head of 1371 x 2708, causal, d = 64, 39.9 / 26.9 / 17.8; 40 heads of
+  // 900 x 900, d = 128, 31 / 55 / -; 2 x 16 heads of 500 x 500, d = 128, 18.8 / 13.0 / -.
+  const bool d128 = a.d == 128;
+  const double lk = a.Lk, lq = a.Lq;
+  const double keys = !a.causal ? lk : lq <= lk ? lk - (lq - 1) / 2 : lk * (lk + 1) / (2 * lq);
+  const double turns128 = tiles(128) * n_bh / 256.0, turns64 = tiles(64) * n_bh / 256.0;
+  const double us_tiled = 3 + fmax((d128 ? 1.28 : 0.95) * lk, (d128 ? 1.05 : 0.65) * turns128 * keys) / 64;
+  const double us_groups = 4 + fmax((d128 ? 1.72 : 1.05) * lk, d128 ? 2.0 * ceil(turns64) * keys : 1.4 * turns64 * keys) / 128;
+  const double us_few = attention_fewrows_us(a, sk, sv, keys);
+  if (us_few < us_tiled && us_few <= us_groups) return launch_attention_fewrows(q, k, v, o, sq, sk, sv, so, a, s);
+  const bool split_keys = us_groups < us_tiled;
+  if (split_keys) { nw = 4; paired = 0; }
+  const int n_qtiles = tiles(split_keys ? 64 : 32 * nw);
   const int64_t grid = (paired ? n_qtiles / 2 : n_qtiles) * n_bh;
   if (grid > INT32_MAX) return hipErrorInvalidValue;
   const float sl2 = a.scale * kLog2e;
-#define RF_LAUNCH_ATTN(DD, NWW, PP)                                                               \
-  hipLaunchKernelGGL((attention_bf16_kernel<DD, NWW, PP>), dim3((unsigned)grid), dim3(NWW * kWave), 0, s, \
+#define RF_LAUNCH_ATTN(...) RF_LAUNCH_ATTN_LDS(0, __VA_ARGS__)
+#define RF_LAUNCH_ATTN_LDS(LDSB, DD, NWW, ...)                                                    \
+  hipLaunchKernelGGL((attention_bf16_kernel<DD, NWW, __VA_ARGS__>), dim3((unsigned)grid), dim3(NWW * kWave), LDSB, s, \
                      (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, sq, sk, sv, so, \
                      a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal, n_qtiles)
   if (a.d == 128) {
-    if (paired && nw == 8) RF_LAUNCH_ATTN(128, 8, true);
+    if (split_keys) RF_LAUNCH_ATTN_LDS(131072, 128, 4, false, 2);
+    else if (paired && nw == 8) RF_LAUNCH_ATTN(128, 8, true);
     else if (paired) RF_LAUNCH_ATTN(128, 4, true);
     else if (nw == 4) RF_LAUNCH_ATTN(128, 4, false);
     else RF_LAUNCH_ATTN(128, 8, false);
   } else if (a.d == 64) {
-    if (paired && nw == 8) RF_LAUNCH_ATTN(64, 8, true);
+    if (split_keys) RF_LAUNCH_ATTN_LDS(65536, 64, 4, false, 2);
+    else if (paired && nw == 8) RF_LAUNCH_ATTN(64, 8, true);
     else if (paired) RF_LAUNCH_ATTN(64, 4, true);
     else if (nw == 4) RF_LAUNCH_ATTN(64, 4, false);
     else RF_LAUNCH_ATTN(64, 8, false);
@@ -542,6 +616,7 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
     return hipErrorInvalidValue;
   }
 #undef RF_LAUNCH_ATTN
+#undef RF_LAUNCH_ATTN_LDS
   return hipGetLastError();
 }
 

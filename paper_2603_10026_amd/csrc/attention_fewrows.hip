@@ -18,6 +18,8 @@
 //
 // DIRECT: the whole key range, O = acc / l in bf16.  Otherwise one chunk of the key axis, its
 // state (m, l, acc) in fp32.
+#include <math.h>
+
 #include "rf_device.h"
 #include "rf_launch.h"
 
@@ -65,12 +67,23 @@ __global__ __launch_bounds__(NW * kWave, few_min_waves(DIRECT)) void attention_f
   // chunk of keys go to one XCD.
   int wg = blockIdx.x;
   if ((gridDim.x & 7) == 0) wg = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-  int rt = wg % n_rtiles;
-  // Under a causal mask the first half of a head's workgroups takes the late rows, which see the
-  // most keys, heaviest first, the second half the early ones, lightest first.
-  if (causal) rt = rt < (n_rtiles + 1) / 2 ? n_rtiles - 1 - rt : rt - (n_rtiles + 1) / 2;
-  rt = __builtin_amdgcn_readfirstlane(rt);
   const int unit = __builtin_amdgcn_readfirstlane(wg / n_rtiles);
+  int rt = wg % n_rtiles;
+  if (causal) {
+    // Late rows see the most keys.  The 32 compute units of an XCD take workgroups one after the
+    // other, so those 32 apart share one: blocks of 32 heavy tiles, heaviest first, and of 32 light
+    // ones, lightest first, take turns, and what is left of a head (all of a short one) runs
+    // upwards in even heads and downwards in odd ones.
+    const int full = n_rtiles & ~63;
+    if (rt < full) {
+      const int i = (rt >> 6) * 32 + (rt & 31);
+      rt = (rt & 32) ? i : n_rtiles - 1 - i;
+    } else {
+      const int i = rt - full;
+      rt = full / 2 + ((unit & 1) ? n_rtiles - full - 1 - i : i);
+    }
+  }
+  rt = __builtin_amdgcn_readfirstlane(rt);
   const int c = __builtin_amdgcn_readfirstlane(unit % S);
   const int hk = __builtin_amdgcn_readfirstlane(unit / S % Hkv);
   const int b = __builtin_amdgcn_readfirstlane(unit / S / Hkv);
@@ -276,23 +289,13 @@ static bool offsets_fit(const AttnShape& a, const Strides4& sk, const Strides4& 
   return a.Lk >= 1 && ok(sk.l) && ok(sv.l);
 }
 
-// Expected times of the two kernels in us.  Both walk the keys in steps, with the chip idle until
-// there is a workgroup per compute unit, and with that many more steps per unit beyond.  Measured
-// per step of 128 keys here: 1.13 us alone, 1.25 in turns (d = 128), 0.75 and 1.1 (d = 64); per
-// step of 64 keys and 128 rows in the tiled kernel: 1.28 and 1.05, 0.95 and 0.65.  One head of
-// 1371 queries over 2708 keys, causal, d = 64: 17.7 us here against 40.0; 4 rows of 16 heads over
-// 1415 keys: 10.8 against 23.0; 8 x 1024 queries and keys, causal, d = 128: 19.4 against 25.0;
-// 16 x 1024, causal, d = 64: 22.0 against 18.1.
-bool attention_fewrows_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
-  if (!offsets_fit(a, sk, sv, kDirectWaves)) return false;
-  const double wg16 = (double)row_tiles(a) * a.B * a.Hkv;
-  const double wg128 = (double)((a.Lq + 127) / 128) * a.B * a.Hq;
-  const double lk = a.Lk, lq = a.Lq;
-  const double keys = !a.causal ? lk : lq <= lk ? lk - (lq - 1) / 2 : lk * (lk + 1) / (2 * lq);  // a row's, on average
+// Expected us.  A workgroup walks the keys in steps of 128, 1.13 us each when it is alone on its
+// compute unit (d = 64: 0.75); more workgroups than units share them, 1.25 (1.1) per step and unit.
+double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv, double keys) {
+  if (!offsets_fit(a, sk, sv, kDirectWaves)) return INFINITY;
   const bool d128 = a.d == 128;
-  const double few = fmax((d128 ? 1.13 : 0.75) * lk, (d128 ? 1.25 : 1.1) * wg16 / 256 * keys) / 128;
-  const double tiled = fmax((d128 ? 1.28 : 0.95) * lk, (d128 ? 1.05 : 0.65) * wg128 / 256 * keys) / 64;
-  return few < tiled;
+  const double turns = (double)row_tiles(a) * a.B * a.Hkv / 256;
+  return 3 + fmax((d128 ? 1.13 : 0.75) * a.Lk, (d128 ? 1.25 : 1.1) * turns * keys) / 128;
 }
 
 hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v, void* o, Strides4 sq,

@@ -36,7 +36,8 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
                                  Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                  const AttnShape& a, hipStream_t s);
 // The same for few query rows; the launchers of the tiled and of the split kernel choose them.
-bool attention_fewrows_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv);
+// (keys: what a row sees on average; infinity for what that kernel does not take)
+double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv, double keys);
 hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v, void* o, Strides4 sq,
                                     Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, hipStream_t s);
 bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv);

@@ -1,5 +1,5 @@
-"""Attention with few query rows against the fp64 oracle: the tiles of attention_fewrows.hip and
-attention_f32_few.hip at their edges and on both sides of the rules that choose them."""
+"""Attention with few query tiles against the fp64 oracle: the tiles of attention_fewrows.hip and
+attention_f32_few.hip and the two key groups of attention_bf16.hip at their edges and on both sides of the rules that choose them."""
 import sys
 
 import numpy as np
@@ -21,6 +21,11 @@ FEW_ATTENTION = [
     ("bf16", 1, 8, 2, 17, 129, 64, False), ("bf16", 3, 4, 4, 1, 257, 128, False), ("bf16", 1, 1, 1, 700, 1030, 64, True),
     ("bf16", 1, 3, 1, 33, 20, 128, True),      # Lk < Lq: early rows see no key, tiles span heads
     ("bf16", 8, 8, 8, 40, 100, 64, True),
+    # 64 rows per workgroup, the keys over two groups of wavefronts: odd numbers of key tiles, tiles that
+    # one group alone sees under the mask, ragged rows and keys
+    ("bf16", 2, 32, 8, 197, 318, 64, False), ("bf16", 4, 8, 2, 300, 314, 64, False), ("bf16", 1, 48, 48, 250, 450, 128, False),
+    ("bf16", 1, 48, 48, 250, 300, 128, False), ("bf16", 1, 48, 48, 250, 330, 128, True), ("bf16", 1, 64, 64, 200, 260, 64, True),
+    ("bf16", 1, 32, 8, 700, 700, 128, True),
     # the tiled kernel from here on: many query tiles
     ("bf16", 8, 32, 32, 200, 130, 64, False), ("bf16", 8, 32, 8, 130, 193, 128, True), ("bf16", 8, 32, 32, 300, 330, 64, True),
     ("f32", 1, 1, 1, 1, 129, 64, False), ("f32", 2, 6, 2, 3, 130, 128, True), ("f32", 1, 4, 1, 5, 511, 64, True),
