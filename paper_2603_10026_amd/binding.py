@@ -1,10 +1,11 @@
-"""ctypes binding over the C-ABI library ``librf.so``.
+"""Binding over the C-ABI library ``librf.so``.
 
-Argument marshalling only: every function builds ``rf_tensor`` descriptors
-from torch tensors (PyTorch is used for device memory and streams) and calls
-the entry point of the same name; all arithmetic runs in the HIP kernels.
-There is no fallback: if the library is missing, or an entry point returns an
-error, a Python exception is raised.
+Argument marshalling only: every function turns torch tensors (PyTorch is used
+for device memory and streams) into ``rf_tensor`` descriptors and calls the
+entry point of the same name, through ``_rfcall`` (``host/pycall.cpp``) or, for
+the diagnostics, ctypes; all arithmetic runs in the HIP kernels.  There is no
+fallback: if a library is missing, or an entry point returns an error, a Python
+exception is raised.
 """
 from __future__ import annotations
 
@@ -171,6 +172,25 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+_call = None
+
+
+def _native():
+    """The entry points that describe tensors in C++ (``_rfcall``, built with ``librf.so``): the
+    same calls as ``tensor_desc`` + ctypes, without a microsecond of Python per tensor."""
+    global _call
+    if _call is None:
+        load_library()
+        try:
+            from . import _rfcall
+        except ImportError as e:
+            raise RuntimeError("_rfcall could not be loaded: build it with `python -m paper_2603_10026_amd.build` "
+                               "(there is no fallback path)") from e
+        _rfcall.init(tensor_desc, _stream)
+        _call = _rfcall
+    return _call
+
+
 def _check(code, where):
     if code != RF_OK:
         raise RfError(code, where)
@@ -178,23 +198,16 @@ def _check(code, where):
 
 def rf_safe_softmax(x, y=None, axis=-1, stream=None):
     """y = softmax(x) over the last axis; returns y (allocated if not given)."""
-    lib = load_library()
     if y is None:
         y = torch.empty_like(x)
-    dx, dy = tensor_desc(x), tensor_desc(y)
-    _check(lib.rf_safe_softmax(ctypes.byref(dx), ctypes.byref(dy), int(axis), _stream(stream)),
-           "rf_safe_softmax")
+    _check((_call or _native()).safe_softmax(x, y, axis, stream), "rf_safe_softmax")
     return y
 
 
 def rf_cascade_attention(q, k, v, scale, causal=False, o=None, stream=None):
-    lib = load_library()
     if o is None:
         o = torch.empty_like(q)
-    dq, dk, dv, do = tensor_desc(q), tensor_desc(k), tensor_desc(v), tensor_desc(o)
-    _check(lib.rf_cascade_attention(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv),
-                                    ctypes.byref(do), float(scale), int(bool(causal)),
-                                    _stream(stream)), "rf_cascade_attention")
+    _check((_call or _native()).cascade_attention(q, k, v, o, scale, causal, stream), "rf_cascade_attention")
     return o
 
 
@@ -209,45 +222,32 @@ def alloc_partial_states(q, num_splits):
 
 def rf_cascade_attention_splitk(q, k, v, num_splits, part_m, part_l, part_acc, scale, causal=False,
                                 stream=None):
-    lib = load_library()
-    dq, dk, dv = tensor_desc(q), tensor_desc(k), tensor_desc(v)
-    dm, dl, da = tensor_desc(part_m), tensor_desc(part_l), tensor_desc(part_acc)
-    _check(lib.rf_cascade_attention_splitk(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv),
-                                           int(num_splits), ctypes.byref(dm), ctypes.byref(dl),
-                                           ctypes.byref(da), float(scale), int(bool(causal)),
-                                           _stream(stream)), "rf_cascade_attention_splitk")
+    _check((_call or _native()).cascade_attention_splitk(q, k, v, num_splits, part_m, part_l, part_acc, scale, causal,
+                                                         stream), "rf_cascade_attention_splitk")
     return part_m, part_l, part_acc
 
 
 def rf_merge_states(part_m, part_l, part_acc, o, stream=None):
-    lib = load_library()
-    dm, dl, da, do = tensor_desc(part_m), tensor_desc(part_l), tensor_desc(part_acc), tensor_desc(o)
-    _check(lib.rf_merge_states(ctypes.byref(dm), ctypes.byref(dl), ctypes.byref(da),
-                               ctypes.byref(do), _stream(stream)), "rf_merge_states")
+    _check((_call or _native()).merge_states(part_m, part_l, part_acc, o, stream), "rf_merge_states")
     return o
 
 
 def rf_rmsnorm_gemm(x, g, w, eps=1e-6, y=None, stream=None):
-    lib = load_library()
     if y is None:
         y = torch.empty((x.shape[0], w.shape[1]), dtype=x.dtype, device=x.device)
-    dx, dg, dw, dy = tensor_desc(x), tensor_desc(g), tensor_desc(w), tensor_desc(y)
-    _check(lib.rf_rmsnorm_gemm(ctypes.byref(dx), ctypes.byref(dg), ctypes.byref(dw),
-                               ctypes.byref(dy), float(eps), _stream(stream)), "rf_rmsnorm_gemm")
+    _check((_call or _native()).rmsnorm_gemm(x, g, w, y, eps, stream), "rf_rmsnorm_gemm")
     return y
 
 
 def rf_variance(x, mean=None, var=None, stream=None):
     """Mean and population variance over the last axis; returns (mean, var), fp32."""
-    lib = load_library()
-    oshape = tuple(x.shape[:-1]) if x.dim() > 1 else (1,)
-    if mean is None:
-        mean = torch.empty(oshape, dtype=torch.float32, device=x.device)
-    if var is None:
-        var = torch.empty(oshape, dtype=torch.float32, device=x.device)
-    dx, dm, dv = tensor_desc(x), tensor_desc(mean), tensor_desc(var)
-    _check(lib.rf_variance(ctypes.byref(dx), ctypes.byref(dm), ctypes.byref(dv), _stream(stream)),
-           "rf_variance")
+    if mean is None or var is None:
+        oshape = tuple(x.shape[:-1]) if x.dim() > 1 else (1,)
+        if mean is None:
+            mean = torch.empty(oshape, dtype=torch.float32, device=x.device)
+        if var is None:
+            var = torch.empty(oshape, dtype=torch.float32, device=x.device)
+    _check((_call or _native()).variance(x, mean, var, stream), "rf_variance")
     return mean, var
 
 
@@ -259,19 +259,15 @@ def rf_moe_routing(x, w, topk, prob=None, idx=None, workspace=None, stream=None)
     """Router scores -> softmax -> top-k; returns (prob [S,topk] f32, idx [S,topk] i32).
     ``workspace``: a uint8 device tensor of at least moe_routing_workspace_bytes(...) bytes
     (allocated here when omitted)."""
-    lib = load_library()
     S, hd = x.shape
-    E = w.shape[1]
     if prob is None:
         prob = torch.empty((S, topk), dtype=torch.float32, device=x.device)
     if idx is None:
         idx = torch.empty((S, topk), dtype=torch.int32, device=x.device)
     if workspace is None:
-        workspace = torch.empty(max(moe_routing_workspace_bytes(S, hd, E), 16), dtype=torch.uint8, device=x.device)
-    dx, dw, dp, di = tensor_desc(x), tensor_desc(w), tensor_desc(prob), tensor_desc(idx)
-    _check(lib.rf_moe_routing(ctypes.byref(dx), ctypes.byref(dw), int(topk), ctypes.byref(dp), ctypes.byref(di),
-                              ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
-                              _stream(stream)), "rf_moe_routing")
+        workspace = torch.empty(max(moe_routing_workspace_bytes(S, hd, w.shape[1]), 16), dtype=torch.uint8,
+                                device=x.device)
+    _check((_call or _native()).moe_routing(x, w, topk, prob, idx, workspace, stream), "rf_moe_routing")
     return prob, idx
 
 
@@ -281,21 +277,15 @@ MOE_ROUTING_NOALLOC_MAX_BYTES = 8 << 20
 def rf_moe_routing_noalloc(x, w, topk, prob, idx, stream=None):
     """rf_moe_routing with the partial scores in the library's own fixed device array: the call
     allocates nothing, so ``prob`` [S,topk] f32 and ``idx`` [S,topk] i32 must be given."""
-    lib = load_library()
-    dx, dw, dp, di = tensor_desc(x), tensor_desc(w), tensor_desc(prob), tensor_desc(idx)
-    _check(lib.rf_moe_routing_noalloc(ctypes.byref(dx), ctypes.byref(dw), int(topk), ctypes.byref(dp),
-                                      ctypes.byref(di), _stream(stream)), "rf_moe_routing_noalloc")
+    _check((_call or _native()).moe_routing_noalloc(x, w, topk, prob, idx, stream), "rf_moe_routing_noalloc")
     return prob, idx
 
 
 def rf_fp8_quant_gemm(a, w, c=None, stream=None):
     """c = dequant(quant_fp8(a) @ w^T): a [M,K] bf16, w [N,K] torch.float8_e4m3fn, c [M,N] bf16."""
-    lib = load_library()
     if c is None:
         c = torch.empty((a.shape[0], w.shape[0]), dtype=torch.bfloat16, device=a.device)
-    da, dw, dc = tensor_desc(a), tensor_desc(w), tensor_desc(c)
-    _check(lib.rf_fp8_quant_gemm(ctypes.byref(da), ctypes.byref(dw), ctypes.byref(dc), _stream(stream)),
-           "rf_fp8_quant_gemm")
+    _check((_call or _native()).fp8_quant_gemm(a, w, c, stream), "rf_fp8_quant_gemm")
     return c
 
 

@@ -1,4 +1,5 @@
-"""Build step: compile the HIP sources for gfx950 into ``librf.so`` (in-tree).
+"""Build step: compile the HIP sources for gfx950 into ``librf.so`` and the host module
+``_rfcall.so`` that the Python binding calls it through (in-tree).
 
 Usage: ``python -m paper_2603_10026_amd.build``  (hipcc cross-compiles without
 a GPU).  The library is written next to this file so that it travels with the
@@ -13,6 +14,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librf.so")
+PYCALL = os.path.join(HERE, "_rfcall.so")
 
 SOURCES = [
     "api.hip",
@@ -77,8 +79,29 @@ def build_library(verbose=True, jobs=8):
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
+    build_pycall(verbose)
     check_waits(verbose)
     return LIB
+
+
+def build_pycall(verbose=True):
+    """Compile the CPython module that hands torch tensors to librf.so (host code only)."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    inc = [os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           # what the HIP and torch headers ask of a plain host compiler
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           *[a for d in inc for a in ("-isystem", d)], os.path.join(HERE, "host", "pycall.cpp"), "-o", PYCALL,
+           f"-L{HERE}", "-l:librf.so", "-Wl,-rpath,$ORIGIN",
+           "-L" + os.path.join(tdir, "lib"), "-ltorch_python", "-ltorch", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
 
 
 def check_waits(verbose=True):

@@ -290,3 +290,46 @@ def test_tensor_descriptor_fields():
         B.tensor_desc(torch.empty(3, dtype=torch.float64))
     with pytest.raises(ValueError):
         B.tensor_desc(torch.empty(1, 1, 1, 1, 1, 1))
+
+
+def test_native_descriptors_match_the_python_ones():
+    """_rfcall reads plain tensors through their C++ object and sends the rest through
+    tensor_desc: the same bytes and the same errors for every form of tensor."""
+    n = B._native()
+    odd = torch.arange(60, dtype=torch.float32)
+    for t in (torch.zeros(7), torch.zeros(2, 0, 5, dtype=torch.bfloat16), torch.zeros(4, 6, dtype=torch.int32)[:, ::2],
+              torch.nn.Parameter(torch.zeros(1, 2, 3, 4, 5)), odd[3:].as_strided((5, 4), (1, 9)), torch.ones(3, 1).expand(3, 8),
+              torch.zeros(8, 16, dtype=torch.float8_e4m3fn).t(), torch.zeros(2, 3, requires_grad=True) * 2):
+        assert n.describe(t) == bytes(B.tensor_desc(t)), t.shape
+
+    class Sub(torch.Tensor):
+        pass
+
+    s = torch.zeros(3, 4).as_subclass(Sub)
+    assert n.describe(s) == bytes(B.tensor_desc(s))
+    for bad in (torch.zeros(3, dtype=torch.float64), torch.zeros(()), torch.zeros((1,) * 6), 3, None,
+                torch.zeros(3, 3).to_sparse()):
+        with pytest.raises(Exception) as native:
+            n.describe(bad)
+        with pytest.raises(Exception) as python:
+            B.tensor_desc(bad)
+        assert type(native.value) is type(python.value), bad
+    with pytest.raises(TypeError):
+        n.safe_softmax(odd, odd)
+
+
+def test_native_calls_refuse_what_the_abi_refuses():
+    x = torch.zeros(4, 8)
+    with pytest.raises(B.RfError):
+        B.rf_safe_softmax(x, torch.zeros(4, 9), stream=0)
+    with pytest.raises(B.RfError):
+        B.rf_safe_softmax(x, axis=0, stream=0)
+    with pytest.raises(B.RfError):
+        B.rf_variance(x, torch.zeros(4), torch.zeros(3), stream=0)
+    h = torch.zeros(1, 2, 4, 64)
+    with pytest.raises(B.RfError):
+        B.rf_cascade_attention(h, h, torch.zeros(1, 2, 5, 64), 1.0, stream=0)
+    with pytest.raises(ValueError):
+        B.rf_cascade_attention(h, h, h, "one", stream=0)
+    with pytest.raises(TypeError):
+        B.rf_safe_softmax(torch.zeros(4, 8, dtype=torch.float64), stream=0)
