@@ -315,13 +315,15 @@ hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v,
   return hipGetLastError();
 }
 
-// While K and V fit the 256 MB memory-side cache and a chunk is a few tiles, the time is latency
-// and this kernel's shorter chain wins (us, here against the streaming kernel): 8.0 / 9.5 for
-// 714 chunks of 63 keys, 15.5 / 18.0 for 1024 of 64 with 32 rows each (two row tiles in parallel
-// here, one after the other there), 36.1 / 40.2 for 1032 of 414.  Beyond, K and V stream from
-// memory and the other kernel's whole-row, non-temporal loads win: 377 / 324 for 8192 of 512.
+// While K and V are small and a chunk is a few tiles, the time is latency and this kernel's shorter
+// chain wins (us, here against the streaming kernel): 8.0 / 9.5 for 714 chunks of 63 keys, 15.5 / 18.0
+// for 1024 of 64 with 32 rows each (two row tiles in parallel here, one after the other there).
+// Beyond, K and V stream from memory and the other kernel's whole-row, non-temporal loads win: at
+// 109 MB the two take the same time on new inputs and this one is 2 us ahead on repeated ones, at 221 MB
+// it is 17 us behind on new inputs (they do not stay in the 256 MB memory-side cache until they are
+// asked for) and 2 on repeated ones, at 2 GB 377 against 324.
 bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
-  return offsets_fit(a, sk, sv, kSplitWaves) && (double)a.B * a.Hkv * a.Lk * a.d * 4 <= 256e6;
+  return offsets_fit(a, sk, sv, kSplitWaves) && (double)a.B * a.Hkv * a.Lk * a.d * 4 <= 128e6;
 }
 
 hipError_t launch_attention_fewrows_splitk(const void* q, const void* k, const void* v, Strides4 sq, Strides4 sk,

@@ -57,7 +57,7 @@ def test_attention_few_query_tiles(rf, dtype, B, Hq, Hkv, Lq, Lk, d, causal):  #
 
 
 def test_splitk_streaming_kernel_agrees_with_the_small_one(rf):  # noqa: F811
-    """More than 256 MB of K and V take the streaming kernel; the same call batch by batch takes the
+    """More than 128 MB of K and V take the streaming kernel; the same call batch by batch takes the
     other.  Their states differ by fp32 rounding and by the bf16 rounding of the probabilities."""
     B, Hq, Hkv, Lq, Lk, S = 4, 24, 8, 7, 16513, 37
     say(f"splitk streaming kernel against the small one B{B} Lk{Lk} S{S}")
