@@ -227,6 +227,9 @@ RF_API rf_status rf_merge_states(const rf_tensor* part_m, const rf_tensor* part_
  *   x : [M, K] bf16   g : [K] bf16   w : [K, N] bf16 (row-major)   y : [M, N] bf16
  *   K % 64 == 0 and N % 8 == 0 are required, and the row pitches of x and w must be below
  *   2^24 elements (RF_ERR_UNSUPPORTED otherwise); M is arbitrary.
+ *   Rounding: x g to bf16 before the product, y to bf16 at the end; everything between is fp32.  The
+ *   tile shape, and with it the order of the fp32 sums over k, is chosen by M, K and N: a row's last
+ *   bits may differ from one batch size to another.
  */
 RF_API rf_status rf_rmsnorm_gemm(const rf_tensor* x, const rf_tensor* g, const rf_tensor* w,
                           rf_tensor* y, float eps, rf_stream stream);

@@ -9,20 +9,20 @@
 //   Y^T = W^T X^T      A = W^T, B = X^T (16x16x32 bf16 MFMA)
 //
 // A lane loads C neighbouring columns of 8 rows of w, which after pairing rows in registers is
-// the A operand of C MFMAs; the row of x is the B operand as it lies in memory.  g is applied
-// on the w side (round(w g) instead of round(x g), one bf16 rounding either way): a workgroup
-// holds 16 C columns of w but may hold more rows of x, and the w values are unpacked for the
-// pairing anyway.  ss is the diagonal of X X^T, taken by the matrix pipe from the operand that
-// is in registers already.
+// the A operand of C MFMAs; the row of x times g, rounded to bf16 as in the large kernel, is the B
+// operand.  (The roundings a row meets do not depend on the kernel its batch selects: what is left
+// between the two is the order of fp32 sums.)  ss is the diagonal of X X^T, taken by the matrix
+// pipe from the x that is in registers already.
 //
 // What bounds it: the 128-byte lines a compute unit can have on their way.  A read of w alone in
-// this pattern takes 15.9 us (4096 x 4096 from HBM, C = 2, 128 workgroups), 17.7 us with whole
-// lines and half the workgroups (C = 4), and cache-policy bits change nothing; the last 50 GB/s
+// this pattern takes 15.9 us when w comes from HBM (4096 x 4096, C = 2, 128 workgroups), 17.7 us with
+// whole lines and half the workgroups (C = 4), and cache-policy bits change nothing; the last 50 GB/s
 // per compute unit are its 32 KB of L1 lines in flight over the memory latency.  Two steps in
 // flight and 4 wavefronts are therefore faster than 8 wavefronts with more (which evict each
-// other's lines): 48 x 4096 x 4096 takes 15.8 us, and 87 us in 128 x 512 tiles.  A few hundred rows
-// are bound by the same lines in either kernel, and 64 x 128 tiles move fewest of them per compute
-// unit in use: 1024 x 8192 x 2048 takes 63 us against 171.
+// other's lines): 48 x 4096 x 4096, repeated on the same w (33 MB: it stays in the memory-side cache),
+// takes 13.8 us a call, and 86.4 in 128 x 512 tiles.  A few hundred rows are bound by the same lines in
+// either kernel, and 64 x 128 tiles move fewest of them per compute unit in use: 1024 x 8192 x 2048
+// takes 57 us against 171.
 #include <math.h>
 
 #include "rf_device.h"
@@ -33,15 +33,25 @@ namespace rf {
 namespace {
 constexpr int kRWaves = 4;
 constexpr int kRThreads = kRWaves * kWave;
+
+// low halves / high halves of two packed bf16 pairs
+__device__ __forceinline__ uint32_t pair_lo(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100u); }
+__device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); }
 }  // namespace
 
-// P: steps of 32 k in flight per wavefront
+// P: steps of 32 k in flight per wavefront.  (Two workgroups per compute unit in the bounds: with
+// more registers to give away the compiler keeps the sums in accumulation registers and copies
+// them around every step, 48 x 4096 x 4096 16.5 us.)
 template <int MT, int C, int P>
-__global__ __launch_bounds__(kRThreads) void rmsnorm_gemm_rows_kernel(
+__global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ g, const bf16_t* __restrict__ w,
     bf16_t* __restrict__ y, int M, int K, int N, int64_t ldx, int64_t ldw, int64_t ldy,
     float inv_k, float eps, int n_mtiles) {
   constexpr int CD = C / 2;  // 32-bit words of w per lane and k-row
+  // Requests are waited for in order.  Two row tiles against a narrow tile of w have as much work in
+  // x g as in pairing w and start it first (48 x 4096 x 4096: 14.5 us, 15.2 the other way round);
+  // the other shapes want w first (32 x 8192 x 1024 in one row tile: 15.6 and 20.3).
+  constexpr bool kXFirst = MT == 2 && C == 2;
   __shared__ f32x4 s_acc[kRWaves][C * MT][kWave];
   __shared__ float s_ss[kRWaves][16 * MT];
 
@@ -82,6 +92,12 @@ __global__ __launch_bounds__(kRThreads) void rmsnorm_gemm_rows_kernel(
     const int ii = min(i, mine - 1);
     const uint32_t k0 = (wave + kRWaves * (ii >> 1)) * 64 + (ii & 1) * 32;
     const uint32_t wo = k0 * ldw2;
+    auto load_x = [&] {
+#pragma unroll
+      for (int t = 0; t < MT; ++t) xr[p][t] = __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane[t], k0 * 2, 0);
+      gr[p] = __builtin_amdgcn_raw_buffer_load_b128(grs, 16 * g4, k0 * 2, 0);
+    };
+    if constexpr (kXFirst) load_x();
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       if constexpr (CD == 4) {
@@ -96,9 +112,7 @@ __global__ __launch_bounds__(kRThreads) void rmsnorm_gemm_rows_kernel(
         for (int d = 0; d < CD; ++d) wr[p][e][d] = v[d];
       }
     }
-#pragma unroll
-    for (int t = 0; t < MT; ++t) xr[p][t] = __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane[t], k0 * 2, 0);
-    gr[p] = __builtin_amdgcn_raw_buffer_load_b128(grs, 16 * g4, k0 * 2, 0);
+    if constexpr (!kXFirst) load_x();
   };
 
   f32x4 acc[C][MT], sq[MT];
@@ -111,22 +125,24 @@ __global__ __launch_bounds__(kRThreads) void rmsnorm_gemm_rows_kernel(
   auto step = [&](int p) {
     u32x4 af[C];
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      const float g0 = bf16_lo(gr[p][e2]), g1 = bf16_hi(gr[p][e2]);
+    for (int e2 = 0; e2 < 4; ++e2)
 #pragma unroll
       for (int d = 0; d < CD; ++d) {
-        const uint32_t r0 = wr[p][2 * e2][d], r1 = wr[p][2 * e2 + 1][d];
-        af[2 * d][e2] = pack_bf16(bf16_lo(r0) * g0, bf16_lo(r1) * g1);
-        af[2 * d + 1][e2] = pack_bf16(bf16_hi(r0) * g0, bf16_hi(r1) * g1);
+        af[2 * d][e2] = pair_lo(wr[p][2 * e2][d], wr[p][2 * e2 + 1][d]);
+        af[2 * d + 1][e2] = pair_hi(wr[p][2 * e2][d], wr[p][2 * e2 + 1][d]);
       }
-    }
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      const bf16x8 b = __builtin_bit_cast(bf16x8, xr[p][t]);
+      const bf16x8 raw = __builtin_bit_cast(bf16x8, xr[p][t]);
+      u32x4 xg;
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2)
+        xg[e2] = pack_bf16(bf16_lo(xr[p][t][e2]) * bf16_lo(gr[p][e2]), bf16_hi(xr[p][t][e2]) * bf16_hi(gr[p][e2]));
+      const bf16x8 b = __builtin_bit_cast(bf16x8, xg);
 #pragma unroll
       for (int c = 0; c < C; ++c)
         acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[c]), b, acc[c][t], 0, 0, 0);
-      sq[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, b, sq[t], 0, 0, 0);
+      sq[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(raw, raw, sq[t], 0, 0, 0);
     }
   };
 

@@ -33,3 +33,24 @@ def test_rmsnorm_gemm_few_rows(rf, M, K, N):  # noqa: F811
     torch.cuda.synchronize()
     check(y[:, 8:N + 8], O.rmsnorm_gemm(x, g, w, 1e-6), "bf16", "rmsnorm_gemm few rows")
     assert bool(torch.isnan(y[:, :8]).all()) and bool(torch.isnan(y[:, N + 8:]).all())
+
+
+def test_rmsnorm_gemm_rows_do_not_depend_on_their_batch(rf):  # noqa: F811
+    """A row of a small batch, which the small tiles serve, and the same row in a batch of 4096 rows,
+    which the 128 x 512 tiles serve, meet the same bf16 roundings (x g, then y): they differ by the
+    order of fp32 sums alone.  Sums of 512 products in two orders lie a few 2^-24 sqrt(512) of their
+    terms apart, 2e-6 of y's scale; a bf16 value has 2^-8 to its neighbour, so that moves the rounding
+    of about one value in a thousand, by one step.  (Rounding w g instead moved half of them.)"""
+    M, K, N = 4096, 512, 4096
+    say(f"rmsnorm_gemm: rows of a batch of {M} against the same rows in small batches")
+    x, g, w = I.rmsnorm_gemm_inputs_device(I.SEED_BASE + 51, M, K, N, device=DEV)
+    whole = rf.rf_rmsnorm_gemm(x, g, w)
+    for rows in (1, 16, 33, 48, 100, 300):
+        part = rf.rf_rmsnorm_gemm(x[7:7 + rows], g, w).double()
+        torch.cuda.synchronize()
+        want = whole[7:7 + rows].double()
+        moved = float((part != want).double().mean())
+        print(f"        {rows} rows: {moved:.2e} of the values moved", flush=True)
+        assert moved <= 5e-3, rows
+        assert float((part - want).norm() / want.norm()) <= 2e-4, rows
+        assert bool(((part - want).abs() <= 2.0 ** -7 * want.abs() + 1e-4 * want.abs().max()).all())
