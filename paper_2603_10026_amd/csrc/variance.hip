@@ -19,6 +19,8 @@
 // goes through chunks of 4, 2 and 1 vectors per lane); lanes merge through DPP / shuffles,
 // wavefronts through LDS.  HBM traffic is one read of x.  Rows may start at any element: all
 // loads are 16-byte vectors at whatever alignment that gives.
+#include <math.h>
+
 #include <type_traits>
 
 #include "rf_device.h"
@@ -51,15 +53,16 @@ __device__ __forceinline__ VarState var_merge_equal(const VarState& a, const Var
   r.m2 = a.m2 + b.m2 + d * d * (0.5f * a.n);
   return r;
 }
-// exact state of the first `cnt` of V values held in registers
+// Exact state of the first `cnt` of V values held in registers.  (Here and below the values are scaled by
+// 1 / V, a power of two, before they are added up: the same bits, and no sum past the end of fp32.)
 template <int V>
 __device__ __forceinline__ VarState var_of_vector(const float* f, int cnt) {
   VarState r;
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < V; ++i) s += (i < cnt) ? f[i] : 0.f;
+  for (int i = 0; i < V; ++i) s = (i < cnt) ? fmaf(f[i], 1.0f / V, s) : s;
   r.n = (float)cnt;
-  r.mean = cnt > 0 ? s / (float)cnt : 0.f;
+  r.mean = cnt > 0 ? s * ((float)V / (float)cnt) : 0.f;
   float q = 0.f;
 #pragma unroll
   for (int i = 0; i < V; ++i) {
@@ -74,9 +77,9 @@ __device__ __forceinline__ VarState var_of_full_vector(const float* f) {
   VarState r;
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < V; ++i) s += f[i];
+  for (int i = 0; i < V; ++i) s = fmaf(f[i], 1.0f / V, s);
   r.n = (float)V;
-  r.mean = s * (1.0f / V);
+  r.mean = s;
   float q = 0.f;
 #pragma unroll
   for (int i = 0; i < V; ++i) {
@@ -149,7 +152,10 @@ __global__ __launch_bounds__(kVarRowsThreads) void variance_rows_kernel(
     return lanes_sum(s);
   };
   const float inv_n = 1.0f / (float)n;
-  const float mean = row_sum([](float v) { return v; }) * inv_n;
+  float mean = row_sum([](float v) { return v; }) * inv_n;
+  // (a sum past the end of fp32 is not a mean past it: the terms are divided first then.  All lanes of
+  // a row agree.)
+  if (!(fabsf(mean) < INFINITY)) mean = row_sum([inv_n](float v) { return v * inv_n; });
   const float m2 = row_sum([mean](float v) { return (v - mean) * (v - mean); });
   if (sub == 0 && row < rows) {
     mean_out[row] = mean;

@@ -4,6 +4,7 @@ lane, wavefronts per row, the registers of a workgroup), at every alignment an e
 x and y aligned differently, in place, with the bytes around every output row left as they were."""
 import sys
 
+import numpy as np
 import pytest
 import torch
 
@@ -63,3 +64,23 @@ def test_variance_ragged_rows(rf, dtype):  # noqa: F811
                 assert float(var.abs().max()) == 0.0
             else:
                 check(var, v_ref, "f32", "variance ragged var")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_variance_mean_of_large_values(rf, dtype):  # noqa: F811
+    """A mean is in range wherever its row is, also where the sum of the row, or of one vector of it, is
+    not: values of 1e36 and of 2e38, in rows of less than a vector up to the longest that stay in
+    registers and beyond, aligned or not."""
+    for n in (3, 5, 33, 64, 250, 1000, 1537, 2047, 2048, 20000, 20001):
+        for rows in (3, 1030) if n < 5000 else (3,):
+            for big in (1e36, 2e38):
+                say(f"variance of large values {dtype} rows={rows} n={n} {big}")
+                rng = np.random.Generator(np.random.PCG64(n))
+                x = I.bf16_round((rng.uniform(0.5, 1.5, (rows, n)) * big).astype(np.float32))
+                x[1] = -x[1]
+                if big < 1e38:
+                    x[2, ::2] *= -0.5
+                mean, var = rf.rf_variance(I.to_torch(x, dtype, DEV))
+                torch.cuda.synchronize()
+                want = x.astype(np.float64).mean(axis=1)
+                assert np.all(np.abs(I.to_numpy(mean) - want) <= 1e-5 * big), (n, big)
