@@ -48,6 +48,19 @@ __device__ __forceinline__ void ragged_store(T* row, int idx, int n, const u32x4
   constexpr int V = Elem<T>::kPerVec;
   __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any*>(row + min(idx * V, n - V)));
 }
+// What the exponents are formed with, exp2(e log2 e + this).  A maximum whose product with log2 e leaves
+// fp32 (rows of nothing but the type's lowest value) is subtracted from the values first.
+template <int N, int V>
+__device__ __forceinline__ float exponent_base(float (&e)[N][V], float m) {
+  if (fabsf(m) >= 2e38f) {
+#pragma unroll
+    for (int c = 0; c < N; ++c)
+#pragma unroll
+      for (int i = 0; i < V; ++i) e[c][i] -= m;
+    return 0.f;
+  }
+  return -m * kLog2e;
+}
 // Exponentials of a vector, in place; returns s + their sum.
 template <int V>
 __device__ __forceinline__ float exp_sum(float s, float* e, float mb) {
@@ -155,7 +168,7 @@ void softmax_row_in_regs_kernel(
       for (int i = 0; i < V; ++i) m = fmaxf(m, e[c][i]);
     m = wave_max(m);
     // cascade stage 2: sum of exp(x - m), exponentials kept for the epilogue
-    const float mb = -m * kLog2e;
+    const float mb = exponent_base(e, m);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       if constexpr (RAGGED) l = ragged_exp_sum<V>(l, e[c], mb, c * kWave + lane, n, (c + 1) * kWave * V <= n);
@@ -210,8 +223,9 @@ __global__ __launch_bounds__(kSoftmaxWavesPerWg * kWave) void softmax_short_rows
   for (int i = 1; i < V; ++i) m = fmaxf(m, e[i]);
 #pragma unroll
   for (int off = LPR / 2; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-  const float mb = -m * kLog2e;
-  float l = RAGGED ? ragged_exp_sum<V>(0.f, e, mb, sub, n, false) : exp_sum<V>(0.f, e, mb);
+#pragma unroll
+  for (int i = 0; i < V; ++i) e[i] -= m;  // (as exponent_base: here cheaper than a branch)
+  float l = RAGGED ? ragged_exp_sum<V>(0.f, e, 0.f, sub, n, false) : exp_sum<V>(0.f, e, 0.f);
 #pragma unroll
   for (int off = LPR / 2; off > 0; off >>= 1) l += __shfl_xor(l, off, kWave);
   const float inv = 1.0f / l;
@@ -265,7 +279,7 @@ __global__ __launch_bounds__(WAVES * kWave) void softmax_row_in_regs_wg_kernel(
 #pragma unroll
   for (int w = 0; w < WAVES; ++w) m = fmaxf(m, s_max[w]);
   // cascade stage 2: sum of exp(x - m), exponentials kept for the epilogue
-  const float mb = -m * kLog2e;
+  const float mb = exponent_base(e, m);
   float l = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
@@ -309,8 +323,11 @@ __global__ __launch_bounds__(kStreamThreads) void softmax_row_streaming_kernel(
   const T* xr = x + row * x_pitch;
   T* yr = y + row * y_pitch;
   const int64_t nvec = n / V;   // full vectors; the rest is handled element-wise
-  // level-1 incremental state per lane
-  float m = -INFINITY, l = 0.f;
+  // Level-1 incremental state per lane.  The reference starts at kLowRef in place of -inf: against it
+  // masked values (-inf or the type's lowest) give 0, as they have to once a larger one arrives, and no
+  // exponent is formed from two infinities.
+  constexpr float kLowRef = -2e38f;
+  float m = kLowRef, l = 0.f;
   {
     const u32x4_any* xv = reinterpret_cast<const u32x4_any*>(xr);
     for (int64_t j = threadIdx.x; j < nvec; j += kStreamThreads) {
@@ -324,7 +341,7 @@ __global__ __launch_bounds__(kStreamThreads) void softmax_row_streaming_kernel(
       float sum = 0.f;
 #pragma unroll
       for (int i = 0; i < V; ++i) sum += fast_exp2(fmaf(f[i], kLog2e, mb));
-      l = l * fast_exp2((m - mn) * kLog2e) + sum;  // exp(m - mn) with m = -inf and l = 0 adds nothing
+      l = l * fast_exp2((m - mn) * kLog2e) + sum;
       m = mn;
     }
   }
@@ -334,21 +351,40 @@ __global__ __launch_bounds__(kStreamThreads) void softmax_row_streaming_kernel(
     l = l * fast_exp2((m - mn) * kLog2e) + fast_exp2((v - mn) * kLog2e);
     m = mn;
   }
-  // merge lane states across the wavefront: l_c * exp(m_c - m)
-  const float mw = wave_max(m);
-  float lw = (m == -INFINITY) ? 0.f : l * fast_exp2((m - mw) * kLog2e);
-  lw = wave_sum(lw);
+  // merge lane states across the wavefront, then across wavefronts: l_c * exp(m_c - m)
   const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) { sm[wave] = mw; sl[wave] = lw; }
-  __syncthreads();
-  float mg = -INFINITY;
+  auto all_max = [&](float v) {
+    v = wave_max(v);
+    if ((threadIdx.x & 63) == 0) sm[wave] = v;
+    __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kStreamThreads / kWave; ++w) mg = fmaxf(mg, sm[w]);
-  float lg = 0.f;
+    for (int w = 0; w < kStreamThreads / kWave; ++w) v = fmaxf(v, sm[w]);
+    return v;
+  };
+  auto all_sum = [&](float v) {
+    v = wave_sum(v);
+    if ((threadIdx.x & 63) == 0) sl[wave] = v;
+    __syncthreads();
+    v = sl[0];
 #pragma unroll
-  for (int w = 0; w < kStreamThreads / kWave; ++w)
-    lg += (sm[w] == -INFINITY) ? 0.f : sl[w] * fast_exp2((sm[w] - mg) * kLog2e);
-  const float inv = 1.0f / lg;
+    for (int w = 1; w < kStreamThreads / kWave; ++w) v += sl[w];
+    return v;
+  };
+  const float mg = all_max(m);
+  if (!(mg > kLowRef && mg < -kLowRef)) {  // uniform
+    // Nothing but masked values, or a maximum whose product with log2 e leaves fp32: one element at a
+    // time, differences first.
+    float mx = -INFINITY, t = 0.f;
+    for (int64_t j = threadIdx.x; j < n; j += kStreamThreads) mx = fmaxf(mx, Elem<T>::load(xr + j));
+    __syncthreads();  // the maxima of the first sweep have been read
+    mx = all_max(mx);
+    for (int64_t j = threadIdx.x; j < n; j += kStreamThreads) t += fast_exp2((Elem<T>::load(xr + j) - mx) * kLog2e);
+    const float inv = 1.0f / all_sum(t);
+    for (int64_t j = threadIdx.x; j < n; j += kStreamThreads)
+      Elem<T>::store(yr + j, fast_exp2((Elem<T>::load(xr + j) - mx) * kLog2e) * inv);
+    return;
+  }
+  const float inv = 1.0f / all_sum(l * fast_exp2((m - mg) * kLog2e));
   const float mb = -mg * kLog2e;
   {
     const u32x4_any* xv = reinterpret_cast<const u32x4_any*>(xr);

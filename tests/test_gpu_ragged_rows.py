@@ -84,3 +84,35 @@ def test_variance_mean_of_large_values(rf, dtype):  # noqa: F811
                 torch.cuda.synchronize()
                 want = x.astype(np.float64).mean(axis=1)
                 assert np.all(np.abs(I.to_numpy(mean) - want) <= 1e-5 * big), (n, big)
+
+
+@pytest.mark.parametrize("mask", ["inf", "lowest"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_softmax_masked_rows(rf, dtype, mask):  # noqa: F811
+    """Masked logits, by -inf or by the type's lowest value: a prefix (every lane's first vectors), a
+    suffix, scattered ones and whole vectors, in every kernel (several rows per wavefront, one, a
+    workgroup, two sweeps), aligned or not.  A row of nothing but the lowest value is uniform, one of
+    nothing but -inf is NaN, as by the definition."""
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    mv = float("-inf") if mask == "inf" else torch.finfo(td).min
+    for n in (5, 24, 100, 1000, 4096, 4099, 16384, 50001, 65537, 70000, 128256):
+        for off in (0, 1):
+            say(f"softmax masked by {mask} {dtype} n={n} offset {off}")
+            x = torch.from_numpy(I.softmax_inputs(I.SEED_BASE + 90 + n, 6, n, 2.0, dtype)).to(td)
+            x[0, : n // 2] = mv
+            x[1, n // 2:] = mv
+            x[2, ::3] = mv
+            x[3, 1:] = mv
+            x[4, : n - n // 40 - 1] = mv
+            x[5] = mv
+            xb = torch.full((6, n + 8), 50.0, dtype=td, device=DEV)
+            xb[:, off:off + n] = x.to(DEV)
+            y = rf.rf_safe_softmax(xb[:, off:off + n], torch.empty((6, n + 8), dtype=td, device=DEV)[:, off:off + n])
+            torch.cuda.synchronize()
+            ref = O.safe_softmax(x[:5].double().numpy())
+            for r in range(5):                     # row by row: their scales differ
+                check(y[r:r + 1], ref[r:r + 1], dtype, f"softmax masked, row {r}")
+            if mask == "inf":
+                assert bool(torch.isnan(y[5]).all())
+            else:
+                assert float((y[5].double() * n - 1).abs().max()) <= 1e-2
