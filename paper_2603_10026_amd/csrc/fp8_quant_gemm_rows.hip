@@ -16,7 +16,8 @@
 //      weight tiles, takes max |a| of its tiles and tells the others the maximum of the run.
 //   2. A tile is quantised with the prefix maximum that includes it, the same codes the large
 //      kernel forms; the sums are rescaled where the maximum moved.  A wavefront's sums are in
-//      units of its own last maximum and are added up as acc * m.
+//      units of its own last maximum; they are added up in units of the token's (as in the large
+//      kernel, only the result has to be in range).
 #include <math.h>
 
 #include "rf_device.h"
@@ -47,7 +48,7 @@ __global__ __launch_bounds__(kFThreads, 2) void fp8_quant_gemm_rows_kernel(
   constexpr int kTiles = NT * MT;
   constexpr int kG = kTiles < kFRedTiles ? kTiles : kFRedTiles;
   static_assert(kTiles % kG == 0 && TPW % PW == 0, "whole groups of tiles");
-  __shared__ float s_max[kFWaves][16 * MT];
+  __shared__ float s_max[kFWaves][16 * MT], s_all[16 * MT];
   __shared__ f32x4 s_red[kFWaves * kG * kWave];
 
   const int tid = threadIdx.x;
@@ -135,15 +136,18 @@ __global__ __launch_bounds__(kFThreads, 2) void fp8_quant_gemm_rows_kernel(
 
   // ---- products ----
   f32x4 acc[NT][MT];  // acc[n][t][r] = C[token 16 t + i16][channel 16 n + 4 g4 + r], in units of m_run[t]
-  float before[MT], m_run[MT], qscale[MT];
+  float before[MT], all[MT], m_run[MT], qscale[MT];
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
     before[t] = 0.f;
+    all[t] = 0.f;
 #pragma unroll
-    for (int wv = 0; wv < kFWaves - 1; ++wv) {
+    for (int wv = 0; wv < kFWaves; ++wv) {
       const float o = s_max[wv][16 * t + i16];
       before[t] = wv < wave ? fmaxf(before[t], o) : before[t];
+      all[t] = fmaxf(all[t], o);
     }
+    if (wave == 0 && g4 == 0) s_all[16 * t + i16] = all[t];
     m_run[t] = 0.f;
     qscale[t] = 0.f;
 #pragma unroll
@@ -188,13 +192,16 @@ __global__ __launch_bounds__(kFThreads, 2) void fp8_quant_gemm_rows_kernel(
   }
 
   // ---- add the wavefronts' sums ----
+  float unit[MT];  // this wavefront's maximum in units of the token's
+#pragma unroll
+  for (int t = 0; t < MT; ++t) unit[t] = (m_run[t] == all[t]) ? 1.0f : m_run[t] * fast_rcp(all[t]);
 #pragma unroll
   for (int q0 = 0; q0 < kTiles; q0 += kG) {
     if (q0 > 0) __syncthreads();  // the previous group's sums have been read
 #pragma unroll
     for (int q = 0; q < kG; ++q) {
       const int t = (q0 + q) % MT, n = (q0 + q) / MT;
-      s_red[(wave * kG + q) * kWave + lane] = acc[n][t] * (m_run[t] * (1.0f / kE4M3Max));
+      s_red[(wave * kG + q) * kWave + lane] = acc[n][t] * unit[t];
     }
     __syncthreads();
     for (int idx = tid; idx < kG * kWave; idx += kFThreads) {
@@ -203,6 +210,7 @@ __global__ __launch_bounds__(kFThreads, 2) void fp8_quant_gemm_rows_kernel(
 #pragma unroll
       for (int wv = 1; wv < kFWaves; ++wv) v += s_red[(wv * kG + q) * kWave + l];
       const int t = (q0 + q) % MT, n = (q0 + q) / MT;
+      v *= s_all[16 * t + (l & 15)] * (1.0f / kE4M3Max);
       const int m = m0 + 16 * t + (l & 15);
       const int col = n0 + 16 * n + 4 * (l >> 4);
       if (m < M && col < N) {  // (N is a multiple of 8: four channels are all in or all out)

@@ -39,3 +39,20 @@ def test_fp8_quant_gemm_few_rows(rf, M, K, N):  # noqa: F811
     torch.cuda.synchronize()
     F.check(I.to_numpy(c[:, 8:N + 8]), a, w, "fp8_quant_gemm few rows", first_max_rows=first)
     assert bool(torch.isnan(c[:, :8]).all()) and bool(torch.isnan(c[:, N + 8:]).all())
+
+
+@pytest.mark.parametrize("M,K,N", [(4, 1024, 256), (40, 2048, 520), (16, 4096, 264), (3, 8192, 264), (2000, 1024, 512)])
+def test_fp8_quant_gemm_only_the_result_has_to_be_in_range(rf, M, K, N):  # noqa: F811
+    """Sums over parts of the contraction axis that leave fp32 while the whole does not: 2^114 times 256 over
+    half of the axis, the same less over the other half.  Every product is exact in FP8, so the result is."""
+    say(f"fp8_quant_gemm range M{M} K{K} N{N}")
+    a = np.full((M, K), 2.0 ** 114, dtype=np.float32)
+    a[:, K // 2:] = -(2.0 ** 114)
+    a[:, K - 16:] = 0.0
+    a[M // 2] *= 0.25
+    w = torch.full((N, K), 256.0, device=DEV).to(torch.float8_e4m3fn)
+    c = rf.rf_fp8_quant_gemm(I.to_torch(a, "bf16", DEV), w)
+    torch.cuda.synchronize()
+    want = torch.full((M, N), 2.0 ** 126, dtype=torch.float64)
+    want[M // 2] *= 0.25
+    assert torch.equal(c.double().cpu(), want)
