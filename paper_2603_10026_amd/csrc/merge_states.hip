@@ -13,7 +13,9 @@ constexpr int kMergeThreads = 256;
 
 constexpr int kPre = 8;  // acc loads a thread can issue before it knows the weights
 
-template <bool OUT_BF16, bool PREFETCHED>
+// PRE 2: at most 64 chunks and kPre per thread.  PRE 1: at most kPre per thread (narrow heads with more
+// chunks): acc is requested at once as well, the weights are formed as for any number.  PRE 0: any number.
+template <bool OUT_BF16, int PRE>
 __global__ __launch_bounds__(kMergeThreads) void merge_states_kernel(
     const float* __restrict__ part_m, const float* __restrict__ part_l,
     const float* __restrict__ part_acc, void* __restrict__ o, int Hq, int Lq, int S, int d,
@@ -35,13 +37,13 @@ __global__ __launch_bounds__(kMergeThreads) void merge_states_kernel(
 
   float m, l, wgt = 0.f;
   f32x4 pre[kPre];
-  if (PREFETCHED) {
-    // At most 64 chunks and kPre per thread: everything is requested at once, so the whole kernel
-    // pays one memory latency, and every wavefront forms m, l and the chunks' weights by itself,
-    // a chunk per lane: no barrier and no second trip for them.
+  float mc = -INFINITY, lc = 0.f;
+  if constexpr (PRE == 2) {
     const int lane = tid & 63;
-    const float mc = lane < S ? pm[lane] : -INFINITY;
-    const float lc = lane < S ? pl[lane] : 0.f;
+    mc = lane < S ? pm[lane] : -INFINITY;
+    lc = lane < S ? pl[lane] : 0.f;
+  }
+  if constexpr (PRE > 0) {
     const int G0 = kMergeThreads / ncol_p2;
     const int c0 = tid % ncol_p2, sg0 = tid / ncol_p2;
 #pragma unroll
@@ -50,6 +52,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_states_kernel(
       pre[i] = (s < S && c0 < d / 4) ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(pa + (int64_t)s * d + 4 * c0))
                                      : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+  }
+  if constexpr (PRE == 2) {
+    // Everything is on its way at once, so the whole kernel pays one memory latency, and every
+    // wavefront forms m, l and the chunks' weights by itself, a chunk per lane: no barrier and no
+    // second trip for them.
     m = wave_max(mc);
     const float m_use = (m == -INFINITY) ? 0.f : m;
     wgt = (mc == -INFINITY) ? -1.f : fast_exp2((mc - m_use) * kLog2e);  // -1: an empty chunk
@@ -83,13 +90,18 @@ __global__ __launch_bounds__(kMergeThreads) void merge_states_kernel(
   const int c = tid % ncol_p2;
   const int sg = tid / ncol_p2;
   f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (PREFETCHED) {
+  if constexpr (PRE > 0) {
     // (the kPre loads of this thread were issued at kernel entry)
 #pragma unroll
     for (int i = 0; i < kPre; ++i) {
       const int s = sg + i * G;
-      const float w = __shfl(wgt, s & 63, 64);  // (all lanes: the weight of chunk s is in lane s)
-      if (s < S && !(w < 0.f)) sum += pre[i] * w;
+      if constexpr (PRE == 2) {
+        const float w = __shfl(wgt, s & 63, 64);  // (all lanes: the weight of chunk s is in lane s)
+        if (s < S && !(w < 0.f)) sum += pre[i] * w;
+      } else if (s < S && c < ncol) {
+        const float ms = pm[s];
+        if (ms != -INFINITY) sum += pre[i] * fast_exp2((ms - m_use) * kLog2e);
+      }
     }
   } else if (c < ncol) {
     for (int s = sg; s < S; s += G) {
@@ -126,12 +138,15 @@ hipError_t launch_merge_states(const float* part_m, const float* part_l, const f
   int p2 = 1;
   while (p2 < ncol) p2 <<= 1;
   if (p2 > kMergeThreads) return hipErrorInvalidValue;
-  const bool pre = S <= kWave && S <= kPre * (kMergeThreads / p2);
+  // (us, PRE 1 against 0: 1024 rows of 128 chunks, d = 64, 6.5 and 10.0; of 200 chunks, d = 32, 7.0 and 10.0)
+  const int pre = S > kPre * (kMergeThreads / p2) ? 0 : S > kWave ? 1 : 2;
 #define RF_MERGE_LAUNCH(B16, PRE)                                                                  \
   hipLaunchKernelGGL((merge_states_kernel<B16, PRE>), dim3((unsigned)rows), dim3(kMergeThreads), 0, \
                      s, part_m, part_l, part_acc, o, Hq, Lq, S, d, p2, so)
-  if (o_is_bf16) { if (pre) RF_MERGE_LAUNCH(true, true); else RF_MERGE_LAUNCH(true, false); }
-  else { if (pre) RF_MERGE_LAUNCH(false, true); else RF_MERGE_LAUNCH(false, false); }
+#define RF_MERGE(B16) \
+  if (pre == 2) RF_MERGE_LAUNCH(B16, 2); else if (pre == 1) RF_MERGE_LAUNCH(B16, 1); else RF_MERGE_LAUNCH(B16, 0)
+  if (o_is_bf16) { RF_MERGE(true); } else { RF_MERGE(false); }
+#undef RF_MERGE
 #undef RF_MERGE_LAUNCH
   return hipGetLastError();
 }

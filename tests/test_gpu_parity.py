@@ -321,6 +321,13 @@ def test_merge_states_alone(rf, S, d, out_dtype):
     check(o, ref, out_dtype, "merge")
 
 
+@pytest.mark.parametrize("S,d,out_dtype", [(64, 64, "f32"), (65, 64, "f32"), (128, 64, "bf16"), (129, 64, "f32"), (200, 32, "f32"),
+                                           (257, 32, "bf16"), (512, 16, "f32"), (1000, 8, "f32"), (65, 100, "f32"), (33, 256, "f32")])
+def test_merge_states_narrow_heads(rf, S, d, out_dtype):
+    """More chunks than a wavefront has lanes, with as many as a workgroup can request at once and one more."""
+    test_merge_states_alone(rf, S, d, out_dtype)
+
+
 # --------------------------------------------------------- RMSNorm + linear
 @pytest.mark.parametrize("M,K,N", [(128, 256, 128), (77, 64, 72), (300, 512, 264), (1, 128, 8), (256, 1024, 384)])
 def test_rmsnorm_gemm_shapes(rf, M, K, N):
