@@ -49,6 +49,15 @@ RF_API rf_status rf_diag_attention_wide(const rf_tensor* q, const rf_tensor* k, 
                                         rf_tensor* o, float scale, rf_stream stream);
 
 /*
+ * Which kernel rf_cascade_attention runs for a call (host code only: the tensors' data is not
+ * looked at and no device is needed), so that a test can state what it covers.  bf16:
+ *   1, 2  tiled, 128 or 256 query rows per workgroup    3, 4  the same with two query tiles each
+ *   5     64 rows, keys over two groups of wavefronts   6     16 packed rows
+ * 0 for calls that it refuses and for other dtypes.
+ */
+RF_API int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal);
+
+/*
  * Measurement aids, not part of the cascaded-reduction path.  They provide the two
  * measured ceilings that roofline fractions are reported next to (a plain copy kernel for
  * HBM, an MFMA-only loop for the matrix pipe) and the reference dispatch that scales the

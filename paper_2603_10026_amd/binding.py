@@ -40,6 +40,7 @@ ENTRY_POINTS = (
 # measurement aids and the fusion-level study, declared in include/rf_diag.h
 DIAG_ENTRY_POINTS = (
     "rf_diag_softmax_level",
+    "rf_diag_attention_route",
     "rf_diag_attention_wide",
     "rf_diag_copy",
     "rf_diag_read",
@@ -110,6 +111,8 @@ def load_library():
     lib.rf_diag_attention_wide.argtypes = [P, P, P, P, ctypes.c_float, ctypes.c_void_p]
     lib.rf_diag_attention_wide.restype = ctypes.c_int
     lib.rf_diag_softmax_level.argtypes = [P, P, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+    lib.rf_diag_attention_route.restype = ctypes.c_int
+    lib.rf_diag_attention_route.argtypes = [P, P, P, ctypes.c_int]
     lib.rf_diag_copy.restype = ctypes.c_int
     lib.rf_diag_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
     lib.rf_diag_read.restype = ctypes.c_int
@@ -297,6 +300,13 @@ def rf_diag_softmax_level(x, y, level, ml_buf=None, stream=None):
     _check(lib.rf_diag_softmax_level(ctypes.byref(dx), ctypes.byref(dy), int(level), p, _stream(stream)),
            "rf_diag_softmax_level")
     return y
+
+
+def rf_diag_attention_route(q, k, v, causal=False):
+    """Number of the kernel that rf_cascade_attention runs for such a call (include/rf_diag.h); works on
+    tensors of any device, ``meta`` among them."""
+    dq, dk, dv = tensor_desc(q), tensor_desc(k), tensor_desc(v)
+    return load_library().rf_diag_attention_route(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv), int(bool(causal)))
 
 
 def rf_diag_attention_wide(q, k, v, scale, o=None, stream=None):

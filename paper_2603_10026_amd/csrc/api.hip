@@ -323,6 +323,13 @@ rf_status rf_cascade_attention(const rf_tensor* q, const rf_tensor* k, const rf_
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
 }
 
+int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal) {
+  rf::AttnShape a{};
+  if (check_qkv(q, k, v, &a) != RF_OK || (a.d != 64 && a.d != 128) || q->dtype != RF_BF16) return 0;
+  a.causal = causal != 0;
+  return (int)rf::attention_bf16_route(a, strides4(k), strides4(v));
+}
+
 rf_status rf_diag_attention_wide(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v,
                                  rf_tensor* o, float scale, rf_stream stream) {
   rf::AttnShape a{};

@@ -551,9 +551,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   }  // pass
 }
 
-hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, void* o, Strides4 sq,
-                                 Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a,
-                                 hipStream_t s) {
+AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
   // Without a mask the larger workgroup wins (fewer loads per MFMA).  Under a causal mask the
   // query tiles of a head see different numbers of keys; a launch with enough heads gives
   // every workgroup two tiles of one head, the heaviest with the lightest and so on inwards,
@@ -573,25 +571,43 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
     }
   }
   // Launches that leave the chip idle: 64 query rows per workgroup with the keys split over two
-  // groups of wavefronts, or 16 rows (attention_fewrows.hip), by expected us.  All walk the keys in
-  // steps that overlap little until there is a workgroup per compute unit, and share the units
-  // beyond.  A tile of 64 keys takes 1.28 us with 128 rows alone on a unit (d = 64: 0.95), and 1.05
-  // (0.65) of the unit's time; a step of the two groups, 128 keys, 1.72 (1.05), and 2.0 (1.4).
+  // groups of wavefronts, or 16 rows (attention_fewrows.hip), by expected us.  The figures are fitted to
+  // the times of all three in 570 random calls (1 to 128 batches of 1 to 256 heads, 1 to 3000
+  // queries, 1 to 9000 keys, with and without a mask), most of them within 10 %.  A workgroup's own cost
+  // matters as much as a key tile's: with few keys per query (many queries before a short context above all)
+  // the tiled kernel's 128 or 256 rows a workgroup win however idle the chip.
   // Measured, tiled / two groups / 16 rows: 16 heads of 512 x 2048, d = 128, 54.5 / 32.1 / 41.6;
   // 3 x 2 heads of 2249 x 4040, causal, 86.1 / 59.4 / 94; 32 heads of 512 x 512, d = 64,
   // 12.7 / 8.6 / 12; one head of 1371 x 2708, causal, d = 64, 39.9 / 26.9 / 17.8; 40 heads of
-  // 900 x 900, d = 128, 31 / 55 / -; 2 x 16 heads of 500 x 500, d = 128, 18.8 / 13.0 / -.
-  const bool d128 = a.d == 128;
-  const double lk = a.Lk, lq = a.Lq;
-  const double keys = !a.causal ? lk : lq <= lk ? lk - (lq - 1) / 2 : lk * (lk + 1) / (2 * lq);
-  const double turns128 = tiles(128) * n_bh / 256.0, turns64 = tiles(64) * n_bh / 256.0;
-  const double us_tiled = 3 + fmax((d128 ? 1.28 : 0.95) * lk, (d128 ? 1.05 : 0.65) * turns128 * keys) / 64;
-  const double us_groups = 4 + fmax((d128 ? 1.72 : 1.05) * lk, d128 ? 2.0 * ceil(turns64) * keys : 1.4 * turns64 * keys) / 128;
-  const double us_few = attention_fewrows_us(a, sk, sv, keys);
-  if (us_few < us_tiled && us_few <= us_groups) return launch_attention_fewrows(q, k, v, o, sq, sk, sv, so, a, s);
-  const bool split_keys = us_groups < us_tiled;
-  if (split_keys) { nw = 4; paired = 0; }
-  const int n_qtiles = tiles(split_keys ? 64 : 32 * nw);
+  // 900 x 900, d = 128, 31 / 55 / -; 2 x 16 heads of 500 x 500, d = 128, 18.8 / 13.0 / -; 20 x 8 heads of
+  // 614 x 80, causal, d = 64, 6.7 / 12.6 / 17.7; 64 x 32 heads of 50 x 300, d = 128, 74 / 101 / -.
+  constexpr AttnCost kTiled4[] = {{3.8, 0.88, 0.75, 0.575}, {4.1, 1.34, 1.47, 1.0}};   // d = 64, d = 128
+  constexpr AttnCost kTiled8[] = {{1.8, 1.19, 3.6, 1.06}, {0.5, 0.7, 6.5, 1.69}};
+  constexpr AttnCost kGroups[] = {{3.7, 1.13, 1.34, 0.71}, {2.4, 1.73, 3.7, 1.75}};
+  const int d128 = a.d == 128;
+  auto us_of = [&](const AttnCost& c, int rows, int step) {
+    const double all = (a.Lk + step - 1) / step;
+    return c.us((double)a.Lk / step + 0.5, (double)tiles(rows) * n_bh, fmin(all, tile_keys(a, rows) / step + 0.5));
+  };
+  const double us_tiled = us_of((nw == 8 ? kTiled8 : kTiled4)[d128], 32 * nw, 64);
+  const double us_groups = us_of(kGroups[d128], 64, 128);
+  const double us_few = attention_fewrows_us(a, sk, sv);
+  if (fmin(us_few, us_groups) < 0.85 * us_tiled)  // (past the fit's error)
+    return us_few <= us_groups ? AttnRoute::kFewRows : AttnRoute::kKeyGroups;
+  return nw == 8 ? (paired ? AttnRoute::kPaired8 : AttnRoute::kTiled8) : paired ? AttnRoute::kPaired4 : AttnRoute::kTiled4;
+}
+
+hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, void* o, Strides4 sq,
+                                 Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a,
+                                 hipStream_t s) {
+  const AttnRoute route = attention_bf16_route(a, sk, sv);
+  if (route == AttnRoute::kFewRows) return launch_attention_fewrows(q, k, v, o, sq, sk, sv, so, a, s);
+  const bool split_keys = route == AttnRoute::kKeyGroups;
+  const bool paired = route == AttnRoute::kPaired4 || route == AttnRoute::kPaired8;
+  const int nw = route == AttnRoute::kTiled8 || route == AttnRoute::kPaired8 ? 8 : 4;
+  const int64_t n_bh = (int64_t)a.B * a.Hq;
+  const int rows = split_keys ? 64 : 32 * nw;
+  const int n_qtiles = (a.Lq + rows - 1) / rows;
   const int64_t grid = (paired ? n_qtiles / 2 : n_qtiles) * n_bh;
   if (grid > INT32_MAX) return hipErrorInvalidValue;
   const float sl2 = a.scale * kLog2e;

@@ -289,13 +289,13 @@ static bool offsets_fit(const AttnShape& a, const Strides4& sk, const Strides4& 
   return a.Lk >= 1 && ok(sk.l) && ok(sv.l);
 }
 
-// Expected us.  A workgroup walks the keys in steps of 128, 1.13 us each when it is alone on its
-// compute unit (d = 64: 0.75); more workgroups than units share them, 1.25 (1.1) per step and unit.
-double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv, double keys) {
+// Expected us, for the comparison with the tiled kernel (fitted together with its figures: see there).  A
+// workgroup walks the keys in steps of 128.
+double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
+  const int64_t wgs = row_tiles(a) * a.B * a.Hkv;
   if (!offsets_fit(a, sk, sv, kDirectWaves)) return INFINITY;
-  const bool d128 = a.d == 128;
-  const double turns = (double)row_tiles(a) * a.B * a.Hkv / 256;
-  return 3 + fmax((d128 ? 1.13 : 0.75) * a.Lk, (d128 ? 1.25 : 1.1) * turns * keys) / 128;
+  constexpr AttnCost d128 = {3.5, 1.21, 0.24, 1.21}, d64 = {3.5, 0.73, 0.15, 0.71};
+  return (a.d == 128 ? d128 : d64).us(a.Lk / 128.0 + 0.5, (double)wgs, tile_keys(a, 16) / 128 + 0.5);
 }
 
 hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v, void* o, Strides4 sq,

@@ -3,6 +3,7 @@
 // enqueues on `s` and returns hipGetLastError().
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace rf {
@@ -23,6 +24,23 @@ struct AttnShape {
   int causal;
 };
 
+// What the attention kernels' rules share: the keys that the last row of a tile of `rows` query rows sees,
+// on average over the tiles, ...
+inline double tile_keys(const AttnShape& a, int rows) {
+  const double lk = a.Lk, lq = a.Lq;
+  if (!a.causal) return lk;
+  const double keys = lq <= lk ? lk - (lq - 1) / 2 : lk * (lk + 1) / (2 * lq);  // a row's, on average
+  return fmin(lk, keys + fmin(rows, lq) / 2);
+}
+// ... and a launch's time in us: workgroups walk `steps` tiles of keys each (`chain` of them the one that
+// sees the most) and share the 256 compute units in turns.
+struct AttnCost {
+  double launch, chain_step, workgroup, step;
+  double us(double chain, double workgroups, double steps) const {
+    return launch + fmax(chain_step * chain, ceil(workgroups / 256) * (workgroup + step * steps));
+  }
+};
+
 hipError_t launch_attention_f32(const float* q, const float* k, const float* v, float* o,
                                 Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                 const AttnShape& a, hipStream_t s);
@@ -32,12 +50,16 @@ bool attention_f32_few_wins(const AttnShape& a, const Strides4& sk, const Stride
 hipError_t launch_attention_f32_few(const float* q, const float* k, const float* v, float* o, Strides4 sq,
                                     Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, hipStream_t s);
 
+// Which kernel serves a bf16 call: workgroups of 4 or 8 wavefronts of 32 query rows, one or two query tiles
+// each, two groups of wavefronts that share the keys, or 16 packed rows (numbered as in rf_diag.h).
+enum class AttnRoute { kTiled4 = 1, kTiled8 = 2, kPaired4 = 3, kPaired8 = 4, kKeyGroups = 5, kFewRows = 6 };
+AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Strides4& sv);
 hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, void* o,
                                  Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                  const AttnShape& a, hipStream_t s);
 // The same for few query rows; the launchers of the tiled and of the split kernel choose them.
-// (keys: what a row sees on average; infinity for what that kernel does not take)
-double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv, double keys);
+// (infinity for what that kernel does not take)
+double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv);
 hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v, void* o, Strides4 sq,
                                     Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, hipStream_t s);
 bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv);

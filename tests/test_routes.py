@@ -1,0 +1,44 @@
+"""Which kernel a call takes, by the library's own rules (no GPU needed): the calls that a rule must leave to the
+general kernel because it serves them faster."""
+import pytest
+import torch
+
+from paper_2603_10026_amd import binding as B
+
+TILED = (1, 2, 3, 4)   # rf_diag_attention_route: one or two query tiles of 128 or 256 rows per workgroup
+KEY_GROUPS, FEW_ROWS = 5, 6
+
+
+def attention_route(Bt, Hq, Hkv, Lq, Lk, d, causal, dtype=torch.bfloat16):
+    q = torch.empty((Bt, Hq, Lq, d), dtype=dtype, device="meta")
+    k = torch.empty((Bt, Hkv, Lk, d), dtype=dtype, device="meta")
+    return B.rf_diag_attention_route(q, k, k, causal)
+
+
+@pytest.mark.parametrize("Bt,Hq,Hkv,Lq,Lk,d,causal", [
+    # many queries before a short context: a workgroup's own cost is all there is (us tiled / taken before:
+    # 12.8 / 38.6, 6.7 / 17.9, 47.3 / 127, 125 / 257, 21.3 / 29.6)
+    (27, 16, 4, 607, 31, 64, True), (20, 8, 8, 614, 80, 64, True), (53, 16, 16, 767, 4, 128, True),
+    (24, 32, 8, 1770, 3, 128, True), (45, 2, 2, 1376, 18, 128, True),
+    # up to 64 rows a head, but more heads than compute units (74 / 101)
+    (64, 32, 32, 50, 300, 128, False),
+    # the benchmark's prefills, a batch of heads beyond one round, no key at all
+    (4, 32, 32, 2048, 2048, 128, False), (4, 32, 32, 2048, 2048, 128, True), (2, 32, 8, 1000, 3001, 128, True),
+    (1, 40, 40, 900, 900, 128, False), (1, 4, 4, 300, 0, 128, False),
+])
+def test_attention_calls_that_stay_with_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d, causal):
+    assert attention_route(Bt, Hq, Hkv, Lq, Lk, d, causal) in TILED
+
+
+@pytest.mark.parametrize("Bt,Hq,Hkv,Lq,Lk,d,causal,route", [
+    # (us tiled / taken: 54.5 / 32.1, 12.7 / 8.6, 39.9 / 17.7, 145.5 / 23.3, 16.1 / 9.2)
+    (1, 16, 16, 512, 2048, 128, False, KEY_GROUPS), (1, 32, 32, 512, 512, 64, False, KEY_GROUPS),
+    (1, 1, 1, 1371, 2708, 64, True, FEW_ROWS), (6, 256, 32, 1, 1389, 128, True, FEW_ROWS), (6, 16, 2, 1, 565, 128, False, FEW_ROWS),
+])
+def test_attention_calls_that_leave_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d, causal, route):
+    assert attention_route(Bt, Hq, Hkv, Lq, Lk, d, causal) == route
+
+
+def test_attention_refusals_have_no_route():
+    assert attention_route(1, 3, 2, 4, 4, 128, False) == 0
+    assert attention_route(1, 2, 2, 4, 4, 96, False) == 0
