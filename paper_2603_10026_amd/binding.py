@@ -41,6 +41,7 @@ ENTRY_POINTS = (
 DIAG_ENTRY_POINTS = (
     "rf_diag_softmax_level",
     "rf_diag_attention_route",
+    "rf_diag_splitk_route",
     "rf_diag_attention_wide",
     "rf_diag_copy",
     "rf_diag_read",
@@ -113,6 +114,8 @@ def load_library():
     lib.rf_diag_softmax_level.argtypes = [P, P, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
     lib.rf_diag_attention_route.restype = ctypes.c_int
     lib.rf_diag_attention_route.argtypes = [P, P, P, ctypes.c_int]
+    lib.rf_diag_splitk_route.restype = ctypes.c_int
+    lib.rf_diag_splitk_route.argtypes = [P, P, P, ctypes.c_int]
     lib.rf_diag_copy.restype = ctypes.c_int
     lib.rf_diag_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
     lib.rf_diag_read.restype = ctypes.c_int
@@ -307,6 +310,12 @@ def rf_diag_attention_route(q, k, v, causal=False):
     tensors of any device, ``meta`` among them."""
     dq, dk, dv = tensor_desc(q), tensor_desc(k), tensor_desc(v)
     return load_library().rf_diag_attention_route(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv), int(bool(causal)))
+
+
+def rf_diag_splitk_route(q, k, v, num_splits):
+    """Number of the kernel that rf_cascade_attention_splitk runs for such a call (include/rf_diag.h)."""
+    dq, dk, dv = tensor_desc(q), tensor_desc(k), tensor_desc(v)
+    return load_library().rf_diag_splitk_route(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv), int(num_splits))
 
 
 def rf_diag_attention_wide(q, k, v, scale, o=None, stream=None):

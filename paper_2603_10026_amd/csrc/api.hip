@@ -330,6 +330,12 @@ int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_ten
   return (int)rf::attention_bf16_route(a, strides4(k), strides4(v));
 }
 
+int rf_diag_splitk_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int num_splits) {
+  rf::AttnShape a{};
+  if (check_qkv(q, k, v, &a) != RF_OK || a.d != 128 || q->dtype != RF_BF16 || num_splits < 1) return 0;
+  return rf::attention_fewrows_splitk_wins(a, strides4(k), strides4(v), num_splits) ? 2 : 1;
+}
+
 rf_status rf_diag_attention_wide(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v,
                                  rf_tensor* o, float scale, rf_stream stream) {
   rf::AttnShape a{};

@@ -322,8 +322,16 @@ hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v,
 // 109 MB the two take the same time on new inputs and this one is 2 us ahead on repeated ones, at 221 MB
 // it is 17 us behind on new inputs (they do not stay in the 256 MB memory-side cache until they are
 // asked for) and 2 on repeated ones, at 2 GB 377 against 324.
-bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
-  return offsets_fit(a, sk, sv, kSplitWaves) && (double)a.B * a.Hkv * a.Lk * a.d * 4 <= 128e6;
+// With one row tile per KV head the two kernels' workgroups do the same work, and the other one streams a
+// long chunk better (K two steps ahead): launches of one round keep chunks up to about 200 keys here,
+// many rounds up to about 400 (11 workgroups with chunks of 2493 keys: 32.7 us here, 21.9 there; 36 of
+// 636, 11.6 and 8.6; 1024 of 94, the rule's figures fitted to 369 calls like these, 11.2 and 12.7).
+bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv, int num_splits) {
+  if (!offsets_fit(a, sk, sv, kSplitWaves) || (double)a.B * a.Hkv * a.Lk * a.d * 4 > 128e6) return false;
+  if (row_tiles(a) > 1) return true;
+  constexpr AttnCost here = {3.6, 0, 0.65, 1.54}, there = {3.1, 0, 1.59, 1.33};
+  const double wgs = (double)a.B * a.Hkv * num_splits, steps = ceil((double)a.Lk / num_splits) / 128;
+  return here.us(0, wgs, steps) < 0.93 * there.us(0, wgs, steps);
 }
 
 hipError_t launch_attention_fewrows_splitk(const void* q, const void* k, const void* v, Strides4 sq, Strides4 sk,

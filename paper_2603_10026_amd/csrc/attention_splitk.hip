@@ -288,7 +288,7 @@ hipError_t launch_attention_splitk_bf16(const void* q, const void* k, const void
                                         float* part_l, float* part_acc, const AttnShape& a,
                                         hipStream_t s) {
   if (a.d != kD) return hipErrorInvalidValue;
-  if (attention_fewrows_splitk_wins(a, sk, sv))
+  if (attention_fewrows_splitk_wins(a, sk, sv, num_splits))
     return launch_attention_fewrows_splitk(q, k, v, sq, sk, sv, num_splits, part_m, part_l, part_acc, a, s);
   const int64_t grid = (int64_t)a.B * a.Hkv * num_splits;
   if (grid > INT32_MAX) return hipErrorInvalidValue;

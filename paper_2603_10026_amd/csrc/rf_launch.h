@@ -62,7 +62,7 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
 double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv);
 hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v, void* o, Strides4 sq,
                                     Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, hipStream_t s);
-bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv);
+bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv, int num_splits);
 hipError_t launch_attention_fewrows_splitk(const void* q, const void* k, const void* v, Strides4 sq, Strides4 sk,
                                            Strides4 sv, int num_splits, float* part_m, float* part_l,
                                            float* part_acc, const AttnShape& a, hipStream_t s);

@@ -42,3 +42,20 @@ def test_attention_calls_that_leave_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d, cau
 def test_attention_refusals_have_no_route():
     assert attention_route(1, 3, 2, 4, 4, 128, False) == 0
     assert attention_route(1, 2, 2, 4, 4, 96, False) == 0
+
+
+STREAMING, SHORT_CHUNKS = 1, 2   # rf_diag_splitk_route
+
+
+@pytest.mark.parametrize("Bt,Hq,Hkv,Lq,Lk,S,route", [
+    # few workgroups with long chunks (us streaming / short chunks: 21.9 / 32.7, 10.1 / 13.8, 8.6 / 11.5, 41 / 53)
+    (11, 4, 1, 1, 2493, 1, STREAMING), (2, 2, 2, 1, 1726, 2, STREAMING), (9, 4, 1, 1, 2543, 4, STREAMING), (1, 32, 4, 1, 8978, 2, STREAMING),
+    (16, 32, 8, 1, 32768, 64, STREAMING),          # K and V beyond the line of 128 MB
+    # short chunks, and several row tiles per KV head (25.5 / 21.2, 328 / 106)
+    (4, 32, 8, 1, 3001, 32, SHORT_CHUNKS), (1, 4, 1, 1, 100, 64, SHORT_CHUNKS), (38, 8, 1, 4, 2700, 4, SHORT_CHUNKS),
+    (2, 64, 8, 128, 2048, 8, SHORT_CHUNKS),
+])
+def test_splitk_routes(Bt, Hq, Hkv, Lq, Lk, S, route):
+    q = torch.empty((Bt, Hq, Lq, 128), dtype=torch.bfloat16, device="meta")
+    k = torch.empty((Bt, Hkv, Lk, 128), dtype=torch.bfloat16, device="meta")
+    assert B.rf_diag_splitk_route(q, k, k, S) == route
