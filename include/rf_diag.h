@@ -53,7 +53,10 @@ RF_API rf_status rf_diag_attention_wide(const rf_tensor* q, const rf_tensor* k, 
  * looked at and no device is needed), so that a test can state what it covers.  bf16:
  *   1, 2  tiled, 128 or 256 query rows per workgroup    3, 4  the same with two query tiles each
  *   5     64 rows, keys over two groups of wavefronts   6     16 packed rows
- * 0 for calls that it refuses and for other dtypes.
+ * fp32:
+ *   11    4 packed rows        12  two tiles of 16 rows per workgroup
+ *   13-15 one tile of 16 rows, keys over 16, 8 or 4 wavefronts
+ * 0 for calls that it refuses.
  * rf_diag_splitk_route, for rf_cascade_attention_splitk: 1 streaming chunks, 2 short chunks.
  */
 RF_API int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal);

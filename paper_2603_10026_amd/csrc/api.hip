@@ -325,8 +325,9 @@ rf_status rf_cascade_attention(const rf_tensor* q, const rf_tensor* k, const rf_
 
 int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal) {
   rf::AttnShape a{};
-  if (check_qkv(q, k, v, &a) != RF_OK || (a.d != 64 && a.d != 128) || q->dtype != RF_BF16) return 0;
+  if (check_qkv(q, k, v, &a) != RF_OK || (a.d != 64 && a.d != 128)) return 0;
   a.causal = causal != 0;
+  if (q->dtype == RF_F32) return (int)rf::attention_f32_route(a, strides4(k), strides4(v));
   return (int)rf::attention_bf16_route(a, strides4(k), strides4(v));
 }
 

@@ -235,24 +235,39 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
   }
 }
 
+// One or two tiles of 16 rows per workgroup.  A compute unit holds one workgroup at a time, and
+// one with two tiles takes 1.4 times as long (K and V cross the L2 once for both): two tiles where they
+// save enough turns.  Under a mask the turns of single tiles differ in length and fill each other's gaps,
+// so that the keys a tile sees on average count, not the turns alone.  Figures fitted to 570 random
+// calls; us with one / two tiles, d = 64: 512 heads of 128 x 512 148 / 111, 32 heads x 32 rows x 600
+// 23.3 / 18.3, 288 workgroups of one tile x 1520 keys, causal, 39.7 / 35.1; 256 workgroups x 512 keys
+// 10.2 / 15.0, 8 heads of 944 x 409, causal, 11.4 / 13.8.  d = 128: two tiles take 8 wavefronts, 512
+// workgroups x 1000 keys 61.9 / 50.3, 8 heads of 1017 x 516, causal, 22.2 / 29.7; on short key axes one
+// tile and 4 wavefronts, two workgroups to a compute unit, do better (512 x 256 keys 18.5 / 19.3), and 8
+// wavefronts where there is a unit for each workgroup (160 x 1546 keys 52.1 with 4, 45.2 with 8).
+AttnF32Route attention_f32_route(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
+  if (attention_f32_few_wins(a, sk, sv)) return AttnF32Route::kFewRows;
+  const int64_t wg16 = (int64_t)((a.Lq + 15) / 16) * a.B * a.Hq, wg32 = (int64_t)((a.Lq + 31) / 32) * a.B * a.Hq;
+  const int d128 = a.d == 128;
+  const bool long_axis = !d128 || a.Lk >= 512;
+  constexpr AttnCost kOne[] = {{2.0, 0, 1.64, 1.83}, {2.6, 4.4, 0, 3.4}}, kTwo[] = {{2.0, 2.67, 1.75, 2.58}, {2.0, 5.5, 1.67, 5.48}};
+  auto us_of = [&](const AttnCost& c, int rows, int64_t wgs) {
+    return c.us(a.Lk / 128.0 + 0.5, (double)wgs, tile_keys(a, rows) / 128 + 0.5);
+  };
+  if (long_axis && wg16 > 256 && us_of(kTwo[d128], 32, wg32) < 0.9 * us_of(kOne[d128], 16, wg16)) return AttnF32Route::kTwoTiles;
+  // few workgroups and many keys: 16 wavefronts share the key axis of a query tile
+  if (!d128) return wg16 < 256 && a.Lk > 128 ? AttnF32Route::kWaves16 : AttnF32Route::kWaves8;
+  return long_axis && wg16 <= 256 ? AttnF32Route::kWaves8 : AttnF32Route::kWaves4;
+}
+
 hipError_t launch_attention_f32(const float* q, const float* k, const float* v, float* o,
                                 Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                 const AttnShape& a, hipStream_t s) {
-  if (attention_f32_few_wins(a, sk, sv)) return launch_attention_f32_few(q, k, v, o, sq, sk, sv, so, a, s);
-  const int64_t wg16 = (int64_t)((a.Lq + 15) / 16) * a.B * a.Hq, wg32 = (int64_t)((a.Lq + 31) / 32) * a.B * a.Hq;
-  // One or two tiles of 16 rows per workgroup.  A compute unit holds one workgroup at a time, and
-  // one with two tiles takes 1.4 times as long (K and V cross the L2 once for both): two tiles as
-  // soon as they save enough turns.  us with one / two tiles, d = 64: 512 heads of 128 x 512
-  // 148 / 111, 32 heads x 32 rows x 600 23.3 / 18.3, 288 workgroups of one tile x 1520 keys, causal,
-  // 39.7 / 35.1; 256 workgroups x 512 keys 10.2 / 15.0.  d = 128 the same with 8 wavefronts: 512
-  // workgroups x 1000 keys 61.9 / 50.3; on shorter key axes one tile and 4 wavefronts, two workgroups
-  // to a compute unit, do better (512 x 256 keys 18.5 / 19.3), and 8 wavefronts where there is a unit
-  // for each workgroup (160 x 1546 keys 52.1 with 4, 45.2 with 8).
-  const double turns1 = (double)((wg16 + 255) / 256), turns2 = 1.42 * (double)((wg32 + 255) / 256);
-  const bool long_axis = a.d == 64 || a.Lk >= 512;
-  const bool two = long_axis && turns2 < turns1;
+  const AttnF32Route route = attention_f32_route(a, sk, sv);
+  if (route == AttnF32Route::kFewRows) return launch_attention_f32_few(q, k, v, o, sq, sk, sv, so, a, s);
+  const bool two = route == AttnF32Route::kTwoTiles;
   const int n_qtiles = two ? (a.Lq + 31) / 32 : (a.Lq + 15) / 16;
-  const int64_t grid = two ? wg32 : wg16;
+  const int64_t grid = (int64_t)n_qtiles * a.B * a.Hq;
   if (grid > INT32_MAX) return hipErrorInvalidValue;
   const float sl2 = a.scale * kLog2e;
 #define RF_LAUNCH_F32(DD, NW, QT)                                                                       \
@@ -260,12 +275,11 @@ hipError_t launch_attention_f32(const float* q, const float* k, const float* v, 
                      sq, sk, sv, so, a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal, n_qtiles)
   if (a.d == 64) {
     if (two) RF_LAUNCH_F32(64, 8, 2);
-    // few workgroups and many keys: 16 wavefronts share the key axis of a query tile
-    else if (grid < 256 && a.Lk > 128) RF_LAUNCH_F32(64, 16, 1);
+    else if (route == AttnF32Route::kWaves16) RF_LAUNCH_F32(64, 16, 1);
     else RF_LAUNCH_F32(64, 8, 1);
   } else {
     if (two) RF_LAUNCH_F32(128, 8, 2);
-    else if (long_axis && grid <= 256) RF_LAUNCH_F32(128, 8, 1);
+    else if (route == AttnF32Route::kWaves8) RF_LAUNCH_F32(128, 8, 1);
     else RF_LAUNCH_F32(128, 4, 1);
   }
 #undef RF_LAUNCH_F32

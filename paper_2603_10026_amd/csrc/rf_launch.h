@@ -41,6 +41,10 @@ struct AttnCost {
   }
 };
 
+// Which kernel serves an fp32 call: tiles of 4 rows, two tiles of 16 per workgroup, or one over 16, 8 or 4
+// wavefronts (numbered as in rf_diag.h).
+enum class AttnF32Route { kFewRows = 11, kTwoTiles = 12, kWaves16 = 13, kWaves8 = 14, kWaves4 = 15 };
+AttnF32Route attention_f32_route(const AttnShape& a, const Strides4& sk, const Strides4& sv);
 hipError_t launch_attention_f32(const float* q, const float* k, const float* v, float* o,
                                 Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                 const AttnShape& a, hipStream_t s);

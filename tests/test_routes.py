@@ -39,6 +39,20 @@ def test_attention_calls_that_leave_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d, cau
     assert attention_route(Bt, Hq, Hkv, Lq, Lk, d, causal) == route
 
 
+F32_FEW_ROWS, F32_TWO_TILES, F32_WAVES16, F32_WAVES8, F32_WAVES4 = 11, 12, 13, 14, 15
+
+
+@pytest.mark.parametrize("Bt,Hq,Hkv,Lq,Lk,d,causal,routes", [
+    # (us with one tile of 16 rows / two: 22.2 / 29.7, 11.4 / 13.8)
+    (1, 8, 8, 1017, 516, 128, True, (F32_WAVES8, F32_WAVES4)), (2, 4, 1, 944, 409, 64, True, (F32_WAVES8,)),
+    # (148 / 111, 61.9 / 50.3)
+    (1, 512, 512, 128, 512, 64, False, (F32_TWO_TILES,)), (1, 64, 64, 128, 1000, 128, False, (F32_TWO_TILES,)),
+    (1, 1, 1, 128, 512, 64, False, (F32_FEW_ROWS,)), (2, 8, 8, 200, 520, 128, True, (F32_WAVES8,)), (2, 8, 8, 100, 200, 64, False, (F32_WAVES16,)),
+])
+def test_fp32_attention_routes(Bt, Hq, Hkv, Lq, Lk, d, causal, routes):
+    assert attention_route(Bt, Hq, Hkv, Lq, Lk, d, causal, torch.float32) in routes
+
+
 def test_attention_refusals_have_no_route():
     assert attention_route(1, 3, 2, 4, 4, 128, False) == 0
     assert attention_route(1, 2, 2, 4, 4, 96, False) == 0
