@@ -63,6 +63,14 @@ RF_API int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const
 RF_API int rf_diag_splitk_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int num_splits);
 
 /*
+ * The output tile that rf_rmsnorm_gemm and rf_fp8_quant_gemm cut a product of contiguous, 16-byte
+ * aligned operands into (host code only): 1000 * rows + columns; 0 for sizes that they refuse.
+ * Tiles of 128 rows are those of the large kernels.
+ */
+RF_API int rf_diag_rmsnorm_gemm_tile(int64_t M, int64_t K, int64_t N);
+RF_API int rf_diag_fp8_quant_gemm_tile(int64_t M, int64_t K, int64_t N);
+
+/*
  * Measurement aids, not part of the cascaded-reduction path.  They provide the two
  * measured ceilings that roofline fractions are reported next to (a plain copy kernel for
  * HBM, an MFMA-only loop for the matrix pipe) and the reference dispatch that scales the

@@ -42,6 +42,8 @@ DIAG_ENTRY_POINTS = (
     "rf_diag_softmax_level",
     "rf_diag_attention_route",
     "rf_diag_splitk_route",
+    "rf_diag_rmsnorm_gemm_tile",
+    "rf_diag_fp8_quant_gemm_tile",
     "rf_diag_attention_wide",
     "rf_diag_copy",
     "rf_diag_read",
@@ -116,6 +118,9 @@ def load_library():
     lib.rf_diag_attention_route.argtypes = [P, P, P, ctypes.c_int]
     lib.rf_diag_splitk_route.restype = ctypes.c_int
     lib.rf_diag_splitk_route.argtypes = [P, P, P, ctypes.c_int]
+    for f in (lib.rf_diag_rmsnorm_gemm_tile, lib.rf_diag_fp8_quant_gemm_tile):
+        f.restype = ctypes.c_int
+        f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
     lib.rf_diag_copy.restype = ctypes.c_int
     lib.rf_diag_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
     lib.rf_diag_read.restype = ctypes.c_int
@@ -316,6 +321,16 @@ def rf_diag_splitk_route(q, k, v, num_splits):
     """Number of the kernel that rf_cascade_attention_splitk runs for such a call (include/rf_diag.h)."""
     dq, dk, dv = tensor_desc(q), tensor_desc(k), tensor_desc(v)
     return load_library().rf_diag_splitk_route(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv), int(num_splits))
+
+
+def rf_diag_rmsnorm_gemm_tile(M, K, N):
+    """(rows, columns) of the output tile that rf_rmsnorm_gemm takes for these sizes."""
+    return divmod(load_library().rf_diag_rmsnorm_gemm_tile(M, K, N), 1000)
+
+
+def rf_diag_fp8_quant_gemm_tile(M, K, N):
+    """(tokens, channels) of the output tile that rf_fp8_quant_gemm takes for these sizes."""
+    return divmod(load_library().rf_diag_fp8_quant_gemm_tile(M, K, N), 1000)
 
 
 def rf_diag_attention_wide(q, k, v, scale, o=None, stream=None):

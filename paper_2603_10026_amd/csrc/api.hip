@@ -331,6 +331,18 @@ int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_ten
   return (int)rf::attention_bf16_route(a, strides4(k), strides4(v));
 }
 
+int rf_diag_rmsnorm_gemm_tile(int64_t M, int64_t K, int64_t N) {
+  if (M < 1 || K < 1 || N < 1 || M > INT32_MAX || K > INT32_MAX || N > INT32_MAX || K % 64 != 0 || N % 8 != 0) return 0;
+  const bool rows = rf::rmsnorm_gemm_rows_wins((int)M, (int)K, (int)N, N, nullptr, N);
+  return rows ? rf::rmsnorm_gemm_rows_tile((int)M, (int)K, (int)N) : 128512;
+}
+
+int rf_diag_fp8_quant_gemm_tile(int64_t M, int64_t K, int64_t N) {
+  if (M < 1 || K < 1 || N < 1 || M > INT32_MAX || K > INT32_MAX || N > INT32_MAX || K % 128 != 0 || N % 8 != 0) return 0;
+  const bool rows = rf::fp8_quant_gemm_rows_wins((int)M, (int)K, (int)N, nullptr, N);
+  return rows ? rf::fp8_quant_gemm_rows_tile((int)M, (int)K, (int)N) : 128000 + 256 * rf::fp8_quant_gemm_blocks((int)M, (int)N);
+}
+
 int rf_diag_splitk_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int num_splits) {
   rf::AttnShape a{};
   if (check_qkv(q, k, v, &a) != RF_OK || a.d != 128 || q->dtype != RF_BF16 || num_splits < 1) return 0;

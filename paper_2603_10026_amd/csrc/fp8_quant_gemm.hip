@@ -526,16 +526,20 @@ __global__ __launch_bounds__(kQThreads, 1) void fp8_quant_gemm_kernel(
   }
 }
 
+// The 512-wide N tile does the most work per byte staged.  When the 256-wide tiling still
+// fits the chip in one round of workgroups (one per compute unit), it is taken instead: it
+// occupies up to twice as many compute units and wastes less of a ragged last tile.
+int fp8_quant_gemm_blocks(int M, int N) {
+  const int64_t n_narrow = ((int64_t)M + kQM - 1) / kQM * (((int64_t)N + 255) / 256);
+  return n_narrow <= 256 ? 1 : 2;
+}
+
 hipError_t launch_fp8_quant_gemm(const void* a, const void* w, void* c, int M, int K, int N,
                                  int64_t lda, int64_t ldw, int64_t ldc, hipStream_t s) {
   if (fp8_quant_gemm_rows_wins(M, K, N, c, ldc))
     return launch_fp8_quant_gemm_rows(a, w, c, M, K, N, lda, ldw, ldc, s);
   const int n_mtiles = (M + kQM - 1) / kQM;
-  // The 512-wide N tile does the most work per byte staged.  When the 256-wide tiling still
-  // fits the chip in one round of workgroups (one per compute unit), it is taken instead: it
-  // occupies up to twice as many compute units and wastes less of a ragged last tile.
-  const int64_t n_narrow = (int64_t)n_mtiles * ((N + 255) / 256);
-  const int ni = n_narrow <= 256 ? 1 : 2;
+  const int ni = fp8_quant_gemm_blocks(M, N);
   const int n_ntiles = (N + 256 * ni - 1) / (256 * ni);
   const int64_t grid = (int64_t)n_mtiles * n_ntiles;
   if (grid > INT32_MAX) return hipErrorInvalidValue;

@@ -236,7 +236,7 @@ inline int tiles_held(int K) { return K <= 2048 ? 2 : K <= 4096 ? 4 : 8; }
 // 9.3 us for 16 x 4096 x 4096 as 1 x 1, 17.6 for 128 x 4096 x 4096 as 2 x 4, 23.5 for
 // 128 x 8192 x 2048 as 1 x 4.
 inline double rows_us(const FShape& r, int M, int K, int N) {
-  const double k = K <= 2048 ? K / 1024.0 : tiles_held(K);  // (all held tiles are fetched)
+  const double k = K <= 2048 ? fmax(K / 1024.0, 1.5) : tiles_held(K);  // (all held tiles are fetched)
   const double one = 1.2 + 2.6 * r.mt + 0.7 * r.nt + (k - 1) * (1.0 + 0.4 * r.mt + 0.2 * r.nt);
   const int n_nt = (N + 16 * r.nt - 1) / (16 * r.nt);
   const double wg_xcd = (double)((M + 16 * r.mt - 1) / (16 * r.mt)) * ((n_nt + 7) / 8);
@@ -253,11 +253,16 @@ FShape best_shape(int M, int K, int N) {
 // The large kernel takes 6 us and 9 for every 1024 k as long as its tiles leave compute units idle
 // (35 to 48 us at 4096 k, 65 to 86 at 8192), whatever the token count.  Both sides at the line:
 // 256 x 4096 x 4096: 33.6 us here, 46.9 there; 384: 49.5 and 48.5.  64 x 8192 x 8192: 46 and 77;
-// 100: 89 and 83.
+// 100: 89 and 83.  1672 x 256 x 40: 13.8 and 7.7 (a handful of channel tiles leaves XCDs idle).
 bool fp8_quant_gemm_rows_wins(int M, int K, int N, const void* c, int64_t ldc) {
   // (8-byte stores of c)
   if (K > 8192 || N % 8 != 0 || reinterpret_cast<uintptr_t>(c) % 8 != 0 || (M > 1 && ldc % 4 != 0)) return false;
   return 1.05 * rows_us(best_shape(M, K, N), M, K, N) < 6.0 + 9.0 * (K / 1024.0);
+}
+
+int fp8_quant_gemm_rows_tile(int M, int K, int N) {
+  const FShape r = best_shape(M, K, N);
+  return 16 * r.mt * 1000 + 16 * r.nt;
 }
 
 hipError_t launch_fp8_quant_gemm_rows(const void* a, const void* w, void* c, int M, int K, int N,

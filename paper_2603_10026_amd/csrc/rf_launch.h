@@ -94,6 +94,7 @@ hipError_t launch_rmsnorm_gemm_bf16(const void* x, const void* g, const void* w,
 
 // The same for few rows, 16-byte aligned rows of y, w within 4 GiB (the launcher above chooses).
 bool rmsnorm_gemm_rows_wins(int M, int K, int N, int64_t ldw, const void* y, int64_t ldy);
+int rmsnorm_gemm_rows_tile(int M, int K, int N);  // 1000 rows + columns of the tile it takes
 hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w, void* y, int M,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
                                     hipStream_t s);
@@ -122,8 +123,11 @@ hipError_t launch_moe_routing_static(const void* x, const void* w, int S, int hd
 hipError_t launch_fp8_quant_gemm(const void* a, const void* w, void* c, int M, int K, int N,
                                  int64_t lda, int64_t ldw, int64_t ldc, hipStream_t s);
 
+int fp8_quant_gemm_blocks(int M, int N);  // tiles of 256 or 512 channels: 1 or 2 blocks
+
 // The same for few tokens, 8-byte aligned rows of c (the launcher above chooses).
 bool fp8_quant_gemm_rows_wins(int M, int K, int N, const void* c, int64_t ldc);
+int fp8_quant_gemm_rows_tile(int M, int K, int N);  // 1000 tokens + channels of the tile it takes
 hipError_t launch_fp8_quant_gemm_rows(const void* a, const void* w, void* c, int M, int K, int N,
                                       int64_t lda, int64_t ldw, int64_t ldc, hipStream_t s);
 

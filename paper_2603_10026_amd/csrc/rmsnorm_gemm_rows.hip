@@ -249,6 +249,11 @@ bool rmsnorm_gemm_rows_wins(int M, int K, int N, int64_t ldw, const void* y, int
   return 1.15 * rows_us(best_shape(M, K, N), M, K, N) < large;
 }
 
+int rmsnorm_gemm_rows_tile(int M, int K, int N) {
+  const RowsShape& r = best_shape(M, K, N);
+  return 16 * r.mt * 1000 + 16 * r.c;
+}
+
 hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w, void* y, int M,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
                                     hipStream_t s) {

@@ -73,3 +73,14 @@ def test_splitk_routes(Bt, Hq, Hkv, Lq, Lk, S, route):
     q = torch.empty((Bt, Hq, Lq, 128), dtype=torch.bfloat16, device="meta")
     k = torch.empty((Bt, Hkv, Lk, 128), dtype=torch.bfloat16, device="meta")
     assert B.rf_diag_splitk_route(q, k, k, S) == route
+
+
+@pytest.mark.parametrize("M,K,N,large", [
+    # many tokens, few channels, a short axis (us large / small tiles: 7.7 / 13.8, 7.7 / 11.0, 10.2 / 13.5, 6.5 / 8.4)
+    (1672, 256, 40, True), (1416, 256, 64, True), (34, 512, 8584, True), (1007, 128, 40, True), (1604, 256, 24, True),
+    (4096, 8192, 3584, True), (100, 8192, 8192, True),
+    # (35.2 / 6.7, 40.5 / 13.6, 47 / 33.6, 77 / 46)
+    (1, 4096, 4096, False), (64, 4096, 4096, False), (256, 4096, 4096, False), (64, 8192, 8192, False), (1, 128, 8, False),
+])
+def test_fp8_tiles(M, K, N, large):
+    assert (B.rf_diag_fp8_quant_gemm_tile(M, K, N)[0] == 128) == large
