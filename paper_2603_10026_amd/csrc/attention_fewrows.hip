@@ -200,17 +200,24 @@ __global__ __launch_bounds__(NW * kWave, few_min_waves(DIRECT)) void attention_f
     const float corr = fast_exp2(m2 - m_use);
     m2 = m_new;
     // ---- stage 2: running sum of exponentials ----
-    float p[8];
+    // (a whole row's sum runs over the rounded probabilities, the values the second product sees, as in
+    // the tiled kernel: their error cancels in O = acc / l.  A chunk's l is the sum itself.)
     float psum = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      p[e] = fast_exp2(sc[e] - m_use);
-      psum += p[e];
-    }
-    l = l * corr + psum;
     u32x4 pb;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pb[e] = pack_bf16(p[2 * e], p[2 * e + 1]);
+    for (int e = 0; e < 4; ++e) {
+      const float p0 = fast_exp2(sc[2 * e] - m_use), p1 = fast_exp2(sc[2 * e + 1] - m_use);
+      pb[e] = pack_bf16(p0, p1);
+      if constexpr (DIRECT) {
+        typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+        psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (uint32_t)pb[e]),
+                                               __builtin_bit_cast(bf16x2, 0x3f803f80u), psum, false);
+      } else {
+        psum += p0;
+        psum += p1;
+      }
+    }
+    l = l * corr + psum;
     // ---- stage 3: acc = acc * corr + V^T P^T (16-bit transpose of V in registers) ----
 #pragma unroll
     for (int tp = 0; tp < VW; ++tp) {

@@ -74,3 +74,25 @@ def test_splitk_streaming_kernel_agrees_with_the_small_one(rf):  # noqa: F811
         assert float(((whole[1][b] - part[1][0]) / part[1][0]).abs().max()) <= 1e-3
         d = (whole[2][b] - part[2][0]).double()
         assert float(d.norm() / part[2][0].double().norm()) <= 2.0 ** -9
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Lq,Lk,d,few", [(8, 32, 8, 1, 5, 128, True), (16, 64, 8, 1, 6, 64, True), (16, 16, 2, 2, 40, 128, True),
+                                                  (4, 32, 32, 200, 5, 128, False)])
+def test_attention_probability_rounding_cancels(rf, B, Hq, Hkv, Lq, Lk, d, few):  # noqa: F811
+    """O = acc / l with both sums over the bf16-rounded probabilities: where V has a mean far from zero, here
+    values in [1.75, 2), the rounding cancels, and what is left is that of the output, 1/sqrt(12) = 0.289 of
+    bf16's spacing there (2^-7) in the mean square.  With l over the unrounded probabilities a row is off by
+    another 2^-9 / sqrt(3 Lk) of its value or so, 0.13 of the spacing for five keys: 0.32 in all."""
+    route = rf.rf_diag_attention_route(*(torch.empty((B, h, n, d), dtype=torch.bfloat16, device="meta")
+                                         for h, n in ((Hq, Lq), (Hkv, Lk), (Hkv, Lk))))
+    assert (route == 6) == few, route
+    say(f"attention rounding of P: B{B} Hq{Hq} Hkv{Hkv} Lq{Lq} Lk{Lk} d{d}")
+    q, k, v = I.attention_inputs(I.SEED_BASE + 75, B, Hq, Hkv, Lq, Lk, d, "bf16")
+    rng = np.random.Generator(np.random.PCG64(75))
+    v = (1.75 + 2.0 ** -7 * rng.integers(0, 32, size=v.shape)).astype(np.float32)
+    o = rf.rf_cascade_attention(*(I.to_torch(a, "bf16", DEV) for a in (q, k, v)), I.default_scale(d))
+    torch.cuda.synchronize()
+    err = (I.to_numpy(o) - O.attention(q, k, v, I.default_scale(d), False)) * 2.0 ** 7
+    rms = float(np.sqrt(np.mean(err ** 2)))
+    print(f"        error {rms:.4f} of the spacing", flush=True)
+    assert rms <= 0.293
