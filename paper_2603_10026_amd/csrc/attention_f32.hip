@@ -12,6 +12,8 @@
 // accumulator layout (lane = query column, registers = key rows) is already
 // the B-operand layout of the second product O^T = V^T P^T: the probabilities
 // never leave their registers.
+#include <type_traits>
+
 #include "rf_device.h"
 #include "rf_launch.h"
 
@@ -37,8 +39,14 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
   asm volatile("" : "+s"(n_qtiles) : "s"(q), "s"(k), "s"(v), "s"(o), "s"(sq.b), "s"(sq.h), "s"(sq.l), "s"(sk.b),
                "s"(sk.h), "s"(sk.l), "s"(sv.b), "s"(sv.h), "s"(sv.l), "s"(so.b), "s"(so.h), "s"(so.l),
                "s"(Hq), "s"(Hkv), "s"(Lq), "s"(Lk), "s"(scale_log2e), "s"(causal));
+  // Groups of whole tiles and the one with a ragged tile in a body each.  A choice per tile joins the registers
+  // of its two sides, and where the compiler copies there it waits for a tile's loads before the next one's
+  // are issued; in one line it also keeps fewer of them (77 registers, 176 before): 9216 workgroups x 872 keys
+  // 543 -> 368 us, 23 heads of 395 x 3967 161 -> 145.  The other instances have no such copies and lose up
+  // to 10 % on short key axes (128 heads of 100 x 300, d = 128, 41.5 -> 46.2).
+  constexpr bool kTwoBodies = D == 64 && NW == 8 && QT == 1;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = kTwoBodies ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
   const int i16 = lane & 15;  // query column / key row / head-dim row inside a tile
   const int g = lane >> 4;    // lane group 0..3
 
@@ -108,13 +116,15 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
   const bool small_pitch = sk.l < (1 << 26) && sv.l < (1 << 26);  // 32-bit byte offsets inside a 16-key tile
   const uint32_t k_lane = (uint32_t)(((int64_t)i16 * sk.l + 4 * g) * 4);
   const uint32_t v_lane = (uint32_t)(((int64_t)(4 * g) * sv.l + DJ * i16) * 4);
-  for (int kt0 = wave; kt0 < n_ktiles; kt0 += NW * TG) {
+  enum { kWhole, kRagged, kEither };  // what the group's tiles are known to be
+  auto group = [&](int kt0, auto kind_tag) {
+    constexpr int kKind = decltype(kind_tag)::value;
     f32x4 kf[TG][DJ];
     f32x4 vf[TG][4][DJ / 4];  // vf[.][u][c][e] = V[key of step u][DJ * i16 + 4c + e]
 #pragma unroll
     for (int jj = 0; jj < TG; ++jj) {
       const int key0 = min(kt0 + NW * jj, n_ktiles - 1) * 16;  // (a surplus slot re-reads the last tile)
-      if (key0 + 16 <= Lk && small_pitch) {
+      if (kKind == kWhole || (kKind == kEither && key0 + 16 <= Lk && small_pitch)) {
         // whole tile: a wavefront-uniform base (scalar unit) plus loop-invariant 32-bit lane
         // offsets, no per-lane 64-bit address arithmetic (which is most of this kernel's set-up)
         const char* kbase = reinterpret_cast<const char*>(kb) + (int64_t)key0 * sk.l * 4;
@@ -196,6 +206,15 @@ __global__ __launch_bounds__(NW * kWave) void attention_f32_kernel(
         }
       }
     }
+  };
+  int kt0 = wave;
+  if constexpr (kTwoBodies) {
+    const int n_whole = small_pitch ? Lk / 16 : 0;
+    for (; kt0 < n_ktiles && min(kt0 + NW * (TG - 1), n_ktiles - 1) < n_whole; kt0 += NW * TG)
+      group(kt0, std::integral_constant<int, kWhole>{});
+    for (; kt0 < n_ktiles; kt0 += NW * TG) group(kt0, std::integral_constant<int, kRagged>{});
+  } else {
+    for (; kt0 < n_ktiles; kt0 += NW * TG) group(kt0, std::integral_constant<int, kEither>{});
   }
 
   // ---- merge the NW wavefront states (level-k fused expression) ----
