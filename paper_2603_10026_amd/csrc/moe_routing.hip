@@ -17,10 +17,9 @@
 //   accumulators are summed through LDS in a fixed order and the fp32 partial
 //   scores of the slice are written to the caller's workspace.
 // Kernel 2 (cascade): a wavefront per token adds the slices' partial scores in slice
-//   order, then runs the cascade over its lanes.  (16 lanes per token with up to 8 experts
-//   each kept a longer chain of compares per TopK round and a quarter of the wavefronts:
-//   with it 2048 x 4096 x 128 experts, top 8, took 18.5 us in all, 64 x 4096 x 128 19.2 and
-//   100 x 8192 x 128, 64 slices, 26.8; now 15.7, 9.8 and 12.0.)
+//   order, then runs the cascade over its lanes; with many tokens 16 lanes each, up to 8 experts
+//   a lane.  (Those keep a longer chain of compares per TopK round and a quarter of the
+//   wavefronts: 2048 x 4096 x 128 experts, top 8, took 16.4 us a call with them, 14.3 without.)
 #include <atomic>
 
 #include "rf_device.h"
@@ -118,6 +117,59 @@ __device__ __forceinline__ void moe_cascade_token(float (&p)[EPL], int E, int la
   if (lane < topk) {
     prob[(int64_t)row * ldp + lane] = my_prob;
     idx[(int64_t)row * ldi + lane] = my_idx;
+  }
+}
+
+// The same on 16 lanes, lane q with experts q EPL ..: four tokens per wavefront.  A TopK round is a longer
+// chain (a compare per expert held, then an exchange of (score, index) pairs), but four tokens share it:
+// the better one as soon as there are tokens enough to fill the chip.
+template <int EPL>
+__device__ __forceinline__ void moe_cascade_token16(const float (&p)[EPL], int q, int row, bool live, int topk,
+                                                    float* __restrict__ prob, int32_t* __restrict__ idx,
+                                                    int64_t ldp, int64_t ldi) {
+  constexpr int E = 16 * EPL;
+  // stage 1: max;  stage 2: sum of exponentials
+  float m = p[0];
+#pragma unroll
+  for (int i = 1; i < EPL; ++i) m = fmaxf(m, p[i]);
+  m = row16_max(m);
+  float t = 0.f;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) t += fast_exp2((p[i] - m) * kLog2e);
+  const float inv_t = 1.0f / row16_sum(t);
+  // stage 3: TopK.  Each round takes the largest remaining score of the token (ties: the
+  // lowest expert index): lane-local best, then a 16-lane merge of (score, index) pairs.
+  uint32_t taken = 0;
+  float my_prob = 0.f;
+  int my_idx = 0;
+  for (int j = 0; j < topk; ++j) {
+    float bv = -INFINITY;
+    int bi = E;  // no candidate
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const bool ok = !((taken >> i) & 1u) && (p[i] > bv);  // strict: keeps the lowest index
+      bv = ok ? p[i] : bv;
+      bi = ok ? q * EPL + i : bi;
+    }
+#define RF_MERGE_TOP(CTRL)                                         \
+  {                                                                \
+    const float ov = dpp_f32<CTRL>(bv);                            \
+    const int oi = dpp_i32<CTRL>(bi);                              \
+    const bool take = (ov > bv) || (ov == bv && oi < bi);          \
+    bv = take ? ov : bv;                                           \
+    bi = take ? oi : bi;                                           \
+  }
+    RF_MERGE_TOP(kDppQuadXor1) RF_MERGE_TOP(kDppQuadXor2) RF_MERGE_TOP(kDppRowHalfMirror) RF_MERGE_TOP(kDppRowMirror)
+#undef RF_MERGE_TOP
+    if (bi / EPL == q && bi < E) taken |= 1u << (bi % EPL);
+    if ((j & 15) == q) {
+      my_prob = fast_exp2((bv - m) * kLog2e) * inv_t;
+      my_idx = bi;
+    }
+  }
+  if (live && q < topk) {
+    prob[(int64_t)row * ldp + q] = my_prob;
+    idx[(int64_t)row * ldi + q] = my_idx;
   }
 }
 
@@ -250,10 +302,13 @@ __global__ __launch_bounds__(kMoeFusedWaves * kWave, 2) void moe_fused_kernel(
 // Multi-segment strategy: NT = E / 32.  part[ks][row][e] = sum over the k slice of x[row,k] w[k,e].
 // (Taking x and w straight into the operands, as the single-segment kernel does, was measured here
 // too: never faster, and up to 2 us slower from 64 tokens on.)
-template <int NT>
+// FUSED: single-segment strategy for many tokens, 64 of them and the whole contraction axis per workgroup
+// (grid y = 1): the scores never leave the chip, the workgroup runs the cascade on them.
+template <int NT, bool FUSED>
 __global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, float* __restrict__ part, int S,
-    int n_kblocks, int64_t ldx, int64_t ldw) {
+    int n_kblocks, int64_t ldx, int64_t ldw, int topk, float* __restrict__ prob,
+    int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
   constexpr int E = 32 * NT;
   constexpr int PPR = E / 8;               // 16-byte pieces per W row
   constexpr int kWTileB = kMoeKB * E * 2;  // [k][e]
@@ -434,16 +489,54 @@ __global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
         }
   }
   __syncthreads();
-  float* prow = part + ((int64_t)ks * S) * E;
+  if constexpr (!FUSED) {
+    float* prow = part + ((int64_t)ks * S) * E;
 #pragma unroll
-  for (int cc = 0; cc < CPW; ++cc) {
-    const int c = wave * CPW + cc;
-    f32x4 v = red[c * 64 + lane];
+    for (int cc = 0; cc < CPW; ++cc) {
+      const int c = wave * CPW + cc;
+      f32x4 v = red[c * 64 + lane];
 #pragma unroll
-    for (int r = 1; r < 4; ++r) v += red[r * (kChunks * 64) + c * 64 + lane];
-    const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
-    const int m = row0 + 32 * mi + i32;
-    if (m < S) *reinterpret_cast<f32x4*>(prow + (int64_t)m * E + 32 * ni + 8 * r4 + 4 * hh) = v;
+      for (int r = 1; r < 4; ++r) v += red[r * (kChunks * 64) + c * 64 + lane];
+      const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
+      const int m = row0 + 32 * mi + i32;
+      if (m < S) *reinterpret_cast<f32x4*>(prow + (int64_t)m * E + 32 * ni + 8 * r4 + 4 * hh) = v;
+    }
+  } else {
+    // sums in the same fixed order, kept in registers until every wavefront has read the four
+    // copies, then laid out [token][expert] at the start of LDS
+    f32x4 sum[CPW];
+#pragma unroll
+    for (int cc = 0; cc < CPW; ++cc) {
+      const int c = wave * CPW + cc;
+      sum[cc] = red[c * 64 + lane];
+#pragma unroll
+      for (int r = 1; r < 4; ++r) sum[cc] += red[r * (kChunks * 64) + c * 64 + lane];
+    }
+    __syncthreads();
+    float* sc = reinterpret_cast<float*>(lds);  // [kMoeRows][E + 4] (padded rows)
+#pragma unroll
+    for (int cc = 0; cc < CPW; ++cc) {
+      const int c = wave * CPW + cc;
+      const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
+      *reinterpret_cast<f32x4*>(sc + (32 * mi + i32) * (E + 4) + 32 * ni + 8 * r4 + 4 * hh) = sum[cc];
+    }
+    __syncthreads();
+    // the cascade: 16 lanes per token, 16 tokens per pass
+    constexpr int EPL = E / 16;
+    const int q = tid & 15;
+#pragma unroll 1
+    for (int pass = 0; pass < kMoeRows / 16; ++pass) {
+      const int tl = 16 * pass + (tid >> 4);
+      const int row = row0 + tl;
+      float p[EPL];
+#pragma unroll
+      for (int i = 0; i < EPL; i += 2) {
+        const float2 v2 = *reinterpret_cast<const float2*>(sc + tl * (E + 4) + q * EPL + i);
+        p[i] = v2.x;
+        p[i + 1] = v2.y;
+      }
+      moe_cascade_token16<EPL>(p, q, row, row < S, topk, prob, idx, ldp, ldi);
+    }
   }
 }
 
@@ -471,6 +564,36 @@ __global__ __launch_bounds__(kCascadeThreads) void moe_cascade_kernel(
   }
   if (E < 64 && lane >= E) p[0] = -INFINITY;
   moe_cascade_token<EPL>(p, E, lane, row, topk, prob, idx, ldp, ldi);
+}
+
+// Many tokens: 16 lanes each.
+constexpr int kCascade16Threads = 64;  // one wavefront = 4 tokens per workgroup
+template <int EPL>
+__global__ __launch_bounds__(kCascade16Threads) void moe_cascade16_kernel(
+    const float* __restrict__ part, int KS, int S, int topk, float* __restrict__ prob,
+    int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
+  constexpr int E = 16 * EPL;
+  const int tid = threadIdx.x;
+  const int q = tid & 15;
+  const int row = blockIdx.x * (kCascade16Threads / 16) + (tid >> 4);
+  const bool live = row < S;
+  const int rrow = live ? row : S - 1;  // dead groups repeat the last token, store nothing
+
+  // scores: slices added in slice order
+  float p[EPL];
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) p[i] = 0.f;
+#pragma unroll 8
+  for (int s = 0; s < KS; ++s) {
+    const float* src = part + ((int64_t)s * S + rrow) * E + q * EPL;
+#pragma unroll
+    for (int i = 0; i < EPL; i += 2) {
+      const float2 v = *reinterpret_cast<const float2*>(src + i);
+      p[i] += v.x;
+      p[i + 1] += v.y;
+    }
+  }
+  moe_cascade_token16<EPL>(p, q, row, live, topk, prob, idx, ldp, ldi);
 }
 
 // Device address of `scratch` on the current device, resolved once per device (with that
@@ -517,6 +640,30 @@ int moe_num_slices(int S, int hd) {
   return ks;
 }
 
+// Many tokens on a short axis: 64 of them per workgroup instead of 16, for a quarter of the trips of w.  Until the
+// 16-token kernel's workgroups exceed one per compute unit it is up to twice as fast; beyond, both take
+// turns, and which one wins depends on the cascade's share.  us a turn, fitted per number of experts; us 64 /
+// 16 tokens: 12000 x 256 x 128 experts, top 1, 8.5 / 15.5, top 16, 29.7 / 33.6; 8000 x 1024 x 64, top 8, 18.2 / 12.3;
+// 4096 x 256 x 128, top 1, 8.4 / 6.5.  (Also where the grid of the 16-token kernel would pass 2^32 threads.)
+static bool moe_fused64_wins(int S, int hd, int E, int topk) {
+  const int64_t wg16 = ((int64_t)S + 15) / 16, wg64 = ((int64_t)S + kMoeRows - 1) / kMoeRows;
+  if (wg16 > UINT32_MAX / (kMoeFusedWaves * kWave)) return true;
+  if (wg16 <= 256) return false;
+  struct Cost { double launch, turn, axis, round; };
+  constexpr Cost c16[] = {{4.1, 0.65, 0.5, 0.26}, {4.0, 1.33, 1.06, 0.26}, {2.0, 3.12, 1.6, 0.41}};
+  constexpr Cost c64[] = {{1.2, 3.78, 3.62, 1.0}, {1.65, 4.05, 4.31, 1.13}, {1.6, 5.11, 6.71, 1.38}};
+  const int e = E / 64;  // 32, 64, 128 experts: 0, 1, 2
+  const double us16 = c16[e].launch + (double)((wg16 + 255) / 256) * (c16[e].turn + (hd > 128 ? c16[e].axis : 0) + c16[e].round * (topk - 1));
+  const int64_t turn = E == 32 ? 512 : 256;  // (two workgroups of 32 experts share a compute unit)
+  const double us64 = c64[e].launch + (double)((wg64 + turn - 1) / turn) * (c64[e].turn + c64[e].axis * hd / 1024 + c64[e].round * (topk - 1));
+  return us64 < us16;
+}
+
+// The cascade's wavefront per token pays off until there are some 14 of them per compute unit: both calls' us
+// with 16 lanes / a wavefront a token, 2560 k, 32 experts, top 16: 2048 tokens 11.0 / 10.0, 4096 12.3 / 13.5,
+// 12000 21.1 / 28.4; 128 experts 19.9 / 16.4, 20.3 / 20.4, 38.6 / 43.1.
+static bool moe_cascade16_wins(int S) { return S > 3584; }
+
 hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E, int topk,
                               int64_t ldx, int64_t ldw, float* prob, int32_t* idx, int64_t ldp,
                               int64_t ldi, float* part, hipStream_t s) {
@@ -527,6 +674,19 @@ hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E
     return hipErrorInvalidValue;
   const bf16_t* xb = (const bf16_t*)x;
   const bf16_t* wb = (const bf16_t*)w;
+  const dim3 grid1((unsigned)((S + kMoeRows - 1) / kMoeRows), (unsigned)KS), block1(kMoeThreads);
+#define RF_MOE_SCORES(NT, FUSED) \
+  hipLaunchKernelGGL((moe_scores_kernel<NT, FUSED>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, \
+                     idx, ldp, ldi)
+  if (hd <= kMoeSingleSegmentMaxHd && moe_fused64_wins(S, hd, E, topk)) {
+    switch (E) {
+      case 32: RF_MOE_SCORES(1, true); break;
+      case 64: RF_MOE_SCORES(2, true); break;
+      case 128: RF_MOE_SCORES(4, true); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   if (hd <= kMoeSingleSegmentMaxHd) {
     // single-segment strategy: scores GEMM and cascade in one kernel
 #define RF_MOE_FUSED(EE)                                                                                   \
@@ -541,15 +701,25 @@ hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E
 #undef RF_MOE_FUSED
     return hipGetLastError();
   }
-  const dim3 grid1((unsigned)((S + kMoeRows - 1) / kMoeRows), (unsigned)KS), block1(kMoeThreads);
   switch (E) {
-    case 32: hipLaunchKernelGGL((moe_scores_kernel<1>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw); break;
-    case 64: hipLaunchKernelGGL((moe_scores_kernel<2>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw); break;
-    case 128: hipLaunchKernelGGL((moe_scores_kernel<4>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw); break;
+    case 32: RF_MOE_SCORES(1, false); break;
+    case 64: RF_MOE_SCORES(2, false); break;
+    case 128: RF_MOE_SCORES(4, false); break;
     default: return hipErrorInvalidValue;
   }
+#undef RF_MOE_SCORES
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (moe_cascade16_wins(S)) {
+    const dim3 grid16((unsigned)((S + kCascade16Threads / 16 - 1) / (kCascade16Threads / 16)));
+#define RF_MOE_CASCADE16(EPL) \
+  hipLaunchKernelGGL((moe_cascade16_kernel<EPL>), grid16, dim3(kCascade16Threads), 0, s, part, KS, S, topk, prob, idx, ldp, ldi)
+    if (E == 32) RF_MOE_CASCADE16(2);
+    else if (E == 64) RF_MOE_CASCADE16(4);
+    else RF_MOE_CASCADE16(8);
+#undef RF_MOE_CASCADE16
+    return hipGetLastError();
+  }
   constexpr int kTokens = kCascadeThreads / kWave;
   const dim3 grid2((unsigned)((S + kTokens - 1) / kTokens)), block2(kCascadeThreads);
   switch (E) {

@@ -25,6 +25,45 @@ def test_moe_routing_edges(rf, S, hd, E, topk):  # noqa: F811
     check_routing(prob, idx, x, w, topk, "moe_routing edges")
 
 
+@pytest.mark.parametrize("S,hd,E,topk", [
+    # 64 tokens per workgroup on a short axis: more than one round of 16 tokens each, ragged last tiles
+    (12001, 256, 128, 1), (12050, 128, 64, 2), (16400, 256, 32, 1), (40003, 384, 128, 16),
+    # 16 lanes per token in the cascade, and the call just below
+    (3584, 1152, 32, 16), (3585, 1152, 32, 16), (4099, 1280, 64, 8), (6001, 1152, 128, 6),
+])
+def test_moe_routing_many_tokens(rf, S, hd, E, topk):  # noqa: F811
+    say(f"moe_routing many tokens S{S} hd{hd} E{E} top{topk}")
+    x, w = I.moe_routing_inputs(I.SEED_BASE + 85 + S, S, hd, E)
+    tx, tw = I.to_torch(x, "bf16", DEV), I.to_torch(w, "bf16", DEV)
+    prob, idx = rf.rf_moe_routing(tx, tw, topk)
+    torch.cuda.synchronize()
+    rows = list(range(0, S, 37)) + list(range(S - 40, S))
+    check_routing(prob[rows], idx[rows], x[rows], w, topk, "moe_routing many tokens")
+    # every token against the same call on a few tokens at a time (other kernels, other orders of the sums):
+    # the same decisions but where two scores lie within their error
+    part = [rf.rf_moe_routing(tx[i:i + 2000], tw, topk) for i in range(0, S, 2000)]
+    same = (torch.cat([p[1] for p in part]) == idx).double().mean()
+    assert float(same) >= 0.999
+    assert float((torch.cat([p[0] for p in part]) - prob).abs().max()) <= 1e-5
+
+
+def test_moe_routing_a_grid_of_more_than_2_to_32_threads(rf):  # noqa: F811
+    """One token repeated 140 million times (a row pitch of 0): 8.75 million workgroups of 512 threads would
+    wrap the grid's 32 bits and leave most tokens without a result."""
+    S, hd, E, topk = 140_000_000, 128, 32, 16
+    say(f"moe_routing S{S}")
+    x = torch.randn((1, hd), dtype=torch.float32, generator=torch.Generator().manual_seed(5)).to(DEV, torch.bfloat16).expand(S, hd)
+    w = torch.randn((hd, E), dtype=torch.float32, generator=torch.Generator().manual_seed(6)).to(DEV, torch.bfloat16)
+    prob = torch.full((S, topk), -1.0, dtype=torch.float32, device=DEV)
+    idx = torch.full((S, topk), -1, dtype=torch.int32, device=DEV)
+    rf.rf_moe_routing(x, w, topk, prob=prob, idx=idx)
+    torch.cuda.synchronize()
+    p, i = torch.topk(torch.softmax(x[0].double() @ w.double(), 0), topk)
+    assert torch.equal(idx[S - 1].long(), i) and float((prob[S - 1].double() - p).abs().max()) <= 1e-5
+    for lo in range(0, S, 10_000_000):
+        assert bool((idx[lo:lo + 10_000_000] == idx[S - 1]).all()) and bool((prob[lo:lo + 10_000_000] == prob[S - 1]).all())
+
+
 def test_moe_routing_infinite_scores(rf):  # noqa: F811
     """An expert whose score is -inf has probability 0 and is never chosen ahead of a finite one."""
     say("moe_routing: -inf scores")
