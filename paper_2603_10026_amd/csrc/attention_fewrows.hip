@@ -296,11 +296,15 @@ static bool offsets_fit(const AttnShape& a, const Strides4& sk, const Strides4& 
   return a.Lk >= 1 && ok(sk.l) && ok(sv.l);
 }
 
+// A grid holds less than 2^32 threads.  (Several row tiles per head make more workgroups here than in the
+// kernels that take over where they do not fit.)
+constexpr int64_t max_workgroups(int nw) { return UINT32_MAX / (nw * kWave); }
+
 // Expected us, for the comparison with the tiled kernel (fitted together with its figures: see there).  A
 // workgroup walks the keys in steps of 128.
 double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
   const int64_t wgs = row_tiles(a) * a.B * a.Hkv;
-  if (!offsets_fit(a, sk, sv, kDirectWaves)) return INFINITY;
+  if (!offsets_fit(a, sk, sv, kDirectWaves) || wgs > max_workgroups(kDirectWaves)) return INFINITY;
   constexpr AttnCost d128 = {3.5, 1.21, 0.24, 1.21}, d64 = {3.5, 0.73, 0.15, 0.71};
   return (a.d == 128 ? d128 : d64).us(a.Lk / 128.0 + 0.5, (double)wgs, tile_keys(a, 16) / 128 + 0.5);
 }
@@ -309,7 +313,7 @@ hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v,
                                     Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, hipStream_t s) {
   const int64_t n_rt = row_tiles(a);
   const int64_t grid = n_rt * a.B * a.Hkv;
-  if (grid > INT32_MAX) return hipErrorInvalidValue;
+  if (grid > max_workgroups(kDirectWaves)) return hipErrorInvalidValue;
 #define RF_FEW(DD)                                                                                              \
   hipLaunchKernelGGL((attention_fewrows_kernel<DD, kDirectWaves, true>), dim3((unsigned)grid),                  \
                      dim3(kDirectWaves * kWave), 0, s, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, sq, sk, \
@@ -335,6 +339,7 @@ hipError_t launch_attention_fewrows(const void* q, const void* k, const void* v,
 // 636, 11.6 and 8.6; 1024 of 94, the rule's figures fitted to 369 calls like these, 11.2 and 12.7).
 bool attention_fewrows_splitk_wins(const AttnShape& a, const Strides4& sk, const Strides4& sv, int num_splits) {
   if (!offsets_fit(a, sk, sv, kSplitWaves) || (double)a.B * a.Hkv * a.Lk * a.d * 4 > 128e6) return false;
+  if ((double)row_tiles(a) * a.B * a.Hkv * num_splits > (double)max_workgroups(kSplitWaves)) return false;
   if (row_tiles(a) > 1) return true;
   constexpr AttnCost here = {3.6, 0, 0.65, 1.54}, there = {3.1, 0, 1.59, 1.33};
   const double wgs = (double)a.B * a.Hkv * num_splits, steps = ceil((double)a.Lk / num_splits) / 128;
@@ -346,7 +351,7 @@ hipError_t launch_attention_fewrows_splitk(const void* q, const void* k, const v
                                            float* part_acc, const AttnShape& a, hipStream_t s) {
   const int64_t n_rt = row_tiles(a);
   const int64_t grid = n_rt * a.B * a.Hkv * num_splits;
-  if (grid > INT32_MAX || a.d != 128) return hipErrorInvalidValue;
+  if (grid > max_workgroups(kSplitWaves) || a.d != 128) return hipErrorInvalidValue;
   const int chunk = (a.Lk + num_splits - 1) / num_splits;
   hipLaunchKernelGGL((attention_fewrows_kernel<128, kSplitWaves, false>), dim3((unsigned)grid),
                      dim3(kSplitWaves * kWave), 0, s, (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, sq, sk, sv,

@@ -53,6 +53,11 @@ def test_fp32_attention_routes(Bt, Hq, Hkv, Lq, Lk, d, causal, routes):
     assert attention_route(Bt, Hq, Hkv, Lq, Lk, d, causal, torch.float32) in routes
 
 
+def test_attention_grids_of_2_to_32_threads_are_left_to_larger_tiles():
+    assert attention_route(1 << 19, 16, 16, 17, 16, 64, False) in TILED       # 2^24 tiles of 16 rows, 2^23 of 128
+    assert attention_route(1 << 18, 16, 16, 17, 16, 64, False) != 0
+
+
 def test_attention_refusals_have_no_route():
     assert attention_route(1, 3, 2, 4, 4, 128, False) == 0
     assert attention_route(1, 2, 2, 4, 4, 96, False) == 0
@@ -68,6 +73,8 @@ STREAMING, SHORT_CHUNKS = 1, 2   # rf_diag_splitk_route
     # short chunks, and several row tiles per KV head (25.5 / 21.2, 328 / 106)
     (4, 32, 8, 1, 3001, 32, SHORT_CHUNKS), (1, 4, 1, 1, 100, 64, SHORT_CHUNKS), (38, 8, 1, 4, 2700, 4, SHORT_CHUNKS),
     (2, 64, 8, 128, 2048, 8, SHORT_CHUNKS),
+    # two row tiles: 2^24 workgroups of 256 threads would pass a grid's 32 bits, half of them do not
+    (1, 1, 1, 17, 64, 1 << 23, STREAMING), (1, 1, 1, 17, 64, (1 << 23) - 1, SHORT_CHUNKS),
 ])
 def test_splitk_routes(Bt, Hq, Hkv, Lq, Lk, S, route):
     q = torch.empty((Bt, Hq, Lq, 128), dtype=torch.bfloat16, device="meta")
