@@ -8,7 +8,7 @@
 // the algorithmic minimum (one read + one write).
 //
 // Rows that start at any element or hold no whole number of vectors take the same kernels with
-// unaligned vectors (below).
+// unaligned vectors (below); rows of less than one vector take a lane each.
 //
 // Kernel 2 (rows too long for the registers of a workgroup): one workgroup streams a row, every
 // lane carrying the level-1 incremental state (m, l) (Appendix A.2,
@@ -237,6 +237,32 @@ __global__ __launch_bounds__(kSoftmaxWavesPerWg * kWave) void softmax_short_rows
   }
 }
 
+// Rows of less than one vector: a lane each, a wavefront per workgroup (pitched rows are a cache line
+// each: spread over the chip).  With a workgroup per row 100000 rows of 5 bf16 values took 52 us, 2.8 here.
+template <typename T>
+__global__ __launch_bounds__(kWave) void softmax_tiny_rows_kernel(
+    const T* __restrict__ x, T* __restrict__ y, int64_t rows, int n, int64_t x_pitch, int64_t y_pitch) {
+  constexpr int N = Elem<T>::kPerVec - 1;
+  const int64_t row = (int64_t)blockIdx.x * kWave + threadIdx.x;
+  if (row >= rows) return;
+  const T* xr = x + row * x_pitch;
+  float e[N], m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    e[i] = i < n ? Elem<T>::load(xr + i) : -INFINITY;
+    m = fmaxf(m, e[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    e[i] = i < n ? fast_exp2((e[i] - m) * kLog2e) : 0.f;
+    l += e[i];
+  }
+  const float inv = 1.0f / l;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i < n) Elem<T>::store(y + row * y_pitch + i, e[i] * inv);
+}
+
 // Long rows that still fit the registers of one workgroup (up to WAVES * 64 lanes * 64 values):
 // one workgroup per row, the row read once and kept as fp32; the two reductions go through
 // the wavefronts' DPP reductions and one LDS exchange each.
@@ -409,7 +435,10 @@ static hipError_t launch_softmax_t(const T* x, T* y, int64_t rows, int64_t n, in
                                    int64_t y_pitch, hipStream_t s) {
   constexpr int V = Elem<T>::kPerVec;
   const int64_t per_chunk = (int64_t)V * kWave;
-  if (n >= V && n <= 32 * V) {
+  if (n < V) {
+    hipLaunchKernelGGL((softmax_tiny_rows_kernel<T>), dim3((unsigned)((rows + kWave - 1) / kWave)), dim3(kWave), 0, s, x, y,
+                       rows, (int)n, x_pitch, y_pitch);
+  } else if (n <= 32 * V) {
     // short rows: 2, 4, 8 or 16 rows per wavefront
     const int nvec = (int)((n + V - 1) / V);
     const int lpr = nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : 32;
@@ -424,7 +453,7 @@ static hipError_t launch_softmax_t(const T* x, T* y, int64_t rows, int64_t n, in
     else if (lpr == 16) RF_SOFTMAX_SHORT(16);
     else RF_SOFTMAX_SHORT(32);
 #undef RF_SOFTMAX_SHORT
-  } else if (n >= V && n <= (64 / V) * per_chunk) {
+  } else if (n <= (64 / V) * per_chunk) {
     // one wavefront per row, at most 64 values per lane
     const int nch = (int)((n + per_chunk - 1) / per_chunk);
     const unsigned grid = (unsigned)((rows + kSoftmaxWavesPerWg - 1) / kSoftmaxWavesPerWg);
@@ -442,7 +471,7 @@ static hipError_t launch_softmax_t(const T* x, T* y, int64_t rows, int64_t n, in
     else if (nch <= 12) RF_SOFTMAX_CASE(12);
     else RF_SOFTMAX_CASE(16);
 #undef RF_SOFTMAX_CASE
-  } else if (n >= V && n <= 16 * 64 * (int64_t)kWave) {
+  } else if (n <= 16 * 64 * (int64_t)kWave) {
     // 2 / 4 / 8 / 16 wavefronts of at most 64 values per lane (rows of 8K, 16K, 32K, 64K values);
     // rows of up to three quarters of that hold 48 values per lane, so that at most a third of
     // the lanes' vectors lie past the end (1000 rows of 20001 bf16 values: 20.1 -> 18.5 us; a
@@ -460,7 +489,7 @@ static hipError_t launch_softmax_t(const T* x, T* y, int64_t rows, int64_t n, in
                        dim3(W * kWave), 0, s, x, y, rows, (int)n, x_pitch, y_pitch);
     RF_SOFTMAX_WG(2) RF_SOFTMAX_WG(4) RF_SOFTMAX_WG(8) RF_SOFTMAX_WG(16)
 #undef RF_SOFTMAX_WG
-  } else {  // longer rows, and rows of less than one vector
+  } else {  // longer rows
     hipLaunchKernelGGL((softmax_row_streaming_kernel<T>), dim3((unsigned)rows),
                        dim3(kStreamThreads), 0, s, x, y, rows, n, x_pitch, y_pitch);
   }

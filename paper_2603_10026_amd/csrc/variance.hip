@@ -11,7 +11,7 @@
 // of the expanded square vanishes).  It is associative and commutative, so the
 // same operator merges vectors, lanes, wavefronts.
 //
-// Short rows take a wavefront or less each (variance_rows_kernel).  For longer ones,
+// Short rows take a wavefront or less each (variance_rows_kernel), those of less than one vector a lane.  For longer ones,
 // one workgroup (4 wavefronts, or 16 when rows are few and long) streams one row once.  Every lane turns each
 // 128-bit vector into an exact state (two passes over 4 or 8 registers), merges
 // the eight vectors of a chunk pairwise (equal counts: no division), and folds
@@ -110,7 +110,7 @@ constexpr int kVarUnroll = 8;  // 128-bit loads in flight per lane in a full chu
 // vectors each, and take the two stages one after the other, each over registers and reduced by
 // shuffles over the lanes of the row.  The workgroup-per-row kernel below spends such a row's time
 // on its barrier and its state merges and leaves lanes idle: 16384 rows of 1000 bf16 values
-// VARA us there, VARB here; 32768 rows of 64 fp32 values VARC and VARD.
+// 20.5 us there, 7.4 here; 32768 rows of 64 fp32 values 30.2 and 3.0.
 // Rows may start at any element: vector idx covers elements idx V .., and the one that would
 // reach past the end is moved back to the last V elements, where it repeats elements of its
 // neighbour, which both sums leave out.
@@ -161,6 +161,24 @@ __global__ __launch_bounds__(kVarRowsThreads) void variance_rows_kernel(
     mean_out[row] = mean;
     var_out[row] = m2 * inv_n;
   }
+}
+
+// Rows of less than one vector: a lane each.  (A workgroup per row, 100000 rows of 5 bf16 values: 107 us,
+// 2.6 here.)
+template <typename T>
+__global__ __launch_bounds__(kWave) void variance_tiny_rows_kernel(
+    const T* __restrict__ x, float* __restrict__ mean_out, float* __restrict__ var_out, int64_t rows, int n,
+    int64_t x_pitch) {
+  constexpr int V = Elem<T>::kPerVec;
+  const int64_t row = (int64_t)blockIdx.x * kWave + threadIdx.x;
+  if (row >= rows) return;
+  const T* xr = x + row * x_pitch;
+  float f[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) f[i] = i < n ? Elem<T>::load(xr + i) : 0.f;
+  const VarState st = var_of_vector<V>(f, n);
+  mean_out[row] = st.mean;
+  var_out[row] = st.m2 / (float)n;
 }
 
 // Longer rows.  kVarWaves wavefronts share a row: 4 when there are enough rows to fill the GPU, 16
@@ -242,11 +260,15 @@ template <typename T>
 static hipError_t launch_variance_t(const T* x, float* mean, float* var, int64_t rows, int64_t n,
                                     int64_t x_pitch, hipStream_t s) {
   constexpr int V = Elem<T>::kPerVec;
+  if (n < V) {
+    hipLaunchKernelGGL((variance_tiny_rows_kernel<T>), dim3((unsigned)((rows + kWave - 1) / kWave)), dim3(kWave), 0, s, x, mean, var, rows, (int)n, x_pitch);
+    return hipGetLastError();
+  }
   const int64_t nvec64 = (n + V - 1) / V;
   // A wavefront per row up to 6 vectors a lane (1.0 to 5 times the workgroup's speed for 16 to
   // 16384 rows), up to 8 where there are rows to fill the GPU (2 times at 16384 rows of 4095 bf16
   // values, 0.96 at 256); with more, too few wavefronts fit the registers (16384 x 4095 fp32: 0.96).
-  if (n >= V && nvec64 <= (rows >= 1024 ? 8 : 6) * kWave) {
+  if (nvec64 <= (rows >= 1024 ? 8 : 6) * kWave) {
     const int nvec = (int)nvec64;
     const int lpr = nvec <= 4 ? 4 : nvec <= 8 ? 8 : nvec <= 16 ? 16 : nvec <= 32 ? 32 : 64;
     const int nch = (nvec + lpr - 1) / lpr;  // 1 for less than 64 lanes

@@ -116,3 +116,28 @@ def test_softmax_masked_rows(rf, dtype, mask):  # noqa: F811
                 assert bool(torch.isnan(y[5]).all())
             else:
                 assert float((y[5].double() * n - 1).abs().max()) <= 1e-2
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 1), ("bf16", 2), ("bf16", 5), ("bf16", 7), ("f32", 1), ("f32", 2), ("f32", 3)])
+def test_rows_of_less_than_one_vector(rf, dtype, n):  # noqa: F811
+    """A lane per row: row counts around a wavefront and a workgroup, pitched and packed, what lies between the
+    rows left as it was."""
+    for rows in (1, 63, 64, 255, 257, 1000):
+        for gap in (0, 3):
+            say(f"tiny rows {dtype} rows={rows} n={n} gap={gap}")
+            x = I.softmax_inputs(I.SEED_BASE + 95, rows, n, 2.0, dtype)
+            t = I.to_torch(x, dtype, DEV)
+            xb = torch.full((rows, n + gap), 50.0, dtype=t.dtype, device=DEV)
+            xb[:, :n] = t
+            yb = torch.full((rows, n + gap), -7.0, dtype=t.dtype, device=DEV)
+            rf.rf_safe_softmax(xb[:, :n], yb[:, :n])
+            mean, var = rf.rf_variance(xb[:, :n])
+            torch.cuda.synchronize()
+            check(yb[:, :n], O.safe_softmax(x), dtype, "softmax tiny rows")
+            assert bool((yb[:, n:] == -7.0).all())
+            m_ref, v_ref = O.variance(x)
+            check(mean, m_ref, "f32", "variance tiny rows, mean")
+            if n > 1:
+                check(var, v_ref, "f32", "variance tiny rows, var")
+            else:
+                assert float(var.abs().max()) == 0.0
