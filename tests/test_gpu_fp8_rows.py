@@ -41,6 +41,46 @@ def test_fp8_quant_gemm_few_rows(rf, M, K, N):  # noqa: F811
     assert bool(torch.isnan(c[:, :8]).all()) and bool(torch.isnan(c[:, N + 8:]).all())
 
 
+# (tokens, channels) of the output tile, 128-k tiles a wavefront holds, and a product that takes them: every
+# instance of the kernel (test_routes.py holds the list against the rule), ragged in both directions where the
+# rule has such a call, runs that leave wavefronts without a tile among them
+FP8_TILES = [
+    ((16, 16), 2, (17, 1024, 1032)), ((16, 32), 2, (5, 128, 4104)), ((16, 64), 2, (15, 896, 8200)),
+    ((32, 16), 2, (545, 640, 8)), ((32, 32), 2, (260, 512, 520)), ((32, 64), 2, (17, 896, 8200)),
+    ((64, 16), 2, (1543, 1024, 8)), ((64, 32), 2, (1025, 2048, 136)), ((64, 64), 2, (400, 1536, 1032)),
+    ((16, 16), 4, (33, 2176, 264)), ((16, 32), 4, (16, 3072, 4104)), ((16, 64), 4, (13, 4096, 8200)),
+    ((32, 16), 4, (545, 2176, 8)), ((32, 32), 4, (260, 3072, 520)), ((32, 64), 4, (20, 2176, 8200)),
+    ((16, 16), 8, (5, 4224, 264)), ((16, 32), 8, (16, 8192, 4104)), ((16, 64), 8, (15, 4224, 8200)),
+]
+
+
+@pytest.mark.parametrize("tile,held,shape", FP8_TILES)
+def test_fp8_quant_gemm_every_tile(rf, tile, held, shape):  # noqa: F811
+    """Tokens of powers of two whose maximum keeps moving: MAX a / m' is an FP8 value for every prefix maximum m',
+    so the result is a @ w^T up to fp32 sums and the rounding of c, whatever the tile."""
+    M, K, N = shape
+    assert rf.rf_diag_fp8_quant_gemm_tile(M, K, N) == tile and held == (2 if K <= 2048 else 4 if K <= 4096 else 8)
+    say(f"fp8_quant_gemm tile {tile} holding {held}: M{M} K{K} N{N}")
+    _, w, w_bits = I.fp8_quant_gemm_inputs(I.SEED_BASE + 61, 1, K, N)
+    rng = np.random.Generator(np.random.PCG64(61 + M))
+    e = rng.integers(-7, 1, size=(M, K))
+    e[::3] = np.sort(e[::3], axis=1)           # rising runs: a rescale in almost every tile
+    a = (np.exp2(e) * rng.choice([-1.0, 1.0], size=(M, K))).astype(np.float32)
+    a[M // 2] = 0.0
+    c = torch.full((M, N + 16), float("nan"), dtype=torch.bfloat16, device=DEV)
+    rf.rf_fp8_quant_gemm(I.to_torch(a, "bf16", DEV), _fp8_tensor(w_bits), c=c[:, 8:N + 8])
+    torch.cuda.synchronize()
+    ta, tw = torch.from_numpy(a).to(DEV).double(), torch.from_numpy(np.asarray(w, dtype=np.float32)).to(DEV).double()
+    want, mass = ta @ tw.T, ta.abs() @ tw.abs().T
+    err = (c[:, 8:N + 8].double() - want).abs()
+    # half a bf16 step, and the FP8 matrix instruction's own sums: it aligns the products of an instruction to
+    # the largest before it adds them, which is worth up to 2^-16 of the sum of the products' magnitudes (the
+    # large kernel, 1152 x 256 x 7424, shows the same 2^-16.0; this one 2^-16.4 at most).  Four times that is
+    # a thousandth of what a missed or doubled rescale, a factor of 2 on a tile of 128 products, would leave.
+    assert bool((err <= 2.0 ** -8 * want.abs() + 2.0 ** -14 * mass).all())
+    assert bool(torch.isnan(c[:, :8]).all()) and bool(torch.isnan(c[:, N + 8:]).all())
+
+
 @pytest.mark.parametrize("M,K,N", [(4, 1024, 256), (40, 2048, 520), (16, 4096, 264), (3, 8192, 264), (2000, 1024, 512)])
 def test_fp8_quant_gemm_only_the_result_has_to_be_in_range(rf, M, K, N):  # noqa: F811
     """Sums over parts of the contraction axis that leave fp32 while the whole does not: 2^114 times 256 over

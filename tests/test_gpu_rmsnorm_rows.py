@@ -35,6 +35,21 @@ def test_rmsnorm_gemm_few_rows(rf, M, K, N):  # noqa: F811
     assert bool(torch.isnan(y[:, :8]).all()) and bool(torch.isnan(y[:, N + 8:]).all())
 
 
+# (rows, columns) of the output tile and products that take it: every instance (test_routes.py holds the list
+# against the rule)
+RMSNORM_TILES = [
+    ((16, 32), (16, 256, 64)), ((16, 64), (5, 192, 8200)), ((16, 64), (13, 1088, 8200)), ((32, 32), (270, 192, 40)),
+    ((32, 64), (601, 128, 72)), ((32, 128), (41, 320, 8200)), ((64, 64), (1999, 192, 72)), ((64, 64), (2000, 64, 8)),
+    ((64, 128), (100, 512, 8200)),
+]
+
+
+@pytest.mark.parametrize("tile,shape", RMSNORM_TILES)
+def test_rmsnorm_gemm_every_tile(rf, tile, shape):  # noqa: F811
+    assert rf.rf_diag_rmsnorm_gemm_tile(*shape) == tile
+    test_rmsnorm_gemm_few_rows(rf, *shape)
+
+
 def test_rmsnorm_gemm_rows_do_not_depend_on_their_batch(rf):  # noqa: F811
     """A row of a small batch, which the small tiles serve, and the same row in a batch of 4096 rows,
     which the 128 x 512 tiles serve, meet the same bf16 roundings (x g, then y): they differ by the

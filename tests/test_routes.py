@@ -1,5 +1,7 @@
 """Which kernel a call takes, by the library's own rules (no GPU needed): the calls that a rule must leave to the
 general kernel because it serves them faster."""
+import sys
+
 import pytest
 import torch
 
@@ -91,3 +93,50 @@ def test_splitk_routes(Bt, Hq, Hkv, Lq, Lk, S, route):
 ])
 def test_fp8_tiles(M, K, N, large):
     assert (B.rf_diag_fp8_quant_gemm_tile(M, K, N)[0] == 128) == large
+
+
+# ---- what the GPU tests cover, held against the rules: a changed rule must not leave a kernel without a test ----
+sys.path.insert(0, __file__.rsplit("/", 1)[0])
+
+
+def test_every_fp8_tile_has_a_gpu_test():
+    from test_gpu_fp8_rows import FP8_TILES
+    for tile, _, shape in FP8_TILES:
+        assert B.rf_diag_fp8_quant_gemm_tile(*shape) == tile, shape
+    held = {2: [(m, n) for m in (16, 32, 64) for n in (16, 32, 64)], 4: [(m, n) for m in (16, 32) for n in (16, 32, 64)],
+            8: [(16, n) for n in (16, 32, 64)]}
+    assert {(t, h) for t, h, _ in FP8_TILES} == {(t, h) for h, ts in held.items() for t in ts}
+    # and the rule takes no other tile, over a grid of sizes
+    for M in (1, 7, 16, 33, 100, 260, 545, 1000, 2000, 4096):
+        for K in (128, 640, 2048, 2176, 4096, 4224, 8192):
+            for N in (8, 136, 520, 1032, 4104, 8200):
+                t = B.rf_diag_fp8_quant_gemm_tile(M, K, N)
+                assert t[0] == 128 or t in held[2 if K <= 2048 else 4 if K <= 4096 else 8], (M, K, N, t)
+
+
+def test_every_rmsnorm_tile_has_a_gpu_test():
+    from test_gpu_rmsnorm_rows import RMSNORM_TILES
+    for tile, shape in RMSNORM_TILES:
+        assert B.rf_diag_rmsnorm_gemm_tile(*shape) == tile, shape
+    tiles = {(16, 32), (16, 64), (32, 32), (32, 64), (32, 128), (64, 64), (64, 128)}
+    assert {t for t, _ in RMSNORM_TILES} == tiles
+    for M in (1, 16, 33, 100, 270, 600, 1000, 2000, 4096):
+        for K in (64, 512, 1088, 4096, 8192):
+            for N in (8, 72, 520, 1032, 4104, 8200):
+                assert B.rf_diag_rmsnorm_gemm_tile(M, K, N) in tiles | {(128, 512)}, (M, K, N)
+
+
+def test_every_attention_kernel_has_gpu_tests_in_each_head_dimension():
+    from test_gpu_few_query_tiles import FEW_ATTENTION
+    from test_gpu_parity import ATTN_CASES
+    from test_gpu_tiled_attention import TILED_ATTENTION
+    for case in TILED_ATTENTION:
+        assert attention_route(*case[2:], torch.bfloat16 if case[1] == "bf16" else torch.float32) == case[0], case
+    seen = {}
+    for case in [*FEW_ATTENTION, *ATTN_CASES, *(c[1:] for c in TILED_ATTENTION)]:
+        r = attention_route(*case[1:], torch.bfloat16 if case[0] == "bf16" else torch.float32)
+        seen.setdefault((r, case[6]), []).append(case)
+    for d in (64, 128):
+        for r in (1, 2, 3, 4, KEY_GROUPS, FEW_ROWS, F32_FEW_ROWS, F32_TWO_TILES, F32_WAVES8):
+            assert len(seen.get((r, d), [])) >= (1 if r in (3, 12) else 2), (r, d, seen.get((r, d)))
+    assert seen[F32_WAVES16, 64] and seen[F32_WAVES4, 128]
