@@ -79,13 +79,19 @@ def build_library(verbose=True, jobs=8):
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
-    build_pycall(verbose)
     check_waits(verbose)
     return LIB
 
 
+def build_all(verbose=True, jobs=8):
+    """librf.so, then the module that the Python binding calls it through."""
+    build_library(verbose, jobs)
+    build_pycall(verbose)
+
+
 def build_pycall(verbose=True):
-    """Compile the CPython module that hands torch tensors to librf.so (host code only)."""
+    """Compile the CPython module that hands torch tensors to librf.so (host code only; needs torch's
+    headers and a C++ compiler, which the library itself does not)."""
     import sysconfig
 
     import torch
@@ -135,5 +141,5 @@ def _drain(procs):
 
 
 if __name__ == "__main__":
-    build_library()
+    build_all()
     print("built", LIB)

@@ -15,9 +15,11 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module")
 def lib():
+    from paper_2603_10026_amd import build
     if not os.path.exists(B.LIB_PATH):
-        from paper_2603_10026_amd import build
         build.build_library(verbose=False)
+    if not os.path.exists(build.PYCALL):
+        build.build_pycall(verbose=False)
     return B.load_library()
 
 
