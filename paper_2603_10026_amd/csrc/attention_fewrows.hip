@@ -34,13 +34,6 @@ constexpr int few_min_waves(bool direct) { return direct ? 2 : 4; }
 // compute unit (70.7, 71.8, 75.0 us for one row tile of 8000 keys: the cache lines the unit has
 // in flight set the pace, 58 GB/s), and 4 leave the smallest merge.
 constexpr int kDirectWaves = 4, kSplitWaves = 4;
-
-__device__ __forceinline__ uint32_t pair_lo(uint32_t x, uint32_t y) {
-  return __builtin_amdgcn_perm(y, x, 0x05040100u);
-}
-__device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) {
-  return __builtin_amdgcn_perm(y, x, 0x07060302u);
-}
 }  // namespace
 
 template <int D, int NW, bool DIRECT>

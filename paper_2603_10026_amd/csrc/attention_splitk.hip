@@ -30,14 +30,6 @@ constexpr int kTileKeys = 32;            // keys per wavefront step
 constexpr int kRowBytes = kD * 2;        // one K/V row
 constexpr int kKTileBytes = kTileKeys * kRowBytes;  // 8 KB per wavefront
 
-// low halves / high halves of two packed bf16 pairs
-__device__ __forceinline__ uint32_t pair_lo(uint32_t x, uint32_t y) {
-  return __builtin_amdgcn_perm(y, x, 0x05040100u);
-}
-__device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) {
-  return __builtin_amdgcn_perm(y, x, 0x07060302u);
-}
-
 }  // namespace
 
 // Two workgroups per compute unit: bounding the registers for three was measured 1.4 % slower

@@ -233,7 +233,7 @@ inline int tiles_held(int K) { return K <= 2048 ? 2 : K <= 4096 ? 4 : 8; }
 // channel tiles are dealt to the 8 XCDs, so some get a row of workgroups more: 168 x 512 x 1272 as
 // 1 x 4, 33 workgroups on half of them, took 11.7 us instead of 7).  Within 10 % of the
 // measured times of all shapes for 512 to 8192 k, 512 to 8192 channels and 1 to 512 tokens, e.g.
-// 9.3 us for 16 x 4096 x 4096 as 1 x 1, 17.6 for 128 x 4096 x 4096 as 2 x 4, 23.5 for
+// 9.5 us for 16 x 4096 x 4096 as 1 x 1, 18.3 for 128 x 4096 x 4096 as 2 x 4, 23.9 for
 // 128 x 8192 x 2048 as 1 x 4.
 inline double rows_us(const FShape& r, int M, int K, int N) {
   const double k = K <= 2048 ? fmax(K / 1024.0, 1.5) : tiles_held(K);  // (all held tiles are fetched)
@@ -252,7 +252,7 @@ FShape best_shape(int M, int K, int N) {
 
 // The large kernel takes 6 us and 9 for every 1024 k as long as its tiles leave compute units idle
 // (35 to 48 us at 4096 k, 65 to 86 at 8192), whatever the token count.  Both sides at the line:
-// 256 x 4096 x 4096: 33.6 us here, 46.9 there; 384: 49.5 and 48.5.  64 x 8192 x 8192: 46 and 77;
+// 256 x 4096 x 4096: 34.3 us here, 46.9 there; 384: 49.5 and 48.5.  64 x 8192 x 8192: 46 and 77;
 // 100: 89 and 83.  1672 x 256 x 40: 13.8 and 7.7 (a handful of channel tiles leaves XCDs idle).
 bool fp8_quant_gemm_rows_wins(int M, int K, int N, const void* c, int64_t ldc) {
   // (8-byte stores of c)

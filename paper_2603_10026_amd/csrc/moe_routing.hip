@@ -65,10 +65,6 @@ __device__ __forceinline__ float wave_sum_valu(float v) {
   return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
-// low halves / high halves of two packed bf16 pairs
-__device__ __forceinline__ uint32_t pair_lo(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100u); }
-__device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); }
-
 }  // namespace
 
 // The cascade of one token, a wavefront per token: p[i] of a lane is the score of expert

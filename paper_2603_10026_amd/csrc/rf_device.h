@@ -37,6 +37,13 @@ __device__ __forceinline__ bf16_t to_bf16(float a) {
 }
 __device__ __forceinline__ float from_bf16(bf16_t a) { return __uint_as_float(((uint32_t)a) << 16); }
 
+// Low halves / high halves of two packed bf16 pairs.
+__device__ __forceinline__ uint32_t pair_lo(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100u); }
+__device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); }
+
+// A 16-byte vector of a row that starts at any element.  (The hardware takes 16-byte accesses at any address.)
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
 // ---- element access by storage type (128-bit vectors) ---------------------
 template <typename T> struct Elem;
 template <> struct Elem<bf16_t> {

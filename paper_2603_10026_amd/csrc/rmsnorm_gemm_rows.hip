@@ -22,7 +22,7 @@
 // other's lines): 48 x 4096 x 4096, repeated on the same w (33 MB: it stays in the memory-side cache),
 // takes 13.8 us a call, and 86.4 in 128 x 512 tiles.  A few hundred rows are bound by the same lines in
 // either kernel, and 64 x 128 tiles move fewest of them per compute unit in use: 1024 x 8192 x 2048
-// takes 57 us against 171.
+// takes 57 to 62 us, by the card, against 171.
 #include <math.h>
 
 #include "rf_device.h"
@@ -33,10 +33,6 @@ namespace rf {
 namespace {
 constexpr int kRWaves = 4;
 constexpr int kRThreads = kRWaves * kWave;
-
-// low halves / high halves of two packed bf16 pairs
-__device__ __forceinline__ uint32_t pair_lo(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x05040100u); }
-__device__ __forceinline__ uint32_t pair_hi(uint32_t x, uint32_t y) { return __builtin_amdgcn_perm(y, x, 0x07060302u); }
 }  // namespace
 
 // P: steps of 32 k in flight per wavefront.  (Two workgroups per compute unit in the bounds: with
@@ -239,8 +235,8 @@ const RowsShape& best_shape(int M, int K, int N) {
 }  // namespace
 
 // The 128 x 512 tiles take 5 us and 20.5 for every 1024 k up to 64 of them, 29 at 256, whatever the
-// row count.  Both sides at the line (us here / there): 1024 x 4096 x 4096 66 / 89, 1500 rows 97 / 90;
-// 768 x 8192 x 8192 170 / 174, 1024 rows 241 / 176; 2048 x 8192 x 2048 123 / 171.
+// row count.  Both sides at the line (us here / there): 1024 x 4096 x 4096 68 / 89, 1500 rows 101 / 90;
+// 768 x 8192 x 8192 171 / 174, 1024 rows 225 / 172; 2048 x 8192 x 2048 117 / 170.
 // (the buffer loads take 32-bit byte offsets inside w; rows of y are stored 16 bytes at a time)
 bool rmsnorm_gemm_rows_wins(int M, int K, int N, int64_t ldw, const void* y, int64_t ldy) {
   if ((int64_t)K * ldw * 2 >= ((int64_t)1 << 32) || (ldy & 7) != 0 || (reinterpret_cast<uintptr_t>(y) & 15) != 0) return false;

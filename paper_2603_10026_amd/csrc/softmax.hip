@@ -32,11 +32,9 @@ namespace {
 // that would reach past the end is moved back to the last V elements, where it repeats up to V - 1
 // elements of its neighbour.  A repeated element does not change a maximum and is stored twice
 // with the same value; only the sum has to leave it out.  Vectors past the end sit in the same
-// place and contribute nothing.  (The hardware takes 16-byte accesses at any address; a wavefront's
-// 1 KB then touches nine 128-byte lines instead of eight.)  256 rows of 50001 fp32 values take
-// 22 us where element-wise accesses and two sweeps took 136; 4096 rows of 4095 bf16 values 13.6
-// where they took 36.5 (4096 rows of 4096: 12.0).
-typedef u32x4 u32x4_any __attribute__((aligned(2)));
+// place and contribute nothing.  (A wavefront's 1 KB then touches nine 128-byte lines instead of
+// eight.)  256 rows of 50001 fp32 values take 22 us where element-wise accesses and two sweeps took
+// 112; 4096 rows of 4095 bf16 values 13.0 where they took 26.5.
 
 template <typename T>
 __device__ __forceinline__ u32x4 ragged_load(const T* row, int idx, int n) {

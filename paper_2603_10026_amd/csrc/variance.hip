@@ -98,9 +98,6 @@ __device__ __forceinline__ VarState var_shfl_xor(const VarState& a, int mask) {
   return b;
 }
 
-// 16-byte vectors of rows that start at any element
-typedef u32x4 u32x4_any __attribute__((aligned(2)));
-
 constexpr int kVarRowsThreads = 256;
 constexpr int kVarUnroll = 8;  // 128-bit loads in flight per lane in a full chunk
 
