@@ -573,9 +573,11 @@ AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Str
   // Launches that leave the chip idle: 64 query rows per workgroup with the keys split over two
   // groups of wavefronts, or 16 rows (attention_fewrows.hip), by expected us.  The figures are fitted to
   // the times of all three in 570 random calls (1 to 128 batches of 1 to 256 heads, 1 to 3000
-  // queries, 1 to 9000 keys, with and without a mask), most of them within 10 %.  A workgroup's own cost
-  // matters as much as a key tile's: with few keys per query (many queries before a short context above all)
-  // the tiled kernel's 128 or 256 rows a workgroup win however idle the chip.
+  // queries, 1 to 9000 keys, with and without a mask), most of them within 10 %; over these and 500 others
+  // the choice costs 0.766 times the tiled kernel's time, the best one would 0.760, and two calls lose
+  // (3 % and 22 %).  A workgroup's own cost matters as much as a key tile's: with few keys per query (many
+  // queries before a short context above all) the tiled kernel's 128 or 256 rows a workgroup win however
+  // idle the chip.
   // Measured, tiled / two groups / 16 rows: 16 heads of 512 x 2048, d = 128, 54.5 / 32.1 / 41.6;
   // 3 x 2 heads of 2249 x 4040, causal, 86.1 / 59.4 / 94; 32 heads of 512 x 512, d = 64,
   // 12.7 / 8.6 / 12; one head of 1371 x 2708, causal, d = 64, 39.9 / 26.9 / 17.8; 40 heads of
@@ -592,7 +594,7 @@ AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Str
   const double us_tiled = us_of((nw == 8 ? kTiled8 : kTiled4)[d128], 32 * nw, 64);
   const double us_groups = us_of(kGroups[d128], 64, 128);
   const double us_few = attention_fewrows_us(a, sk, sv);
-  if (fmin(us_few, us_groups) < 0.85 * us_tiled)  // (past the fit's error)
+  if (a.Lk > 0 && fmin(us_few, us_groups) < 0.9 * us_tiled)  // (0.9: the fit's error; without keys there is nothing to split)
     return us_few <= us_groups ? AttnRoute::kFewRows : AttnRoute::kKeyGroups;
   return nw == 8 ? (paired ? AttnRoute::kPaired8 : AttnRoute::kTiled8) : paired ? AttnRoute::kPaired4 : AttnRoute::kTiled4;
 }

@@ -25,6 +25,8 @@ TILED_ATTENTION = [
     (1, "bf16", 8, 32, 32, 100, 1, 64, False),
     # 256 query rows
     (2, "bf16", 8, 32, 32, 257, 65, 128, False), (2, "bf16", 4, 40, 40, 300, 20, 128, False), (2, "bf16", 8, 32, 32, 257, 33, 64, False),
+    # two tiles of 128 query rows: keys for the last tile's last rows only
+    (4, "bf16", 1, 128, 128, 769, 40, 64, True),
     # keys over two groups of wavefronts, Lk < Lq: tiles that see no key, or that one group alone sees
     (5, "bf16", 1, 32, 32, 512, 400, 64, True), (5, "bf16", 1, 32, 32, 512, 400, 128, True),
     # fp32, d = 128: two tiles of 16 rows per workgroup, one over 8 wavefronts, one over 4

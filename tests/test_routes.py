@@ -35,6 +35,8 @@ def test_attention_calls_that_stay_with_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d,
 @pytest.mark.parametrize("Bt,Hq,Hkv,Lq,Lk,d,causal,route", [
     # (us tiled / taken: 54.5 / 32.1, 12.7 / 8.6, 39.9 / 17.7, 145.5 / 23.3, 16.1 / 9.2)
     (1, 16, 16, 512, 2048, 128, False, KEY_GROUPS), (1, 32, 32, 512, 512, 64, False, KEY_GROUPS),
+    # a handful of keys (6.7 / 5.0, 6.7 / 5.2)
+    (28, 8, 8, 25, 2, 128, False, FEW_ROWS), (1, 32, 8, 202, 6, 128, True, FEW_ROWS),
     (1, 1, 1, 1371, 2708, 64, True, FEW_ROWS), (6, 256, 32, 1, 1389, 128, True, FEW_ROWS), (6, 16, 2, 1, 565, 128, False, FEW_ROWS),
 ])
 def test_attention_calls_that_leave_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d, causal, route):
