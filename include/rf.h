@@ -178,6 +178,22 @@ RF_API rf_status rf_fp8_quant_gemm(const rf_tensor* a, const rf_tensor* w, rf_te
                                    rf_stream stream);
 
 /*
+ * rf_fp8_quant_gemm with device memory for the quantised tokens: every element is quantised
+ * with the maximum of its whole row (a prefix like any other in the promises above), by a
+ * launch of its own, and the contraction works on the codes.
+ *   workspace : device memory, 16-byte aligned, at least
+ *       rf_fp8_quant_gemm_workspace_bytes(M, K, N) bytes; contents need no initialisation and
+ *       are undefined afterwards.  Too small or misaligned: RF_ERR_WORKSPACE.  Concurrent calls
+ *       must not share a workspace.
+ * The size is 0 where a single launch serves the problem faster (few tokens, a short axis), and
+ * at most 128 MiB + 64 KiB: more tokens go through it in turns.  With a size of 0, and where
+ * the rows of w lie 2^23 or more bytes apart, the call is rf_fp8_quant_gemm.
+ */
+RF_API size_t rf_fp8_quant_gemm_workspace_bytes(int64_t M, int64_t K, int64_t N);
+RF_API rf_status rf_fp8_quant_gemm_ws(const rf_tensor* a, const rf_tensor* w, rf_tensor* c,
+                                      void* workspace, size_t workspace_bytes, rf_stream stream);
+
+/*
  * Fused attention, single-segment strategy (Section 4.3; Appendix A.2):
  *   P = scale * Q K^T;  m = max_j P;  t = sum_j exp(P-m);  O = sum_j exp(P-m)/t * V[j]
  * with the running state (m, l, acc) kept on chip and acc divided by l once

@@ -36,6 +36,8 @@ ENTRY_POINTS = (
     "rf_moe_routing",
     "rf_moe_routing_noalloc",
     "rf_fp8_quant_gemm",
+    "rf_fp8_quant_gemm_workspace_bytes",
+    "rf_fp8_quant_gemm_ws",
 )
 # measurement aids and the fusion-level study, declared in include/rf_diag.h
 DIAG_ENTRY_POINTS = (
@@ -44,6 +46,7 @@ DIAG_ENTRY_POINTS = (
     "rf_diag_splitk_route",
     "rf_diag_rmsnorm_gemm_tile",
     "rf_diag_fp8_quant_gemm_tile",
+    "rf_diag_fp8_quant_gemm_ws_tile",
     "rf_diag_attention_wide",
     "rf_diag_copy",
     "rf_diag_read",
@@ -110,6 +113,10 @@ def load_library():
     lib.rf_moe_routing_noalloc.argtypes = [P, P, ctypes.c_int, P, P, ctypes.c_void_p]
     lib.rf_fp8_quant_gemm.restype = ctypes.c_int
     lib.rf_fp8_quant_gemm.argtypes = [P, P, P, ctypes.c_void_p]
+    lib.rf_fp8_quant_gemm_workspace_bytes.restype = ctypes.c_size_t
+    lib.rf_fp8_quant_gemm_workspace_bytes.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
+    lib.rf_fp8_quant_gemm_ws.restype = ctypes.c_int
+    lib.rf_fp8_quant_gemm_ws.argtypes = [P, P, P, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     lib.rf_diag_softmax_level.restype = ctypes.c_int
     lib.rf_diag_attention_wide.argtypes = [P, P, P, P, ctypes.c_float, ctypes.c_void_p]
     lib.rf_diag_attention_wide.restype = ctypes.c_int
@@ -118,7 +125,7 @@ def load_library():
     lib.rf_diag_attention_route.argtypes = [P, P, P, ctypes.c_int]
     lib.rf_diag_splitk_route.restype = ctypes.c_int
     lib.rf_diag_splitk_route.argtypes = [P, P, P, ctypes.c_int]
-    for f in (lib.rf_diag_rmsnorm_gemm_tile, lib.rf_diag_fp8_quant_gemm_tile):
+    for f in (lib.rf_diag_rmsnorm_gemm_tile, lib.rf_diag_fp8_quant_gemm_tile, lib.rf_diag_fp8_quant_gemm_ws_tile):
         f.restype = ctypes.c_int
         f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
     lib.rf_diag_copy.restype = ctypes.c_int
@@ -293,7 +300,9 @@ def rf_moe_routing_noalloc(x, w, topk, prob, idx, stream=None):
 
 
 def rf_fp8_quant_gemm(a, w, c=None, stream=None):
-    """c = dequant(quant_fp8(a) @ w^T): a [M,K] bf16, w [N,K] torch.float8_e4m3fn, c [M,N] bf16."""
+    """c = dequant(quant_fp8(a) @ w^T): a [M,K] bf16, w [N,K] torch.float8_e4m3fn, c [M,N] bf16.
+    Where rf_fp8_quant_gemm_ws is faster its workspace comes from torch's caching allocator, on the
+    call's stream, and goes back to it at return."""
     if c is None:
         c = torch.empty((a.shape[0], w.shape[0]), dtype=torch.bfloat16, device=a.device)
     _check((_call or _native()).fp8_quant_gemm(a, w, c, stream), "rf_fp8_quant_gemm")
@@ -331,6 +340,11 @@ def rf_diag_rmsnorm_gemm_tile(M, K, N):
 def rf_diag_fp8_quant_gemm_tile(M, K, N):
     """(tokens, channels) of the output tile that rf_fp8_quant_gemm takes for these sizes."""
     return divmod(load_library().rf_diag_fp8_quant_gemm_tile(M, K, N), 1000)
+
+
+def rf_diag_fp8_quant_gemm_ws_tile(M, K, N):
+    """(tokens, channels) of the tile that rf_fp8_quant_gemm_ws takes; (0, 0) where it is rf_fp8_quant_gemm."""
+    return divmod(load_library().rf_diag_fp8_quant_gemm_ws_tile(M, K, N), 1000)
 
 
 def rf_diag_attention_wide(q, k, v, scale, o=None, stream=None):

@@ -23,6 +23,7 @@ SOURCES = [
     "moe_routing.hip",
     "fp8_quant_gemm.hip",
     "fp8_quant_gemm_rows.hip",
+    "fp8_quant_gemm_two_pass.hip",
     "attention_f32.hip",
     "attention_f32_few.hip",
     "attention_bf16.hip",

@@ -140,7 +140,7 @@ int rf_describe_cascade(const char* entry, rf_stage* out, int cap) {
   else if (!strcmp(entry, "rf_rmsnorm_gemm")) { src = kRms; n = 2; }
   else if (!strcmp(entry, "rf_variance")) { src = kRms; n = 2; }  // sum, then sum
   else if (!strcmp(entry, "rf_moe_routing")) { src = kRouting; n = 3; }
-  else if (!strcmp(entry, "rf_fp8_quant_gemm")) { src = kQuant; n = 2; }
+  else if (!strcmp(entry, "rf_fp8_quant_gemm") || !strcmp(entry, "rf_fp8_quant_gemm_ws")) { src = kQuant; n = 2; }
   else return -1;
   if (out != nullptr)
     for (int i = 0; i < n && i < cap; ++i) out[i] = src[i];
@@ -272,26 +272,58 @@ rf_status rf_moe_routing_noalloc(const rf_tensor* x, const rf_tensor* w, int top
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
 }
 
-rf_status rf_fp8_quant_gemm(const rf_tensor* a, const rf_tensor* w, rf_tensor* c, rf_stream stream) {
+namespace {
+// Argument checks shared by the two FP8 entry points.
+rf_status check_fp8_quant_gemm(const rf_tensor* a, const rf_tensor* w, const rf_tensor* c, bool* empty) {
   rf_status st;
+  *empty = false;
   if ((st = check_tensor(a, 2, 2)) != RF_OK) return st;
   if ((st = check_tensor(w, 2, 2, RF_FP8_E4M3)) != RF_OK) return st;
   if ((st = check_tensor(c, 2, 2)) != RF_OK) return st;
   if (a->dtype != RF_BF16 || w->dtype != RF_FP8_E4M3 || c->dtype != RF_BF16) return RF_ERR_UNSUPPORTED;
   const int64_t M = a->shape[0], K = a->shape[1], N = w->shape[0];
   if (w->shape[1] != K || c->shape[0] != M || c->shape[1] != N) return RF_ERR_INVALID_ARG;
-  if (M == 0 || N == 0) return RF_OK;
+  if (M == 0 || N == 0) { *empty = true; return RF_OK; }
   if (K == 0 || K % 128 != 0 || N % 8 != 0) return RF_ERR_UNSUPPORTED;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX) return RF_ERR_UNSUPPORTED;
-  for (const rf_tensor* t : {a, w, (const rf_tensor*)c})
+  for (const rf_tensor* t : {a, w, c})
     if (t->shape[1] > 1 && t->stride[1] != 1) return RF_ERR_UNSUPPORTED;
   if (a->data == nullptr || w->data == nullptr || c->data == nullptr) return RF_ERR_INVALID_ARG;
   if (!aligned16(a) || !aligned16(w) || !aligned16(c)) return RF_ERR_ALIGNMENT;
   if (128 * a->stride[0] * 2 >= ((int64_t)1 << 32) || N * w->stride[0] >= ((int64_t)1 << 32))
     return RF_ERR_UNSUPPORTED;
-  hipError_t e = rf::launch_fp8_quant_gemm(a->data, w->data, c->data, (int)M, (int)K, (int)N,
-                                           a->stride[0], w->stride[0], c->stride[0],
+  return RF_OK;
+}
+}  // namespace
+
+rf_status rf_fp8_quant_gemm(const rf_tensor* a, const rf_tensor* w, rf_tensor* c, rf_stream stream) {
+  bool empty;
+  const rf_status st = check_fp8_quant_gemm(a, w, c, &empty);
+  if (st != RF_OK || empty) return st;
+  hipError_t e = rf::launch_fp8_quant_gemm(a->data, w->data, c->data, (int)a->shape[0], (int)a->shape[1],
+                                           (int)w->shape[0], a->stride[0], w->stride[0], c->stride[0],
                                            (hipStream_t)stream);
+  return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
+}
+
+size_t rf_fp8_quant_gemm_workspace_bytes(int64_t M, int64_t K, int64_t N) {
+  if (M < 1 || K < 1 || N < 1 || M > INT32_MAX || K > INT32_MAX || N > INT32_MAX || K % 128 != 0 || N % 8 != 0) return 0;
+  if (!rf::fp8_quant_gemm_two_pass_wins((int)M, (int)K, (int)N, rf::fp8_quant_gemm_us((int)M, (int)K, (int)N))) return 0;
+  return rf::fp8_quant_gemm_two_pass_bytes((int)M, (int)K);
+}
+
+rf_status rf_fp8_quant_gemm_ws(const rf_tensor* a, const rf_tensor* w, rf_tensor* c, void* workspace,
+                               size_t workspace_bytes, rf_stream stream) {
+  bool empty;
+  const rf_status st = check_fp8_quant_gemm(a, w, c, &empty);
+  if (st != RF_OK || empty) return st;
+  const int64_t M = a->shape[0], K = a->shape[1], N = w->shape[0];
+  const size_t need = rf_fp8_quant_gemm_workspace_bytes(M, K, N);
+  if (need == 0 || w->stride[0] >= (1 << 23)) return rf_fp8_quant_gemm(a, w, c, stream);
+  if (workspace == nullptr || reinterpret_cast<uintptr_t>(workspace) % 16 != 0 || workspace_bytes < need)
+    return RF_ERR_WORKSPACE;
+  hipError_t e = rf::launch_fp8_quant_gemm_two_pass(a->data, w->data, c->data, (int)M, (int)K, (int)N, a->stride[0],
+                                                    w->stride[0], c->stride[0], workspace, (hipStream_t)stream);
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
 }
 
@@ -341,6 +373,11 @@ int rf_diag_fp8_quant_gemm_tile(int64_t M, int64_t K, int64_t N) {
   if (M < 1 || K < 1 || N < 1 || M > INT32_MAX || K > INT32_MAX || N > INT32_MAX || K % 128 != 0 || N % 8 != 0) return 0;
   const bool rows = rf::fp8_quant_gemm_rows_wins((int)M, (int)K, (int)N, nullptr, N);
   return rows ? rf::fp8_quant_gemm_rows_tile((int)M, (int)K, (int)N) : 128000 + 256 * rf::fp8_quant_gemm_blocks((int)M, (int)N);
+}
+
+int rf_diag_fp8_quant_gemm_ws_tile(int64_t M, int64_t K, int64_t N) {
+  if (rf_fp8_quant_gemm_workspace_bytes(M, K, N) == 0) return 0;
+  return rf::fp8_quant_gemm_two_pass_tile((int)M, (int)K, (int)N);
 }
 
 int rf_diag_splitk_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int num_splits) {

@@ -260,6 +260,8 @@ bool fp8_quant_gemm_rows_wins(int M, int K, int N, const void* c, int64_t ldc) {
   return 1.05 * rows_us(best_shape(M, K, N), M, K, N) < 6.0 + 9.0 * (K / 1024.0);
 }
 
+double fp8_quant_gemm_rows_us(int M, int K, int N) { return rows_us(best_shape(M, K, N), M, K, N); }
+
 int fp8_quant_gemm_rows_tile(int M, int K, int N) {
   const FShape r = best_shape(M, K, N);
   return 16 * r.mt * 1000 + 16 * r.nt;

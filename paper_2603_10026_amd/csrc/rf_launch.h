@@ -131,6 +131,19 @@ int fp8_quant_gemm_rows_tile(int M, int K, int N);  // 1000 tokens + channels of
 hipError_t launch_fp8_quant_gemm_rows(const void* a, const void* w, void* c, int M, int K, int N,
                                       int64_t lda, int64_t ldw, int64_t ldc, hipStream_t s);
 
+// Expected us of the launch above.
+double fp8_quant_gemm_us(int M, int K, int N);
+double fp8_quant_gemm_rows_us(int M, int K, int N);
+
+// The same with a workspace of fp8_quant_gemm_two_pass_bytes(M, K) bytes, 16-byte aligned, for the tokens' codes:
+// quantisation and contraction in a launch each.  16-byte aligned rows of c, ldw < 2^23.
+constexpr int64_t kFp8WorkspaceMax = (int64_t)128 << 20;
+bool fp8_quant_gemm_two_pass_wins(int M, int K, int N, double single_us);
+size_t fp8_quant_gemm_two_pass_bytes(int M, int K);
+int fp8_quant_gemm_two_pass_tile(int M, int K, int N);  // 1000 tokens + channels of the tile it takes
+hipError_t launch_fp8_quant_gemm_two_pass(const void* a, const void* w, void* c, int M, int K, int N, int64_t lda,
+                                          int64_t ldw, int64_t ldc, void* workspace, hipStream_t s);
+
 // Fusion-level study of the softmax cascade (bf16 rows, n % 8 == 0, n <= 8192): level 0 =
 // unfused (three kernels; ml_buf holds 2 * rows floats), 1 = fused per lane, 2 = per
 // wavefront (the shipped kernel), 3 = per workgroup, 4 = across workgroups (two kernels;

@@ -7,6 +7,9 @@
 // object.  Only plain tensors and parameters are: subclasses, ill-typed arguments and everything
 // else that has behaviour of its own in Python go through binding.tensor_desc / binding._stream,
 // which also raise the errors.
+#include <c10/hip/HIPCachingAllocator.h>
+#include <c10/hip/HIPFunctions.h>
+#include <c10/hip/HIPGraphsC10Utils.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -20,8 +23,8 @@ namespace {
 PyObject* g_tensor_desc = nullptr;  // binding.tensor_desc: tensor -> object with rf_tensor's bytes
 PyObject* g_stream = nullptr;       // binding._stream: any stream argument -> object with .value
 
-// Fills *d; false with a Python error set on failure.  *on_gpu becomes true for a GPU tensor.
-bool describe(PyObject* obj, rf_tensor* d, bool* on_gpu) {
+// Fills *d; false with a Python error set on failure.  *device becomes the device of a plain GPU tensor.
+bool describe(PyObject* obj, rf_tensor* d, int* device) {
   if (THPVariable_CheckExact(obj)) {
     const at::Tensor& t = THPVariable_Unpack(obj);
     int dtype = -1;
@@ -46,7 +49,7 @@ bool describe(PyObject* obj, rf_tensor* d, bool* on_gpu) {
       d->dtype = static_cast<rf_dtype>(dtype);
       d->ndim = static_cast<int>(n);
       d->data = empty ? nullptr : t.data_ptr();
-      if (t.is_cuda()) *on_gpu = true;
+      if (t.is_cuda()) *device = t.device().index();
       return true;
     }
   }
@@ -63,8 +66,8 @@ bool describe(PyObject* obj, rf_tensor* d, bool* on_gpu) {
   return PyErr_Occurred() == nullptr;
 }
 
-bool stream_of(PyObject* obj, bool on_gpu, rf_stream* s) {
-  if (obj == Py_None && on_gpu) {  // (a GPU tensor exists, so torch has set up its devices)
+bool stream_of(PyObject* obj, int device, rf_stream* s) {
+  if (obj == Py_None && device >= 0) {  // (a GPU tensor exists, so torch has set up its devices)
     *s = c10::hip::getCurrentHIPStream().stream();
     return true;
   }
@@ -101,12 +104,63 @@ bool count(Py_ssize_t n, Py_ssize_t want) {
 
 // N tensors (from args[0] on), then the stream (last argument).
 template <int N>
-bool describe_all(PyObject* const* args, Py_ssize_t n, rf_tensor (&d)[N], const int (&at)[N], rf_stream* s) {
-  bool on_gpu = false;
+bool describe_all(PyObject* const* args, Py_ssize_t n, rf_tensor (&d)[N], const int (&at)[N], rf_stream* s,
+                  int* device = nullptr) {
+  int dev = -1;
   for (int i = 0; i < N; ++i)
-    if (!describe(args[at[i]], &d[i], &on_gpu)) return false;
-  return stream_of(args[n - 1], on_gpu, s);
+    if (!describe(args[at[i]], &d[i], &dev)) return false;
+  if (device != nullptr) *device = dev;
+  return stream_of(args[n - 1], dev, s);
 }
+
+// Device memory for one call, from torch's caching allocator: it is handed out for the call's stream
+// and given back at the end of the call, so that whoever gets it next on that stream runs behind the
+// call's kernels, and another stream does not get it.  `data` is null where there is none (no plain
+// tensor on the current device, no memory left, an allocator that is not torch's own); the call then
+// does without.  So does a call in a capture that torch does not know of: replays of such a graph
+// would run on memory that has been handed on.  torch's own captures take from the graph's pool.
+class Scratch {
+ public:
+  Scratch(size_t bytes, int device, rf_stream s) {
+    if (bytes == 0 || device < 0) return;
+    try {
+      if (device != c10::hip::current_device()) return;
+      const hipStream_t stream = static_cast<hipStream_t>(s);
+      hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+      }
+      if (capture == hipStreamCaptureStatusNone) {
+        data_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream);
+      } else if (stream == c10::hip::getCurrentHIPStream().stream()) {
+        c10::hip::HIPStreamCaptureModeGuard relaxed{hipStreamCaptureModeRelaxed};
+        data_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream);
+        if (!in_graph_pool()) release();
+      }
+    } catch (...) {
+      release();
+    }
+  }
+  ~Scratch() { release(); }
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  void* data() const { return data_; }
+
+ private:
+  void release() {
+    if (data_ != nullptr) c10::hip::HIPCachingAllocator::raw_delete(data_);
+    data_ = nullptr;
+  }
+  bool in_graph_pool() const {
+    const size_t at = reinterpret_cast<size_t>(data_);
+    for (const auto& seg : c10::hip::HIPCachingAllocator::snapshot().segments)
+      if (at >= static_cast<size_t>(seg.address) && at - static_cast<size_t>(seg.address) < seg.total_size)
+        return seg.owner_private_pool_id.first != 0 || seg.owner_private_pool_id.second != 0;
+    return false;
+  }
+  void* data_ = nullptr;
+};
 
 // The interpreter is free while the C ABI validates and launches.
 template <typename F>
@@ -205,7 +259,13 @@ PyObject* py_fp8_quant_gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
   HANDLE_TH_ERRORS
   rf_tensor d[3];
   rf_stream s;
-  if (!count(n, 4) || !describe_all<3>(args, n, d, {0, 1, 2}, &s)) return nullptr;
+  int device;
+  if (!count(n, 4) || !describe_all<3>(args, n, d, {0, 1, 2}, &s, &device)) return nullptr;
+  const size_t bytes =
+      d[0].ndim == 2 && d[1].ndim == 2 ? rf_fp8_quant_gemm_workspace_bytes(d[0].shape[0], d[0].shape[1], d[1].shape[0]) : 0;
+  const Scratch scratch(bytes, device, s);
+  if (scratch.data() != nullptr)
+    return call([&] { return rf_fp8_quant_gemm_ws(&d[0], &d[1], &d[2], scratch.data(), bytes, s); });
   return call([&] { return rf_fp8_quant_gemm(&d[0], &d[1], &d[2], s); });
   END_HANDLE_TH_ERRORS
 }
@@ -257,8 +317,8 @@ PyObject* py_moe_routing_noalloc(PyObject*, PyObject* const* args, Py_ssize_t n)
 PyObject* py_describe(PyObject*, PyObject* const* args, Py_ssize_t n) {
   HANDLE_TH_ERRORS
   rf_tensor d;
-  bool on_gpu = false;
-  if (!count(n, 1) || !describe(args[0], &d, &on_gpu)) return nullptr;
+  int device = -1;
+  if (!count(n, 1) || !describe(args[0], &d, &device)) return nullptr;
   return PyBytes_FromStringAndSize(reinterpret_cast<const char*>(&d), sizeof(d));
   END_HANDLE_TH_ERRORS
 }

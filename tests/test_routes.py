@@ -116,6 +116,33 @@ def test_every_fp8_tile_has_a_gpu_test():
                 assert t[0] == 128 or t in held[2 if K <= 2048 else 4 if K <= 4096 else 8], (M, K, N, t)
 
 
+def test_every_fp8_two_pass_tile_has_a_gpu_test():
+    from test_gpu_fp8_two_pass import TWO_PASS_TILES
+    tiles = {(256, 256), (128, 256), (128, 128), (64, 128), (64, 64), (32, 64), (32, 32)}
+    assert {t for t, _ in TWO_PASS_TILES} == tiles
+    for tile, shape in TWO_PASS_TILES:
+        assert B.rf_diag_fp8_quant_gemm_ws_tile(*shape) == tile, shape
+    for M in (1, 16, 33, 100, 260, 545, 1000, 2000, 4096, 70000):
+        for K in (128, 640, 2048, 4096, 8192):
+            for N in (8, 136, 520, 1032, 4104, 8200):
+                assert B.rf_diag_fp8_quant_gemm_ws_tile(M, K, N) in tiles | {(0, 0)}, (M, K, N)
+
+
+@pytest.mark.parametrize("M,K,N,two", [
+    # few tokens or a short axis stay in one launch (us one launch / two: 6.5 / 7.2, 4.3 / 6.3, 4.7 / 6.0)
+    (1, 4096, 4096, False), (1, 1920, 1432, False), (9, 640, 1288, False), (1672, 256, 40, False),
+    # (142 / 108, 46 / 21, 42.6 / 13.4, 13.5 / 8.5, 46 / 15.8, 21.6 / 9.2)
+    (4096, 8192, 3584, True), (1348, 3456, 2336, True), (141, 3456, 7200, True), (64, 4096, 4096, True), (64, 8192, 8192, True),
+    (18, 5248, 5712, True),
+    # nothing that rf_fp8_quant_gemm refuses, no axis beyond 32-bit offsets
+    (300, 100, 1000, False), (300, 1152, 1001, False), (0, 1152, 1000, False), (300, -128, 1000, False), (300, 1 << 23, 1024, False),
+])
+def test_fp8_workspace(M, K, N, two):
+    nbytes = B.load_library().rf_fp8_quant_gemm_workspace_bytes(M, K, N)
+    assert (nbytes > 0) == two and nbytes <= (128 << 20) + (64 << 10)
+    assert (B.rf_diag_fp8_quant_gemm_ws_tile(M, K, N) != (0, 0)) == two
+
+
 def test_every_rmsnorm_tile_has_a_gpu_test():
     from test_gpu_rmsnorm_rows import RMSNORM_TILES
     for tile, shape in RMSNORM_TILES:
