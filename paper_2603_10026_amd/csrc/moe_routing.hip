@@ -8,18 +8,16 @@
 // The router GEMM is skinny (a few thousand tokens x 32..128 experts) and its
 // cost is reading x once, so the contraction axis is split over workgroups:
 //
-// Kernel 1 (scores): workgroup (row block of 64 tokens, k slice).  x and w tiles
-//   of 128 k go HBM -> LDS with direct-to-LDS 128-bit loads two tiles ahead of their
-//   use (three LDS stages, all requested up front), one barrier per tile.  The product is computed
-//   transposed, P^T = W^T X^T, with 32x32x16 bf16 MFMAs: W^T fragments come from 64-bit LDS transpose reads, X
-//   fragments from 128-bit reads.  The four wavefronts split the eight 16-wide
-//   contraction steps of a tile, so every LDS byte is read exactly once; their
-//   accumulators are summed through LDS in a fixed order and the fp32 partial
-//   scores of the slice are written to the caller's workspace.
+// Kernel 1 (scores): workgroup (row block of 4096 / E tokens, k slice).  x and w tiles
+//   of 128 k go HBM -> LDS with direct-to-LDS 128-bit loads three tiles ahead of their
+//   use (four LDS stages), one barrier per tile.  32x32x16 bf16 MFMAs: X fragments come from 128-bit
+//   LDS reads, W fragments from 64-bit transpose reads.  A wavefront owns 32 tokens x 32 experts; the fp32
+//   partial scores of the slice are written to the caller's workspace.
 // Kernel 2 (cascade): a wavefront per token adds the slices' partial scores in slice
 //   order, then runs the cascade over its lanes; with many tokens 16 lanes each, up to 8 experts
-//   a lane.  (Those keep a longer chain of compares per TopK round and a quarter of the
-//   wavefronts: 2048 x 4096 x 128 experts, top 8, took 16.4 us a call with them, 14.3 without.)
+//   a lane.
+#include <math.h>
+
 #include <atomic>
 
 #include "rf_device.h"
@@ -67,14 +65,14 @@ __device__ __forceinline__ float wave_sum_valu(float v) {
 
 }  // namespace
 
-// The cascade of one token, a wavefront per token: p[i] of a lane is the score of expert
-// 64 i + lane (-inf past the last expert).  The chain of the TopK rounds is what this costs; a
-// round is one maximum over the lanes (vector-ALU swaps), after which the scalar unit finds the
-// lowest expert that holds it in the comparison masks.
+// The cascade of one token, a wavefront per token: p[i] of a lane is the score of expert EPL lane + i
+// (-inf past the last expert).  Here for any scores: a round of the TopK is one maximum over the lanes
+// (vector-ALU swaps), after which the scalar unit finds the lowest expert that holds it in the
+// comparison masks.
 template <int EPL>
-__device__ __forceinline__ void moe_cascade_token(float (&p)[EPL], int E, int lane, int row, int topk,
-                                                  float* __restrict__ prob, int32_t* __restrict__ idx,
-                                                  int64_t ldp, int64_t ldi) {
+__device__ __forceinline__ void moe_cascade_token_any(float (&p)[EPL], int E, int lane, int row, int topk,
+                                                      float* __restrict__ prob, int32_t* __restrict__ idx,
+                                                      int64_t ldp, int64_t ldi) {
   // stage 1: max;  stage 2: sum of exponentials
   float m = p[0];
 #pragma unroll
@@ -82,7 +80,7 @@ __device__ __forceinline__ void moe_cascade_token(float (&p)[EPL], int E, int la
   m = wave_max_valu(m);
   float t = 0.f;
 #pragma unroll
-  for (int i = 0; i < EPL; ++i) t += 64 * i + lane < E ? fast_exp2((p[i] - m) * kLog2e) : 0.f;
+  for (int i = 0; i < EPL; ++i) t += EPL * lane + i < E ? fast_exp2((p[i] - m) * kLog2e) : 0.f;
   t = wave_sum_valu(t);
   const float inv_t = 1.0f / t;
   // stage 3: TopK.  Each round takes the largest remaining score of the token (ties: the lowest
@@ -99,12 +97,12 @@ __device__ __forceinline__ void moe_cascade_token(float (&p)[EPL], int E, int la
 #pragma unroll
       for (int i = EPL - 1; i >= 0; --i) {
         const uint64_t mask = __builtin_amdgcn_ballot_w64(p[i] == bv);
-        if (mask != 0) bi = 64 * i + __builtin_ctzll(mask);
+        if (mask != 0) bi = min(bi, EPL * __builtin_ctzll(mask) + i);
       }
     }
     bv = bi == E ? -INFINITY : bv;
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) p[i] = bi == 64 * i + lane ? -INFINITY : p[i];
+    for (int i = 0; i < EPL; ++i) p[i] = bi == EPL * lane + i ? -INFINITY : p[i];
     if (lane == j) {
       my_prob = fast_exp2((bv - m) * kLog2e) * inv_t;
       my_idx = bi;
@@ -114,6 +112,77 @@ __device__ __forceinline__ void moe_cascade_token(float (&p)[EPL], int E, int la
     prob[(int64_t)row * ldp + lane] = my_prob;
     idx[(int64_t)row * ldi + lane] = my_idx;
   }
+}
+
+// The same where no score is NaN or -inf and no two of the best are equal, which is nearly always.
+// The chain of the TopK rounds is what this costs, so a round is nothing but the maximum: scores become
+// integers of the same order (maxima fold into the lane exchange), an expert that holds the maximum
+// keeps the round's number as its place and drops out, and at the end every expert with a place
+// stores its own result.  2048 x 1024 x 128 experts, top 8, in one launch 9.1 -> 7.4 us, 16 x 896 x 128 8.5 -> 6.9.
+template <int EPL>
+__device__ __forceinline__ void moe_cascade_token(float (&p)[EPL], int E, int lane, int row, int topk,
+                                                  float* __restrict__ prob, int32_t* __restrict__ idx,
+                                                  int64_t ldp, int64_t ldi) {
+  const bool live = EPL * lane < E;
+  bool odd = false;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) odd = odd || (live && !(p[i] > -INFINITY));
+  if (__builtin_amdgcn_ballot_w64(odd) != 0) {
+    moe_cascade_token_any<EPL>(p, E, lane, row, topk, prob, idx, ldp, ldi);
+    return;
+  }
+  constexpr int kOut = INT32_MIN;  // below every score
+  int key[EPL], place[EPL];
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    const int b = (int)__float_as_uint(p[i] + 0.f);  // (-0 is 0)
+    key[i] = live ? b ^ ((b >> 31) & 0x7fffffff) : kOut;
+    place[i] = topk;
+  }
+  auto wave_max_key = [](int v) {
+    v = max(v, dpp_i32<kDppQuadXor1>(v));
+    v = max(v, dpp_i32<kDppQuadXor2>(v));
+    v = max(v, dpp_i32<kDppRowHalfMirror>(v));
+    v = max(v, dpp_i32<kDppRowMirror>(v));
+    auto s = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = max((int)s[0], (int)s[1]);
+    s = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return max((int)s[0], (int)s[1]);
+  };
+  float m = 0.f;
+  for (int j = 0; j < topk; ++j) {
+    int best = key[0];
+#pragma unroll
+    for (int i = 1; i < EPL; ++i) best = max(best, key[i]);
+    best = wave_max_key(best);
+    if (j == 0) m = __uint_as_float((uint32_t)(best ^ ((best >> 31) & 0x7fffffff)));
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const bool hit = key[i] == best;
+      place[i] = hit ? j : place[i];
+      key[i] = hit ? kOut : key[i];
+    }
+  }
+  int placed = 0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) placed += __builtin_popcountll(__builtin_amdgcn_ballot_w64(place[i] < topk));
+  if (placed != topk) {  // equal scores among the best
+    moe_cascade_token_any<EPL>(p, E, lane, row, topk, prob, idx, ldp, ldi);
+    return;
+  }
+  float e[EPL], t = 0.f;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) {
+    e[i] = fast_exp2((p[i] - m) * kLog2e);
+    t += live ? e[i] : 0.f;
+  }
+  const float inv_t = 1.0f / wave_sum_valu(t);
+#pragma unroll
+  for (int i = 0; i < EPL; ++i)
+    if (place[i] < topk) {
+      prob[(int64_t)row * ldp + place[i]] = e[i] * inv_t;
+      idx[(int64_t)row * ldi + place[i]] = EPL * lane + i;
+    }
 }
 
 // The same on 16 lanes, lane q with experts q EPL ..: four tokens per wavefront.  A TopK round is a longer
@@ -283,7 +352,7 @@ __global__ __launch_bounds__(kMoeFusedWaves * kWave, 2) void moe_fused_kernel(
     float p[EPL];
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      const int e = 64 * i + lane;
+      const int e = EPL * lane + i;
       p[i] = -INFINITY;
       if (e < E) {
         p[i] = s_p[0][tok][e];
@@ -295,16 +364,148 @@ __global__ __launch_bounds__(kMoeFusedWaves * kWave, 2) void moe_fused_kernel(
   }
 }
 
-// Multi-segment strategy: NT = E / 32.  part[ks][row][e] = sum over the k slice of x[row,k] w[k,e].
-// (Taking x and w straight into the operands, as the single-segment kernel does, was measured here
-// too: never faster, and up to 2 us slower from 64 tokens on.)
-// FUSED: single-segment strategy for many tokens, 64 of them and the whole contraction axis per workgroup
-// (grid y = 1): the scores never leave the chip, the workgroup runs the cascade on them.
-template <int NT, bool FUSED>
-__global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
+// Multi-segment strategy: part[ks][row][e] = sum over the k slice of x[row,k] w[k,e].  A workgroup takes
+// 4096 / E tokens, a wavefront 32 of them and 32 experts: nothing is added up between wavefronts, and
+// with 32 tokens of 128 experts half as many slices fill the chip as with 64, so half the partial
+// scores pass through memory.  What bounds it is that one trip: launch, the first tile's latency, x at
+// the rate of memory, the partial scores.  Both launches, 64 tokens a workgroup with the tiles' steps dealt to
+// the wavefronts / this: 2048 x 4096 x 128, top 8, 15.9 / 11.9 us, 512 x 4096 x 128 13.3 / 7.9,
+// 2869 x 7552 x 128 29.0 / 21.0, 2940 x 3456 x 64 15.8 / 10.2; 32 experts 1 to 5 % (4056 x 4096: 10.6 / 11.1).
+template <int E>
+struct MoeTile {
+  static constexpr int kWaveE = E / 32, kWaveT = 4 / kWaveE;  // wavefronts along experts and tokens
+  static constexpr int kTokens = 32 * kWaveT;
+  static constexpr int kXB = kTokens * kMoeKB * 2, kWB = kMoeKB * E * 2;  // [token][k] and [k][expert]
+  static constexpr int kStageB = kXB + kWB;
+  static constexpr int kStages = 4;
+  static_assert(kStages == 4, "three tiles in flight: the waits below");
+};
+
+template <int E>
+__global__ __launch_bounds__(kMoeThreads, 1) void moe_scores_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, float* __restrict__ part, int S,
-    int n_kblocks, int64_t ldx, int64_t ldw, int topk, float* __restrict__ prob,
-    int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
+    int n_kblocks, int64_t ldx, int64_t ldw) {
+  using T = MoeTile<E>;
+  constexpr int PPR = E / 8;                // 16-byte pieces of a row of w
+  constexpr int kXLoads = T::kXB / 4096, kWLoads = T::kWB / 4096;  // direct-to-LDS loads per wavefront and tile
+  constexpr int kLoads = kXLoads + kWLoads, NS = T::kStages;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * T::kStageB];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i32 = lane & 31, hh = lane >> 5;
+  const int wt = wave % T::kWaveT, we = wave / T::kWaveT;
+  const int row0 = blockIdx.x * T::kTokens;
+  const int KS = gridDim.y, ks = blockIdx.y;
+  const int b0 = (int)((int64_t)n_kblocks * ks / KS);  // this slice's tiles: b0 .. b0 + nb - 1
+  const int nb = (int)((int64_t)n_kblocks * (ks + 1) / KS) - b0;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
+
+  uint32_t x_off[kXLoads], w_off[kWLoads];
+#pragma unroll
+  for (int e = 0; e < kXLoads; ++e) {
+    const int row = 4 * (kXLoads * wave + e) + (lane >> 4);
+    const int piece = (lane & 15) ^ fXm(row);
+    x_off[e] = (uint32_t)(((int64_t)min(row0 + row, S - 1) * ldx + 8 * piece) * 2);
+  }
+#pragma unroll
+  for (int e = 0; e < kWLoads; ++e) {
+    const int p = 64 * (kWLoads * wave + e) + lane;
+    const int krow = p / PPR;
+    const int piece = (p % PPR) ^ fWm<PPR>(krow);
+    w_off[e] = (uint32_t)(((int64_t)krow * ldw + 8 * piece) * 2);
+  }
+  auto request = [&](int blk, int stage) {  // tile b0 + blk
+    const int b = b0 + blk;
+    const char* xt = reinterpret_cast<const char*>(x) + (int64_t)b * kMoeKB * 2;
+    const char* wt_ = reinterpret_cast<const char*>(w) + (int64_t)b * kMoeKB * ldw * 2;
+#pragma unroll
+    for (int e = 0; e < kLoads; ++e) {
+      const bool tok = e < kXLoads;
+      const uint32_t dst = lds_base + stage * T::kStageB +
+                           (tok ? (kXLoads * wave + e) * 1024 : T::kXB + (kWLoads * wave + e - kXLoads) * 1024);
+      const uint32_t off = tok ? x_off[tok ? e : 0] : w_off[tok ? 0 : e - kXLoads];
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :
+                   : "s"(dst), "v"(off), "s"(tok ? xt : wt_)
+                   : "memory", "m0");
+    }
+  };
+
+  // ---- fragments ----
+  // A operand (tokens): lane (i32, hh) reads row 32 wt + i32, slot 2 kk + hh.
+  // B operand (experts) by transpose reads: lane = 32 hh + 16 g2 + 4 j + a reads 8 bytes of k-row
+  // 16 kk + 8 hh + 4 w2 + j at expert 32 we + 16 g2 + 4 a
+  const int xrow = 32 * wt + i32;
+  uint32_t x_at[8], w_at[2];
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) x_at[kk] = xrow * 256 + (((2 * kk + hh) ^ fXm(xrow)) << 4);
+  {
+    const int i16 = lane & 15, g2 = (lane >> 4) & 1;
+    const int j = i16 >> 2, c = i16 & 3;
+    const int piece = (32 * we + 16 * g2 + 4 * c) >> 3;
+#pragma unroll
+    for (int w2 = 0; w2 < 2; ++w2) {
+      const int krow = 8 * hh + 4 * w2 + j;  // (+ 16 kk: the swizzle looks at the row mod 4)
+      w_at[w2] = T::kXB + krow * (E * 2) + ((piece ^ fWm<PPR>(krow)) << 4) + 8 * (c & 1);
+    }
+  }
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+
+  f32x16 acc;  // rows = tokens, columns = experts
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+
+  // NS - 1 tiles are in flight; the one that follows them goes to the stage that the tile before this one left.
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < nb) request(t, t);
+  int stage = 0;
+  for (int blk = 0; blk < nb; ++blk) {
+    // this tile has landed (loads retire in order: the younger tiles' may be in flight), and the reads of the
+    // tile before are back; then both hold for every wavefront
+    if (blk + 2 < nb) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads) : "memory");
+    else if (blk + 1 < nb) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kLoads) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (blk + NS - 1 < nb) request(blk + NS - 1, stage == 0 ? NS - 1 : stage - 1);
+    const uint32_t at = stage * T::kStageB;
+    u32x4 bx[8];
+    s16x4 bw[8][2];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      bx[kk] = *reinterpret_cast<const u32x4*>(lds + at + x_at[kk]);
+#pragma unroll
+      for (int w2 = 0; w2 < 2; ++w2)
+        bw[kk][w2] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(lds + at + w_at[w2] + kk * 16 * (E * 2)));
+    }
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      const auto b = __builtin_shufflevector(bw[kk][0], bw[kk][1], 0, 1, 2, 3, 4, 5, 6, 7);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bx[kk]), __builtin_bit_cast(bf16x8, b), acc,
+                                                    0, 0, 0);
+    }
+    stage = stage == NS - 1 ? 0 : stage + 1;
+  }
+
+  // A register is one token's 32 experts over 32 lanes: 128 contiguous bytes.
+  float* dst = part + ((int64_t)ks * S + row0 + 32 * wt) * E + 32 * we + i32;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int t = 8 * (r >> 2) + 4 * hh + (r & 3);
+    if (row0 + 32 * wt + t < S) dst[(int64_t)t * E] = acc[r];
+  }
+}
+
+// Single-segment strategy for many tokens: 64 of them and the whole contraction axis per workgroup; the
+// scores never leave the chip, the workgroup runs the cascade on them.  NT = E / 32.
+template <int NT>
+__global__ __launch_bounds__(kMoeThreads) void moe_fused64_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, int S, int n_kblocks, int64_t ldx,
+    int64_t ldw, int topk, float* __restrict__ prob, int32_t* __restrict__ idx, int64_t ldp,
+    int64_t ldi) {
   constexpr int E = 32 * NT;
   constexpr int PPR = E / 8;               // 16-byte pieces per W row
   constexpr int kWTileB = kMoeKB * E * 2;  // [k][e]
@@ -322,11 +523,7 @@ __global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
   const int i32 = lane & 31;
   const int hh = lane >> 5;
   const int row0 = blockIdx.x * kMoeRows;
-  const int KS = gridDim.y;
-  const int ks = blockIdx.y;
-  // this slice's tiles: [b0, b1)
-  const int b0 = (int)((int64_t)n_kblocks * ks / KS);
-  const int b1 = (int)((int64_t)n_kblocks * (ks + 1) / KS);
+  const int b0 = 0, b1 = n_kblocks;
 
   const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
@@ -485,64 +682,53 @@ __global__ __launch_bounds__(kMoeThreads) void moe_scores_kernel(
         }
   }
   __syncthreads();
-  if constexpr (!FUSED) {
-    float* prow = part + ((int64_t)ks * S) * E;
+  // sums in the same fixed order, kept in registers until every wavefront has read the four
+  // copies, then laid out [token][expert] at the start of LDS
+  f32x4 sum[CPW];
 #pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      const int c = wave * CPW + cc;
-      f32x4 v = red[c * 64 + lane];
+  for (int cc = 0; cc < CPW; ++cc) {
+    const int c = wave * CPW + cc;
+    sum[cc] = red[c * 64 + lane];
 #pragma unroll
-      for (int r = 1; r < 4; ++r) v += red[r * (kChunks * 64) + c * 64 + lane];
-      const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
-      const int m = row0 + 32 * mi + i32;
-      if (m < S) *reinterpret_cast<f32x4*>(prow + (int64_t)m * E + 32 * ni + 8 * r4 + 4 * hh) = v;
-    }
-  } else {
-    // sums in the same fixed order, kept in registers until every wavefront has read the four
-    // copies, then laid out [token][expert] at the start of LDS
-    f32x4 sum[CPW];
+    for (int r = 1; r < 4; ++r) sum[cc] += red[r * (kChunks * 64) + c * 64 + lane];
+  }
+  __syncthreads();
+  float* sc = reinterpret_cast<float*>(lds);  // [kMoeRows][E + 4] (padded rows)
 #pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      const int c = wave * CPW + cc;
-      sum[cc] = red[c * 64 + lane];
-#pragma unroll
-      for (int r = 1; r < 4; ++r) sum[cc] += red[r * (kChunks * 64) + c * 64 + lane];
-    }
-    __syncthreads();
-    float* sc = reinterpret_cast<float*>(lds);  // [kMoeRows][E + 4] (padded rows)
-#pragma unroll
-    for (int cc = 0; cc < CPW; ++cc) {
-      const int c = wave * CPW + cc;
-      const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
-      *reinterpret_cast<f32x4*>(sc + (32 * mi + i32) * (E + 4) + 32 * ni + 8 * r4 + 4 * hh) = sum[cc];
-    }
-    __syncthreads();
-    // the cascade: 16 lanes per token, 16 tokens per pass
-    constexpr int EPL = E / 16;
-    const int q = tid & 15;
+  for (int cc = 0; cc < CPW; ++cc) {
+    const int c = wave * CPW + cc;
+    const int ni = c >> 3, mi = (c >> 2) & 1, r4 = c & 3;
+    *reinterpret_cast<f32x4*>(sc + (32 * mi + i32) * (E + 4) + 32 * ni + 8 * r4 + 4 * hh) = sum[cc];
+  }
+  __syncthreads();
+  // the cascade: 16 lanes per token, 16 tokens per pass
+  constexpr int EPL = E / 16;
+  const int q = tid & 15;
 #pragma unroll 1
-    for (int pass = 0; pass < kMoeRows / 16; ++pass) {
-      const int tl = 16 * pass + (tid >> 4);
-      const int row = row0 + tl;
-      float p[EPL];
+  for (int pass = 0; pass < kMoeRows / 16; ++pass) {
+    const int tl = 16 * pass + (tid >> 4);
+    const int row = row0 + tl;
+    float p[EPL];
 #pragma unroll
-      for (int i = 0; i < EPL; i += 2) {
-        const float2 v2 = *reinterpret_cast<const float2*>(sc + tl * (E + 4) + q * EPL + i);
-        p[i] = v2.x;
-        p[i + 1] = v2.y;
-      }
-      moe_cascade_token16<EPL>(p, q, row, row < S, topk, prob, idx, ldp, ldi);
+    for (int i = 0; i < EPL; i += 2) {
+      const float2 v2 = *reinterpret_cast<const float2*>(sc + tl * (E + 4) + q * EPL + i);
+      p[i] = v2.x;
+      p[i + 1] = v2.y;
     }
+    moe_cascade_token16<EPL>(p, q, row, row < S, topk, prob, idx, ldp, ldi);
   }
 }
 
 constexpr int kCascadeThreads = 256;  // 4 tokens per workgroup
 
-template <int E>
+// U slices are requested at a time.  (A remainder loop would wait for each: 512 x 4096 x 128 experts took 11.9 us
+// with 15 slices in batches of 16, 8.6 with 16.)
+template <int E, int U>
 __global__ __launch_bounds__(kCascadeThreads) void moe_cascade_kernel(
     const float* __restrict__ part, int KS, int S, int topk, float* __restrict__ prob,
     int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
   constexpr int EPL = E > 64 ? E / 64 : 1;
+  typedef __attribute__((__vector_size__(EPL * sizeof(float)))) float vec_t;
   const int lane = threadIdx.x & 63;
   const int row = __builtin_amdgcn_readfirstlane(blockIdx.x * (kCascadeThreads / kWave) + (threadIdx.x >> 6));
   if (row >= S) return;
@@ -550,13 +736,16 @@ __global__ __launch_bounds__(kCascadeThreads) void moe_cascade_kernel(
   float p[EPL];
 #pragma unroll
   for (int i = 0; i < EPL; ++i) p[i] = 0.f;
-  const float* src = part + (int64_t)row * E + (E < 64 ? min(lane, E - 1) : lane);
-  const int64_t slice = (int64_t)S * E;
-#pragma unroll 8
-  for (int s = 0; s < KS; ++s) {
+  const int at = E < 64 ? min(lane, E - 1) : lane;
+  for (int s0 = 0; s0 < KS; s0 += U) {
+    vec_t v[U];
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) p[i] += src[64 * i];
-    src += slice;
+    for (int u = 0; u < U; ++u)
+      v[u] = reinterpret_cast<const vec_t*>(part + ((int64_t)min(s0 + u, KS - 1) * S + row) * E)[at];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) p[i] += s0 + u < KS ? v[u][i] : 0.f;
   }
   if (E < 64 && lane >= E) p[0] = -INFINITY;
   moe_cascade_token<EPL>(p, E, lane, row, topk, prob, idx, ldp, ldi);
@@ -564,7 +753,7 @@ __global__ __launch_bounds__(kCascadeThreads) void moe_cascade_kernel(
 
 // Many tokens: 16 lanes each.
 constexpr int kCascade16Threads = 64;  // one wavefront = 4 tokens per workgroup
-template <int EPL>
+template <int EPL, int U>
 __global__ __launch_bounds__(kCascade16Threads) void moe_cascade16_kernel(
     const float* __restrict__ part, int KS, int S, int topk, float* __restrict__ prob,
     int32_t* __restrict__ idx, int64_t ldp, int64_t ldi) {
@@ -575,19 +764,25 @@ __global__ __launch_bounds__(kCascade16Threads) void moe_cascade16_kernel(
   const bool live = row < S;
   const int rrow = live ? row : S - 1;  // dead groups repeat the last token, store nothing
 
-  // scores: slices added in slice order
+  // scores: slices added in slice order, U of them requested at a time
   float p[EPL];
 #pragma unroll
   for (int i = 0; i < EPL; ++i) p[i] = 0.f;
-#pragma unroll 8
-  for (int s = 0; s < KS; ++s) {
-    const float* src = part + ((int64_t)s * S + rrow) * E + q * EPL;
+  for (int s0 = 0; s0 < KS; s0 += U) {
+    float2 v[U][EPL / 2];
 #pragma unroll
-    for (int i = 0; i < EPL; i += 2) {
-      const float2 v = *reinterpret_cast<const float2*>(src + i);
-      p[i] += v.x;
-      p[i + 1] += v.y;
+    for (int u = 0; u < U; ++u) {
+      const float* src = part + ((int64_t)min(s0 + u, KS - 1) * S + rrow) * E + q * EPL;
+#pragma unroll
+      for (int i = 0; i < EPL / 2; ++i) v[u][i] = reinterpret_cast<const float2*>(src)[i];
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < EPL / 2; ++i) {
+        p[2 * i] += s0 + u < KS ? v[u][i].x : 0.f;
+        p[2 * i + 1] += s0 + u < KS ? v[u][i].y : 0.f;
+      }
   }
   moe_cascade_token16<EPL>(p, q, row, live, topk, prob, idx, ldp, ldi);
 }
@@ -610,7 +805,7 @@ static float* moe_static_scratch() {
 hipError_t launch_moe_routing_static(const void* x, const void* w, int S, int hd, int E, int topk,
                                      int64_t ldx, int64_t ldw, float* prob, int32_t* idx,
                                      int64_t ldp, int64_t ldi, hipStream_t s) {
-  if ((size_t)moe_num_slices(S, hd) * (size_t)S * (size_t)E * sizeof(float) > kMoeStaticScratchBytes)
+  if ((size_t)moe_num_slices(S, hd, E) * (size_t)S * (size_t)E * sizeof(float) > kMoeStaticScratchBytes)
     return hipErrorInvalidValue;  // (the C-ABI layer has already refused this size)
   float* part = moe_static_scratch();
   if (part == nullptr) return hipErrorInvalidSymbol;
@@ -625,15 +820,29 @@ hipError_t launch_moe_routing_static(const void* x, const void* w, int S, int hd
 // 13.7 and 7.9 us at 2048.
 constexpr int kMoeSingleSegmentMaxHd = 1024;
 
-int moe_num_slices(int S, int hd) {
+// How the axis is cut: a workgroup (one per compute unit) costs 1.2 us and 0.3 us for each of its tiles of 128 k
+// (0.7 with 128 tokens of 32 experts), a slice 0.05 us and 0.29 us for each MB of partial scores.  Fitted to 90 problems of
+// 1 to 6000 tokens and 1152 to 8192 k with every cut from 1 to 64; the one it takes is 0.8 % from the best on
+// average, 6 % at most.  2048 x 4096 x 128: 4 slices 11.9 us, 2 14.9; 512 x 4096 x 128: 8 slices 7.9, 16 8.8;
+// 2869 x 7552 x 128: 2 slices 21.2, 3, which the compute units take in two turns, 27.2.
+int moe_num_slices(int S, int hd, int E) {
   if (hd <= kMoeSingleSegmentMaxHd) return 1;  // (one slice is still what the workspace query promises room for)
-  const int n_rb = (S + kMoeRows - 1) / kMoeRows;
+  const int64_t n_rb = ((int64_t)S * E + 4095) / 4096;
   const int n_kblocks = hd / kMoeKB;
-  int ks = (256 + n_rb - 1) / n_rb;  // aim at one workgroup per CU
-  if (ks > n_kblocks) ks = n_kblocks;
-  if (ks > 64) ks = 64;
-  if (ks < 1) ks = 1;
-  return ks;
+  const double turn = ceil(256.0 / n_rb), turn64 = ceil(256.0 / ceil(S / 64.0));  // (two slices help 2^13 to 2^14 tokens too)
+  const int most = (int)fmin(fmin(64, n_kblocks), fmax(turn, turn64));
+  int best = 1;
+  double best_us = 0;
+  for (int ks = 1; ks <= most; ++ks) {
+    const double tiles = (n_kblocks + ks - 1) / ks;
+    const double us = ceil((double)n_rb * ks / 256) * (1.25 + (E == 32 ? 0.74 : E == 64 ? 0.31 : 0.33) * tiles) + 0.053 * ks +
+                      0.286 * 4e-6 * S * E * ks;
+    if (ks == 1 || us < best_us) {
+      best = ks;
+      best_us = us;
+    }
+  }
+  return best;
 }
 
 // Many tokens on a short axis: 64 of them per workgroup instead of 16, for a quarter of the trips of w.  Until the
@@ -655,32 +864,32 @@ static bool moe_fused64_wins(int S, int hd, int E, int topk) {
   return us64 < us16;
 }
 
-// The cascade's wavefront per token pays off until there are some 14 of them per compute unit: both calls' us
-// with 16 lanes / a wavefront a token, 2560 k, 32 experts, top 16: 2048 tokens 11.0 / 10.0, 4096 12.3 / 13.5,
-// 12000 21.1 / 28.4; 128 experts 19.9 / 16.4, 20.3 / 20.4, 38.6 / 43.1.
-static bool moe_cascade16_wins(int S) { return S > 3584; }
+// The cascade's wavefront per token pays off until there are some 32 of them per compute unit: both calls' us with 16 lanes /
+// a wavefront a token: 2457 x 7552 x 64, top 6, 15.2 / 13.8; 6126 x 2816 x 64, top 8, 14.6 / 13.4; 8101 x 1920 x 128,
+// top 1, 15.3 / 15.3; 10983 x 2176 x 32, top 1, 13.8 / 14.7.
+static bool moe_cascade16_wins(int S) { return S > 8192; }
 
 hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E, int topk,
                               int64_t ldx, int64_t ldw, float* prob, int32_t* idx, int64_t ldp,
                               int64_t ldi, float* part, hipStream_t s) {
   const int n_kblocks = hd / kMoeKB;
-  const int KS = moe_num_slices(S, hd);
+  const int KS = moe_num_slices(S, hd, E);
   // 32-bit lane offsets inside x and inside one 128-row tile of w
   if ((int64_t)S * ldx * 2 >= ((int64_t)1 << 32) || (int64_t)kMoeKB * ldw * 2 >= ((int64_t)1 << 32))
     return hipErrorInvalidValue;
   const bf16_t* xb = (const bf16_t*)x;
   const bf16_t* wb = (const bf16_t*)w;
-  const dim3 grid1((unsigned)((S + kMoeRows - 1) / kMoeRows), (unsigned)KS), block1(kMoeThreads);
-#define RF_MOE_SCORES(NT, FUSED) \
-  hipLaunchKernelGGL((moe_scores_kernel<NT, FUSED>), grid1, block1, 0, s, xb, wb, part, S, n_kblocks, ldx, ldw, topk, prob, \
-                     idx, ldp, ldi)
-  if (hd <= kMoeSingleSegmentMaxHd && moe_fused64_wins(S, hd, E, topk)) {
+    if (hd <= kMoeSingleSegmentMaxHd && moe_fused64_wins(S, hd, E, topk)) {
+#define RF_MOE_FUSED64(NT)                                                                                        \
+  hipLaunchKernelGGL((moe_fused64_kernel<NT>), dim3((unsigned)((S + kMoeRows - 1) / kMoeRows)), dim3(kMoeThreads), 0, s, xb, \
+                     wb, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi)
     switch (E) {
-      case 32: RF_MOE_SCORES(1, true); break;
-      case 64: RF_MOE_SCORES(2, true); break;
-      case 128: RF_MOE_SCORES(4, true); break;
+      case 32: RF_MOE_FUSED64(1); break;
+      case 64: RF_MOE_FUSED64(2); break;
+      case 128: RF_MOE_FUSED64(4); break;
       default: return hipErrorInvalidValue;
     }
+#undef RF_MOE_FUSED64
     return hipGetLastError();
   }
   if (hd <= kMoeSingleSegmentMaxHd) {
@@ -697,10 +906,13 @@ hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E
 #undef RF_MOE_FUSED
     return hipGetLastError();
   }
+#define RF_MOE_SCORES(EE)                                                                                         \
+  hipLaunchKernelGGL((moe_scores_kernel<EE>), dim3((unsigned)((S + MoeTile<EE>::kTokens - 1) / MoeTile<EE>::kTokens), (unsigned)KS), \
+                     dim3(kMoeThreads), 0, s, xb, wb, part, S, n_kblocks, ldx, ldw)
   switch (E) {
-    case 32: RF_MOE_SCORES(1, false); break;
-    case 64: RF_MOE_SCORES(2, false); break;
-    case 128: RF_MOE_SCORES(4, false); break;
+    case 32: RF_MOE_SCORES(32); break;
+    case 64: RF_MOE_SCORES(64); break;
+    case 128: RF_MOE_SCORES(128); break;
     default: return hipErrorInvalidValue;
   }
 #undef RF_MOE_SCORES
@@ -708,22 +920,35 @@ hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E
   if (e != hipSuccess) return e;
   if (moe_cascade16_wins(S)) {
     const dim3 grid16((unsigned)((S + kCascade16Threads / 16 - 1) / (kCascade16Threads / 16)));
-#define RF_MOE_CASCADE16(EPL) \
-  hipLaunchKernelGGL((moe_cascade16_kernel<EPL>), grid16, dim3(kCascade16Threads), 0, s, part, KS, S, topk, prob, idx, ldp, ldi)
-    if (E == 32) RF_MOE_CASCADE16(2);
-    else if (E == 64) RF_MOE_CASCADE16(4);
-    else RF_MOE_CASCADE16(8);
+#define RF_MOE_CASCADE16(EPL, U) \
+  hipLaunchKernelGGL((moe_cascade16_kernel<EPL, U>), grid16, dim3(kCascade16Threads), 0, s, part, KS, S, topk, prob, idx, ldp, ldi)
+#define RF_MOE_CASCADE16_U(EPL)           \
+  if (KS == 1) RF_MOE_CASCADE16(EPL, 1);  \
+  else if (KS == 2) RF_MOE_CASCADE16(EPL, 2); \
+  else RF_MOE_CASCADE16(EPL, 4)
+    if (E == 32) { RF_MOE_CASCADE16_U(2); }
+    else if (E == 64) { RF_MOE_CASCADE16_U(4); }
+    else { RF_MOE_CASCADE16_U(8); }
+#undef RF_MOE_CASCADE16_U
 #undef RF_MOE_CASCADE16
     return hipGetLastError();
   }
   constexpr int kTokens = kCascadeThreads / kWave;
   const dim3 grid2((unsigned)((S + kTokens - 1) / kTokens)), block2(kCascadeThreads);
+#define RF_MOE_CASCADE(EE, U) \
+  hipLaunchKernelGGL((moe_cascade_kernel<EE, U>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi)
+#define RF_MOE_CASCADE_U(EE)              \
+  if (KS <= 4) RF_MOE_CASCADE(EE, 4);     \
+  else if (KS <= 8) RF_MOE_CASCADE(EE, 8); \
+  else RF_MOE_CASCADE(EE, 16)
   switch (E) {
-    case 32: hipLaunchKernelGGL((moe_cascade_kernel<32>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
-    case 64: hipLaunchKernelGGL((moe_cascade_kernel<64>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
-    case 128: hipLaunchKernelGGL((moe_cascade_kernel<128>), grid2, block2, 0, s, part, KS, S, topk, prob, idx, ldp, ldi); break;
+    case 32: RF_MOE_CASCADE_U(32); break;
+    case 64: RF_MOE_CASCADE_U(64); break;
+    case 128: RF_MOE_CASCADE_U(128); break;
     default: return hipErrorInvalidValue;
   }
+#undef RF_MOE_CASCADE_U
+#undef RF_MOE_CASCADE
   return hipGetLastError();
 }
 

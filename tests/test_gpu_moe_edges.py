@@ -78,3 +78,56 @@ def test_moe_routing_infinite_scores(rf):  # noqa: F811
         p, i = torch.topk(torch.softmax(s, 0), 8)
         assert torch.equal(idx[1].long(), i)
         assert float(((prob[1].double() - p) / p).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("S,hd,E,topk", [
+    # token tiles of 32, 64, 128 (128, 64, 32 experts); slices of 1 to 7 tiles of 128 k, uneven ones, more slices than a
+    # batch of the cascade (16), one slice of a long axis
+    (31, 1152, 128, 8), (33, 8192, 128, 16), (63, 1280, 64, 1), (65, 4224, 64, 8), (127, 2176, 32, 4), (129, 8064, 32, 8),
+    (1999, 3712, 128, 6), (2940, 3456, 64, 6), (3257, 1408, 32, 8), (4000, 5504, 128, 2), (8193, 1152, 128, 3), (8200, 2048, 64, 5),
+])
+def test_moe_routing_slices(rf, S, hd, E, topk):  # noqa: F811
+    say(f"moe_routing slices S{S} hd{hd} E{E} top{topk}")
+    x, w = I.moe_routing_inputs(I.SEED_BASE + 90 + S, S, hd, E)
+    big = torch.full((S, hd + 64), float("nan"), dtype=torch.bfloat16, device=DEV)
+    big[:, 8:hd + 8] = I.to_torch(x, "bf16", DEV)
+    ws = torch.full((rf.moe_routing_workspace_bytes(S, hd, E) // 4,), float("nan"), dtype=torch.float32, device=DEV)
+    prob, idx = rf.rf_moe_routing(big[:, 8:hd + 8], I.to_torch(w, "bf16", DEV), topk, workspace=ws)
+    torch.cuda.synchronize()
+    rows = sorted(set(range(0, S, 29)) | set(range(max(0, S - 40), S)))
+    check_routing(prob[rows], idx[rows], x[rows], w, topk, "moe_routing slices")
+
+
+@pytest.mark.parametrize("hd", [128, 1152])
+@pytest.mark.parametrize("E", [32, 64, 128])
+def test_moe_routing_equal_scores_in_every_place(rf, hd, E):  # noqa: F811
+    """Scores that are exact sums: equal ones around every place of the TopK, zeros of either sign, negative scores
+    only, and NaN, which is nobody's score and everybody's probability."""
+    say(f"moe_routing equal scores hd{hd} E{E}")
+    gen = torch.Generator().manual_seed(hd + E)
+    S = 40
+    x = torch.zeros((S, hd), dtype=torch.float32)
+    x[:, 0], x[:, 1] = 1.0, 1.0
+    w = torch.zeros((hd, E), dtype=torch.float32)
+    w[0] = torch.randint(-6, 3, (E,), generator=gen).float() / 4          # many equal scores
+    x[20:, 2] = 1.0
+    w[2] = torch.randperm(E, generator=gen).float() / 8 - 32.0             # rows from 20 on: mostly distinct, all negative
+    for topk in (1, 7, 8, 16):
+        prob, idx = rf.rf_moe_routing(x.to(DEV, torch.bfloat16), w.to(DEV, torch.bfloat16), topk)
+        torch.cuda.synchronize()
+        s = x.double() @ w.double()
+        order = torch.argsort(s, dim=1, descending=True, stable=True)[:, :topk]   # equal scores: lowest index first
+        assert torch.equal(idx.cpu().long(), order)
+        want = torch.gather(torch.softmax(s, 1), 1, order)
+        assert float(((prob.cpu().double() - want) / want).abs().max()) <= 1e-5
+    z = torch.zeros((hd, E), dtype=torch.float32)
+    z[0, ::2] = -0.0                                                       # scores of -0 and 0 are equal
+    prob, idx = rf.rf_moe_routing(x.to(DEV, torch.bfloat16), z.to(DEV, torch.bfloat16), 8)
+    torch.cuda.synchronize()
+    assert bool((idx.cpu() == torch.arange(8, dtype=torch.int32)).all())
+    w[0, 3] = float("nan")
+    prob, idx = rf.rf_moe_routing(x.to(DEV, torch.bfloat16), w.to(DEV, torch.bfloat16), 8)
+    torch.cuda.synchronize()
+    s[:, 3] = -1e30
+    order = torch.argsort(s, dim=1, descending=True, stable=True)[:, :8]
+    assert torch.equal(idx.cpu().long(), order) and bool(torch.isnan(prob).all())
