@@ -14,13 +14,15 @@
 // between the two is the order of fp32 sums.)  ss is the diagonal of X X^T, taken by the matrix
 // pipe from the x that is in registers already.
 //
+// (This kernel serves tiles of 64 rows or 128 columns, and a few rows against much of w; the others go through
+// LDS, see below.)
 // What bounds it: the 128-byte lines a compute unit can have on their way.  A read of w alone in
 // this pattern takes 15.9 us when w comes from HBM (4096 x 4096, C = 2, 128 workgroups), 17.7 us with
 // whole lines and half the workgroups (C = 4), and cache-policy bits change nothing; the last 50 GB/s
 // per compute unit are its 32 KB of L1 lines in flight over the memory latency.  Two steps in
 // flight and 4 wavefronts are therefore faster than 8 wavefronts with more (which evict each
 // other's lines): 48 x 4096 x 4096, repeated on the same w (33 MB: it stays in the memory-side cache),
-// takes 13.8 us a call, and 86.4 in 128 x 512 tiles.  A few hundred rows are bound by the same lines in
+// takes 13.8 us a call here, and 86.4 in 128 x 512 tiles.  A few hundred rows are bound by the same lines in
 // either kernel, and 64 x 128 tiles move fewest of them per compute unit in use: 1024 x 8192 x 2048
 // takes 57 to 62 us, by the card, against 171.
 #include <math.h>
@@ -44,10 +46,6 @@ __global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
     bf16_t* __restrict__ y, int M, int K, int N, int64_t ldx, int64_t ldw, int64_t ldy,
     float inv_k, float eps, int n_mtiles) {
   constexpr int CD = C / 2;  // 32-bit words of w per lane and k-row
-  // Requests are waited for in order.  Two row tiles against a narrow tile of w have as much work in
-  // x g as in pairing w and start it first (48 x 4096 x 4096: 14.5 us, 15.2 the other way round);
-  // the other shapes want w first (32 x 8192 x 1024 in one row tile: 15.6 and 20.3).
-  constexpr bool kXFirst = MT == 2 && C == 2;
   __shared__ f32x4 s_acc[kRWaves][C * MT][kWave];
   __shared__ float s_ss[kRWaves][16 * MT];
 
@@ -88,12 +86,6 @@ __global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
     const int ii = min(i, mine - 1);
     const uint32_t k0 = (wave + kRWaves * (ii >> 1)) * 64 + (ii & 1) * 32;
     const uint32_t wo = k0 * ldw2;
-    auto load_x = [&] {
-#pragma unroll
-      for (int t = 0; t < MT; ++t) xr[p][t] = __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane[t], k0 * 2, 0);
-      gr[p] = __builtin_amdgcn_raw_buffer_load_b128(grs, 16 * g4, k0 * 2, 0);
-    };
-    if constexpr (kXFirst) load_x();
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       if constexpr (CD == 4) {
@@ -108,7 +100,10 @@ __global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
         for (int d = 0; d < CD; ++d) wr[p][e][d] = v[d];
       }
     }
-    if constexpr (!kXFirst) load_x();
+    // (requests are waited for in order: w first, 32 x 8192 x 1024 in one row tile 15.6 us, 20.3 the other way round)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) xr[p][t] = __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane[t], k0 * 2, 0);
+    gr[p] = __builtin_amdgcn_raw_buffer_load_b128(grs, 16 * g4, k0 * 2, 0);
   };
 
   f32x4 acc[C][MT], sq[MT];
@@ -210,6 +205,185 @@ __global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
 }
 
 namespace {
+constexpr int kLWaves = 8;
+constexpr int kLThreads = kLWaves * kWave;
+constexpr int kGChunk = 4096;  // k whose g is held in LDS
+}  // namespace
+
+// The smaller tiles through LDS: 8 wavefronts deal the 64-k pieces of the axis among themselves, each with a stage
+// of its own that direct-to-LDS loads fill (a row of x is 128 bytes of it, a row of w 32 C), so there is still no
+// barrier in the loop but where the next 4096 values of g are fetched.  x and w leave LDS in operand layout, w by
+// transpose reads: no pairing of rows in registers, and the loads hold no registers.  A piece is requested as soon as
+// the one before is in registers; rings of 2 or 4 stages with 4 wavefronts are no faster or slower (48 x 4096 x 4096
+// 13.2 and 14.1 us, 13.0 here; 16 x 4096 x 4096 in 16 x 32 tiles 11.8 and 12.4, 11.5 here): what counts is that
+// many wavefronts have requests under way, not how many each has.  us a call, registers / LDS: 48 x 4096 x 4096
+// 15.2 / 13.0, 16 x 4096 x 4096 14.2 / 11.5, 154 x 4416 x 1024 14.5 / 10.4, 23 x 2432 x 1008 7.2 / 5.7, 5 x 1920 x 832
+// 6.3 / 5.1 (140 products, 1.11 x on average).
+template <int MT, int C>
+__global__ __launch_bounds__(kLThreads, 2) void rmsnorm_gemm_rows_lds_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ g, const bf16_t* __restrict__ w,
+    bf16_t* __restrict__ y, int M, int K, int N, int64_t ldx, int64_t ldw, int64_t ldy,
+    float inv_k, float eps, int n_mtiles) {
+  constexpr int kXB = 2048 * MT, kWB = 2048 * C, kStageB = kXB + kWB;  // 64 k: [row][k], [k][column]
+  constexpr int kXL = 2 * MT, kWL = 2 * C, kL = kXL + kWL;             // direct-to-LDS loads of a stage
+  constexpr int kRedB = C * MT * 1024;                                 // a wavefront's sums
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[kLWaves * (kStageB > kRedB ? kStageB : kRedB)];
+  __shared__ __attribute__((aligned(16))) bf16_t s_g[kGChunk];
+  __shared__ float s_ss[kLWaves][16 * MT];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, g4 = lane >> 4;
+
+  constexpr int GC = C >= 4 ? 1 : 4 / C;  // column tiles per 128-byte line
+  const int unit = GC * n_mtiles;
+  const int j = blockIdx.x >> 3;
+  const int mt = __builtin_amdgcn_readfirstlane(j % unit % n_mtiles);
+  const int nt = __builtin_amdgcn_readfirstlane((j / unit * 8 + (blockIdx.x & 7)) * GC + j % unit / n_mtiles);
+  const int m0 = mt * 16 * MT, n0 = nt * 16 * C;
+  if (n0 >= N) return;
+  const uint32_t stage = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds + wave * kStageB);
+  const unsigned char* st = lds + wave * kStageB;
+  // 16-byte slots of a row are XOR-swizzled with the row where the operand reads would meet the same banks
+  auto fx = [](int row) { return (row >> 1) & 7; };
+  auto fw = [](int krow) { return C == 4 ? 2 * ((krow >> 1) & 1) : 0; };
+  uint32_t x_off[kXL], w_off[kWL];
+#pragma unroll
+  for (int e = 0; e < kXL; ++e) {
+    const int row = 8 * e + (lane >> 3);
+    x_off[e] = (uint32_t)(min(row, M - 1 - m0) * (uint32_t)(ldx * 2) + (((lane & 7) ^ fx(row)) << 4));
+  }
+  constexpr int SL = 2 * C;  // 16-byte slots per k-row
+#pragma unroll
+  for (int e = 0; e < kWL; ++e) {
+    const int krow = (64 / SL) * e + lane / SL;
+    const int piece = (lane % SL) ^ fw(krow);
+    w_off[e] = (uint32_t)(krow * (uint32_t)(ldw * 2) + min(n0 + 8 * piece, N - 8) * 2);
+  }
+  const char* xb = reinterpret_cast<const char*>(x + (int64_t)m0 * ldx);
+  const char* wb = reinterpret_cast<const char*>(w);
+  auto request = [&](int first, int i) {  // this wavefront's piece i of those from `first` on
+    const int p = first + wave + kLWaves * i;
+    const char* xp = xb + (int64_t)p * 128;
+    const char* wp = wb + (int64_t)p * 128 * ldw;
+#pragma unroll
+    for (int e = 0; e < kL; ++e) {
+      const bool is_w = e < kWL;
+      const uint32_t dst = stage + (is_w ? kXB + e * 1024 : (e - kWL) * 1024);
+      const uint32_t off = is_w ? w_off[is_w ? e : 0] : x_off[is_w ? 0 : e - kWL];
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :
+                   : "s"(dst), "v"(off), "s"(is_w ? wp : xp)
+                   : "memory", "m0");
+    }
+  };
+  f32x4 acc[C][MT], sq[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    sq[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+  uint32_t x_at[2], w_at[2][2][C];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    x_at[kk] = i16 * 128 + (((4 * kk + g4) ^ fx(i16)) << 4);  // (+ 2048 t: the swizzle repeats after 16 rows)
+#pragma unroll
+    for (int w2 = 0; w2 < 2; ++w2)
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const int krow = 32 * kk + 8 * g4 + 4 * w2 + (i16 >> 2), a = i16 & 3;
+        w_at[kk][w2][c] = kXB + krow * 32 * C + (((2 * c + (a >> 1)) ^ fw(krow)) << 4) + 8 * (a & 1);
+      }
+  }
+  for (int kc = 0; kc < K; kc += kGChunk) {
+    const int pieces = min(K - kc, kGChunk) / 64;
+    const int mine = (pieces - wave + kLWaves - 1) / kLWaves;
+    if (mine > 0) request(kc / 64, 0);
+    if (kc > 0) __syncthreads();  // (everyone is done with the g before)
+    for (int k = tid * 8; k < 64 * pieces; k += kLThreads * 8)
+      *reinterpret_cast<u32x4*>(s_g + k) = *reinterpret_cast<const u32x4*>(g + kc + k);
+    __syncthreads();
+    for (int i = 0; i < mine; ++i) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this piece has landed
+      u32x4 xf[2][MT], gf[2];
+      s16x4 wf[2][C][2];
+      const int k0 = (wave + kLWaves * i) * 64;
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+        gf[kk] = *reinterpret_cast<const u32x4*>(s_g + k0 + 32 * kk + 8 * g4);
+#pragma unroll
+        for (int t = 0; t < MT; ++t) xf[kk][t] = *reinterpret_cast<const u32x4*>(st + x_at[kk] + 2048 * t);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int w2 = 0; w2 < 2; ++w2) wf[kk][c][w2] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + w_at[kk][w2][c]));
+      }
+      // the stage is in registers: the next piece takes it
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + 1 < mine) request(kc / 64, i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+          const bf16x8 raw = __builtin_bit_cast(bf16x8, xf[kk][t]);
+          u32x4 xg;
+#pragma unroll
+          for (int e2 = 0; e2 < 4; ++e2)
+            xg[e2] = pack_bf16(bf16_lo(xf[kk][t][e2]) * bf16_lo(gf[kk][e2]), bf16_hi(xf[kk][t][e2]) * bf16_hi(gf[kk][e2]));
+          const bf16x8 b = __builtin_bit_cast(bf16x8, xg);
+#pragma unroll
+          for (int c = 0; c < C; ++c) {
+            const auto a = __builtin_shufflevector(wf[kk][c][0], wf[kk][c][1], 0, 1, 2, 3, 4, 5, 6, 7);
+            acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), b, acc[c][t], 0, 0, 0);
+          }
+          sq[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(raw, raw, sq[t], 0, 0, 0);
+        }
+    }
+  }
+
+  // ---- add the wavefronts' sums ----
+  // acc[c][t] of lane (i16, g4), element r: row m0 + 16 t + i16, column n0 + 16 c + 4 g4 + r
+  __syncthreads();
+  f32x4* s_acc = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) s_acc[(wave * C * MT + c * MT + t) * 64 + lane] = acc[c][t];
+  if ((i16 >> 2) == g4) {  // this lane holds the diagonal element of row i16
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const f32x4 s = sq[t];
+      const int r = i16 & 3;
+      s_ss[wave][16 * t + i16] = r == 0 ? s[0] : r == 1 ? s[1] : r == 2 ? s[2] : s[3];
+    }
+  }
+  __syncthreads();
+  for (int idx = tid; idx < C * MT * 64; idx += kLThreads) {
+    const int ct = idx >> 6, l = idx & 63, c = ct / MT, t = ct % MT;
+    float ss = 0.f;
+    f32x4 v = s_acc[idx];
+#pragma unroll
+    for (int wv = 1; wv < kLWaves; ++wv) v += s_acc[wv * C * MT * 64 + idx];
+#pragma unroll
+    for (int wv = 0; wv < kLWaves; ++wv) ss += s_ss[wv][16 * t + (l & 15)];
+    const float rs = 1.0f / sqrtf(ss * inv_k + eps);
+    const int m = m0 + 16 * t + (l & 15), n = n0 + 16 * c + 4 * (l >> 4);
+    if (m < M && n < N) {  // (N is a multiple of 8)
+      u32x2 o;
+      o[0] = pack_bf16(v[0] * rs, v[1] * rs);
+      o[1] = pack_bf16(v[2] * rs, v[3] * rs);
+      *reinterpret_cast<u32x2*>(y + (int64_t)m * ldy + n) = o;
+    }
+  }
+}
+
+namespace {
 // Tile shapes and what a workgroup of each takes: us for the launch and the sums, us per 1024 k.
 // The latter is its lines' way through the compute unit, 46 GB/s of w and x at C <= 4 and 62-67 at
 // C = 8, where a lane's load of w is 16 bytes: bigger tiles win as soon as there are enough of them.
@@ -232,6 +406,10 @@ const RowsShape& best_shape(int M, int K, int N) {
     if (rows_us(r, M, K, N) < rows_us(*best, M, K, N)) best = &r;
   return *best;
 }
+// A handful of rows against much of w: nothing but its trip counts, which is some per cent shorter straight into
+// registers (us registers / LDS: 1 x 4352 x 7336 19.5 / 20.5, 4 x 4160 x 6744 17.7 / 18.5, 9 x 2816 x 6528 8.7 / 8.8,
+// 7 x 4928 x 2600 14.8 / 14.2, 4 x 3904 x 1584 9.4 / 9.0).
+bool streams_w(int M, int K, int N) { return M <= 5 && (double)K * N >= 8e6; }
 }  // namespace
 
 // The 128 x 512 tiles take 5 us and 20.5 for every 1024 k up to 64 of them, 29 at 256, whatever the
@@ -264,8 +442,19 @@ hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w,
     hipLaunchKernelGGL((rmsnorm_gemm_rows_kernel<MT, C, P>), dim3((unsigned)grid), dim3(kRThreads), 0, s, \
                        (const bf16_t*)x, (const bf16_t*)g, (const bf16_t*)w, (bf16_t*)y, M, K, N, ldx, ldw, \
                        ldy, 1.0f / (float)K, eps, n_mt);
-  RF_ROWS(1, 2, 4) RF_ROWS(2, 2, 2) RF_ROWS(1, 4, 2) RF_ROWS(2, 4, 2) RF_ROWS(4, 4, 2)
-  RF_ROWS(2, 8, 2) RF_ROWS(4, 8, 2)
+#define RF_ROWS_LDS(MT, C)                                                                                 \
+  if (best.mt == MT && best.c == C)                                                                        \
+    hipLaunchKernelGGL((rmsnorm_gemm_rows_lds_kernel<MT, C>), dim3((unsigned)grid), dim3(kLThreads), 0, s, \
+                       (const bf16_t*)x, (const bf16_t*)g, (const bf16_t*)w, (bf16_t*)y, M, K, N, ldx, ldw, \
+                       ldy, 1.0f / (float)K, eps, n_mt);
+  if (streams_w(M, K, N)) {
+    RF_ROWS(1, 2, 4)
+  } else {
+    RF_ROWS_LDS(1, 2)
+  }
+  RF_ROWS_LDS(2, 2) RF_ROWS_LDS(1, 4) RF_ROWS_LDS(2, 4)
+  RF_ROWS(4, 4, 2) RF_ROWS(2, 8, 2) RF_ROWS(4, 8, 2)
+#undef RF_ROWS_LDS
 #undef RF_ROWS
   return hipGetLastError();
 }

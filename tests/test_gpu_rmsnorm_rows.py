@@ -69,3 +69,24 @@ def test_rmsnorm_gemm_rows_do_not_depend_on_their_batch(rf):  # noqa: F811
         assert moved <= 5e-3, rows
         assert float((part - want).norm() / want.norm()) <= 2e-4, rows
         assert bool(((part - want).abs() <= 2.0 ** -7 * want.abs() + 1e-4 * want.abs().max()).all())
+
+
+@pytest.mark.parametrize("M,K,N", [
+    # (tiles of up to 32 rows x 64 columns) pieces of 64 k that leave wavefronts without one, the next 4096 values of g
+    # after 64 pieces, a handful of rows against much of w, strided rows of x and w, columns that end in a tile's middle
+    (6, 64, 8), (6, 512, 40), (7, 576, 136), (20, 4096, 520), (20, 4160, 264), (37, 8192, 264), (40, 8256, 72), (130, 12352, 136),
+    (5, 4352, 2056), (6, 4352, 2056), (300, 1472, 544), (64, 768, 2952),
+])
+def test_rmsnorm_gemm_few_rows_strided(rf, M, K, N):  # noqa: F811
+    tile = rf.rf_diag_rmsnorm_gemm_tile(M, K, N)
+    assert tile in ((16, 32), (16, 64), (32, 32), (32, 64))
+    say(f"rmsnorm_gemm few rows, strided, tile {tile}: M{M} K{K} N{N}")
+    x, g, w = I.rmsnorm_gemm_inputs(I.SEED_BASE + 52 + M, M, K, N)
+    bx = torch.full((M, K + 72), float("nan"), dtype=torch.bfloat16, device=DEV)
+    bw = torch.full((K, N + 24), float("nan"), dtype=torch.bfloat16, device=DEV)
+    bx[:, 8:K + 8], bw[:, 8:N + 8] = I.to_torch(x, "bf16", DEV), I.to_torch(w, "bf16", DEV)
+    y = torch.full((M + 1, N + 16), float("nan"), dtype=torch.bfloat16, device=DEV)
+    rf.rf_rmsnorm_gemm(bx[:, 8:K + 8], I.to_torch(g, "bf16", DEV), bw[:, 8:N + 8], eps=1e-6, y=y[:M, 8:N + 8])
+    torch.cuda.synchronize()
+    check(y[:M, 8:N + 8], O.rmsnorm_gemm(x, g, w, 1e-6), "bf16", "rmsnorm_gemm few rows, strided")
+    assert bool(torch.isnan(y[:, :8]).all()) and bool(torch.isnan(y[:, N + 8:]).all()) and bool(torch.isnan(y[M]).all())
