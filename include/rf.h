@@ -208,6 +208,23 @@ RF_API rf_status rf_cascade_attention(const rf_tensor* q, const rf_tensor* k, co
                                rf_tensor* o, float scale, int causal, rf_stream stream);
 
 /*
+ * rf_cascade_attention with device memory for partial states: where few query rows meet a long
+ * context, the keys are cut into chunks whose states are merged as in the multi-segment
+ * strategy below (the number of chunks is the library's choice).
+ *   workspace : device memory, 16-byte aligned, at least
+ *       rf_cascade_attention_workspace_bytes(q, k, v, causal) bytes (which looks at shapes,
+ *       strides and types only); contents need no initialisation and are undefined afterwards.
+ *       Too small or misaligned: RF_ERR_WORKSPACE.  Concurrent calls must not share a workspace.
+ * The size is 0 where a single launch serves the call faster (the call is then
+ * rf_cascade_attention) and for arguments that are refused, and at most 128 MiB.
+ */
+RF_API size_t rf_cascade_attention_workspace_bytes(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v,
+                               int causal);
+RF_API rf_status rf_cascade_attention_ws(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v,
+                               rf_tensor* o, float scale, int causal, void* workspace,
+                               size_t workspace_bytes, rf_stream stream);
+
+/*
  * Multi-segment strategy, first half (Section 4.3; Appendix A.4 partial
  * kernel): the key axis is cut into num_splits chunks, chunk c covering keys
  * [c*ceil(Lk/S), min(Lk,(c+1)*ceil(Lk/S))), and each chunk's state is written:

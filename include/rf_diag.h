@@ -60,6 +60,8 @@ RF_API rf_status rf_diag_attention_wide(const rf_tensor* q, const rf_tensor* k, 
  * rf_diag_splitk_route, for rf_cascade_attention_splitk: 1 streaming chunks, 2 short chunks.
  */
 RF_API int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal);
+/* Chunks of keys that rf_cascade_attention_ws cuts a call into; 0 where it is rf_cascade_attention. */
+RF_API int rf_diag_attention_ws_chunks(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal);
 RF_API int rf_diag_splitk_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int num_splits);
 
 /*

@@ -28,6 +28,8 @@ ENTRY_POINTS = (
     "rf_describe_cascade",
     "rf_safe_softmax",
     "rf_cascade_attention",
+    "rf_cascade_attention_workspace_bytes",
+    "rf_cascade_attention_ws",
     "rf_cascade_attention_splitk",
     "rf_merge_states",
     "rf_rmsnorm_gemm",
@@ -43,6 +45,7 @@ ENTRY_POINTS = (
 DIAG_ENTRY_POINTS = (
     "rf_diag_softmax_level",
     "rf_diag_attention_route",
+    "rf_diag_attention_ws_chunks",
     "rf_diag_splitk_route",
     "rf_diag_rmsnorm_gemm_tile",
     "rf_diag_fp8_quant_gemm_tile",
@@ -96,6 +99,11 @@ def load_library():
     lib.rf_safe_softmax.argtypes = [P, P, ctypes.c_int, ctypes.c_void_p]
     lib.rf_cascade_attention.restype = ctypes.c_int
     lib.rf_cascade_attention.argtypes = [P, P, P, P, ctypes.c_float, ctypes.c_int, ctypes.c_void_p]
+    lib.rf_cascade_attention_workspace_bytes.restype = ctypes.c_size_t
+    lib.rf_cascade_attention_workspace_bytes.argtypes = [P, P, P, ctypes.c_int]
+    lib.rf_cascade_attention_ws.restype = ctypes.c_int
+    lib.rf_cascade_attention_ws.argtypes = [P, P, P, P, ctypes.c_float, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t,
+                                            ctypes.c_void_p]
     lib.rf_cascade_attention_splitk.restype = ctypes.c_int
     lib.rf_cascade_attention_splitk.argtypes = [P, P, P, ctypes.c_int, P, P, P, ctypes.c_float,
                                                 ctypes.c_int, ctypes.c_void_p]
@@ -123,6 +131,8 @@ def load_library():
     lib.rf_diag_softmax_level.argtypes = [P, P, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
     lib.rf_diag_attention_route.restype = ctypes.c_int
     lib.rf_diag_attention_route.argtypes = [P, P, P, ctypes.c_int]
+    lib.rf_diag_attention_ws_chunks.restype = ctypes.c_int
+    lib.rf_diag_attention_ws_chunks.argtypes = [P, P, P, ctypes.c_int]
     lib.rf_diag_splitk_route.restype = ctypes.c_int
     lib.rf_diag_splitk_route.argtypes = [P, P, P, ctypes.c_int]
     for f in (lib.rf_diag_rmsnorm_gemm_tile, lib.rf_diag_fp8_quant_gemm_tile, lib.rf_diag_fp8_quant_gemm_ws_tile):
@@ -223,6 +233,8 @@ def rf_safe_softmax(x, y=None, axis=-1, stream=None):
 
 
 def rf_cascade_attention(q, k, v, scale, causal=False, o=None, stream=None):
+    """Where rf_cascade_attention_ws is faster its workspace comes from torch's caching allocator, on the call's
+    stream, and goes back to it at return."""
     if o is None:
         o = torch.empty_like(q)
     _check((_call or _native()).cascade_attention(q, k, v, o, scale, causal, stream), "rf_cascade_attention")
@@ -324,6 +336,12 @@ def rf_diag_attention_route(q, k, v, causal=False):
     tensors of any device, ``meta`` among them."""
     dq, dk, dv = tensor_desc(q), tensor_desc(k), tensor_desc(v)
     return load_library().rf_diag_attention_route(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv), int(bool(causal)))
+
+
+def rf_diag_attention_ws_chunks(q, k, v, causal=False):
+    """Chunks of keys that rf_cascade_attention_ws cuts such a call into; 0 where it is rf_cascade_attention."""
+    dq, dk, dv = tensor_desc(q), tensor_desc(k), tensor_desc(v)
+    return load_library().rf_diag_attention_ws_chunks(ctypes.byref(dq), ctypes.byref(dk), ctypes.byref(dv), int(bool(causal)))
 
 
 def rf_diag_splitk_route(q, k, v, num_splits):

@@ -135,7 +135,7 @@ int rf_describe_cascade(const char* entry, rf_stage* out, int cap) {
   const rf_stage* src = nullptr;
   int n = 0;
   if (!strcmp(entry, "rf_safe_softmax")) { src = kSoftmax; n = 2; }
-  else if (!strcmp(entry, "rf_cascade_attention") || !strcmp(entry, "rf_cascade_attention_splitk") ||
+  else if (!strcmp(entry, "rf_cascade_attention") || !strcmp(entry, "rf_cascade_attention_ws") || !strcmp(entry, "rf_cascade_attention_splitk") ||
            !strcmp(entry, "rf_merge_states")) { src = kAttention; n = 3; }
   else if (!strcmp(entry, "rf_rmsnorm_gemm")) { src = kRms; n = 2; }
   else if (!strcmp(entry, "rf_variance")) { src = kRms; n = 2; }  // sum, then sum
@@ -327,23 +327,42 @@ rf_status rf_fp8_quant_gemm_ws(const rf_tensor* a, const rf_tensor* w, rf_tensor
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
 }
 
-rf_status rf_cascade_attention(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v,
-                               rf_tensor* o, float scale, int causal, rf_stream stream) {
-  rf::AttnShape a{};
+namespace {
+// Argument checks shared by the two attention entry points.
+rf_status check_attention(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, const rf_tensor* o, float scale,
+                          int causal, rf::AttnShape* a, bool* empty) {
   rf_status st;
-  if ((st = check_qkv(q, k, v, &a)) != RF_OK) return st;
+  *empty = false;
+  if ((st = check_qkv(q, k, v, a)) != RF_OK) return st;
   if ((st = check_tensor(o, 4, 4)) != RF_OK) return st;
   if (o->dtype != q->dtype) return RF_ERR_UNSUPPORTED;
   if (!same_shape(o, q)) return RF_ERR_INVALID_ARG;
   if (o->shape[3] > 1 && o->stride[3] != 1) return RF_ERR_UNSUPPORTED;
-  if (a.d != 64 && a.d != 128) return RF_ERR_UNSUPPORTED;
-  if (numel(q) == 0) return RF_OK;
+  if (a->d != 64 && a->d != 128) return RF_ERR_UNSUPPORTED;
+  if (numel(q) == 0) { *empty = true; return RF_OK; }
   if (q->data == nullptr || o->data == nullptr) return RF_ERR_INVALID_ARG;
-  if (a.Lk > 0 && (k->data == nullptr || v->data == nullptr)) return RF_ERR_INVALID_ARG;
-  if (!aligned16(q) || !aligned16(o) || (a.Lk > 0 && (!aligned16(k) || !aligned16(v))))
+  if (a->Lk > 0 && (k->data == nullptr || v->data == nullptr)) return RF_ERR_INVALID_ARG;
+  if (!aligned16(q) || !aligned16(o) || (a->Lk > 0 && (!aligned16(k) || !aligned16(v))))
     return RF_ERR_ALIGNMENT;
-  a.scale = scale;
-  a.causal = causal != 0;
+  a->scale = scale;
+  a->causal = causal != 0;
+  return RF_OK;
+}
+
+// Chunks of keys with a workspace, by the shapes and strides alone; 0 for refused arguments too.
+int attention_chunks(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal, rf::AttnShape* a) {
+  if (check_qkv(q, k, v, a) != RF_OK || (a->d != 64 && a->d != 128) || q->dtype != RF_BF16 || numel(q) == 0) return 0;
+  a->causal = causal != 0;
+  return rf::attention_bf16_chunks(*a, strides4(k), strides4(v));
+}
+}  // namespace
+
+rf_status rf_cascade_attention(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v,
+                               rf_tensor* o, float scale, int causal, rf_stream stream) {
+  rf::AttnShape a{};
+  bool empty;
+  const rf_status st = check_attention(q, k, v, o, scale, causal, &a, &empty);
+  if (st != RF_OK || empty) return st;
   hipError_t e;
   if (q->dtype == RF_F32)
     e = rf::launch_attention_f32((const float*)q->data, (const float*)k->data,
@@ -353,6 +372,34 @@ rf_status rf_cascade_attention(const rf_tensor* q, const rf_tensor* k, const rf_
     e = rf::launch_attention_bf16(q->data, k->data, v->data, o->data, strides4(q), strides4(k),
                                   strides4(v), strides4(o), a, (hipStream_t)stream);
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
+}
+
+size_t rf_cascade_attention_workspace_bytes(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal) {
+  rf::AttnShape a{};
+  const int n = attention_chunks(q, k, v, causal, &a);
+  return n == 0 ? 0 : rf::attention_bf16_split_bytes(a, n);
+}
+
+rf_status rf_cascade_attention_ws(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, rf_tensor* o,
+                                  float scale, int causal, void* workspace, size_t workspace_bytes,
+                                  rf_stream stream) {
+  rf::AttnShape a{};
+  bool empty;
+  const rf_status st = check_attention(q, k, v, o, scale, causal, &a, &empty);
+  if (st != RF_OK || empty) return st;
+  const int n = attention_chunks(q, k, v, causal, &a);
+  if (n == 0) return rf_cascade_attention(q, k, v, o, scale, causal, stream);
+  if (workspace == nullptr || reinterpret_cast<uintptr_t>(workspace) % 16 != 0 ||
+      workspace_bytes < rf::attention_bf16_split_bytes(a, n))
+    return RF_ERR_WORKSPACE;
+  hipError_t e = rf::launch_attention_bf16_split(q->data, k->data, v->data, o->data, strides4(q), strides4(k),
+                                                 strides4(v), strides4(o), a, n, workspace, (hipStream_t)stream);
+  return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
+}
+
+int rf_diag_attention_ws_chunks(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal) {
+  rf::AttnShape a{};
+  return attention_chunks(q, k, v, causal, &a);
 }
 
 int rf_diag_attention_route(const rf_tensor* q, const rf_tensor* k, const rf_tensor* v, int causal) {

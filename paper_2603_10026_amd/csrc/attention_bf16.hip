@@ -67,11 +67,14 @@ __device__ __forceinline__ void wait_vmem_all() {
 // KG = 2: two groups of NW / 2 wavefronts each, with K/V buffers of their own, take the key tiles in
 // turn for the same NW / 2 * 32 query rows; their states are merged through LDS at the end.  For
 // launches that leave compute units idle: twice the workgroups, half the key tiles in each.
-template <int D, int NW, bool PAIRED, int KG = 1>
+// SPLIT: a workgroup takes one of n_chunks runs of chunk_tiles key tiles and writes its state, [row][chunk] with the
+// maximum in log2 units, for attention_bf16_sum_kernel.
+template <int D, int NW, bool PAIRED, int KG = 1, bool SPLIT = false>
 __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     bf16_t* __restrict__ o, Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so, int Hq, int Hkv,
-    int Lq, int Lk, float scale_log2e, int causal, int n_qtiles) {
+    int Lq, int Lk, float scale_log2e, int causal, int n_qtiles, int n_chunks, int chunk_tiles,
+    float* __restrict__ part_m, float* __restrict__ part_l, float* __restrict__ part_acc) {
   constexpr bool paired = PAIRED;
   constexpr int KS = D / 16;                 // contraction steps of S^T = K Q^T
   constexpr int DT = D / 32;                 // 32-row tiles of O^T
@@ -82,6 +85,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   constexpr int kWaves = NW / KG;            // wavefronts that share a key tile
   constexpr int kBQ = 32 * kWaves;           // query rows per workgroup
   static_assert(KG == 1 || (KG == 2 && !PAIRED), "two key groups, one query tile");
+  static_assert(!SPLIT || KG == 2, "chunks of keys go with two key groups");
   constexpr int LD_PER_WAVE = kBK / ROWS_PER_LD / kWaves;
 
   // Two K/V slots.  Layout: the K slots, then the V slots; the K address registers point at the
@@ -113,11 +117,19 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   //    head-major order of the unmasked case applies.
   int qt, bh;
   const int n_units = paired ? n_qtiles / 2 : n_qtiles;  // workgroups per head
-  const int n_bh = gridDim.x / n_units;
+  unsigned grid = gridDim.x, block = blockIdx.x;
+  int chunk = 0;
+  if constexpr (SPLIT) {
+    grid /= n_chunks;
+    chunk = __builtin_amdgcn_readfirstlane(block / grid);
+    block -= chunk * grid;
+  }
+  const int first_tile = SPLIT ? chunk * chunk_tiles : 0;
+  const int n_bh = grid / n_units;
   if ((n_bh & 7) == 0) {
     const int hx = n_bh >> 3;            // heads per XCD
-    const int xcd = blockIdx.x & 7;
-    const int j = blockIdx.x >> 3;       // arrival order inside the XCD
+    const int xcd = block & 7;
+    const int j = block >> 3;       // arrival order inside the XCD
     if (causal && !paired) {
       qt = n_qtiles - 1 - j / hx;
       bh = xcd * hx + j % hx;
@@ -126,8 +138,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
       bh = xcd * hx + j / n_units;
     }
   } else {
-    qt = n_units - 1 - (int)(blockIdx.x / n_bh);
-    bh = blockIdx.x % n_bh;
+    qt = n_units - 1 - (int)(block / n_bh);
+    bh = block % n_bh;
   }
   // (integer division runs on the vector unit even for wave-uniform operands: hand the results
   // back to the scalar unit here, once, so that everything derived from them, the K/V base
@@ -166,7 +178,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
       (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds + (KG == 1 ? 0 : kg * (2 * NS * TILEB));
   // LDS address of this wavefront's first load in K slot 0, on the scalar unit
   const uint32_t dma_base = __builtin_amdgcn_readfirstlane(lds_base + wave * LD_PER_WAVE * 1024);
-  auto issue_one = [&](int key0, int buf, int e, int is_v) {
+  auto issue_one = [&](int key0, int buf, int e, int is_v) __attribute__((always_inline)) {
     const uint32_t dst_addr = dma_base + is_v * NS * TILEB + buf * TILEB + e * 1024;
     const bf16_t* base = is_v ? vb : kb;
     const int64_t ld = is_v ? sv.l : sk.l;
@@ -195,7 +207,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
                    : "memory", "m0");
     }
   };
-  auto issue_loads = [&](int key0, int buf) {
+  auto issue_loads = [&](int key0, int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < LD_PER_WAVE; ++e) {
       issue_one(key0, buf, e, 0);
@@ -208,7 +220,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   {
     const int last_row0 = min(Lq - 1, qt * kBQ + kBQ - 1);
     const int wg_last0 = causal ? min(Lk - 1, last_row0 + (Lk - Lq)) : Lk - 1;
-    if (wg_last0 >= kg * kBK) issue_loads(kg * kBK, 0);
+    if (wg_last0 >= (first_tile + kg) * kBK && (!SPLIT || kg < chunk_tiles)) issue_loads((first_tile + kg) * kBK, 0);
   }
 
   // ---- LDS read offsets (loop invariant) ----
@@ -272,7 +284,8 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   const int wave_min_last = causal ? min(Lk - 1, q0 + wave * 32 + shift) : Lk - 1;
   const int wave_last = causal ? min(Lk - 1, min(Lq - 1, q0 + wave * 32 + 31) + shift) : Lk - 1;
   const int wg_last = causal ? min(Lk - 1, min(Lq - 1, q0 + kBQ - 1) + shift) : Lk - 1;
-  const int n_ktiles = wg_last >= 0 ? wg_last / kBK + 1 : 0;
+  const int all_ktiles = wg_last >= 0 ? wg_last / kBK + 1 : 0;
+  const int n_ktiles = SPLIT ? min(all_ktiles, first_tile + chunk_tiles) : all_ktiles;
 
   float m_ref = -INFINITY, l = 0.f;
   f32x16 acc[DT];
@@ -300,14 +313,14 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
 
   // One key tile.  BUF is a compile-time constant so that every LDS access of the tile is a
   // register plus an immediate offset.
-  auto tile_step = [&](int kt, auto buf_tag) {
+  auto tile_step = [&](int kt, auto buf_tag) __attribute__((always_inline)) {
     constexpr int BUF = decltype(buf_tag)::value;
     constexpr int FILL = BUF ^ 1;   // slot of the tile requested during this one
     const int key0 = kt * kBK;
     wait_vmem_all();   // this wavefront's share of tile kt has landed
     __syncthreads();   // everyone's share has landed; everyone is done reading the other slot
     const bool more = kt + KG < n_ktiles;
-    if (key0 > wave_last) {  // nothing visible for this wavefront (uniform): only fetch its share
+    if (key0 > wave_last || (SPLIT && kt >= n_ktiles)) {  // nothing visible for this wavefront (uniform): only fetch its share
       if (more) issue_loads(key0 + KG * kBK, FILL);
       return;
     }
@@ -329,7 +342,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
     constexpr int kPerIssue = kLoads < KS ? 1 : kLoads / KS;    // or loads per step
     static_assert(kLoads * kIssueEvery == KS * kPerIssue, "loads spread evenly over the contraction steps");
     static_assert(2 * (KS - 1) <= 15, "the wait counts below fit the LDS counter");
-    auto st_step = [&](auto kk_tag) {
+    auto st_step = [&](auto kk_tag) __attribute__((always_inline)) {
       constexpr int kk = decltype(kk_tag)::value;
       // the two fragments of this step are back once at most the younger ones are in flight
       u32x4& k0 = kq[kk][0];
@@ -470,7 +483,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
 
   if (pass && n_ktiles > 0) issue_loads(0, 0);   // (first pass: requested during the set-up)
   // (every key group takes as many turns, for the barriers in them: a tile past the end is skipped)
-  for (int kt = 0; kt < n_ktiles; kt += 2 * KG) {
+  for (int kt = first_tile; kt < n_ktiles; kt += 2 * KG) {
     tile_step(kt + kg, std::integral_constant<int, 0>{});
     if (kt + KG < n_ktiles) tile_step(kt + KG + kg, std::integral_constant<int, 1>{});
   }
@@ -507,6 +520,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
     const float m_use = (m == -INFINITY) ? 0.f : m;
     const float w0 = fast_exp2(m_ref - m_use), w1 = fast_exp2(m1 - m_use);  // 0 for an empty state
     l = l * w0 + s_ml[wave][1][lane] * w1;
+    m_ref = m;
 #pragma unroll
     for (int t = 0; t < DT; ++t)
 #pragma unroll
@@ -515,6 +529,31 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
 #pragma unroll
         for (int j = 0; j < 4; ++j) acc[t][4 * r4 + j] = acc[t][4 * r4 + j] * w0 + o1[j] * w1;
       }
+  }
+  if constexpr (SPLIT) {
+    // the state of this chunk, whole rows through this wavefront's part of the first group's K/V buffers
+    constexpr int kPitch = D + 4, kQuads = D / 4;
+    static_assert(kWaves * 32 * kPitch * 4 <= 2 * NS * TILEB, "the rows fit the K/V buffers");
+    float* rows = reinterpret_cast<float*>(lds) + wave * (32 * kPitch);
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        *reinterpret_cast<f32x4*>(rows + i32 * kPitch + 32 * t + 8 * r4 + 4 * hh) =
+            f32x4{acc[t][4 * r4], acc[t][4 * r4 + 1], acc[t][4 * r4 + 2], acc[t][4 * r4 + 3]};
+    const int64_t row0 = ((int64_t)b * Hq + h) * Lq + q0 + wave * 32;
+    if (hh == 0 && my_q < Lq) {
+      part_m[(row0 + i32) * n_chunks + chunk] = m_ref;
+      part_l[(row0 + i32) * n_chunks + chunk] = l;
+    }
+#pragma unroll
+    for (int i = 0; i < 32 * kQuads / kWave; ++i) {
+      const int row = i * (kWave / kQuads) + lane / kQuads, quad = lane % kQuads;
+      const f32x4 w = *reinterpret_cast<const f32x4*>(rows + row * kPitch + 4 * quad);
+      if (q0 + wave * 32 + row < Lq)
+        *reinterpret_cast<f32x4*>(part_acc + ((row0 + row) * n_chunks + chunk) * D + 4 * quad) = w;
+    }
+    return;
   }
   const float inv = l > 0.f ? 1.0f / l : 0.f;
   if constexpr (KG == 1) __syncthreads();
@@ -551,7 +590,57 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
   }  // pass
 }
 
-AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
+// O of the rows whose chunks' states the split kernel wrote: D / 4 lanes a row, a few chunks requested at a time.
+constexpr int kSumThreads = 256;
+template <int D>
+__global__ __launch_bounds__(kSumThreads) void attention_bf16_sum_kernel(
+    const float* __restrict__ part_m, const float* __restrict__ part_l, const float* __restrict__ part_acc,
+    bf16_t* __restrict__ o, Strides4 so, int Hq, int Lq, int rows, int n_chunks) {
+  constexpr int kQuads = D / 4, U = 8;
+  const int row = blockIdx.x * (kSumThreads / kQuads) + threadIdx.x / kQuads, quad = threadIdx.x % kQuads;
+  if (row >= rows) return;
+  const float* pm = part_m + (int64_t)row * n_chunks;
+  const float* pl = part_l + (int64_t)row * n_chunks;
+  const float* pa = part_acc + (int64_t)row * n_chunks * D + 4 * quad;
+  float m = -INFINITY, l = 0.f;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  for (int c0 = 0; c0 < n_chunks; c0 += U) {
+    float mc[U], lc[U];
+    f32x4 ac[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = min(c0 + u, n_chunks - 1);
+      mc[u] = pm[c];
+      lc[u] = pl[c];
+      ac[u] = *reinterpret_cast<const f32x4*>(pa + (int64_t)c * D);
+    }
+    float m_new = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      mc[u] = c0 + u < n_chunks ? mc[u] : -INFINITY;
+      m_new = fmaxf(m_new, mc[u]);
+    }
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float corr = fast_exp2(m - m_use);
+    l *= corr;
+    sum *= corr;
+    m = m_new;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float w = fast_exp2(mc[u] - m_use);  // 0 for an empty state
+      l += lc[u] * w;
+      sum += ac[u] * w;
+    }
+  }
+  const float inv = l > 0.f ? 1.0f / l : 0.f;
+  const int i = row % Lq, bh = row / Lq;
+  u32x2 w;
+  w[0] = pack_bf16(sum[0] * inv, sum[1] * inv);
+  w[1] = pack_bf16(sum[2] * inv, sum[3] * inv);
+  *reinterpret_cast<u32x2*>(o + (int64_t)(bh / Hq) * so.b + (int64_t)(bh % Hq) * so.h + (int64_t)i * so.l + 4 * quad) = w;
+}
+
+static AttnRoute route_of(const AttnShape& a, const Strides4& sk, const Strides4& sv, double* us) {
   // Without a mask the larger workgroup wins (fewer loads per MFMA).  Under a causal mask the
   // query tiles of a head see different numbers of keys; a launch with enough heads gives
   // every workgroup two tiles of one head, the heaviest with the lightest and so on inwards,
@@ -594,9 +683,59 @@ AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Str
   const double us_tiled = us_of((nw == 8 ? kTiled8 : kTiled4)[d128], 32 * nw, 64);
   const double us_groups = us_of(kGroups[d128], 64, 128);
   const double us_few = attention_fewrows_us(a, sk, sv);
-  if (a.Lk > 0 && fmin(us_few, us_groups) < 0.9 * us_tiled)  // (0.9: the fit's error; without keys there is nothing to split)
+  *us = us_tiled;
+  if (a.Lk > 0 && fmin(us_few, us_groups) < 0.9 * us_tiled) {  // (0.9: the fit's error; without keys there is nothing to split)
+    *us = fmin(us_few, us_groups);
     return us_few <= us_groups ? AttnRoute::kFewRows : AttnRoute::kKeyGroups;
+  }
   return nw == 8 ? (paired ? AttnRoute::kPaired8 : AttnRoute::kTiled8) : paired ? AttnRoute::kPaired4 : AttnRoute::kTiled4;
+}
+
+AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
+  double us;
+  return route_of(a, sk, sv, &us);
+}
+
+// Chunks of keys that a call with a workspace is cut into (64 rows and two key groups per workgroup, the states
+// added up by a second launch); 0 where one launch serves it better.  Few rows before a long context leave most
+// compute units idle, or have each of them walk all keys behind the latency of memory: us one launch / split, 2 x 8 heads
+// of 242 x 7136, d = 64, 43.0 / 21.1; 8 heads of 1 x 8192, d = 128, 73.5 / 13.3; 2 x 4 of 1506 x 7356, causal, d = 64,
+// 69.5 / 47.1; 3 x 2 of 3111 x 4823, causal, d = 128, 102.0 / 85.9; but 3 x 8 of 109 x 1115, causal, d = 128,
+// 14.9 / 16.0; 2 x 8 of 1097 x 2467, causal, d = 64, 28.5 / 29.3.  The figures are fitted to 422 cuts of 100 random
+// calls (4 % off on average, 19 % at most); of those, 39 are split by this rule, and are 2.0 times faster for it, the
+// least 1.2.  (3.5: what a second launch adds to a call that is waited for.)
+int attention_bf16_chunks(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
+  // (no shorter context had anything to gain, and small calls should not wait for the arithmetic below)
+  if (a.Lk < 1024) return 0;
+  struct Cost { double launch, chain, workgroup, step, mb; };
+  constexpr Cost kCost[] = {{6.24, 1.09, 0.60, 0.66, 0.325}, {5.60, 1.87, 1.95, 1.72, 0.285}};  // d = 64, d = 128
+  const Cost& c = kCost[a.d == 128];
+  double one;
+  route_of(a, sk, sv, &one);
+  const double most = 0.9 * one - 3.5;
+  const double rows = (double)a.B * a.Hq * a.Lq, tiles64 = ceil(a.Lq / 64.0) * a.B * a.Hq;
+  if (c.launch > most || rows > INT32_MAX / 64) return 0;
+  const int n_ktiles = (a.Lk + kBK - 1) / kBK;
+  const double seen = tile_keys(a, 64) / a.Lk;  // of a chunk's keys, on average
+  int best = 0;
+  double best_us = most;
+  for (int n = 2; n <= 32 && n <= n_ktiles; ++n) {
+    const int chunk = (n_ktiles + n - 1) / n;
+    if ((n_ktiles + chunk - 1) / chunk != n) continue;  // (fewer chunks of this size cover the keys)
+    const double bytes = rows * n * (a.d + 2) * 4, wgs = tiles64 * n, steps = chunk / 2.0;
+    if (bytes > (double)kAttnWorkspaceMax || wgs > INT32_MAX / 256) break;
+    const double us = c.launch + fmax(c.chain * (steps + 0.5), ceil(wgs / 256) * (c.workgroup + c.step * (steps * seen + 0.5))) +
+                      c.mb * 2e-6 * bytes;
+    if (us < best_us) {
+      best_us = us;
+      best = n;
+    }
+  }
+  return best;
+}
+
+size_t attention_bf16_split_bytes(const AttnShape& a, int n_chunks) {
+  return (size_t)a.B * a.Hq * a.Lq * n_chunks * (a.d + 2) * 4;
 }
 
 hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, void* o, Strides4 sq,
@@ -617,7 +756,7 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
 #define RF_LAUNCH_ATTN_LDS(LDSB, DD, NWW, ...)                                                    \
   hipLaunchKernelGGL((attention_bf16_kernel<DD, NWW, __VA_ARGS__>), dim3((unsigned)grid), dim3(NWW * kWave), LDSB, s, \
                      (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, sq, sk, sv, so, \
-                     a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal, n_qtiles)
+                     a.Hq, a.Hkv, a.Lq, a.Lk, sl2, a.causal, n_qtiles, 1, 0, nullptr, nullptr, nullptr)
   if (a.d == 128) {
     if (split_keys) RF_LAUNCH_ATTN_LDS(131072, 128, 4, false, 2);
     else if (paired && nw == 8) RF_LAUNCH_ATTN(128, 8, true);
@@ -635,6 +774,34 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
   }
 #undef RF_LAUNCH_ATTN
 #undef RF_LAUNCH_ATTN_LDS
+  return hipGetLastError();
+}
+
+hipError_t launch_attention_bf16_split(const void* q, const void* k, const void* v, void* o, Strides4 sq,
+                                       Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, int n_chunks,
+                                       void* workspace, hipStream_t s) {
+  const int n_qtiles = (a.Lq + 63) / 64, n_ktiles = (a.Lk + kBK - 1) / kBK;
+  const int64_t rows = (int64_t)a.B * a.Hq * a.Lq, grid = (int64_t)n_qtiles * a.B * a.Hq * n_chunks;
+  if (grid > INT32_MAX / 256 || rows > INT32_MAX / 64) return hipErrorInvalidValue;
+  const int chunk_tiles = (n_ktiles + n_chunks - 1) / n_chunks;
+  float* part_acc = (float*)workspace;
+  float* part_m = part_acc + rows * n_chunks * a.d;
+  float* part_l = part_m + rows * n_chunks;
+  const float sl2 = a.scale * kLog2e;
+#define RF_SPLIT(DD)                                                                                                 \
+  hipLaunchKernelGGL((attention_bf16_kernel<DD, 4, false, 2, true>), dim3((unsigned)grid), dim3(4 * kWave), 1024 * DD, s, \
+                     (const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)v, (bf16_t*)o, sq, sk, sv, so, a.Hq, a.Hkv, a.Lq, \
+                     a.Lk, sl2, a.causal, n_qtiles, n_chunks, chunk_tiles, part_m, part_l, part_acc);                \
+  hipLaunchKernelGGL((attention_bf16_sum_kernel<DD>), dim3((unsigned)((rows + 1024 / DD - 1) / (1024 / DD))),        \
+                     dim3(kSumThreads), 0, s, part_m, part_l, part_acc, (bf16_t*)o, so, a.Hq, a.Lq, (int)rows, n_chunks)
+  if (a.d == 128) {
+    RF_SPLIT(128);
+  } else if (a.d == 64) {
+    RF_SPLIT(64);
+  } else {
+    return hipErrorInvalidValue;
+  }
+#undef RF_SPLIT
   return hipGetLastError();
 }
 

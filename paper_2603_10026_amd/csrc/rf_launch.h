@@ -61,6 +61,14 @@ AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Str
 hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, void* o,
                                  Strides4 sq, Strides4 sk, Strides4 sv, Strides4 so,
                                  const AttnShape& a, hipStream_t s);
+// The same with a workspace of attention_bf16_split_bytes bytes, 16-byte aligned, for the states of n_chunks chunks
+// of keys; attention_bf16_chunks: how many, 0 for none.
+constexpr int64_t kAttnWorkspaceMax = (int64_t)128 << 20;
+int attention_bf16_chunks(const AttnShape& a, const Strides4& sk, const Strides4& sv);
+size_t attention_bf16_split_bytes(const AttnShape& a, int n_chunks);
+hipError_t launch_attention_bf16_split(const void* q, const void* k, const void* v, void* o, Strides4 sq,
+                                       Strides4 sk, Strides4 sv, Strides4 so, const AttnShape& a, int n_chunks,
+                                       void* workspace, hipStream_t s);
 // The same for few query rows; the launchers of the tiled and of the split kernel choose them.
 // (infinity for what that kernel does not take)
 double attention_fewrows_us(const AttnShape& a, const Strides4& sk, const Strides4& sv);

@@ -198,9 +198,14 @@ PyObject* py_cascade_attention(PyObject*, PyObject* const* args, Py_ssize_t n) {
   rf_tensor d[4];
   float scale;
   rf_stream s;
-  if (!count(n, 7) || !describe_all<4>(args, n, d, {0, 1, 2, 3}, &s) || !to_float(args[4], &scale)) return nullptr;
+  int device;
+  if (!count(n, 7) || !describe_all<4>(args, n, d, {0, 1, 2, 3}, &s, &device) || !to_float(args[4], &scale)) return nullptr;
   const int causal = PyObject_IsTrue(args[5]);
   if (causal < 0) return nullptr;
+  const size_t bytes = rf_cascade_attention_workspace_bytes(&d[0], &d[1], &d[2], causal);
+  const Scratch scratch(bytes, device, s);
+  if (scratch.data() != nullptr)
+    return call([&] { return rf_cascade_attention_ws(&d[0], &d[1], &d[2], &d[3], scale, causal, scratch.data(), bytes, s); });
   return call([&] { return rf_cascade_attention(&d[0], &d[1], &d[2], &d[3], scale, causal, s); });
   END_HANDLE_TH_ERRORS
 }

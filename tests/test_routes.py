@@ -1,5 +1,6 @@
 """Which kernel a call takes, by the library's own rules (no GPU needed): the calls that a rule must leave to the
 general kernel because it serves them faster."""
+import ctypes
 import sys
 
 import pytest
@@ -41,6 +42,26 @@ def test_attention_calls_that_stay_with_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d,
 ])
 def test_attention_calls_that_leave_the_tiled_kernel(Bt, Hq, Hkv, Lq, Lk, d, causal, route):
     assert attention_route(Bt, Hq, Hkv, Lq, Lk, d, causal) == route
+
+
+def test_attention_with_a_workspace():
+    from test_gpu_attention_split import SPLIT_ATTENTION, _chunks
+    for case in SPLIT_ATTENTION:
+        assert 2 <= _chunks(case) <= 32, case
+    # (us one launch / split: 14.9 / 16.0, 28.5 / 29.3, 5.5 / 7.9, 22.7 / 50.7, 9.1 / 12.9); the benchmark's prefills; no keys
+    for case in [(3, 8, 8, 109, 1115, 128, True), (2, 8, 8, 1097, 2467, 64, True), (3, 2, 1, 8, 276, 64, False),
+                 (4, 32, 16, 200, 639, 128, False), (1, 32, 8, 76, 490, 128, False), (4, 32, 32, 2048, 2048, 128, False),
+                 (4, 32, 32, 2048, 2048, 128, True), (2, 32, 8, 1000, 3001, 128, True), (1, 4, 4, 3, 0, 128, False),
+                 (1, 4, 3, 3, 8192, 128, False), (1, 4, 4, 3, 8192, 96, False), (0, 4, 4, 3, 8192, 128, False)]:
+        assert _chunks(case) == 0, case
+    assert _chunks((1, 4, 4, 3, 8192, 128, False), torch.float32) == 0
+    # the states stay below 128 MB
+    for case in [(8, 64, 8, 3000, 8192, 64, True), (1, 1, 1, 100000, 8192, 64, False), (64, 64, 64, 64, 100000, 128, False)]:
+        q = torch.empty((case[0], case[1], case[3], case[5]), dtype=torch.bfloat16, device="meta")
+        k = torch.empty((case[0], case[2], case[4], case[5]), dtype=torch.bfloat16, device="meta")
+        dq, dk = B.tensor_desc(q), B.tensor_desc(k)
+        r = ctypes.byref
+        assert B.load_library().rf_cascade_attention_workspace_bytes(r(dq), r(dk), r(dk), int(case[6])) <= 128 << 20
 
 
 F32_FEW_ROWS, F32_TWO_TILES, F32_WAVES16, F32_WAVES8, F32_WAVES4 = 11, 12, 13, 14, 15
