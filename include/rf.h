@@ -267,6 +267,21 @@ RF_API rf_status rf_merge_states(const rf_tensor* part_m, const rf_tensor* part_
 RF_API rf_status rf_rmsnorm_gemm(const rf_tensor* x, const rf_tensor* g, const rf_tensor* w,
                           rf_tensor* y, float eps, rf_stream stream);
 
+/*
+ * rf_rmsnorm_gemm with device memory for x g: the norm and the product in a launch each, with the
+ * same roundings.
+ *   workspace : device memory, 16-byte aligned, at least
+ *       rf_rmsnorm_gemm_workspace_bytes(M, K, N) bytes; contents need no initialisation and are
+ *       undefined afterwards.  Too small or misaligned: RF_ERR_WORKSPACE.  Concurrent calls must
+ *       not share a workspace.
+ * The size is 0 where a single launch serves the problem faster (the call is then
+ * rf_rmsnorm_gemm), and at most 128 MiB + 64 KiB: more rows go through it in turns.
+ */
+RF_API size_t rf_rmsnorm_gemm_workspace_bytes(int64_t M, int64_t K, int64_t N);
+RF_API rf_status rf_rmsnorm_gemm_ws(const rf_tensor* x, const rf_tensor* g, const rf_tensor* w,
+                          rf_tensor* y, float eps, void* workspace, size_t workspace_bytes,
+                          rf_stream stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -71,7 +71,9 @@ RF_API int rf_diag_splitk_route(const rf_tensor* q, const rf_tensor* k, const rf
  */
 RF_API int rf_diag_rmsnorm_gemm_tile(int64_t M, int64_t K, int64_t N);
 RF_API int rf_diag_fp8_quant_gemm_tile(int64_t M, int64_t K, int64_t N);
-/* The tile of the contraction that rf_fp8_quant_gemm_ws runs on the quantised tokens; 0 where it is rf_fp8_quant_gemm. */
+/* The tile of the product that the entry points with a workspace run in a launch of its own; 0 where they are the
+ * ones without. */
+RF_API int rf_diag_rmsnorm_gemm_ws_tile(int64_t M, int64_t K, int64_t N);
 RF_API int rf_diag_fp8_quant_gemm_ws_tile(int64_t M, int64_t K, int64_t N);
 
 /*

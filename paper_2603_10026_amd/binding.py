@@ -33,6 +33,8 @@ ENTRY_POINTS = (
     "rf_cascade_attention_splitk",
     "rf_merge_states",
     "rf_rmsnorm_gemm",
+    "rf_rmsnorm_gemm_workspace_bytes",
+    "rf_rmsnorm_gemm_ws",
     "rf_variance",
     "rf_moe_routing_workspace_bytes",
     "rf_moe_routing",
@@ -49,6 +51,7 @@ DIAG_ENTRY_POINTS = (
     "rf_diag_splitk_route",
     "rf_diag_rmsnorm_gemm_tile",
     "rf_diag_fp8_quant_gemm_tile",
+    "rf_diag_rmsnorm_gemm_ws_tile",
     "rf_diag_fp8_quant_gemm_ws_tile",
     "rf_diag_attention_wide",
     "rf_diag_copy",
@@ -111,6 +114,10 @@ def load_library():
     lib.rf_merge_states.argtypes = [P, P, P, P, ctypes.c_void_p]
     lib.rf_rmsnorm_gemm.restype = ctypes.c_int
     lib.rf_rmsnorm_gemm.argtypes = [P, P, P, P, ctypes.c_float, ctypes.c_void_p]
+    lib.rf_rmsnorm_gemm_workspace_bytes.restype = ctypes.c_size_t
+    lib.rf_rmsnorm_gemm_workspace_bytes.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
+    lib.rf_rmsnorm_gemm_ws.restype = ctypes.c_int
+    lib.rf_rmsnorm_gemm_ws.argtypes = [P, P, P, P, ctypes.c_float, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p]
     lib.rf_variance.restype = ctypes.c_int
     lib.rf_variance.argtypes = [P, P, P, ctypes.c_void_p]
     lib.rf_moe_routing_workspace_bytes.restype = ctypes.c_size_t
@@ -135,7 +142,8 @@ def load_library():
     lib.rf_diag_attention_ws_chunks.argtypes = [P, P, P, ctypes.c_int]
     lib.rf_diag_splitk_route.restype = ctypes.c_int
     lib.rf_diag_splitk_route.argtypes = [P, P, P, ctypes.c_int]
-    for f in (lib.rf_diag_rmsnorm_gemm_tile, lib.rf_diag_fp8_quant_gemm_tile, lib.rf_diag_fp8_quant_gemm_ws_tile):
+    for f in (lib.rf_diag_rmsnorm_gemm_tile, lib.rf_diag_fp8_quant_gemm_tile, lib.rf_diag_rmsnorm_gemm_ws_tile,
+              lib.rf_diag_fp8_quant_gemm_ws_tile):
         f.restype = ctypes.c_int
         f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
     lib.rf_diag_copy.restype = ctypes.c_int
@@ -263,6 +271,8 @@ def rf_merge_states(part_m, part_l, part_acc, o, stream=None):
 
 
 def rf_rmsnorm_gemm(x, g, w, eps=1e-6, y=None, stream=None):
+    """Where rf_rmsnorm_gemm_ws is faster its workspace comes from torch's caching allocator, on the call's
+    stream, and goes back to it at return."""
     if y is None:
         y = torch.empty((x.shape[0], w.shape[1]), dtype=x.dtype, device=x.device)
     _check((_call or _native()).rmsnorm_gemm(x, g, w, y, eps, stream), "rf_rmsnorm_gemm")
@@ -358,6 +368,11 @@ def rf_diag_rmsnorm_gemm_tile(M, K, N):
 def rf_diag_fp8_quant_gemm_tile(M, K, N):
     """(tokens, channels) of the output tile that rf_fp8_quant_gemm takes for these sizes."""
     return divmod(load_library().rf_diag_fp8_quant_gemm_tile(M, K, N), 1000)
+
+
+def rf_diag_rmsnorm_gemm_ws_tile(M, K, N):
+    """(rows, columns) of the tile that rf_rmsnorm_gemm_ws takes; (0, 0) where it is rf_rmsnorm_gemm."""
+    return divmod(load_library().rf_diag_rmsnorm_gemm_ws_tile(M, K, N), 1000)
 
 
 def rf_diag_fp8_quant_gemm_ws_tile(M, K, N):

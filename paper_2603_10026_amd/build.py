@@ -33,6 +33,7 @@ SOURCES = [
     "merge_states.hip",
     "rmsnorm_gemm.hip",
     "rmsnorm_gemm_rows.hip",
+    "rmsnorm_gemm_two_pass.hip",
     "diag.hip",
 ]
 

@@ -137,7 +137,7 @@ int rf_describe_cascade(const char* entry, rf_stage* out, int cap) {
   if (!strcmp(entry, "rf_safe_softmax")) { src = kSoftmax; n = 2; }
   else if (!strcmp(entry, "rf_cascade_attention") || !strcmp(entry, "rf_cascade_attention_ws") || !strcmp(entry, "rf_cascade_attention_splitk") ||
            !strcmp(entry, "rf_merge_states")) { src = kAttention; n = 3; }
-  else if (!strcmp(entry, "rf_rmsnorm_gemm")) { src = kRms; n = 2; }
+  else if (!strcmp(entry, "rf_rmsnorm_gemm") || !strcmp(entry, "rf_rmsnorm_gemm_ws")) { src = kRms; n = 2; }
   else if (!strcmp(entry, "rf_variance")) { src = kRms; n = 2; }  // sum, then sum
   else if (!strcmp(entry, "rf_moe_routing")) { src = kRouting; n = 3; }
   else if (!strcmp(entry, "rf_fp8_quant_gemm") || !strcmp(entry, "rf_fp8_quant_gemm_ws")) { src = kQuant; n = 2; }
@@ -530,9 +530,11 @@ rf_status rf_merge_states(const rf_tensor* part_m, const rf_tensor* part_l,
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
 }
 
-rf_status rf_rmsnorm_gemm(const rf_tensor* x, const rf_tensor* g, const rf_tensor* w, rf_tensor* y,
-                          float eps, rf_stream stream) {
+namespace {
+// Argument checks shared by the two RMSNorm entry points.
+rf_status check_rmsnorm_gemm(const rf_tensor* x, const rf_tensor* g, const rf_tensor* w, const rf_tensor* y, bool* empty) {
   rf_status st;
+  *empty = false;
   if ((st = check_tensor(x, 2, 2)) != RF_OK) return st;
   if ((st = check_tensor(g, 1, 1)) != RF_OK) return st;
   if ((st = check_tensor(w, 2, 2)) != RF_OK) return st;
@@ -546,17 +548,52 @@ rf_status rf_rmsnorm_gemm(const rf_tensor* x, const rf_tensor* g, const rf_tenso
       (K > 1 && g->stride[0] != 1))
     return RF_ERR_UNSUPPORTED;
   if (M > INT32_MAX || K > INT32_MAX || N > INT32_MAX) return RF_ERR_UNSUPPORTED;
-  if (M == 0 || N == 0) return RF_OK;
+  if (M == 0 || N == 0) { *empty = true; return RF_OK; }
   if (K == 0 || K % 64 != 0 || N % 8 != 0) return RF_ERR_UNSUPPORTED;
   if (x->data == nullptr || g->data == nullptr || w->data == nullptr || y->data == nullptr)
     return RF_ERR_INVALID_ARG;
   if (!aligned16(x) || !aligned16(g) || !aligned16(w) || !aligned16(y)) return RF_ERR_ALIGNMENT;
-  // the kernel addresses a 128-row tile of x and a 64-row tile of w with 32-bit byte offsets
+  // the kernels address a 128-row tile of x and a 64-row tile of w with 32-bit byte offsets
   if (x->stride[0] >= (1 << 24) || w->stride[0] >= (1 << 24)) return RF_ERR_UNSUPPORTED;
-  hipError_t e = rf::launch_rmsnorm_gemm_bf16(x->data, g->data, w->data, y->data, (int)M, (int)K,
-                                              (int)N, x->stride[0], w->stride[0], y->stride[0], eps,
+  return RF_OK;
+}
+}  // namespace
+
+rf_status rf_rmsnorm_gemm(const rf_tensor* x, const rf_tensor* g, const rf_tensor* w, rf_tensor* y,
+                          float eps, rf_stream stream) {
+  bool empty;
+  const rf_status st = check_rmsnorm_gemm(x, g, w, y, &empty);
+  if (st != RF_OK || empty) return st;
+  hipError_t e = rf::launch_rmsnorm_gemm_bf16(x->data, g->data, w->data, y->data, (int)x->shape[0], (int)x->shape[1],
+                                              (int)w->shape[1], x->stride[0], w->stride[0], y->stride[0], eps,
                                               (hipStream_t)stream);
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
+}
+
+size_t rf_rmsnorm_gemm_workspace_bytes(int64_t M, int64_t K, int64_t N) {
+  if (M < 1 || K < 1 || N < 1 || M > INT32_MAX || K > INT32_MAX || N > INT32_MAX || K % 64 != 0 || N % 8 != 0) return 0;
+  if (!rf::rmsnorm_gemm_two_pass_wins((int)M, (int)K, (int)N, rf::rmsnorm_gemm_us((int)M, (int)K, (int)N))) return 0;
+  return rf::rmsnorm_gemm_two_pass_bytes((int)M, (int)K);
+}
+
+rf_status rf_rmsnorm_gemm_ws(const rf_tensor* x, const rf_tensor* g, const rf_tensor* w, rf_tensor* y, float eps,
+                             void* workspace, size_t workspace_bytes, rf_stream stream) {
+  bool empty;
+  const rf_status st = check_rmsnorm_gemm(x, g, w, y, &empty);
+  if (st != RF_OK || empty) return st;
+  const int64_t M = x->shape[0], K = x->shape[1], N = w->shape[1];
+  const size_t need = rf_rmsnorm_gemm_workspace_bytes(M, K, N);
+  if (need == 0) return rf_rmsnorm_gemm(x, g, w, y, eps, stream);
+  if (workspace == nullptr || reinterpret_cast<uintptr_t>(workspace) % 16 != 0 || workspace_bytes < need)
+    return RF_ERR_WORKSPACE;
+  hipError_t e = rf::launch_rmsnorm_gemm_two_pass(x->data, g->data, w->data, y->data, (int)M, (int)K, (int)N, x->stride[0],
+                                                  w->stride[0], y->stride[0], eps, workspace, (hipStream_t)stream);
+  return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
+}
+
+int rf_diag_rmsnorm_gemm_ws_tile(int64_t M, int64_t K, int64_t N) {
+  if (rf_rmsnorm_gemm_workspace_bytes(M, K, N) == 0) return 0;
+  return rf::rmsnorm_gemm_two_pass_tile((int)M, (int)K, (int)N);
 }
 
 rf_status rf_diag_softmax_level(const rf_tensor* x, rf_tensor* y, int level, float* ml_buf,

@@ -107,6 +107,18 @@ hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
                                     hipStream_t s);
 
+double rmsnorm_gemm_us(int M, int K, int N);  // expected us of one of the launches above
+
+// The same with a workspace of rmsnorm_gemm_two_pass_bytes(M, K) bytes, 16-byte aligned, for x g: the norm and
+// the contraction in a launch each.  16-byte aligned rows of y.
+constexpr int64_t kNormWorkspaceMax = (int64_t)128 << 20;
+bool rmsnorm_gemm_two_pass_wins(int M, int K, int N, double single_us);
+size_t rmsnorm_gemm_two_pass_bytes(int M, int K);
+int rmsnorm_gemm_two_pass_tile(int M, int K, int N);  // 1000 rows + columns of the tile it takes
+hipError_t launch_rmsnorm_gemm_two_pass(const void* x, const void* g, const void* w, void* y, int M, int K, int N,
+                                        int64_t ldx, int64_t ldw, int64_t ldy, float eps, void* workspace,
+                                        hipStream_t s);
+
 // Rows of length n (pitch in elements); mean, var: one float per row.
 hipError_t launch_variance(const void* x, bool is_bf16, float* mean, float* var, int64_t rows,
                            int64_t n, int64_t x_pitch, hipStream_t s);

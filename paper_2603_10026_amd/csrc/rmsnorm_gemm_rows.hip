@@ -416,11 +416,19 @@ bool streams_w(int M, int K, int N) { return M <= 5 && (double)K * N >= 8e6; }
 // row count.  Both sides at the line (us here / there): 1024 x 4096 x 4096 68 / 89, 1500 rows 101 / 90;
 // 768 x 8192 x 8192 171 / 174, 1024 rows 225 / 172; 2048 x 8192 x 2048 117 / 170.
 // (the buffer loads take 32-bit byte offsets inside w; rows of y are stored 16 bytes at a time)
+static double large_us(int M, int K, int N) {
+  const double wg = (double)((M + 127) / 128) * ((N + 511) / 512);
+  return 5.0 + (K / 1024.0) * (20.5 + 8.5 * fmin(fmax((wg - 64) / 192, 0.0), 1.0)) * ceil(wg / 256);
+}
 bool rmsnorm_gemm_rows_wins(int M, int K, int N, int64_t ldw, const void* y, int64_t ldy) {
   if ((int64_t)K * ldw * 2 >= ((int64_t)1 << 32) || (ldy & 7) != 0 || (reinterpret_cast<uintptr_t>(y) & 15) != 0) return false;
-  const double wg = (double)((M + 127) / 128) * ((N + 511) / 512);
-  const double large = 5.0 + (K / 1024.0) * (20.5 + 8.5 * fmin(fmax((wg - 64) / 192, 0.0), 1.0)) * ceil(wg / 256);
-  return 1.15 * rows_us(best_shape(M, K, N), M, K, N) < large;
+  return 1.15 * rows_us(best_shape(M, K, N), M, K, N) < large_us(M, K, N);
+}
+// Expected us of the call in one launch.  (Tiles of up to 32 x 64 take 0.9 times what the rule's figures say.)
+double rmsnorm_gemm_us(int M, int K, int N) {
+  const RowsShape& r = best_shape(M, K, N);
+  if (!rmsnorm_gemm_rows_wins(M, K, N, N, nullptr, N)) return large_us(M, K, N);
+  return (r.mt <= 2 && r.c <= 4 ? 0.9 : 1.0) * rows_us(r, M, K, N);
 }
 
 int rmsnorm_gemm_rows_tile(int M, int K, int N) {

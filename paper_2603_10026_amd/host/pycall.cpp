@@ -244,7 +244,13 @@ PyObject* py_rmsnorm_gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
   rf_tensor d[4];
   float eps;
   rf_stream s;
-  if (!count(n, 6) || !describe_all<4>(args, n, d, {0, 1, 2, 3}, &s) || !to_float(args[4], &eps)) return nullptr;
+  int device;
+  if (!count(n, 6) || !describe_all<4>(args, n, d, {0, 1, 2, 3}, &s, &device) || !to_float(args[4], &eps)) return nullptr;
+  const size_t bytes =
+      d[0].ndim == 2 && d[2].ndim == 2 ? rf_rmsnorm_gemm_workspace_bytes(d[0].shape[0], d[0].shape[1], d[2].shape[1]) : 0;
+  const Scratch scratch(bytes, device, s);
+  if (scratch.data() != nullptr)
+    return call([&] { return rf_rmsnorm_gemm_ws(&d[0], &d[1], &d[2], &d[3], eps, scratch.data(), bytes, s); });
   return call([&] { return rf_rmsnorm_gemm(&d[0], &d[1], &d[2], &d[3], eps, s); });
   END_HANDLE_TH_ERRORS
 }

@@ -176,6 +176,32 @@ def test_every_rmsnorm_tile_has_a_gpu_test():
                 assert B.rf_diag_rmsnorm_gemm_tile(M, K, N) in tiles | {(128, 512)}, (M, K, N)
 
 
+def test_every_rmsnorm_two_pass_tile_has_a_gpu_test():
+    from test_gpu_rmsnorm_two_pass import NORM_TILES
+    tiles = {(256, 256), (128, 256), (128, 128), (64, 128), (64, 64)}
+    assert {t for t, _ in NORM_TILES} == tiles
+    for tile, shape in NORM_TILES:
+        assert B.rf_diag_rmsnorm_gemm_ws_tile(*shape) == tile, shape
+    for M in (1, 48, 100, 600, 1000, 2000, 4096, 30000):
+        for K in (64, 512, 1088, 4096, 8192):
+            for N in (8, 520, 1032, 4104, 8200):
+                assert B.rf_diag_rmsnorm_gemm_ws_tile(M, K, N) in tiles | {(0, 0)}, (M, K, N)
+
+
+@pytest.mark.parametrize("M,K,N,two", [
+    # (us one launch / two: 12.1 / 18, 5.7 / 8.9, 26.9 / 24.9 and 3.5 more alone, 126.9 / 123.7)
+    (48, 4096, 4096, False), (300, 1024, 1024, False), (323, 3200, 4208, False), (4096, 4096, 4096, False), (1, 64, 8, False),
+    # (90.7 / 69.3, 62.2 / 41.4, 34.0 / 21.9, 30.3 / 20.0)
+    (2048, 4096, 4096, True), (1024, 4096, 4096, True), (600, 2048, 4096, True), (2727, 1152, 1360, True),
+    # nothing that rf_rmsnorm_gemm refuses, no axis beyond 32-bit offsets
+    (1024, 4000, 4096, False), (1024, 4096, 4097, False), (0, 4096, 4096, False), (1024, -64, 4096, False), (1024, 1 << 22, 4096, False),
+])
+def test_rmsnorm_workspace(M, K, N, two):
+    nbytes = B.load_library().rf_rmsnorm_gemm_workspace_bytes(M, K, N)
+    assert (nbytes > 0) == two and nbytes <= (128 << 20) + (64 << 10)
+    assert (B.rf_diag_rmsnorm_gemm_ws_tile(M, K, N) != (0, 0)) == two
+
+
 def test_every_attention_kernel_has_gpu_tests_in_each_head_dimension():
     from test_gpu_few_query_tiles import FEW_ATTENTION
     from test_gpu_parity import ATTN_CASES
