@@ -397,8 +397,11 @@ double tile_us(const GShape& g, int M, int K, int N) {
 }
 int best_tile(int M, int K, int N) {
   int best = 0;
-  for (int i = 1; i < (int)(sizeof(kGShapes) / sizeof(kGShapes[0])); ++i)
-    if (tile_us(kGShapes[i], M, K, N) < tile_us(kGShapes[best], M, K, N)) best = i;
+  double best_us = tile_us(kGShapes[0], M, K, N);
+  for (int i = 1; i < (int)(sizeof(kGShapes) / sizeof(kGShapes[0])); ++i) {
+    const double us = tile_us(kGShapes[i], M, K, N);
+    if (us < best_us) best = i, best_us = us;
+  }
   return best;
 }
 int64_t slab_bytes(int64_t rows, int64_t K) { return (rows + kPadRows - 1) / kPadRows * kPadRows * K + 4 * ((rows + 3) / 4 * 4); }
@@ -416,6 +419,7 @@ int slab_rows(int M, int K) {
 bool fp8_quant_gemm_two_pass_wins(int M, int K, int N, double single_us) {
   if (K >= (1 << 23) || slab_rows(M, K) < (M < 2048 ? M : 2048)) return false;  // 32-bit offsets inside a tile
   const double quant = 1.9 + 3.0 * M * (double)K / 7.2e6;
+  if (quant + 2.9 + 3.5 >= 0.95 * single_us) return false;  // (no tile takes less: the smallest calls end here, their host time counts)
   return quant + tile_us(kGShapes[best_tile(M, K, N)], M, K, N) + 3.5 < 0.95 * single_us;
 }
 

@@ -406,10 +406,23 @@ const RowsShape& best_shape(int M, int K, int N) {
     if (rows_us(r, M, K, N) < rows_us(*best, M, K, N)) best = &r;
   return *best;
 }
-// A handful of rows against much of w: nothing but its trip counts, which is some per cent shorter straight into
-// registers (us registers / LDS: 1 x 4352 x 7336 19.5 / 20.5, 4 x 4160 x 6744 17.7 / 18.5, 9 x 2816 x 6528 8.7 / 8.8,
-// 7 x 4928 x 2600 14.8 / 14.2, 4 x 3904 x 1584 9.4 / 9.0).
-bool streams_w(int M, int K, int N) { return M <= 5 && (double)K * N >= 8e6; }
+// Which of the tiles that have both kernels take operands straight into registers.  The LDS kernel's 8 wavefronts
+// need a piece of 64 k each, and its requests under way are what its stages hold: straight is the shorter way where a
+// short axis leaves half of the wavefronts without a piece, and where w comes from beyond the L2 to so many workgroups
+// that their number has the requests under way.  us straight / LDS, three sets of operands in turn: 3 x 256 x 4752
+// 3.2 / 3.4, 153 x 384 x 744 3.9 / 4.1; 3 x 704 x 7608 5.8 / 6.1; 1 x 2304 x 1208 6.7 / 7.2, but 1 x 2240 x 416
+// 5.9 / 4.6; 3 x 4992 x 1056 10.0 / 10.7; 19 x 2816 x 5744 11.3 / 12.2, 8 x 4160 x 5424 14.6 / 15.0, but 48 x 4096 x
+// 4096 14.9 / 13.3, 16 x 4096 x 4096 14.3 / 12.4, 13 x 2048 x 6168 9.9 / 9.6, 21 x 7488 x 7208 37.9 / 34.9.  Over 420 products
+// of 1 to 400 rows LDS throughout is 1.067 times as fast as straight throughout, this rule 1.07; LDS alone loses
+// up to 8 %.
+bool straight(const RowsShape& r, int M, int K, int N) {
+  if (r.mt == 2 && r.c == 4) return false;
+  const double w = (double)K * N;
+  if (K <= (r.mt == 2 ? 512 : 256)) return true;
+  if (M <= 2 && K > 2048 && w >= 1.8e6) return true;
+  if (M <= 5 && (K > 4096 || w >= 4.5e6)) return true;
+  return N >= 5200 && (K > 1024 || r.mt == 2);
+}
 }  // namespace
 
 // The 128 x 512 tiles take 5 us and 20.5 for every 1024 k up to 64 of them, 29 at 256, whatever the
@@ -455,12 +468,11 @@ hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w,
     hipLaunchKernelGGL((rmsnorm_gemm_rows_lds_kernel<MT, C>), dim3((unsigned)grid), dim3(kLThreads), 0, s, \
                        (const bf16_t*)x, (const bf16_t*)g, (const bf16_t*)w, (bf16_t*)y, M, K, N, ldx, ldw, \
                        ldy, 1.0f / (float)K, eps, n_mt);
-  if (streams_w(M, K, N)) {
-    RF_ROWS(1, 2, 4)
+  if (straight(best, M, K, N)) {
+    RF_ROWS(1, 2, 4) RF_ROWS(2, 2, 2) RF_ROWS(1, 4, 2)
   } else {
-    RF_ROWS_LDS(1, 2)
+    RF_ROWS_LDS(1, 2) RF_ROWS_LDS(2, 2) RF_ROWS_LDS(1, 4) RF_ROWS_LDS(2, 4)
   }
-  RF_ROWS_LDS(2, 2) RF_ROWS_LDS(1, 4) RF_ROWS_LDS(2, 4)
   RF_ROWS(4, 4, 2) RF_ROWS(2, 8, 2) RF_ROWS(4, 8, 2)
 #undef RF_ROWS_LDS
 #undef RF_ROWS

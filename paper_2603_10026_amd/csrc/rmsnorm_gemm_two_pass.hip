@@ -300,8 +300,11 @@ double tile_us(const NShape& g, int M, int K, int N) {
 }
 int best_tile(int M, int K, int N) {
   int best = 0;
-  for (int i = 1; i < (int)(sizeof(kNShapes) / sizeof(kNShapes[0])); ++i)
-    if (tile_us(kNShapes[i], M, K, N) < tile_us(kNShapes[best], M, K, N)) best = i;
+  double best_us = tile_us(kNShapes[0], M, K, N);
+  for (int i = 1; i < (int)(sizeof(kNShapes) / sizeof(kNShapes[0])); ++i) {
+    const double us = tile_us(kNShapes[i], M, K, N);
+    if (us < best_us) best = i, best_us = us;
+  }
   return best;
 }
 // Rows beyond what kNormWorkspaceMax holds go slab by slab through the same workspace.
@@ -319,6 +322,7 @@ int64_t padded(int rows) { return ((int64_t)rows + kPadRows - 1) / kPadRows * kP
 bool rmsnorm_gemm_two_pass_wins(int M, int K, int N, double single_us) {
   if (K >= (1 << 22) || slab_rows(M, K) < (M < 2048 ? M : 2048)) return false;  // 32-bit offsets inside a tile
   const double first = 1.9 + 4.0 * M * (double)K / 6.5e6;
+  if (first + 3.1 + 3.5 >= 0.92 * single_us) return false;  // (no tile takes less: the smallest calls end here, their host time counts)
   return first + tile_us(kNShapes[best_tile(M, K, N)], M, K, N) + 3.5 < 0.92 * single_us;
 }
 

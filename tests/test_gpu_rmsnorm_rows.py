@@ -76,6 +76,9 @@ def test_rmsnorm_gemm_rows_do_not_depend_on_their_batch(rf):  # noqa: F811
     # after 64 pieces, a handful of rows against much of w, strided rows of x and w, columns that end in a tile's middle
     (6, 64, 8), (6, 512, 40), (7, 576, 136), (20, 4096, 520), (20, 4160, 264), (37, 8192, 264), (40, 8256, 72), (130, 12352, 136),
     (5, 4352, 2056), (6, 4352, 2056), (300, 1472, 544), (64, 768, 2952),
+    # both sides of the rule on short axes, on a row or two and on wide products
+    (9, 256, 4280), (9, 320, 4280), (153, 512, 744), (153, 576, 744), (2, 2112, 1736), (3, 2112, 1736), (20, 1088, 5192),
+    (20, 1088, 5208), (13, 1088, 8200), (13, 1024, 8200),
 ])
 def test_rmsnorm_gemm_few_rows_strided(rf, M, K, N):  # noqa: F811
     tile = rf.rf_diag_rmsnorm_gemm_tile(M, K, N)
