@@ -410,8 +410,8 @@ const RowsShape& best_shape(int M, int K, int N) {
 // need a piece of 64 k each, and its requests under way are what its stages hold: straight is the shorter way where a
 // short axis leaves half of the wavefronts without a piece, and where w comes from beyond the L2 to so many workgroups
 // that their number has the requests under way.  us straight / LDS, three sets of operands in turn: 3 x 256 x 4752
-// 3.2 / 3.4, 153 x 384 x 744 3.9 / 4.1; 3 x 704 x 7608 5.8 / 6.1; 1 x 2304 x 1208 6.7 / 7.2, but 1 x 2240 x 416
-// 5.9 / 4.6; 3 x 4992 x 1056 10.0 / 10.7; 19 x 2816 x 5744 11.3 / 12.2, 8 x 4160 x 5424 14.6 / 15.0, but 48 x 4096 x
+// 3.2 / 3.4, 153 x 384 x 744 3.9 / 4.1; 3 x 704 x 7608 5.8 / 6.1; 1 x 2304 x 1208 6.7 / 7.2, 1 x 1280 x 2136 5.0 / 5.3, but 1 x 2240 x 416
+// 5.9 / 4.6, 1 x 1664 x 1920 5.4 / 4.9; 3 x 4992 x 1056 10.0 / 10.7; 19 x 2816 x 5744 11.3 / 12.2, 8 x 4160 x 5424 14.6 / 15.0, but 48 x 4096 x
 // 4096 14.9 / 13.3, 16 x 4096 x 4096 14.3 / 12.4, 13 x 2048 x 6168 9.9 / 9.6, 21 x 7488 x 7208 37.9 / 34.9.  Over 420 products
 // of 1 to 400 rows LDS throughout is 1.067 times as fast as straight throughout, this rule 1.07; LDS alone loses
 // up to 8 %.
@@ -420,6 +420,7 @@ bool straight(const RowsShape& r, int M, int K, int N) {
   const double w = (double)K * N;
   if (K <= (r.mt == 2 ? 512 : 256)) return true;
   if (M <= 2 && K > 2048 && w >= 1.8e6) return true;
+  if (M <= 3 && K >= 900 && w >= 2.6e6) return true;
   if (M <= 5 && (K > 4096 || w >= 4.5e6)) return true;
   return N >= 5200 && (K > 1024 || r.mt == 2);
 }

@@ -77,7 +77,7 @@ def test_rmsnorm_gemm_rows_do_not_depend_on_their_batch(rf):  # noqa: F811
     (6, 64, 8), (6, 512, 40), (7, 576, 136), (20, 4096, 520), (20, 4160, 264), (37, 8192, 264), (40, 8256, 72), (130, 12352, 136),
     (5, 4352, 2056), (6, 4352, 2056), (300, 1472, 544), (64, 768, 2952),
     # both sides of the rule on short axes, on a row or two and on wide products
-    (9, 256, 4280), (9, 320, 4280), (153, 512, 744), (153, 576, 744), (2, 2112, 1736), (3, 2112, 1736), (20, 1088, 5192),
+    (9, 256, 4280), (9, 320, 4280), (153, 512, 744), (153, 576, 744), (2, 2112, 1736), (3, 2112, 1736), (3, 896, 2952), (3, 960, 2952), (20, 1088, 5192),
     (20, 1088, 5208), (13, 1088, 8200), (13, 1024, 8200),
 ])
 def test_rmsnorm_gemm_few_rows_strided(rf, M, K, N):  # noqa: F811
