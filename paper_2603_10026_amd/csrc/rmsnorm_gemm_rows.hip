@@ -14,8 +14,8 @@
 // between the two is the order of fp32 sums.)  ss is the diagonal of X X^T, taken by the matrix
 // pipe from the x that is in registers already.
 //
-// (This kernel serves tiles of 64 rows or 128 columns, and a few rows against much of w; the others go through
-// LDS, see below.)
+// (This kernel serves tiles of 64 rows or 128 columns, and of the smaller ones those that `straight` below names;
+// the others go through LDS.)
 // What bounds it: the 128-byte lines a compute unit can have on their way.  A read of w alone in
 // this pattern takes 15.9 us when w comes from HBM (4096 x 4096, C = 2, 128 workgroups), 17.7 us with
 // whole lines and half the workgroups (C = 4), and cache-policy bits change nothing; the last 50 GB/s
@@ -46,6 +46,10 @@ __global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
     bf16_t* __restrict__ y, int M, int K, int N, int64_t ldx, int64_t ldw, int64_t ldy,
     float inv_k, float eps, int n_mtiles) {
   constexpr int CD = C / 2;  // 32-bit words of w per lane and k-row
+  // Requests are waited for in order.  Two row tiles against a narrow tile of w have as much work in
+  // x g as in pairing w and start it first (48 x 4096 x 4096: 14.5 us, 15.2 the other way round);
+  // the other shapes want w first (32 x 8192 x 1024 in one row tile: 15.6 and 20.3).
+  constexpr bool kXFirst = MT == 2 && C == 2;
   __shared__ f32x4 s_acc[kRWaves][C * MT][kWave];
   __shared__ float s_ss[kRWaves][16 * MT];
 
@@ -86,6 +90,12 @@ __global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
     const int ii = min(i, mine - 1);
     const uint32_t k0 = (wave + kRWaves * (ii >> 1)) * 64 + (ii & 1) * 32;
     const uint32_t wo = k0 * ldw2;
+    auto load_x = [&] {
+#pragma unroll
+      for (int t = 0; t < MT; ++t) xr[p][t] = __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane[t], k0 * 2, 0);
+      gr[p] = __builtin_amdgcn_raw_buffer_load_b128(grs, 16 * g4, k0 * 2, 0);
+    };
+    if constexpr (kXFirst) load_x();
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       if constexpr (CD == 4) {
@@ -100,10 +110,7 @@ __global__ __launch_bounds__(kRThreads, 2) void rmsnorm_gemm_rows_kernel(
         for (int d = 0; d < CD; ++d) wr[p][e][d] = v[d];
       }
     }
-    // (requests are waited for in order: w first, 32 x 8192 x 1024 in one row tile 15.6 us, 20.3 the other way round)
-#pragma unroll
-    for (int t = 0; t < MT; ++t) xr[p][t] = __builtin_amdgcn_raw_buffer_load_b128(xrs, x_lane[t], k0 * 2, 0);
-    gr[p] = __builtin_amdgcn_raw_buffer_load_b128(grs, 16 * g4, k0 * 2, 0);
+    if constexpr (!kXFirst) load_x();
   };
 
   f32x4 acc[C][MT], sq[MT];
