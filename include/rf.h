@@ -178,9 +178,9 @@ RF_API rf_status rf_fp8_quant_gemm(const rf_tensor* a, const rf_tensor* w, rf_te
                                    rf_stream stream);
 
 /*
- * rf_fp8_quant_gemm with device memory for the quantised tokens: every element is quantised
- * with the maximum of its whole row (a prefix like any other in the promises above), by a
- * launch of its own, and the contraction works on the codes.
+ * rf_fp8_quant_gemm with device memory for the quantised tokens: the same codes, formed by a
+ * launch of their own, and a contraction that reads them.  Its result is rf_fp8_quant_gemm's up to
+ * the order of fp32 sums.
  *   workspace : device memory, 16-byte aligned, at least
  *       rf_fp8_quant_gemm_workspace_bytes(M, K, N) bytes; contents need no initialisation and
  *       are undefined afterwards.  Too small or misaligned: RF_ERR_WORKSPACE.  Concurrent calls

@@ -324,7 +324,8 @@ def rf_moe_routing_noalloc(x, w, topk, prob, idx, stream=None):
 def rf_fp8_quant_gemm(a, w, c=None, stream=None):
     """c = dequant(quant_fp8(a) @ w^T): a [M,K] bf16, w [N,K] torch.float8_e4m3fn, c [M,N] bf16.
     Where rf_fp8_quant_gemm_ws is faster its workspace comes from torch's caching allocator, on the
-    call's stream, and goes back to it at return."""
+    call's stream, and goes back to it at return.  With memory or without, the codes are the same:
+    results differ by the order of fp32 sums at most."""
     if c is None:
         c = torch.empty((a.shape[0], w.shape[0]), dtype=torch.bfloat16, device=a.device)
     _check((_call or _native()).fp8_quant_gemm(a, w, c, stream), "rf_fp8_quant_gemm")

@@ -1,28 +1,30 @@
 // FP8 per-token quantisation + GEMM in two launches, for callers that hand over a workspace:
-//   1. fp8_quant_rows_kernel: m_i = max_k |a[i,k]| and the codes q(MAX a[i,k] / m_i), MAX = 448,
-//      one read of a;
-//   2. fp8_gemm_kernel: c[i,n] = (m_i / MAX) sum_k code[i,k] w[n,k].
-// The single-launch kernels quantise a token tile once for every 256 or 512 channels beside the
-// matrix pipe and rescale their sums whenever a running maximum moves; here the contraction is
-// nothing but matrix instructions and their operands, and half the token bytes.
+//   1. fp8_quant_rows_kernel: for every tile of 128 k the maximum m' of the token up to the tile's end
+//      and the codes q(MAX a / m') of the tile, MAX = 448, one read of a;
+//   2. fp8_gemm_kernel: the incremental sum over the tiles, acc = acc * (m'_old / m'_new) + code . w,
+//      c = acc * m / MAX.
+// The single-launch kernels form the same codes once for every 256 or 512 channels beside the matrix
+// pipe; here the contraction reads them, half the token bytes, and all that is left beside its matrix
+// instructions is the rescaling.  Where one wavefront sums the whole axis (WK = 1) the result is that of
+// the 128-token single-launch tiles to the bit.
 //
 // The contraction.  C^T = W A_q^T with v_mfma_f32_32x32x64_f8f6f4 (A = channels, B = tokens: an
-// accumulator lane holds one token, one scale).  A workgroup of 4 wavefronts owns a tile of
+// accumulator lane holds one token, one scale).  A workgroup of 4 or 8 wavefronts owns a tile of
 // 32 TM WM tokens x 32 TN WN channels; tokens and channels both lie with k innermost, so a stage
-// is KH x 64 bytes of every row, fetched by direct-to-LDS loads into a ring of NS stages and read
-// as the operands lie.  In phase t a wavefront multiplies stage t, whose operands it already
-// holds in registers, requests those of stage t+1 behind its first MFMAs, and requests stage t+NS
-// into the slot that stage t left: no wavefront waits for LDS data behind the one barrier of a
+// is KH x 64 bytes of every row and the tokens' maxima, fetched by direct-to-LDS loads into a ring of
+// NS stages and read as the operands lie.  In phase t a wavefront multiplies stage t, whose operands
+// it already holds in registers, requests those of stage t+1 behind its first MFMAs, and requests stage
+// t+NS into the slot that stage t left: no wavefront waits for LDS data behind the one barrier of a
 // phase, and a tile has NS - 1 phases to arrive.
 //
-// What bounds it.  Large products: the matrix pipe beside LDS (a 256 x 256 tile over 4 wavefronts
-// reads 64 KB of operands and writes 32 KB of tiles per 64 k, 768 of the 1024 clocks that its
-// matrix instructions take).  4096 x 8192 x 3584: 15.8 us of quantisation (6.3 TB/s) + 92.5 us of
-// contraction (2.6 PFLOP/s), where the single launch takes 142 to 160; 4096 x 3584 x 8192: 148 ->
-// 109.  Smaller ones: the lines a compute unit has in flight (50 to 70 GB/s each), so tiles are
+// What bounds it.  Large products: the matrix pipe beside LDS (a 256 x 256 tile over 8 wavefronts reads
+// 96 KB of operands and writes 32 KB of tiles per 64 k) and the sums' rescaling, which most tiles of 32
+// tokens need for one of them.  4096 x 8192 x 3584: 17.6 us of quantisation (5.7 TB/s) + 113 us of contraction
+// (2.1 PFLOP/s), 130 in all where the single launch takes 176 on the same card; 4096 x 3584 x 8192: 152 -> 125.
+// Smaller ones: the lines a compute unit has in flight (50 to 70 GB/s each), so tiles are
 // made as small as fills the chip, and below 64 x 64 the wavefronts take parts of the axis (WK)
-// rather than of the tile: 1348 x 3456 x 2336 46 -> 21 us, 141 x 3456 x 7200 42.6 -> 13.4,
-// 64 x 8192 x 8192 46 -> 15.8, 64 x 4096 x 4096 13.5 -> 8.5.
+// rather than of the tile: 1348 x 3456 x 2336 48 -> 26 us, 141 x 3456 x 7200 43 -> 17,
+// 36 x 12800 x 2008 121 -> 20.
 #include <math.h>
 
 #include <type_traits>
@@ -53,77 +55,122 @@ __device__ __forceinline__ u16x2 absmax8(u16x2 m, const u32x4& r) {
 }
 }  // namespace
 
-// WPR wavefronts per row, VPT vectors of 8 values per lane held in registers (VPT = 0: a row of
-// any length is read twice, the second time from the cache).
+// Codes and prefix maxima of a row.  16 lanes (a DPP row) hold a tile of 128 k; WPR wavefronts per row, VPT vectors of
+// 8 values per lane held in registers.  Rows of any length (VPT = 0) go chunk by chunk, 16 tiles at a time: a tile is
+// quantised with the maximum up to its own end, so nothing is read twice.
 template <int VPT, int WPR>
 __global__ __launch_bounds__(kGThreads) void fp8_quant_rows_kernel(const bf16_t* __restrict__ a,
                                                                    unsigned char* __restrict__ codes,
-                                                                   float* __restrict__ row_max, int M, int K,
-                                                                   int64_t lda) {
-  constexpr int kRows = 4 / WPR;
-  __shared__ float s_max[4];
-  const int wave = threadIdx.x >> 6;
-  const int row = blockIdx.x * kRows + (WPR == 1 ? wave : 0);
-  const int vec = WPR == 1 ? (threadIdx.x & 63) : threadIdx.x;  // this lane's first vector of the row
-  const int step = 64 * WPR;
-  const int nv = K / 8;
-  if (WPR == 1 && row >= M) return;
+                                                                   float* __restrict__ maxima, int M, int K,
+                                                                   int64_t lda, int pitch, int run) {
+  constexpr int kTiles = VPT > 0 ? 4 * WPR * VPT : 32;  // (VPT = 0: two chunks of 16, in turn)
+  static_assert(VPT == 0 ? WPR == 4 : kTiles <= 64, "a lane per tile in the scan");
+  __shared__ float s_max[WPR == 4 ? kTiles : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int row = blockIdx.x * 4 + wave;
+  if constexpr (WPR == 4) {
+    // runs of rows on one XCD (workgroups are dealt to the 8 in turn): their maxima share lines
+    const int j = blockIdx.x >> 3;
+    row = (j / run * 8 + (blockIdx.x & 7)) * run + j % run;
+  }
+  if (row >= M) return;
+  const int vec = WPR == 1 ? lane : threadIdx.x;  // this lane's first vector of the row
+  const int in_step = vec >> 4;                   // and its tile
+  constexpr int kStep = 64 * WPR, kStepTiles = 4 * WPR;
+  const int nv = K / 8, nk = K / 128;
   const u32x4* src = reinterpret_cast<const u32x4*>(a + (int64_t)row * lda);
   u32x2* dst = reinterpret_cast<u32x2*>(codes + (int64_t)row * K);
-  constexpr int kHeld = VPT > 0 ? VPT : 1;
-  u32x4 x[kHeld];
-  u16x2 mx = {0, 0};
-  if constexpr (VPT > 0) {
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) x[i] = src[min(vec + i * step, nv - 1)];
-#pragma unroll
-    for (int i = 0; i < VPT; ++i) mx = absmax8(mx, x[i]);
-  } else {
-    for (int i = vec; i < nv; i += step) mx = absmax8(mx, src[i]);
-  }
-  float m = __uint_as_float((uint32_t)(mx[0] > mx[1] ? mx[0] : mx[1]) << 16);
-  m = wave_max(m);
-  if constexpr (WPR == 4) {
-    if ((threadIdx.x & 63) == 0) s_max[wave] = m;
-    __syncthreads();
-    m = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
-  }
-  if (vec == 0) row_max[row] = m;
-  const float s = m > 0.f ? kE4M3Max / m : 0.f;  // IEEE division: it decides the codes
-  auto put = [&](int i, const u32x4& v) {
+  float* out = maxima + row;
+  auto put = [&](int i, const u32x4& v, float m) {
+    const float s = m > 0.f ? kE4M3Max / m : 0.f;  // IEEE division: it decides the codes
     u32x2 o;
     o[0] = (uint32_t)codes4(v[0], v[1], s);
     o[1] = (uint32_t)codes4(v[2], v[3], s);
     dst[i] = o;
+    if ((lane & 15) == 0) out[(int64_t)(i >> 4) * pitch] = m;
+  };
+  auto tile_max = [](const u32x4& v) {
+    const u16x2 m = absmax8(u16x2{0, 0}, v);
+    return row16_max(__uint_as_float((uint32_t)(m[0] > m[1] ? m[0] : m[1]) << 16));
   };
   if constexpr (VPT > 0) {
+    u32x4 x[VPT];
+    float mine[VPT];  // maximum of this lane's tile
 #pragma unroll
-    for (int i = 0; i < VPT; ++i)
-      if (vec + i * step < nv) put(vec + i * step, x[i]);
+    for (int i = 0; i < VPT; ++i) x[i] = src[min(vec + i * kStep, nv - 1)];
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) mine[i] = tile_max(x[i]);
+    // prefix maxima, a tile per lane (tiles past the end come after all others)
+    float upto;
+    if constexpr (WPR == 4) {
+#pragma unroll
+      for (int i = 0; i < VPT; ++i)
+        if ((lane & 15) == 0) s_max[i * kStepTiles + in_step] = mine[i];
+      __syncthreads();
+      upto = s_max[lane % kTiles];
+    } else {
+      upto = __shfl(mine[0], (lane & 3) * 16, 64);
+#pragma unroll
+      for (int i = 1; i < VPT; ++i) {
+        const float o = __shfl(mine[i], (lane & 3) * 16, 64);
+        upto = (lane >> 2) == i ? o : upto;
+      }
+    }
+#pragma unroll
+    for (int d = 1; d < kTiles; d *= 2) {
+      const float o = __shfl_up(upto, d, 64);
+      upto = lane >= d ? fmaxf(upto, o) : upto;
+    }
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+      const float m = __shfl(upto, i * kStepTiles + in_step, 64);
+      if (vec + i * kStep < nv) put(vec + i * kStep, x[i], m);
+    }
   } else {
-    for (int i = vec; i < nv; i += step) put(i, src[i]);
+    float before = 0.f;
+    u32x4 x = src[min(vec, nv - 1)];
+    for (int i = vec, turn = 0; i < nv + vec; i += kStep, turn ^= 1) {
+      const u32x4 following = src[min(i + kStep, nv - 1)];
+      const float mine = tile_max(x);
+      if ((lane & 15) == 0) s_max[16 * turn + in_step] = mine;
+      __syncthreads();  // (a wavefront is at most one chunk ahead: two buffers do)
+      float upto = s_max[16 * turn + (lane & 15)];
+#pragma unroll
+      for (int d = 1; d < 16; d *= 2) {
+        const float o = __shfl_up(upto, d, 16);
+        upto = (lane & 15) >= d ? fmaxf(upto, o) : upto;
+      }
+      const float m = fmaxf(before, __shfl(upto, in_step, 16));
+      before = fmaxf(before, __shfl(upto, 15, 16));
+      if (i < nv) put(i, x, m);
+      x = following;
+    }
   }
 }
 
 template <int TM, int TN, int WM, int WN, int WK, int KH, int NS>
 struct GTile {
-  static_assert(WM * WN * WK == 4, "4 wavefronts");
+  static constexpr int kWaves = WM * WN * WK, kThreads = kWaves * kWave;
+  static_assert(kWaves == 4 || (kWaves == 8 && WK == 1), "4 or 8 wavefronts");
   static constexpr int kM = 32 * TM * WM, kN = 32 * TN * WN;
   static constexpr int kRowB = 64 * KH;                  // bytes of a row in a stage
   static constexpr int kGroupB = (kM + kN) * kRowB;      // what one of the WK parts of a stage holds
-  static constexpr int kStageB = WK * kGroupB;
-  // direct-to-LDS loads per wavefront and stage
-  static constexpr int kLoadsA = WK * kM * kRowB / 4096, kLoadsW = WK * kN * kRowB / 4096, kLoads = kLoadsA + kLoadsW;
-  static_assert(WK * kM * kRowB % 4096 == 0 && WK * kN * kRowB % 4096 == 0, "whole loads");
+  static constexpr int kMaxAt = WK * kGroupB, kStageB = kMaxAt + WK * kM * 4;  // the tokens' maxima behind the operands
+  // direct-to-LDS loads per wavefront and stage, one of them for maxima (64 each: wavefronts share them where they are fewer)
+  static constexpr int kLoadsA = WK * kM * kRowB / (1024 * kWaves), kLoadsW = WK * kN * kRowB / (1024 * kWaves);
+  static constexpr int kLoads = kLoadsA + kLoadsW + 1;
+  static constexpr int kMaxLoads = WK * kM / 64;
+  static_assert(kMaxLoads >= 1 && kMaxLoads <= 4 && WK * kM % 64 == 0 && (kM % 64 == 0 || kM == 32), "a load of maxima each");
+  static_assert(WK * kM * kRowB % (1024 * kWaves) == 0 && WK * kN * kRowB % (1024 * kWaves) == 0, "whole loads");
   // output staging: 32 tokens per wavefront (padded rows); with WK > 1 the sums of all wavefronts before that
-  static constexpr int kOutB = WK > 1 ? 4 * TM * TN * 4096 + 4 * 32 * 80 : 4 * 32 * (64 * TN + 16);
+  static constexpr int kOutB = WK > 1 ? 4 * TM * TN * 4096 + 4 * 32 * 80 : kWaves * 32 * (64 * TN + 16);
   static constexpr int kLdsB = NS * kStageB > kOutB ? NS * kStageB : kOutB;
 };
 
 template <int TM, int TN, int WM, int WN, int WK, int KH, int NS, int OCC>
-__global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
-    const unsigned char* __restrict__ codes, const float* __restrict__ row_max, const unsigned char* __restrict__ w,
-    bf16_t* __restrict__ c, int M, int K, int N, int64_t ldw, int64_t ldc, int n_mtiles, int n_ntiles) {
+__global__ __launch_bounds__(WM * WN * WK * kWave, OCC) void fp8_gemm_kernel(
+    const unsigned char* __restrict__ codes, const float* __restrict__ maxima, const unsigned char* __restrict__ w,
+    bf16_t* __restrict__ c, int M, int K, int N, int64_t ldw, int64_t ldc, int pitch, int n_mtiles, int n_ntiles) {
   using T = GTile<TM, TN, WM, WN, WK, KH, NS>;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[T::kLdsB];
   const int lane = threadIdx.x & 63;
@@ -164,20 +211,33 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
   uint32_t a_off[T::kLoadsA], w_off[T::kLoadsW];  // from the tile's first row; + piece * kRowB
 #pragma unroll
   for (int e = 0; e < T::kLoadsA; ++e) {
-    const int row = (4 * e + wave) % kLA * kRowsL + lrow;  // (the workspace holds whole tiles of rows)
+    const int row = (T::kWaves * e + wave) % kLA * kRowsL + lrow;  // (the workspace holds whole tiles of rows)
     a_off[e] = (uint32_t)(row * K + ((lslot ^ swz(row)) << 4));
   }
 #pragma unroll
   for (int e = 0; e < T::kLoadsW; ++e) {
-    const int row = (4 * e + wave) % kLW * kRowsL + lrow;  // channels past the end repeat the last one
+    const int row = (T::kWaves * e + wave) % kLW * kRowsL + lrow;  // channels past the end repeat the last one
     w_off[e] = (uint32_t)(min(row, N - 1 - n0) * (int)ldw + ((lslot ^ swz(row)) << 4));
   }
   const unsigned char* abase = codes + (int64_t)m0 * K;
   const unsigned char* wbase = w + (int64_t)n0 * ldw;
+  const int max_at = wave % T::kMaxLoads * 64 + lane;  // this lane's maximum in a stage: [part of the axis][token]
+  const int max_grp = max_at / T::kM;
+  const uint32_t max_off = (uint32_t)min(m0 + max_at % T::kM, M - 1) * 4;  // (tokens past the end repeat the last one)
   // load e of stage t (past the end of the axis the last piece once more, which nothing multiplies)
   auto request = [&](int e, int t, uint32_t slot_off) {
+    if (e == T::kLoads - 1) {
+      const int tile = min(t * WK + max_grp, n_pieces - 1) / (2 / KH);
+      const uint32_t dst = lds_base + slot_off + T::kMaxAt + wave % T::kMaxLoads * 256;
+      const uint32_t off = max_off + (uint32_t)tile * (uint32_t)pitch * 4;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                   :
+                   : "s"(dst), "v"(off), "s"(maxima)
+                   : "memory", "m0");
+      return;
+    }
     const bool tok = e < T::kLoadsA;
-    const int idx = 4 * (tok ? e : e - T::kLoadsA) + wave;
+    const int idx = T::kWaves * (tok ? e : e - T::kLoadsA) + wave;
     const int per = tok ? kLA : kLW;
     const int grp = idx / per;
     const unsigned char* base = (tok ? abase : wbase) + (int64_t)min(t * WK + grp, n_pieces - 1) * T::kRowB;
@@ -218,6 +278,13 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[n][m][r] = 0.f;
   i32x8 ft[2][KH][TM], fw[2][KH][TN];  // operands of the stage being multiplied and of the next
+  float mx[2][TM];                     // and the maxima of this lane's tokens up to there
+  float m_run[TM];                     // the sums are in units of these
+#pragma unroll
+  for (int m = 0; m < TM; ++m) m_run[m] = 0.f;
+  auto read_max = [&](int m, uint32_t slot_off) {
+    return *reinterpret_cast<const float*>(lds + slot_off + T::kMaxAt + (wk * T::kM + (wm * TM + m) * 32 + i32) * 4);
+  };
 
 #define RF_FENCE __builtin_amdgcn_sched_barrier(0);
   // Stages 0 .. NS-1 are requested (surplus ones re-read the last), the operands of stage 0 read.
@@ -235,12 +302,26 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
 #pragma unroll
     for (int i = 0; i < TN; ++i) fw[0][kh][i] = read_w(kh, i, 0);
   }
+#pragma unroll
+  for (int m = 0; m < TM; ++m) mx[0][m] = read_max(m, 0);
+  // Brings the sums of token block m to the units of a stage, where one of its tokens has a new maximum (uniform).
+  auto rescale = [&](auto cur_c, int m) __attribute__((always_inline)) {
+    const float m_new = mx[decltype(cur_c)::value][m];
+    if (__builtin_amdgcn_ballot_w64(!(m_new == m_run[m])) != 0) {
+      const float corr = m_new == m_run[m] ? 1.0f : m_run[m] * fast_rcp(m_new);
+      m_run[m] = m_new;
+#pragma unroll
+      for (int n = 0; n < TN; ++n)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[n][m][r] *= corr;
+    }
+  };
 
   // Phase t: see the head of the file.  `cur`: which set of operand registers stage t is in.
   constexpr int kMfmas = KH * TM * TN, kReads = KH * (TM + TN);
   constexpr int kRate = (2 * kReads + kMfmas - 1) / kMfmas;  // operands behind an MFMA: all in the first half
   uint32_t slot = 0;  // byte offset of stage t's ring slot
-  auto phase = [&](auto cur_c, int t) {
+  auto phase = [&](auto cur_c, int t) __attribute__((always_inline)) {
     constexpr int cur = decltype(cur_c)::value, nxt = cur ^ 1;
     const uint32_t next = slot == (NS - 1) * T::kStageB ? 0 : slot + T::kStageB;
     // stage t+1 has landed, for every wavefront; stage t's slot has been read by all of them
@@ -251,13 +332,18 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
 #pragma unroll
       for (int i = 0; i < TN; ++i) asm volatile("" : "+v"(fw[cur][kh][i]));
     }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+      if (KH == 2 || cur == 0) asm volatile("" : "+v"(mx[cur][i]));
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * T::kLoads) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     RF_FENCE
 #pragma unroll
     for (int q = 0; q < kMfmas; ++q) {
-      const int kh = q / (TM * TN), n = q / TM % TN, m = q % TM;
+      const int kh = q / (TM * TN), m = q / TN % TM, n = q % TN;
+      // a block's rescaling runs behind the MFMAs of the one before (stages of 64 k: every other one starts a tile)
+      if (kh == 0 && n == 0 && (KH == 2 || cur == 0)) rescale(cur_c, m);
       acc[n][m] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[cur][kh][n], ft[cur][kh][m], acc[n][m], 0, 0, 0, 0, 0, 0);
 #pragma unroll
       for (int f = min(kReads, q * kRate); f < min(kReads, (q + 1) * kRate); ++f) {
@@ -265,6 +351,7 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
         if (i < TM) ft[nxt][fk][i < TM ? i : 0] = read_t(fk, i, next);
         else fw[nxt][fk][i < TM ? 0 : i - TM] = read_w(fk, i - TM, next);
       }
+      if (q < TM && (KH == 2 || nxt == 0)) mx[nxt][q < TM ? q : 0] = read_max(q, next);
 #pragma unroll
       for (int e = q * T::kLoads / kMfmas; e < (q + 1) * T::kLoads / kMfmas; ++e) request(e, t + NS, slot);
       RF_FENCE
@@ -284,8 +371,10 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
       constexpr int cur = decltype(cur_c)::value;
       if ((n_stages - 1) * WK + wk < n_pieces) {
 #pragma unroll
+        for (int m = 0; m < TM; ++m) rescale(cur_c, m);
+#pragma unroll
         for (int q = 0; q < kMfmas; ++q) {
-          const int kh = q / (TM * TN), n = q / TM % TN, m = q % TM;
+          const int kh = q / (TM * TN), m = q / TN % TM, n = q % TN;
           acc[n][m] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fw[cur][kh][n], ft[cur][kh][m], acc[n][m], 0, 0, 0, 0, 0, 0);
         }
       }
@@ -311,13 +400,20 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
   if constexpr (WK > 1) {
     // the sums over parts of the axis meet in LDS, a 32 x 32 block per wavefront in turn
     f32x4* red = reinterpret_cast<f32x4*>(lds);
+    const float* m_all = maxima + (int64_t)(K / 128 - 1) * pitch;  // the tokens' own maxima
+    float unit[TM];                                                // this wavefront's in units of those
+#pragma unroll
+    for (int m = 0; m < TM; ++m) {
+      const float all = m_all[min(m0 + (wm * TM + m) * 32 + i32, M - 1)];
+      unit[m] = m_run[m] == all ? 1.0f : m_run[m] * fast_rcp(all);
+    }
 #pragma unroll
     for (int b = 0; b < TM * TN; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         f32x4 v;
 #pragma unroll
-        for (int x = 0; x < 4; ++x) v[x] = acc[b / TM][b % TM][4 * r + x];
+        for (int x = 0; x < 4; ++x) v[x] = acc[b / TM][b % TM][4 * r + x] * unit[b % TM];
         red[((wave * TM * TN + b) * 4 + r) * 64 + lane] = v;
       }
     __syncthreads();
@@ -325,7 +421,7 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
     for (int b = wk; b < TM * TN; b += WK) {
       const int n = b / TM, m = b % TM;
       const int tok0 = m0 + (wm * TM + m) * 32;
-      const float f = tok0 + i32 < M ? row_max[tok0 + i32] * (1.0f / kE4M3Max) : 0.f;
+      const float f = m_all[min(tok0 + i32, M - 1)] * (1.0f / kE4M3Max);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         f32x4 v = red[(((wave % (WM * WN)) * TM * TN + b) * 4 + r) * 64 + lane];
@@ -351,7 +447,7 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
 #pragma unroll
   for (int m = 0; m < TM; ++m) {
     const int tok0 = m0 + (wm * TM + m) * 32;
-    const float f = tok0 + i32 < M ? row_max[tok0 + i32] * (1.0f / kE4M3Max) : 0.f;
+    const float f = m_run[m] * (1.0f / kE4M3Max);
 #pragma unroll
     for (int n = 0; n < TN; ++n)
 #pragma unroll
@@ -376,24 +472,29 @@ __global__ __launch_bounds__(kGThreads, OCC) void fp8_gemm_kernel(
 
 namespace {
 // The tiles: token and channel blocks of 32 per wavefront; wavefronts along tokens, channels and the axis;
-// 64-byte pieces of a row per stage; stages; workgroups a compute unit is to hold.  With them the expected us of
-// a launch: `launch` + rounds over the 256 compute units x (`round` + `piece` per 128 k).  Fitted to graph
-// replays of every tile on 260 products of 1 to 4096 tokens, 16 to 8192 channels and 512 to 8192 k (within 10 %
-// for nine in ten); the tile chosen by them takes 0.3 % more than the best one, 13 % at worst.
-struct GShape { int m, n; double launch, round, piece; };
-#define RF_GTILES(X)                                                                               \
-  X(0, (4, 4, 2, 2, 1, 1, 4, 1), 0.0, 6.3, 1.095) X(1, (2, 4, 2, 2, 1, 2, 3, 1), 0.0, 5.4, 0.553)  \
-  X(2, (2, 2, 2, 2, 1, 2, 4, 1), 0.0, 4.3, 0.338) X(3, (1, 2, 2, 2, 1, 2, 3, 2), 1.4, 1.7, 0.271)  \
-  X(4, (1, 1, 2, 2, 1, 2, 4, 2), 1.9, 1.0, 0.173) X(5, (1, 1, 1, 2, 2, 2, 4, 1), 1.1, 2.0, 0.125)  \
-  X(6, (1, 1, 1, 1, 4, 2, 4, 1), 1.2, 2.1, 0.084)
+// 64-byte pieces of a row per stage; stages; wavefronts a SIMD is to hold.  (Two: the sums then stay in registers that
+// the vector ALU reaches; the 512-register form would move each of them over and back to rescale it.)  With them the
+// expected us of a launch: `launch` + rounds over the 256 compute units x (`round` + (`piece` + `full` x the share of
+// the units in use) per 128 k), where a second workgroup of a compute unit takes `second` of the first one's time,
+// + the stores of c.  Fitted to graph replays of every tile on 330 products of 1 to 4096 tokens, 32 to 8192 channels
+// and 512 to 8192 k (within 12 % for nine in ten); the tile chosen by them takes 0.4 % more than the best one, 9 %
+// at worst.
+struct GShape { int m, n; double launch, round, piece, full, second; };
+#define RF_GTILES(X)                                                                                                   \
+  X(0, (4, 2, 2, 4, 1, 1, 4, 2), 0.0, 4.93, 1.133, 0.529, 1.0) X(1, (2, 2, 2, 2, 1, 2, 2, 2), 1.88, 0.78, 0.67, 0.188, 0.054) \
+  X(2, (1, 2, 2, 2, 1, 2, 3, 2), 2.65, 0.27, 0.326, 0.099, 0.435) X(3, (1, 1, 2, 2, 1, 2, 4, 2), 2.04, 0.62, 0.226, 0.077, 0.375) \
+  X(4, (1, 1, 1, 2, 2, 2, 4, 1), 1.4, 1.67, 0.17, 0.029, 1.0) X(5, (1, 1, 1, 1, 4, 2, 4, 1), 1.37, 1.94, 0.104, 0.018, 1.0)
 #define RF_SHAPE_OF(TM, TN, WM, WN, WK, KH, NS, OCC) 32 * TM * WM, 32 * TN * WN
-#define RF_SHAPE(I, P, L, R, S) {RF_SHAPE_OF P, L, R, S},
+#define RF_THREADS_OF(TM, TN, WM, WN, WK, KH, NS, OCC) WM * WN * WK * kWave
+#define RF_SHAPE(I, P, L, R, S, F, W) {RF_SHAPE_OF P, L, R, S, F, W},
 constexpr GShape kGShapes[] = {RF_GTILES(RF_SHAPE)};
 constexpr int kPadRows = 256;  // the codes hold whole tiles of rows
 
 double tile_us(const GShape& g, int M, int K, int N) {
   const double tiles = ceil((double)M / g.m) * ceil((double)N / g.n);
-  return g.launch + ceil(tiles / 256) * (g.round + g.piece * (K / 128));
+  const double rounds = ceil(tiles / 256), seconds = floor(rounds / 2);
+  return g.launch + (rounds - seconds * (1.0 - g.second)) * (g.round + (g.piece + g.full * tiles / (256 * rounds)) * (K / 128)) +
+         M * (double)N / 1.5e6;
 }
 int best_tile(int M, int K, int N) {
   int best = 0;
@@ -404,26 +505,29 @@ int best_tile(int M, int K, int N) {
   }
   return best;
 }
-int64_t slab_bytes(int64_t rows, int64_t K) { return (rows + kPadRows - 1) / kPadRows * kPadRows * K + 4 * ((rows + 3) / 4 * 4); }
+int64_t padded(int rows) { return ((int64_t)rows + kPadRows - 1) / kPadRows * kPadRows; }
+// Bytes of a row: its codes and a maximum for every 128 of them.
+int64_t row_bytes(int64_t K) { return K + K / 32; }
 // Tokens beyond what kFp8WorkspaceMax holds go slab by slab through the same workspace.
 int slab_rows(int M, int K) {
-  const int64_t fit = kFp8WorkspaceMax / ((int64_t)K + 4) / kPadRows * kPadRows;
+  const int64_t fit = kFp8WorkspaceMax / row_bytes(K) / kPadRows * kPadRows;
   return (int)(fit < M ? fit : M);
 }
 }  // namespace
 
-// Both launches against the single one.  The quantisation reads a and writes the codes (2.2 us for the smallest,
-// 15.9 for 4096 x 8192).  A second launch adds some 3.5 us to a call that is waited for (none to calls in a row):
-// 12 x 2432 x 5664 takes 7.1 us here and 9.0 there in a row, but 26.4 and 21.7 alone, and stays there;
-// 64 x 4096 x 4096 takes 8.5 and 13.5 in a row and the same alone.
+// Both launches against the single one.  The quantisation reads a and writes the codes (2.7 us for the smallest,
+// 17.7 for 4096 x 8192).  A second launch adds some 3.5 us to a call that is waited for (none to calls in a row);
+// 0.9 for the fits' errors.  Of the 330 products above this takes 122, 1.86 times faster in a row, the least 1.25.  (Below 8 tokens
+// the single launch's figure is too high at a long axis: 2 x 5248 x 2408 takes 11.0 there and 10.9 here.)
 bool fp8_quant_gemm_two_pass_wins(int M, int K, int N, double single_us) {
   if (K >= (1 << 23) || slab_rows(M, K) < (M < 2048 ? M : 2048)) return false;  // 32-bit offsets inside a tile
-  const double quant = 1.9 + 3.0 * M * (double)K / 7.2e6;
-  if (quant + 2.9 + 3.5 >= 0.95 * single_us) return false;  // (no tile takes less: the smallest calls end here, their host time counts)
-  return quant + tile_us(kGShapes[best_tile(M, K, N)], M, K, N) + 3.5 < 0.95 * single_us;
+  if (M < 8) return false;
+  const double most = 0.9 * single_us - 3.5 - 2.6 - 0.46e-6 * M * (double)K;
+  if (most <= 3.4) return false;  // (no tile takes less: the smallest calls end here, their host time counts)
+  return tile_us(kGShapes[best_tile(M, K, N)], M, K, N) < most;
 }
 
-size_t fp8_quant_gemm_two_pass_bytes(int M, int K) { return (size_t)slab_bytes(slab_rows(M, K), K); }
+size_t fp8_quant_gemm_two_pass_bytes(int M, int K) { return (size_t)(padded(slab_rows(M, K)) * row_bytes(K)); }
 
 int fp8_quant_gemm_two_pass_tile(int M, int K, int N) {
   const GShape g = kGShapes[best_tile(M, K, N)];
@@ -431,11 +535,13 @@ int fp8_quant_gemm_two_pass_tile(int M, int K, int N) {
 }
 
 namespace {
-void launch_quant(const bf16_t* a, unsigned char* codes, float* row_max, int M, int K, int64_t lda, hipStream_t s) {
+void launch_quant(const bf16_t* a, unsigned char* codes, float* maxima, int M, int K, int64_t lda, int pitch, hipStream_t s) {
   const int nv = K / 8;
+  const int run = M >= 2048 ? 32 : 1;
 #define RF_QUANT(VPT, WPR)                                                                                        \
-  hipLaunchKernelGGL((fp8_quant_rows_kernel<VPT, WPR>), dim3((unsigned)((M + 4 / WPR - 1) / (4 / WPR))),          \
-                     dim3(kGThreads), 0, s, a, codes, row_max, M, K, lda)
+  hipLaunchKernelGGL((fp8_quant_rows_kernel<VPT, WPR>),                                                          \
+                     dim3((unsigned)(WPR == 1 ? (M + 3) / 4 : (M + 8 * run - 1) / (8 * run) * (8 * run))),        \
+                     dim3(kGThreads), 0, s, a, codes, maxima, M, K, lda, pitch, run)
   if (nv <= 64) RF_QUANT(1, 1);
   else if (nv <= 128) RF_QUANT(2, 1);
   else if (nv <= 256) RF_QUANT(1, 4);
@@ -450,7 +556,8 @@ hipError_t launch_fp8_quant_gemm_two_pass(const void* a, const void* w, void* c,
                                           int64_t ldw, int64_t ldc, void* workspace, hipStream_t s) {
   const int slab = slab_rows(M, K);
   unsigned char* codes = (unsigned char*)workspace;
-  float* row_max = (float*)(codes + (int64_t)(slab + kPadRows - 1) / kPadRows * kPadRows * K);
+  const int pitch = (int)padded(slab);
+  float* maxima = (float*)(codes + (int64_t)pitch * K);  // [tile of 128 k][row]
   for (int r0 = 0; r0 < M; r0 += slab) {
     const int rows = M - r0 < slab ? M - r0 : slab;
     const int tile = best_tile(rows, K, N);
@@ -458,13 +565,13 @@ hipError_t launch_fp8_quant_gemm_two_pass(const void* a, const void* w, void* c,
     const int n_mt = (rows + g.m - 1) / g.m, n_nt = (N + g.n - 1) / g.n;
     // a grid of 2^32 threads or more is not launched whole
     if ((int64_t)n_mt * n_nt >= ((int64_t)1 << 32) / kGThreads) return hipErrorInvalidValue;
-    launch_quant((const bf16_t*)a + r0 * lda, codes, row_max, rows, K, lda, s);
+    launch_quant((const bf16_t*)a + r0 * lda, codes, maxima, rows, K, lda, pitch, s);
     bf16_t* cs = (bf16_t*)c + r0 * ldc;
 #define RF_GEMM_OF(TM, TN, WM, WN, WK, KH, NS, OCC) fp8_gemm_kernel<TM, TN, WM, WN, WK, KH, NS, OCC>
-#define RF_GEMM(I, P, L, R, S)                                                                                    \
+#define RF_GEMM(I, P, L, R, S, F, W)                                                                                   \
   if (tile == I)                                                                                                  \
-    hipLaunchKernelGGL((RF_GEMM_OF P), dim3((unsigned)(n_mt * n_nt)), dim3(kGThreads), 0, s, codes, row_max,      \
-                       (const unsigned char*)w, cs, rows, K, N, ldw, ldc, n_mt, n_nt);
+    hipLaunchKernelGGL((RF_GEMM_OF P), dim3((unsigned)(n_mt * n_nt)), dim3(RF_THREADS_OF P), 0, s, codes, maxima, \
+                       (const unsigned char*)w, cs, rows, K, N, ldw, ldc, pitch, n_mt, n_nt);
     RF_GTILES(RF_GEMM)
 #undef RF_GEMM
     if (hipError_t e = hipGetLastError()) return e;

@@ -155,8 +155,8 @@ hipError_t launch_fp8_quant_gemm_rows(const void* a, const void* w, void* c, int
 double fp8_quant_gemm_us(int M, int K, int N);
 double fp8_quant_gemm_rows_us(int M, int K, int N);
 
-// The same with a workspace of fp8_quant_gemm_two_pass_bytes(M, K) bytes, 16-byte aligned, for the tokens' codes:
-// quantisation and contraction in a launch each.  16-byte aligned rows of c, ldw < 2^23.
+// The same with a workspace of fp8_quant_gemm_two_pass_bytes(M, K) bytes, 16-byte aligned, for the tokens' codes
+// and maxima: quantisation and contraction in a launch each, the same codes.  16-byte aligned rows of c, ldw < 2^23.
 constexpr int64_t kFp8WorkspaceMax = (int64_t)128 << 20;
 bool fp8_quant_gemm_two_pass_wins(int M, int K, int N, double single_us);
 size_t fp8_quant_gemm_two_pass_bytes(int M, int K);

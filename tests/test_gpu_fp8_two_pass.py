@@ -1,6 +1,6 @@
 """FP8 quant + GEMM with a workspace: the quantisation and every tile of the contraction of
-fp8_quant_gemm_two_pass.hip against the two-pass definition, at the edges of their tiles, of the
-pieces that their stages and wavefronts take along k, and of the workspace."""
+fp8_quant_gemm_two_pass.hip against the incremental definition and against the single launch, at the
+edges of their tiles, of the pieces that their stages and wavefronts take along k, and of the workspace."""
 import ctypes
 import sys
 
@@ -21,11 +21,15 @@ pytestmark = pytest.mark.gpu
 # (tokens, channels) of the tile and products that take it: ragged in both directions, axes that leave stages,
 # wavefronts and vectors of the quantisation without work
 TWO_PASS_TILES = [
-    ((256, 256), (2521, 256, 6496)), ((256, 256), (2755, 3072, 3800)),
-    ((128, 256), (3923, 1152, 4736)), ((128, 256), (978, 3840, 7032)), ((128, 128), (1348, 3456, 2344)), ((128, 128), (641, 8320, 4104)),
-    ((64, 128), (141, 3456, 7208)), ((64, 128), (1333, 640, 976)), ((64, 64), (119, 640, 5936)), ((64, 64), (545, 5760, 1736)),
-    ((32, 64), (39, 5632, 4552)), ((32, 64), (300, 1152, 1000)), ((32, 32), (36, 7680, 2008)), ((32, 32), (33, 4224, 3080)),
+    ((256, 256), (2755, 3072, 3800)), ((256, 256), (1408, 6272, 6168)), ((256, 256), (3059, 1536, 5200)),
+    ((128, 128), (3923, 1152, 4736)), ((128, 128), (978, 3840, 7032)), ((128, 128), (3247, 512, 4728)),
+    ((64, 128), (1348, 3456, 2344)), ((64, 128), (641, 8320, 4104)), ((64, 128), (2102, 512, 7736)),
+    ((64, 64), (141, 3456, 7208)), ((64, 64), (119, 640, 5936)), ((64, 64), (545, 5760, 1736)),
+    ((32, 64), (39, 5632, 4552)), ((32, 64), (74, 768, 5208)), ((32, 64), (647, 8832, 504)),
+    ((32, 32), (33, 4224, 3080)), ((32, 32), (3153, 640, 16)), ((32, 32), (8, 4224, 8)), ((32, 32), (36, 12800, 2008)),
 ]
+# tokens x channels of the single launch's large tiles, over axes that its rings go round many times
+LARGE_TILES = [((128, 256), (900, 8320, 5000)), ((128, 256), (131, 4224, 7208)), ((128, 512), (1100, 4224, 7400)), ((128, 512), (1999, 8320, 4104))]
 
 
 def _abi(a, w, c, ws=None, ws_bytes=0):
@@ -37,16 +41,32 @@ def _abi(a, w, c, ws=None, ws_bytes=0):
     return lib.rf_fp8_quant_gemm_ws(r(d[0]), r(d[1]), r(d[2]), ctypes.c_void_p(ws.data_ptr()), ws_bytes, B._stream(None))
 
 
-def _close(c, ta, tw):
-    """c against the definition in fp64, from codes that torch rounds.  Every token is quantised with its whole
-    maximum, so what is left is half a bf16 step and the matrix instruction's own sums: it aligns the products of
-    an instruction to the largest before it adds them, up to 2^-16 of the products' magnitudes; four times that."""
-    m = ta.abs().amax(1, keepdim=True)
+def _dequantised(ta):
+    """The elements as quantised with the maximum of their row up to the end of their tile of 128 k, in fp64."""
+    M, K = ta.shape
+    t = ta.view(M, K // 128, 128)
+    m = t.abs().amax(2, keepdim=True).cummax(1).values
     # (448.0 / m would be 448 times a reciprocal: not the IEEE quotient)
-    codes = torch.where(m > 0, ta * (torch.full_like(m, 448.0) / m), torch.zeros_like(ta)).to(torch.float8_e4m3fn).double()
-    want = codes @ tw.double().T * (m.double() / 448.0)
-    mass = codes.abs() @ tw.double().abs().T * (m.double() / 448.0)
+    codes = torch.where(m > 0, t * (torch.full_like(m, 448.0) / m), torch.zeros_like(t)).to(torch.float8_e4m3fn).double()
+    return (codes * (m.double() / 448.0)).view(M, K)
+
+
+def _close(c, ta, tw):
+    """c against the definition in fp64, from codes that torch rounds.  What is left is half a bf16 step, the
+    reciprocals of the rescaling (2^-22 each) and the matrix instruction's own sums: it aligns the products of
+    an instruction to the largest before it adds them, up to 2^-16 of the products' magnitudes; four times that."""
+    hat = _dequantised(ta)
+    want, mass = hat @ tw.double().T, hat.abs() @ tw.double().abs().T
     assert bool(((c.double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -14 * mass).all())
+
+
+def _rising(M, K, seed):
+    """Tokens whose maximum moves in almost every tile (a third of them), somewhere, or never; none a power of two."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    a = rng.standard_normal((M, K)).astype(np.float32)
+    a[::3] *= np.exp2(np.linspace(-6, 3, K)).astype(np.float32)
+    a[1::3, :128] *= 8.0
+    return I.bf16_round(a)
 
 
 @pytest.mark.parametrize("tile,shape", TWO_PASS_TILES)
@@ -54,7 +74,8 @@ def test_fp8_two_pass_every_tile(rf, tile, shape):  # noqa: F811
     M, K, N = shape
     assert rf.rf_diag_fp8_quant_gemm_ws_tile(M, K, N) == tile
     say(f"fp8_quant_gemm two passes, tile {tile}: M{M} K{K} N{N}")
-    a, w, w_bits = I.fp8_quant_gemm_inputs(I.SEED_BASE + 70, M, K, N)
+    _, w, w_bits = I.fp8_quant_gemm_inputs(I.SEED_BASE + 70, 1, K, N)
+    a = _rising(M, K, 70 + M)
     a[M // 2] = 0.0
     big = torch.full((M + 1, K + 64), float("nan"), dtype=torch.bfloat16, device=DEV)
     big[:M, 8:K + 8] = I.to_torch(a, "bf16", DEV)
@@ -68,26 +89,77 @@ def test_fp8_two_pass_every_tile(rf, tile, shape):  # noqa: F811
     assert bool(torch.isnan(c[:, :8]).all()) and bool(torch.isnan(c[:, N + 8:]).all()) and bool(torch.isnan(c[M]).all())
 
 
-@pytest.mark.parametrize("M,K,N", [(300, 1152, 1000), (256, 4096, 1032)])
+@pytest.mark.parametrize("tile,shape", TWO_PASS_TILES)
+def test_fp8_result_does_not_depend_on_a_workspace(rf, tile, shape):  # noqa: F811
+    """The binding, which has memory here, and the C entry point without any: the same codes, so the same result up
+    to the order of fp32 sums; to the bit where both add a tile of 128 k after the other."""
+    M, K, N = shape
+    say(f"fp8_quant_gemm with and without a workspace: M{M} K{K} N{N}")
+    _, w, w_bits = I.fp8_quant_gemm_inputs(I.SEED_BASE + 78, 1, K, N)
+    ta, tw = I.to_torch(_rising(M, K, 78 + M), "bf16", DEV), _fp8_tensor(w_bits)
+    one = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+    assert _abi(ta, tw, one) == B.RF_OK
+    two = rf.rf_fp8_quant_gemm(ta, tw)
+    torch.cuda.synchronize()
+    if rf.rf_diag_fp8_quant_gemm_tile(M, K, N)[0] == 128 and tile[0] >= 64:
+        assert torch.equal(one, two)
+    else:
+        # sums that lie on either side of a rounding boundary leave as neighbours: a bf16 step, 2^-7 of the value at
+        # most, beside what the sums themselves differ by
+        mass = _dequantised(ta.float()).abs() @ tw.double().abs().T
+        assert bool(((one.double() - two.double()).abs() <= 2.0 ** -7 * one.double().abs() + 2.0 ** -14 * mass).all())
+
+
+@pytest.mark.parametrize("M,K,N", [(256, 2944, 1032), (171, 4224, 520), (600, 2048, 1032)])
 def test_fp8_two_pass_against_the_oracle(rf, M, K, N):  # noqa: F811
     say(f"fp8_quant_gemm two passes, oracle: M{M} K{K} N{N}")
     assert rf.rf_diag_fp8_quant_gemm_ws_tile(M, K, N) != (0, 0)
     a, w, w_bits = I.fp8_quant_gemm_inputs(I.SEED_BASE + 71, M, K, N)
+    first = list(range(0, M, 3))                         # these tokens have their maximum in the first element
+    a[first, 0] = I.bf16_round(1.5 * np.max(np.abs(a[first]), axis=1))
     c = rf.rf_fp8_quant_gemm(I.to_torch(a, "bf16", DEV), _fp8_tensor(w_bits))
     torch.cuda.synchronize()
-    F.check(I.to_numpy(c), a, w, "fp8_quant_gemm two passes", first_max_rows=list(range(M)))
+    F.check(I.to_numpy(c), a, w, "fp8_quant_gemm two passes", first_max_rows=first)
 
 
-def test_fp8_two_pass_infinities_and_nan(rf):  # noqa: F811
+@pytest.mark.parametrize("tile,shape", LARGE_TILES)
+def test_fp8_large_tiles_without_a_workspace(rf, tile, shape):  # noqa: F811
+    """The 128-token tiles of the single launch, which the binding takes only where it has no memory: long axes, late
+    maxima, strided operands."""
+    M, K, N = shape
+    assert rf.rf_diag_fp8_quant_gemm_tile(M, K, N) == tile
+    say(f"fp8_quant_gemm single launch, tile {tile}: M{M} K{K} N{N}")
+    _, w, w_bits = I.fp8_quant_gemm_inputs(I.SEED_BASE + 79, 1, K, N)
+    a = _rising(M, K, 79 + M)
+    a[M // 2] = 0.0
+    rng = np.random.Generator(np.random.PCG64(80))       # powers of two in rising runs: a @ w^T itself
+    a[5::7] = (np.exp2(np.sort(rng.integers(-7, 1, size=(len(a[5::7]), K)), axis=1)) *
+               rng.choice([-1.0, 1.0], size=(len(a[5::7]), K))).astype(np.float32)
+    big = torch.full((M + 1, K + 64), float("nan"), dtype=torch.bfloat16, device=DEV)
+    big[:M, 8:K + 8] = I.to_torch(a, "bf16", DEV)
+    wide = torch.full((N, K + 128), 1.0, device=DEV).to(torch.float8_e4m3fn)
+    wide.view(torch.uint8)[:, 16:K + 16] = _fp8_tensor(w_bits).view(torch.uint8)
+    c = torch.full((M + 1, N + 16), float("nan"), dtype=torch.bfloat16, device=DEV)
+    assert _abi(big[:M, 8:K + 8], wide[:, 16:K + 16], c[:M, 8:N + 8]) == B.RF_OK
+    torch.cuda.synchronize()
+    _close(c[:M, 8:N + 8], torch.from_numpy(a).to(DEV), torch.from_numpy(np.asarray(w, dtype=np.float32)).to(DEV))
+    ta, tw = torch.from_numpy(a[5::7]).to(DEV).double(), torch.from_numpy(np.asarray(w, dtype=np.float32)).to(DEV).double()
+    want, mass = ta @ tw.T, ta.abs() @ tw.abs().T
+    assert bool(((c[5:M:7, 8:N + 8].double() - want).abs() <= 2.0 ** -8 * want.abs() + 2.0 ** -14 * mass).all())
+    assert bool(torch.isnan(c[:, :8]).all()) and bool(torch.isnan(c[:, N + 8:]).all()) and bool(torch.isnan(c[M]).all())
+
+
+@pytest.mark.parametrize("M,K,N", [(600, 2048, 1032), (171, 4224, 520)])
+def test_fp8_two_pass_infinities_and_nan(rf, M, K, N):  # noqa: F811
     """A token with an infinity or a NaN gives NaN, the others what they gave without it."""
-    M, K, N = 300, 1152, 1000
+    assert rf.rf_diag_fp8_quant_gemm_ws_tile(M, K, N) != (0, 0)
     a, w, w_bits = I.fp8_quant_gemm_inputs(I.SEED_BASE + 72, M, K, N)
     ta, tw = I.to_torch(a, "bf16", DEV), _fp8_tensor(w_bits)
     clean = rf.rf_fp8_quant_gemm(ta, tw)
-    ta[7, 5], ta[40, K - 1], ta[299, 600] = float("inf"), float("nan"), float("-inf")
+    ta[7, 5], ta[40, K - 1], ta[M - 1, 600] = float("inf"), float("nan"), float("-inf")
     c = rf.rf_fp8_quant_gemm(ta, tw)
     torch.cuda.synchronize()
-    bad = [7, 40, 299]
+    bad = [7, 40, M - 1]
     assert bool(torch.isnan(c[bad]).all())
     keep = [i for i in range(M) if i not in bad]
     assert torch.equal(c[keep], clean[keep])
@@ -107,7 +179,7 @@ def test_fp8_tokens_beyond_the_workspace_go_in_turns(rf):  # noqa: F811
 
 
 def test_fp8_workspace_is_checked(rf):  # noqa: F811
-    M, K, N = 300, 1152, 1000
+    M, K, N = 600, 2048, 1032
     a, w = I.fp8_quant_gemm_inputs_device(I.SEED_BASE + 74, M, K, N, DEV)
     c = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
     need = B.load_library().rf_fp8_quant_gemm_workspace_bytes(M, K, N)

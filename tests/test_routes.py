@@ -139,7 +139,7 @@ def test_every_fp8_tile_has_a_gpu_test():
 
 def test_every_fp8_two_pass_tile_has_a_gpu_test():
     from test_gpu_fp8_two_pass import TWO_PASS_TILES
-    tiles = {(256, 256), (128, 256), (128, 128), (64, 128), (64, 64), (32, 64), (32, 32)}
+    tiles = {(256, 256), (128, 128), (64, 128), (64, 64), (32, 64), (32, 32)}
     assert {t for t, _ in TWO_PASS_TILES} == tiles
     for tile, shape in TWO_PASS_TILES:
         assert B.rf_diag_fp8_quant_gemm_ws_tile(*shape) == tile, shape
@@ -149,11 +149,19 @@ def test_every_fp8_two_pass_tile_has_a_gpu_test():
                 assert B.rf_diag_fp8_quant_gemm_ws_tile(M, K, N) in tiles | {(0, 0)}, (M, K, N)
 
 
+def test_every_large_fp8_tile_has_a_gpu_test_in_one_launch():
+    """The binding takes two launches for most of what the 128-token tiles serve: cases that the C entry point runs."""
+    from test_gpu_fp8_two_pass import LARGE_TILES
+    assert {t for t, _ in LARGE_TILES} == {(128, 256), (128, 512)}
+    for tile, shape in LARGE_TILES:
+        assert B.rf_diag_fp8_quant_gemm_tile(*shape) == tile and shape[1] >= 4096, shape
+
+
 @pytest.mark.parametrize("M,K,N,two", [
-    # few tokens or a short axis stay in one launch (us one launch / two: 6.5 / 7.2, 4.3 / 6.3, 4.7 / 6.0)
-    (1, 4096, 4096, False), (1, 1920, 1432, False), (9, 640, 1288, False), (1672, 256, 40, False),
-    # (142 / 108, 46 / 21, 42.6 / 13.4, 13.5 / 8.5, 46 / 15.8, 21.6 / 9.2)
-    (4096, 8192, 3584, True), (1348, 3456, 2336, True), (141, 3456, 7200, True), (64, 4096, 4096, True), (64, 8192, 8192, True),
+    # few tokens or a short axis stay in one launch (us one launch / two: 6.5 / 7.2, 4.3 / 6.3, 4.7 / 6.0, 13.5 / 11.5 and 3.5 more alone)
+    (1, 4096, 4096, False), (1, 1920, 1432, False), (9, 640, 1288, False), (1672, 256, 40, False), (64, 4096, 4096, False),
+    # (176 / 130, 48 / 26, 43 / 17, 46 / 19, 22 / 13)
+    (4096, 8192, 3584, True), (1348, 3456, 2336, True), (141, 3456, 7200, True), (64, 8192, 8192, True),
     (18, 5248, 5712, True),
     # nothing that rf_fp8_quant_gemm refuses, no axis beyond 32-bit offsets
     (300, 100, 1000, False), (300, 1152, 1001, False), (0, 1152, 1000, False), (300, -128, 1000, False), (300, 1 << 23, 1024, False),
