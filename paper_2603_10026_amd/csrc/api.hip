@@ -205,7 +205,7 @@ rf_status rf_variance(const rf_tensor* x, rf_tensor* mean, rf_tensor* var, rf_st
 
 size_t rf_moe_routing_workspace_bytes(int64_t S, int64_t hd, int64_t E) {
   if (S <= 0 || hd <= 0 || E <= 0 || S > INT32_MAX || hd > INT32_MAX) return 0;
-  return (size_t)rf::moe_num_slices((int)S, (int)hd, (int)E) * (size_t)S * (size_t)E * sizeof(float);
+  return (size_t)rf::moe_workspace_slices((int)S, (int)hd) * (size_t)S * (size_t)E * sizeof(float);
 }
 
 namespace {

@@ -805,7 +805,7 @@ static float* moe_static_scratch() {
 hipError_t launch_moe_routing_static(const void* x, const void* w, int S, int hd, int E, int topk,
                                      int64_t ldx, int64_t ldw, float* prob, int32_t* idx,
                                      int64_t ldp, int64_t ldi, hipStream_t s) {
-  if ((size_t)moe_num_slices(S, hd, E) * (size_t)S * (size_t)E * sizeof(float) > kMoeStaticScratchBytes)
+  if ((size_t)moe_workspace_slices(S, hd) * (size_t)S * (size_t)E * sizeof(float) > kMoeStaticScratchBytes)
     return hipErrorInvalidValue;  // (the C-ABI layer has already refused this size)
   float* part = moe_static_scratch();
   if (part == nullptr) return hipErrorInvalidSymbol;
@@ -820,17 +820,23 @@ hipError_t launch_moe_routing_static(const void* x, const void* w, int S, int hd
 // 13.7 and 7.9 us at 2048.
 constexpr int kMoeSingleSegmentMaxHd = 1024;
 
+// What a workspace holds: a slice for each round of 256 workgroups of 64 tokens.  The size a caller asks for, and what is
+// refused as too small or too large, hang on this alone: how the kernels cut the axis inside it is free to change.
+// (Rows of scores come to 16384 and less than S more, so a workspace for S tokens serves most smaller batches too.)
+int moe_workspace_slices(int S, int hd) {
+  if (hd <= kMoeSingleSegmentMaxHd) return 1;  // (one slice is still what the workspace query promises room for)
+  const int64_t n_rb = ((int64_t)S + kMoeRows - 1) / kMoeRows;
+  return (int)fmin(fmin((double)((256 + n_rb - 1) / n_rb), 64), hd / kMoeKB);
+}
+
 // How the axis is cut: a workgroup (one per compute unit) costs 1.2 us and 0.3 us for each of its tiles of 128 k
 // (0.7 with 128 tokens of 32 experts), a slice 0.05 us and 0.29 us for each MB of partial scores.  Fitted to 90 problems of
 // 1 to 6000 tokens and 1152 to 8192 k with every cut from 1 to 64; the one it takes is 0.8 % from the best on
 // average, 6 % at most.  2048 x 4096 x 128: 4 slices 11.9 us, 2 14.9; 512 x 4096 x 128: 8 slices 7.9, 16 8.8;
 // 2869 x 7552 x 128: 2 slices 21.2, 3, which the compute units take in two turns, 27.2.
 int moe_num_slices(int S, int hd, int E) {
-  if (hd <= kMoeSingleSegmentMaxHd) return 1;  // (one slice is still what the workspace query promises room for)
   const int64_t n_rb = ((int64_t)S * E + 4095) / 4096;
-  const int n_kblocks = hd / kMoeKB;
-  const double turn = ceil(256.0 / n_rb), turn64 = ceil(256.0 / ceil(S / 64.0));  // (two slices help 2^13 to 2^14 tokens too)
-  const int most = (int)fmin(fmin(64, n_kblocks), fmax(turn, turn64));
+  const int n_kblocks = hd / kMoeKB, most = moe_workspace_slices(S, hd);
   int best = 1;
   double best_us = 0;
   for (int ks = 1; ks <= most; ++ks) {
@@ -879,7 +885,7 @@ hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E
     return hipErrorInvalidValue;
   const bf16_t* xb = (const bf16_t*)x;
   const bf16_t* wb = (const bf16_t*)w;
-    if (hd <= kMoeSingleSegmentMaxHd && moe_fused64_wins(S, hd, E, topk)) {
+  if (hd <= kMoeSingleSegmentMaxHd && moe_fused64_wins(S, hd, E, topk)) {
 #define RF_MOE_FUSED64(NT)                                                                                        \
   hipLaunchKernelGGL((moe_fused64_kernel<NT>), dim3((unsigned)((S + kMoeRows - 1) / kMoeRows)), dim3(kMoeThreads), 0, s, xb, \
                      wb, S, n_kblocks, ldx, ldw, topk, prob, idx, ldp, ldi)

@@ -172,6 +172,21 @@ def test_fp8_workspace(M, K, N, two):
     assert (B.rf_diag_fp8_quant_gemm_ws_tile(M, K, N) != (0, 0)) == two
 
 
+def test_moe_workspace_of_a_large_batch_serves_smaller_ones():
+    """The size is 4 E bytes for each token and slice, a slice for every round of 256 workgroups of 64 tokens: 16384 rows
+    of scores and less than S more, whatever the kernels make of it."""
+    size = B.moe_routing_workspace_bytes
+    for hd in (64, 1024, 1152, 2176, 4096, 8192):
+        for E in (32, 64, 128):
+            for S in [*range(1, 20000, 37), 5440, 6000, 8000, 1 << 20, (1 << 31) - 1]:
+                slices = 1 if hd <= 1024 else min(-(-256 // -(-S // 64)), 64, hd // 128)
+                assert size(S, hd, E) == slices * S * E * 4, (S, hd, E)
+    # a program that asks once, for 8000 tokens
+    assert all(size(S, 4096, 128) <= size(8000, 4096, 128) for S in range(1, 8001))
+    # and what the entry point without a workspace takes of the largest hidden size: every other one is too large for it
+    assert [S for S in range(2048, 16385, 512) if size(S, 8192, 128) <= B.MOE_ROUTING_NOALLOC_MAX_BYTES] == [2048, 4096, 8192, 16384]
+
+
 def test_every_rmsnorm_tile_has_a_gpu_test():
     from test_gpu_rmsnorm_rows import RMSNORM_TILES
     for tile, shape in RMSNORM_TILES:

@@ -36,7 +36,9 @@ def _one(rf, seed, S, hd, E, topk):
 
 def test_noalloc_matches_workspace_entry_point_twice(rf):
     assert rf.moe_routing_workspace_bytes(2048, 4096, 128) <= rf.MOE_ROUTING_NOALLOC_MAX_BYTES
-    _one(rf, 31, 2048, 4096, 128, 8)       # the largest table shape: fills the scratch array
+    assert rf.moe_routing_workspace_bytes(16384, 1152, 128) == rf.MOE_ROUTING_NOALLOC_MAX_BYTES
+    _one(rf, 30, 16384, 1152, 128, 8)      # one slice, every byte of the scratch array
+    _one(rf, 31, 2048, 4096, 128, 8)       # the largest table shape
     _one(rf, 32, 300, 1024, 64, 4)         # smaller, ragged last row block, fewer slices and experts
     _one(rf, 33, 2048, 8192, 64, 8)
 
