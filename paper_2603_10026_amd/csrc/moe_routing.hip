@@ -369,8 +369,8 @@ __global__ __launch_bounds__(kMoeFusedWaves * kWave, 2) void moe_fused_kernel(
 // with 32 tokens of 128 experts half as many slices fill the chip as with 64, so half the partial
 // scores pass through memory.  What bounds it is that one trip: launch, the first tile's latency, x at
 // the rate of memory, the partial scores.  Both launches, 64 tokens a workgroup with the tiles' steps dealt to
-// the wavefronts / this: 2048 x 4096 x 128, top 8, 15.9 / 11.9 us, 512 x 4096 x 128 13.3 / 7.9,
-// 2869 x 7552 x 128 29.0 / 21.0, 2940 x 3456 x 64 15.8 / 10.2; 32 experts 1 to 5 % (4056 x 4096: 10.6 / 11.1).
+// the wavefronts / this: 2048 x 4096 x 128, top 8, 17.4 / 13.3 us, 512 x 4096 x 128 15.4 / 9.5,
+// 3000 x 8192 x 128 31.5 / 26.2, 2048 x 8192 x 64 14.2 / 13.5; 32 experts 4096 x 4096 12.4 / 11.9.
 template <int E>
 struct MoeTile {
   static constexpr int kWaveE = E / 32, kWaveT = 4 / kWaveE;  // wavefronts along experts and tokens
@@ -381,15 +381,21 @@ struct MoeTile {
   static_assert(kStages == 4, "three tiles in flight: the waits below");
 };
 
-template <int E>
-__global__ __launch_bounds__(kMoeThreads, 1) void moe_scores_kernel(
+// NA sums for a tile's eight steps of 16 k in turn, added up pairwise at the end, with 8 after every 16 tiles too: no
+// chain is longer than those of four wavefronts that share a tile's steps over a third of the axis.  One chain over a
+// slice is 0.3 us faster and its error against 64 bits larger, 2048 x 4096 x 128 3.7e-7 (here 2.0e-7), 6000 x 8192 x 128
+// 16e-7 (2.2e-7).  (Adding up costs some 0.5 us each time, so short slices make do with 4 sums.)  LDS is handed over by
+// the launch: with its size known the compiler would keep the sums in registers that the vector ALU does not reach.
+constexpr int kMoeFoldTiles = 16;
+template <int E, int NA>
+__global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, float* __restrict__ part, int S,
     int n_kblocks, int64_t ldx, int64_t ldw) {
   using T = MoeTile<E>;
   constexpr int PPR = E / 8;                // 16-byte pieces of a row of w
   constexpr int kXLoads = T::kXB / 4096, kWLoads = T::kWB / 4096;  // direct-to-LDS loads per wavefront and tile
   constexpr int kLoads = kXLoads + kWLoads, NS = T::kStages;
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[NS * T::kStageB];
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -453,9 +459,21 @@ __global__ __launch_bounds__(kMoeThreads, 1) void moe_scores_kernel(
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
 
-  f32x16 acc;  // rows = tokens, columns = experts
+  f32x16 acc[NA], sum;  // rows = tokens, columns = experts
+  auto clear = [&](f32x16& v) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int r = 0; r < 16; ++r) v[r] = 0.f;
+  };
+#pragma unroll
+  for (int c = 0; c < NA; ++c) clear(acc[c]);
+  clear(sum);
+  auto fold = [&]() {
+#pragma unroll
+    for (int h = NA / 2; h >= 1; h /= 2)
+#pragma unroll
+      for (int c = 0; c < h; ++c) acc[c] += acc[c + h];
+    sum += acc[0];
+  };
 
   // NS - 1 tiles are in flight; the one that follows them goes to the stage that the tile before this one left.
 #pragma unroll
@@ -484,18 +502,24 @@ __global__ __launch_bounds__(kMoeThreads, 1) void moe_scores_kernel(
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) {
       const auto b = __builtin_shufflevector(bw[kk][0], bw[kk][1], 0, 1, 2, 3, 4, 5, 6, 7);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bx[kk]), __builtin_bit_cast(bf16x8, b), acc,
-                                                    0, 0, 0);
+      acc[kk % NA] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bx[kk]), __builtin_bit_cast(bf16x8, b),
+                                                        acc[kk % NA], 0, 0, 0);
     }
     stage = stage == NS - 1 ? 0 : stage + 1;
+    if (NA == 8 && blk % kMoeFoldTiles == kMoeFoldTiles - 1) {
+      fold();
+#pragma unroll
+      for (int c = 0; c < NA; ++c) clear(acc[c]);
+    }
   }
+  fold();
 
   // A register is one token's 32 experts over 32 lanes: 128 contiguous bytes.
   float* dst = part + ((int64_t)ks * S + row0 + 32 * wt) * E + 32 * we + i32;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int t = 8 * (r >> 2) + 4 * hh + (r & 3);
-    if (row0 + 32 * wt + t < S) dst[(int64_t)t * E] = acc[r];
+    if (row0 + 32 * wt + t < S) dst[(int64_t)t * E] = sum[r];
   }
 }
 
@@ -912,15 +936,20 @@ hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E
 #undef RF_MOE_FUSED
     return hipGetLastError();
   }
-#define RF_MOE_SCORES(EE)                                                                                         \
-  hipLaunchKernelGGL((moe_scores_kernel<EE>), dim3((unsigned)((S + MoeTile<EE>::kTokens - 1) / MoeTile<EE>::kTokens), (unsigned)KS), \
-                     dim3(kMoeThreads), 0, s, xb, wb, part, S, n_kblocks, ldx, ldw)
+  const bool long_slices = (n_kblocks + KS - 1) / KS > 8;
+#define RF_MOE_SCORES_NA(EE, NA)                                                                                  \
+  hipLaunchKernelGGL((moe_scores_kernel<EE, NA>), dim3((unsigned)((S + MoeTile<EE>::kTokens - 1) / MoeTile<EE>::kTokens), (unsigned)KS), \
+                     dim3(kMoeThreads), MoeTile<EE>::kStages * MoeTile<EE>::kStageB, s, xb, wb, part, S, n_kblocks, ldx, ldw)
+#define RF_MOE_SCORES(EE)                    \
+  if (long_slices) RF_MOE_SCORES_NA(EE, 8); \
+  else RF_MOE_SCORES_NA(EE, 4)
   switch (E) {
     case 32: RF_MOE_SCORES(32); break;
     case 64: RF_MOE_SCORES(64); break;
     case 128: RF_MOE_SCORES(128); break;
     default: return hipErrorInvalidValue;
   }
+#undef RF_MOE_SCORES_NA
 #undef RF_MOE_SCORES
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

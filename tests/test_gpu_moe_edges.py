@@ -131,3 +131,23 @@ def test_moe_routing_equal_scores_in_every_place(rf, hd, E):  # noqa: F811
     s[:, 3] = -1e30
     order = torch.argsort(s, dim=1, descending=True, stable=True)[:, :8]
     assert torch.equal(idx.cpu().long(), order) and bool(torch.isnan(prob).all())
+
+
+@pytest.mark.parametrize("S,hd,E,topk,error", [
+    (2048, 4096, 128, 8, 2.03e-7), (5620, 3200, 128, 8, 2.01e-7), (6000, 8192, 128, 4, 2.68e-7), (2048, 8192, 64, 8, 1.95e-7),
+    (4096, 4096, 32, 4, 1.58e-7),
+])
+def test_moe_routing_error_against_64_bits(rf, S, hd, E, topk, error):  # noqa: F811
+    """The probabilities' distance from fp64, as four wavefronts with a quarter of a tile's steps each left it, and a
+    seventh more: short slices and long ones that are added up on the way.  (One chain of sums over a slice is 1.3, with
+    long slices up to 6 times as far off.)"""
+    say(f"moe_routing error S{S} hd{hd} E{E} top{topk}")
+    off = []
+    for seed in (3, 4, 5):
+        x, w = I.moe_routing_inputs_device(seed, S, hd, E, device=DEV)
+        prob, idx = rf.rf_moe_routing(x, w, topk)
+        torch.cuda.synchronize()
+        want = torch.softmax(x.double() @ w.double(), 1).gather(1, idx.long())
+        off.append(float((prob.double() - want).norm() / want.norm()))
+    print(f"        {off}", flush=True)
+    assert sum(off) / 3 <= 1.15 * error
