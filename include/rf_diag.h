@@ -71,6 +71,9 @@ RF_API int rf_diag_splitk_route(const rf_tensor* q, const rf_tensor* k, const rf
  */
 RF_API int rf_diag_rmsnorm_gemm_tile(int64_t M, int64_t K, int64_t N);
 RF_API int rf_diag_fp8_quant_gemm_tile(int64_t M, int64_t K, int64_t N);
+/* Whether a tile of up to 32 x 64 of rf_rmsnorm_gemm takes its operands straight into registers (1) or through LDS (0);
+ * w_pitch: elements between rows of w. */
+RF_API int rf_diag_rmsnorm_gemm_straight(int64_t M, int64_t K, int64_t N, int64_t w_pitch);
 /* The tile of the product that the entry points with a workspace run in a launch of its own; 0 where they are the
  * ones without. */
 RF_API int rf_diag_rmsnorm_gemm_ws_tile(int64_t M, int64_t K, int64_t N);

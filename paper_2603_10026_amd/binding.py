@@ -51,6 +51,7 @@ DIAG_ENTRY_POINTS = (
     "rf_diag_splitk_route",
     "rf_diag_rmsnorm_gemm_tile",
     "rf_diag_fp8_quant_gemm_tile",
+    "rf_diag_rmsnorm_gemm_straight",
     "rf_diag_rmsnorm_gemm_ws_tile",
     "rf_diag_fp8_quant_gemm_ws_tile",
     "rf_diag_attention_wide",
@@ -146,6 +147,8 @@ def load_library():
               lib.rf_diag_fp8_quant_gemm_ws_tile):
         f.restype = ctypes.c_int
         f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64]
+    lib.rf_diag_rmsnorm_gemm_straight.restype = ctypes.c_int
+    lib.rf_diag_rmsnorm_gemm_straight.argtypes = [ctypes.c_int64] * 4
     lib.rf_diag_copy.restype = ctypes.c_int
     lib.rf_diag_copy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
     lib.rf_diag_read.restype = ctypes.c_int
@@ -369,6 +372,11 @@ def rf_diag_rmsnorm_gemm_tile(M, K, N):
 def rf_diag_fp8_quant_gemm_tile(M, K, N):
     """(tokens, channels) of the output tile that rf_fp8_quant_gemm takes for these sizes."""
     return divmod(load_library().rf_diag_fp8_quant_gemm_tile(M, K, N), 1000)
+
+
+def rf_diag_rmsnorm_gemm_straight(M, K, N, w_pitch=None):
+    """True where rf_rmsnorm_gemm takes a tile of up to 32 x 64 with operands straight into registers."""
+    return bool(load_library().rf_diag_rmsnorm_gemm_straight(M, K, N, N if w_pitch is None else w_pitch))
 
 
 def rf_diag_rmsnorm_gemm_ws_tile(M, K, N):

@@ -591,6 +591,11 @@ rf_status rf_rmsnorm_gemm_ws(const rf_tensor* x, const rf_tensor* g, const rf_te
   return e == hipSuccess ? RF_OK : RF_ERR_LAUNCH;
 }
 
+int rf_diag_rmsnorm_gemm_straight(int64_t M, int64_t K, int64_t N, int64_t w_pitch) {
+  const int tile = rf_diag_rmsnorm_gemm_tile(M, K, N);
+  return tile != 0 && tile / 1000 <= 32 && tile % 1000 <= 64 && rf::rmsnorm_gemm_rows_straight((int)M, (int)K, (int)N, w_pitch);
+}
+
 int rf_diag_rmsnorm_gemm_ws_tile(int64_t M, int64_t K, int64_t N) {
   if (rf_rmsnorm_gemm_workspace_bytes(M, K, N) == 0) return 0;
   return rf::rmsnorm_gemm_two_pass_tile((int)M, (int)K, (int)N);

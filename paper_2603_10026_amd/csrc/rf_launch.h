@@ -103,6 +103,7 @@ hipError_t launch_rmsnorm_gemm_bf16(const void* x, const void* g, const void* w,
 // The same for few rows, 16-byte aligned rows of y, w within 4 GiB (the launcher above chooses).
 bool rmsnorm_gemm_rows_wins(int M, int K, int N, int64_t ldw, const void* y, int64_t ldy);
 int rmsnorm_gemm_rows_tile(int M, int K, int N);  // 1000 rows + columns of the tile it takes
+bool rmsnorm_gemm_rows_straight(int M, int K, int N, int64_t ldw);  // small tiles: operands straight into registers
 hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w, void* y, int M,
                                     int K, int N, int64_t ldx, int64_t ldw, int64_t ldy, float eps,
                                     hipStream_t s);

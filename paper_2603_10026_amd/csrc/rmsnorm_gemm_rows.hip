@@ -413,23 +413,23 @@ const RowsShape& best_shape(int M, int K, int N) {
     if (rows_us(r, M, K, N) < rows_us(*best, M, K, N)) best = &r;
   return *best;
 }
-// Which of the tiles that have both kernels take operands straight into registers.  The LDS kernel's 8 wavefronts
-// need a piece of 64 k each, and its requests under way are what its stages hold: straight is the shorter way where a
-// short axis leaves half of the wavefronts without a piece, and where w comes from beyond the L2 to so many workgroups
-// that their number has the requests under way.  us straight / LDS, three sets of operands in turn: 3 x 256 x 4752
-// 3.2 / 3.4, 153 x 384 x 744 3.9 / 4.1; 3 x 704 x 7608 5.8 / 6.1; 1 x 2304 x 1208 6.7 / 7.2, 1 x 1280 x 2136 5.0 / 5.3, but 1 x 2240 x 416
-// 5.9 / 4.6, 1 x 1664 x 1920 5.4 / 4.9; 3 x 4992 x 1056 10.0 / 10.7; 19 x 2816 x 5744 11.3 / 12.2, 8 x 4160 x 5424 14.6 / 15.0, but 48 x 4096 x
-// 4096 14.9 / 13.3, 16 x 4096 x 4096 14.3 / 12.4, 13 x 2048 x 6168 9.9 / 9.6, 21 x 7488 x 7208 37.9 / 34.9.  Over 420 products
-// of 1 to 400 rows LDS throughout is 1.067 times as fast as straight throughout, this rule 1.07; LDS alone loses
-// up to 8 %.
-bool straight(const RowsShape& r, int M, int K, int N) {
+// Which of the tiles that have both kernels take operands straight into registers.  LDS serves every tile whose w comes
+// out of an L2 (several row tiles, which share it: 0.87 to 0.98 of the time in 365 of 365 products), and rows of w that all
+// start on the same memory channels (a pitch of whole 256 bytes, which piles up the 4 or 8 rows that a register load
+// of w touches: 0.88, 1.02 at most).  What is left is one row tile whose w comes from memory once.  There straight is the
+// shorter way, by up to 10 %, where a short axis leaves the LDS kernel's 8 wavefronts without a piece of 64 k each, where many
+// workgroups have requests enough under way, and with a handful of rows, whose LDS stages are mostly padding, already
+// where few of them do, the fewer the longer the axis.  us straight / LDS, three sets of operands in turn: 48 x 4096 x
+// 4096 15.3 / 13.6, 16 x 4096 x 4096 14.7 / 12.6, 37 x 2880 x 616 9.0 / 8.4; 19 x 1408 x 4784 7.55 / 7.9, 18 x 1024 x 6648 7.1 / 7.6,
+// 3 x 2304 x 872 6.9 / 7.4, 2 x 768 x 4792 5.0 / 5.3, 1 x 448 x 8776 5.65 / 6.1.  Of 2100 products of 1 to 400 rows, two thirds
+// of them drawn after the lines were placed, one is slower than straight by more than 2 % (1 x 7296 x 120, 2.8); the
+// others gain 1.08 on average, 1.10 if every one took its better kernel.
+bool straight(const RowsShape& r, int M, int K, int N, int64_t ldw) {
   if (r.mt == 2 && r.c == 4) return false;
-  const double w = (double)K * N;
-  if (K <= (r.mt == 2 ? 512 : 256)) return true;
-  if (M <= 2 && K > 2048 && w >= 1.8e6) return true;
-  if (M <= 3 && K >= 900 && w >= 2.6e6) return true;
-  if (M <= 5 && (K > 4096 || w >= 4.5e6)) return true;
-  return N >= 5200 && (K > 1024 || r.mt == 2);
+  if (K <= 256) return true;
+  if (M > 16 * r.mt || ldw % 128 == 0) return false;
+  const int wg = (N + 16 * r.c - 1) / (16 * r.c);
+  return wg > 128 || (M <= 5 && wg > (K <= 2048 ? 40 : K <= 4096 ? 20 : 16));
 }
 }  // namespace
 
@@ -451,6 +451,8 @@ double rmsnorm_gemm_us(int M, int K, int N) {
   if (!rmsnorm_gemm_rows_wins(M, K, N, N, nullptr, N)) return large_us(M, K, N);
   return (r.mt <= 2 && r.c <= 4 ? 0.9 : 1.0) * rows_us(r, M, K, N);
 }
+
+bool rmsnorm_gemm_rows_straight(int M, int K, int N, int64_t ldw) { return straight(best_shape(M, K, N), M, K, N, ldw); }
 
 int rmsnorm_gemm_rows_tile(int M, int K, int N) {
   const RowsShape& r = best_shape(M, K, N);
@@ -476,7 +478,7 @@ hipError_t launch_rmsnorm_gemm_rows(const void* x, const void* g, const void* w,
     hipLaunchKernelGGL((rmsnorm_gemm_rows_lds_kernel<MT, C>), dim3((unsigned)grid), dim3(kLThreads), 0, s, \
                        (const bf16_t*)x, (const bf16_t*)g, (const bf16_t*)w, (bf16_t*)y, M, K, N, ldx, ldw, \
                        ldy, 1.0f / (float)K, eps, n_mt);
-  if (straight(best, M, K, N)) {
+  if (straight(best, M, K, N, ldw)) {
     RF_ROWS(1, 2, 4) RF_ROWS(2, 2, 2) RF_ROWS(1, 4, 2)
   } else {
     RF_ROWS_LDS(1, 2) RF_ROWS_LDS(2, 2) RF_ROWS_LDS(1, 4) RF_ROWS_LDS(2, 4)

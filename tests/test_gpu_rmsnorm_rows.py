@@ -71,18 +71,36 @@ def test_rmsnorm_gemm_rows_do_not_depend_on_their_batch(rf):  # noqa: F811
         assert bool(((part - want).abs() <= 2.0 ** -7 * want.abs() + 1e-4 * want.abs().max()).all())
 
 
-@pytest.mark.parametrize("M,K,N", [
-    # (tiles of up to 32 rows x 64 columns) pieces of 64 k that leave wavefronts without one, the next 4096 values of g
-    # after 64 pieces, a handful of rows against much of w, strided rows of x and w, columns that end in a tile's middle
-    (6, 64, 8), (6, 512, 40), (7, 576, 136), (20, 4096, 520), (20, 4160, 264), (37, 8192, 264), (40, 8256, 72), (130, 12352, 136),
-    (5, 4352, 2056), (6, 4352, 2056), (300, 1472, 544), (64, 768, 2952),
-    # both sides of the rule on short axes, on a row or two and on wide products
-    (9, 256, 4280), (9, 320, 4280), (153, 512, 744), (153, 576, 744), (2, 2112, 1736), (3, 2112, 1736), (3, 896, 2952), (3, 960, 2952), (20, 1088, 5192),
-    (20, 1088, 5208), (13, 1088, 8200), (13, 1024, 8200),
-])
-def test_rmsnorm_gemm_few_rows_strided(rf, M, K, N):  # noqa: F811
+# (tiles of up to 32 rows x 64 columns; w in rows of N + 24) operands straight into registers or through LDS, and products
+# that go there: every instance (test_routes.py holds the list against the rule)
+STRAIGHT, LDS = True, False
+RMSNORM_SMALL_TILES = [
+    # pieces of 64 k that leave wavefronts without one, the next 4096 values of g after 64 pieces, a handful of rows
+    # against much of w, columns that end in a tile's middle
+    (STRAIGHT, (6, 64, 8)), (LDS, (6, 512, 40)), (LDS, (7, 576, 136)), (LDS, (20, 4096, 520)), (LDS, (20, 4160, 264)), (LDS, (37, 8192, 264)),
+    (LDS, (40, 8256, 72)), (LDS, (130, 12352, 136)), (STRAIGHT, (5, 4352, 2056)), (LDS, (6, 4352, 2056)), (LDS, (300, 1472, 544)),
+    (LDS, (64, 768, 2952)),
+    # both sides of the rule: short axes
+    (STRAIGHT, (9, 256, 4280)), (STRAIGHT, (153, 256, 744)), (LDS, (153, 320, 744)), (LDS, (153, 512, 744)), (LDS, (153, 576, 744)),
+    (STRAIGHT, (5, 192, 8200)), (STRAIGHT, (20, 256, 5192)), (STRAIGHT, (33, 256, 4104)),
+    # one row tile before many columns, several row tiles
+    (STRAIGHT, (9, 320, 4104)), (LDS, (9, 320, 4080)), (STRAIGHT, (9, 320, 4280)), (STRAIGHT, (13, 1024, 8200)), (STRAIGHT, (13, 1088, 8200)),
+    (LDS, (34, 1344, 4192)), (STRAIGHT, (20, 1088, 5192)), (STRAIGHT, (20, 1088, 5208)), (STRAIGHT, (32, 1088, 5192)), (LDS, (33, 1088, 5192)),
+    # up to five rows: fewer columns the longer the axis
+    (STRAIGHT, (5, 1024, 1288)), (LDS, (5, 1024, 1272)), (LDS, (6, 1024, 1288)), (STRAIGHT, (5, 2112, 648)), (LDS, (5, 2112, 632)),
+    (STRAIGHT, (5, 4160, 520)), (LDS, (5, 4160, 504)), (STRAIGHT, (2, 2112, 1736)), (STRAIGHT, (3, 2112, 1736)), (STRAIGHT, (3, 896, 2952)),
+    (STRAIGHT, (3, 960, 2952)),
+    # rows of w 256 bytes apart or a multiple
+    (LDS, (9, 320, 4072)), (LDS, (5, 4352, 2024)),
+]
+
+
+@pytest.mark.parametrize("straight,shape", RMSNORM_SMALL_TILES)
+def test_rmsnorm_gemm_few_rows_strided(rf, straight, shape):  # noqa: F811
+    M, K, N = shape
     tile = rf.rf_diag_rmsnorm_gemm_tile(M, K, N)
     assert tile in ((16, 32), (16, 64), (32, 32), (32, 64))
+    assert rf.rf_diag_rmsnorm_gemm_straight(M, K, N, N + 24) == straight
     say(f"rmsnorm_gemm few rows, strided, tile {tile}: M{M} K{K} N{N}")
     x, g, w = I.rmsnorm_gemm_inputs(I.SEED_BASE + 52 + M, M, K, N)
     bx = torch.full((M, K + 72), float("nan"), dtype=torch.bfloat16, device=DEV)

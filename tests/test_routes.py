@@ -199,6 +199,31 @@ def test_every_rmsnorm_tile_has_a_gpu_test():
                 assert B.rf_diag_rmsnorm_gemm_tile(M, K, N) in tiles | {(128, 512)}, (M, K, N)
 
 
+def test_every_kernel_of_the_small_rmsnorm_tiles_has_a_gpu_test():
+    from test_gpu_rmsnorm_rows import RMSNORM_SMALL_TILES
+    tile, straight = B.rf_diag_rmsnorm_gemm_tile, B.rf_diag_rmsnorm_gemm_straight
+    for want, shape in RMSNORM_SMALL_TILES:
+        assert straight(*shape, shape[2] + 24) == want, shape
+    both = {((16, 32), True), ((16, 32), False), ((16, 64), True), ((16, 64), False), ((32, 32), True), ((32, 32), False),
+            ((32, 64), False)}
+    assert {(tile(*s), want) for want, s in RMSNORM_SMALL_TILES} == both
+    for M in (1, 5, 16, 17, 33, 100, 400):
+        for K in (64, 256, 512, 2048, 4096, 8192):
+            for N in (8, 136, 520, 1032, 4104, 8200):
+                if tile(M, K, N) in {t for t, _ in both}:
+                    assert (tile(M, K, N), straight(M, K, N)) in both, (M, K, N)
+
+
+@pytest.mark.parametrize("M,K,N,straight", [
+    # one row tile against many columns, a handful of rows (us straight / LDS: 6.9 / 7.4, 5.0 / 5.3, 7.55 / 7.9, 5.65 / 6.1, 6.1 / 6.35)
+    (3, 2304, 872, True), (2, 768, 4792, True), (19, 1408, 4784, True), (1, 448, 8776, True), (3, 704, 7608, True),
+    # several row tiles, rows of w on the same memory channels (15.3 / 13.6, 14.7 / 12.6, 9.0 / 8.4, 5.8 / 4.1)
+    (48, 4096, 4096, False), (16, 4096, 4096, False), (37, 2880, 616, False), (4, 5952, 512, False),
+])
+def test_small_rmsnorm_products_take_the_kernel_that_serves_them_faster(M, K, N, straight):
+    assert B.rf_diag_rmsnorm_gemm_straight(M, K, N) == straight
+
+
 def test_every_rmsnorm_two_pass_tile_has_a_gpu_test():
     from test_gpu_rmsnorm_two_pass import NORM_TILES
     tiles = {(256, 256), (128, 256), (128, 128), (64, 128), (64, 64)}
