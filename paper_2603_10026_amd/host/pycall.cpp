@@ -119,22 +119,24 @@ bool describe_all(PyObject* const* args, Py_ssize_t n, rf_tensor (&d)[N], const 
 // tensor on the current device, no memory left, an allocator that is not torch's own); the call then
 // does without.  So does a call in a capture that torch does not know of: replays of such a graph
 // would run on memory that has been handed on.  torch's own captures take from the graph's pool.
+// The allocator may have to ask the driver for memory, which a capture in global mode on
+// any other thread forbids to threads that have not relaxed their own mode.
 class Scratch {
  public:
   Scratch(size_t bytes, int device, rf_stream s) {
     if (bytes == 0 || device < 0) return;
     try {
-      if (device != c10::hip::current_device()) return;
       const hipStream_t stream = static_cast<hipStream_t>(s);
+      if (device != c10::hip::current_device()) return;
       hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
         (void)hipGetLastError();
         return;
       }
+      c10::hip::HIPStreamCaptureModeGuard relaxed{hipStreamCaptureModeRelaxed};
       if (capture == hipStreamCaptureStatusNone) {
         data_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream);
       } else if (stream == c10::hip::getCurrentHIPStream().stream()) {
-        c10::hip::HIPStreamCaptureModeGuard relaxed{hipStreamCaptureModeRelaxed};
         data_ = c10::hip::HIPCachingAllocator::raw_alloc_with_stream(bytes, stream);
         if (!in_graph_pool()) release();
       }

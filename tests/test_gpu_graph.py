@@ -1,5 +1,6 @@
 """The library under HIP graph capture: every entry point only launches kernels on
-the stream it is given (no allocation, no memset, no synchronisation), so a
+the stream it is given (no memset, no synchronisation; where the binding hands a call a
+workspace, torch's allocator has it from the graph's pool), so a
 sequence of calls can be captured once and replayed.  Each replay is checked
 bit for bit against the eager result, with eager work and synchronisations
 between the replays, and the eager result is checked against the oracle.
