@@ -119,7 +119,8 @@ bool describe_all(PyObject* const* args, Py_ssize_t n, rf_tensor (&d)[N], const 
 // tensor on the current device, no memory left, an allocator that is not torch's own); the call then
 // does without.  So does a call in a capture that torch does not know of: replays of such a graph
 // would run on memory that has been handed on.  torch's own captures take from the graph's pool.
-// The allocator may have to ask the driver for memory, which a capture in global mode on
+// So does a call on hipStreamPerThread: the handle is one, the streams are many, and the allocator goes
+// by the handle.  The allocator may have to ask the driver for memory, which a capture in global mode on
 // any other thread forbids to threads that have not relaxed their own mode.
 class Scratch {
  public:
@@ -127,7 +128,7 @@ class Scratch {
     if (bytes == 0 || device < 0) return;
     try {
       const hipStream_t stream = static_cast<hipStream_t>(s);
-      if (device != c10::hip::current_device()) return;
+      if (device != c10::hip::current_device() || stream == hipStreamPerThread) return;
       hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
       if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
         (void)hipGetLastError();

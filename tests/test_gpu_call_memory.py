@@ -1,5 +1,6 @@
 """The memory that the binding hands to calls which take a workspace (bf16 attention cut over the keys, RMSNorm + linear
-and FP8 quant + GEMM in two launches): beside a capture on another thread, and in a capture that torch does not know of."""
+and FP8 quant + GEMM in two launches): beside a capture on another thread, in a capture that torch does not know of, and
+on the stream handle that means another stream to every thread."""
 import ctypes
 import sys
 import threading
@@ -122,3 +123,19 @@ def test_a_capture_that_torch_does_not_know_of(rf, name):  # noqa: F811
         junk = torch.full((op.need,), 0xff, dtype=torch.uint8, device=DEV)
         del junk
     assert hip.hipGraphExecDestroy(execg) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+@pytest.mark.parametrize("name", OPS)
+def test_the_stream_handle_that_is_another_stream_on_every_thread(rf, name):  # noqa: F811
+    """hipStreamPerThread (handle 2): memory given back for one thread's stream must not go to another's, so there is
+    none."""
+    say(f"{name} on hipStreamPerThread")
+    op = Op(name)
+    want = op.result(op.one)
+    op.out.zero_()
+    torch.cuda.synchronize()
+    taken = torch.cuda.memory_stats()["allocation.all.allocated"]
+    op.call(2)
+    torch.cuda.synchronize()
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == taken
+    assert torch.equal(op.out, want)
