@@ -148,6 +148,7 @@ __global__ __launch_bounds__(kGThreads) void fp8_quant_rows_kernel(const bf16_t*
   }
 }
 
+namespace {
 template <int TM, int TN, int WM, int WN, int WK, int KH, int NS>
 struct GTile {
   static constexpr int kWaves = WM * WN * WK, kThreads = kWaves * kWave;
@@ -166,6 +167,7 @@ struct GTile {
   static constexpr int kOutB = WK > 1 ? 4 * TM * TN * 4096 + 4 * 32 * 80 : kWaves * 32 * (64 * TN + 16);
   static constexpr int kLdsB = NS * kStageB > kOutB ? NS * kStageB : kOutB;
 };
+}  // namespace
 
 template <int TM, int TN, int WM, int WN, int WK, int KH, int NS, int OCC>
 __global__ __launch_bounds__(WM * WN * WK * kWave, OCC) void fp8_gemm_kernel(

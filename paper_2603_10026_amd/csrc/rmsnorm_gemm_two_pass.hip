@@ -81,6 +81,7 @@ __global__ __launch_bounds__(kGThreads) void rms_rows_kernel(const bf16_t* __res
   if (vec == 0) row_scale[row] = 1.0f / sqrtf(ss * inv_k + eps);
 }
 
+namespace {
 template <int TM, int TN, int WM, int WN, int KH, int NS>
 struct GTile {
   static_assert(WM * WN == 4, "4 wavefronts");
@@ -92,6 +93,7 @@ struct GTile {
   static constexpr int kOutB = 4 * 32 * (64 * TN + 16);
   static constexpr int kLdsB = NS * kStageB > kOutB ? NS * kStageB : kOutB;
 };
+}  // namespace
 
 template <int TM, int TN, int WM, int WN, int KH, int NS, int OCC>
 __global__ __launch_bounds__(kGThreads, OCC) void bf16_gemm_kernel(

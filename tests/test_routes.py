@@ -264,3 +264,20 @@ def test_every_attention_kernel_has_gpu_tests_in_each_head_dimension():
         for r in (1, 2, 3, 4, KEY_GROUPS, FEW_ROWS, F32_FEW_ROWS, F32_TWO_TILES, F32_WAVES8):
             assert len(seen.get((r, d), [])) >= (1 if r in (3, 12) else 2), (r, d, seen.get((r, d)))
     assert seen[F32_WAVES16, 64] and seen[F32_WAVES4, 128]
+
+
+def test_types_of_one_name_stay_in_one_source():
+    """Every source is a translation unit of namespace rf: a type that two of them define has to be in an unnamed
+    namespace (one definition rule)."""
+    import glob
+    import os
+    import re
+    where = {}
+    for path in sorted(glob.glob(os.path.join(os.path.dirname(B.__file__), "csrc", "*.hip"))):
+        unnamed = False
+        for line in open(path):
+            unnamed = line.startswith("namespace {") or (unnamed and not line.startswith("}  // namespace"))
+            m = re.match(r"(?:struct|class|enum class)\s+(\w+)\s*[{:]", line)
+            if m and not unnamed:
+                where.setdefault(m.group(1), []).append(os.path.basename(path))
+    assert where and all(len(files) == 1 for files in where.values()), where
