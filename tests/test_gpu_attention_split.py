@@ -74,6 +74,46 @@ def test_attention_split_scales(rf, case, scale):  # noqa: F811
     check(o, O.attention(q, k, v, scale, case[6]), "bf16", f"attention split {case} scale {scale}")
 
 
+@pytest.mark.parametrize("case", [(1, 8, 8, 5, 5000, 64, False), (1, 1, 1, 1598, 5977, 64, True), (1, 4, 4, 3, 4065, 128, False)])
+def test_attention_split_infinities_and_nan(rf, case):  # noqa: F811
+    """What is no number stays where fp64 has it: a query of NaN in its row; values of NaN or infinity in their column of
+    the rows that see the key; a score of +inf in its row, one of -inf nowhere."""
+    Bt, Hq, Hkv, Lq, Lk, d, causal = case
+    assert _chunks(case) >= 2
+    say(f"attention split {case}: infinities and NaN")
+    q, k, v = (I.to_torch(a, "bf16", DEV) for a in _inputs(case, I.SEED_BASE + 99))
+    sc, inf, nan = I.default_scale(d), float("inf"), float("nan")
+    clean = rf.rf_cascade_attention(q, k, v, sc, causal)
+    q[:, 0, Lq - 1, 3] = nan
+    v[:, 0, 7, 5], v[:, 0, Lk // 2, 9] = nan, inf
+    if Hkv > 2:                                           # scores of either infinity, in heads of their own
+        q[:, 1, :, 0], q[:, 2, :, 0] = 1.0, 1.0
+        k[:, 1, Lk // 3, 0], k[:, 2, Lk // 3, 0] = inf, -inf
+    o = rf.rf_cascade_attention(q, k, v, sc, causal)
+    torch.cuda.synchronize()
+    qd, kd, vd = (t.double().cpu() for t in (q, k, v))
+    kd, vd = (t.repeat_interleave(Hq // Hkv, 1) for t in (kd, vd))
+    p = qd @ kd.transpose(2, 3).contiguous() * sc
+    if causal:
+        p.masked_fill_(torch.ones(Lq, Lk).triu(Lk - Lq + 1).bool(), -inf)
+    p = torch.softmax(p, -1)
+    want = torch.matmul(p, vd)
+    # (0 times what is no number is none either, in the sum over the keys that a row sees not; the kernels skip those tiles)
+    hidden = [(key, col) for key, col in ((7, 5), (Lk // 2, 9))]
+    o, clean = o.double().cpu(), clean.double().cpu()
+    for key, col in hidden:
+        sees = torch.arange(Lq) + (Lk - Lq if causal else Lk) >= key
+        assert bool((~torch.isfinite(o[:, 0, sees, col])).all())
+    assert bool(torch.isnan(o[:, 0, Lq - 1]).all())
+    keep = [c for c in range(d) if c not in (5, 9)]
+    assert torch.equal(o[:, 0, :Lq - 1][..., keep], clean[:, 0, :Lq - 1][..., keep])
+    if Hkv > 2:
+        assert bool(torch.isnan(want[:, 1]).all()) and bool(torch.isnan(o[:, 1]).all())
+        assert bool(torch.isfinite(o[:, 2]).all())
+        assert float((o[:, 2] - want[:, 2]).norm() / want[:, 2].norm()) <= 1e-2
+        assert torch.equal(o[:, 3], clean[:, 3])
+
+
 def test_attention_split_workspace(rf):  # noqa: F811
     """The C entry point: sizes and alignment are checked, nothing is read before it is written; another stream and
     a graph whose workspace is handed out between replays give the same result."""

@@ -98,6 +98,23 @@ def test_rmsnorm_two_pass_against_one_launch(rf):  # noqa: F811
         del junk
 
 
+@pytest.mark.parametrize("shape", [(1201, 384, 12968), (1164, 960, 1488), (2651, 1792, 352), (857, 6016, 1032), (577, 9024, 1032)])
+def test_rmsnorm_two_pass_infinities_and_nan(rf, shape):  # noqa: F811
+    """A row with an infinity or a NaN gives NaN, as its scale is 0 or none; the others give what they gave without it."""
+    M, K, N = shape
+    assert rf.rf_diag_rmsnorm_gemm_ws_tile(M, K, N) != (0, 0)
+    say(f"rmsnorm_gemm two passes, infinities and NaN: M{M} K{K} N{N}")
+    x, g, w = _inputs(shape, I.SEED_BASE + 56)
+    clean = rf.rf_rmsnorm_gemm(x, g, w)
+    bad = [0, 7, M // 2, M - 1]
+    x[0, 5], x[7, K - 1], x[M // 2, K // 2], x[M - 1, 0] = float("inf"), float("nan"), float("-inf"), float("nan")
+    y = rf.rf_rmsnorm_gemm(x, g, w)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(y[bad]).all())
+    keep = [i for i in range(M) if i not in bad]
+    assert torch.equal(y[keep], clean[keep])
+
+
 def test_rmsnorm_rows_beyond_the_workspace_go_in_turns(rf):  # noqa: F811
     M, K, N = 20001, 4096, 520
     nbytes = B.load_library().rf_rmsnorm_gemm_workspace_bytes(M, K, N)
