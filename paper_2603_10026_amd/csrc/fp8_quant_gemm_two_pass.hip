@@ -491,6 +491,7 @@ struct GShape { int m, n; double launch, round, piece, full, second; };
 #define RF_SHAPE(I, P, L, R, S, F, W) {RF_SHAPE_OF P, L, R, S, F, W},
 constexpr GShape kGShapes[] = {RF_GTILES(RF_SHAPE)};
 constexpr int kPadRows = 256;  // the codes hold whole tiles of rows
+constexpr int kMaxThreads = 512;  // of a workgroup
 
 double tile_us(const GShape& g, int M, int K, int N) {
   const double tiles = ceil((double)M / g.m) * ceil((double)N / g.n);
@@ -560,13 +561,13 @@ hipError_t launch_fp8_quant_gemm_two_pass(const void* a, const void* w, void* c,
   unsigned char* codes = (unsigned char*)workspace;
   const int pitch = (int)padded(slab);
   float* maxima = (float*)(codes + (int64_t)pitch * K);  // [tile of 128 k][row]
-  for (int r0 = 0; r0 < M; r0 += slab) {
-    const int rows = M - r0 < slab ? M - r0 : slab;
+  for (int64_t r0 = 0; r0 < M; r0 += slab) {
+    const int rows = (int)(M - r0 < slab ? M - r0 : slab);
     const int tile = best_tile(rows, K, N);
     const GShape g = kGShapes[tile];
     const int n_mt = (rows + g.m - 1) / g.m, n_nt = (N + g.n - 1) / g.n;
     // a grid of 2^32 threads or more is not launched whole
-    if ((int64_t)n_mt * n_nt >= ((int64_t)1 << 32) / kGThreads) return hipErrorInvalidValue;
+    if ((int64_t)n_mt * n_nt >= ((int64_t)1 << 32) / kMaxThreads) return hipErrorInvalidValue;
     launch_quant((const bf16_t*)a + r0 * lda, codes, maxima, rows, K, lda, pitch, s);
     bf16_t* cs = (bf16_t*)c + r0 * ldc;
 #define RF_GEMM_OF(TM, TN, WM, WN, WK, KH, NS, OCC) fp8_gemm_kernel<TM, TN, WM, WN, WK, KH, NS, OCC>

@@ -345,8 +345,8 @@ hipError_t launch_rmsnorm_gemm_two_pass(const void* x, const void* g, const void
   bf16_t* xg = (bf16_t*)workspace;
   float* row_scale = (float*)(xg + padded(slab) * K);
   const int nv = K / 8;
-  for (int r0 = 0; r0 < M; r0 += slab) {
-    const int rows = M - r0 < slab ? M - r0 : slab;
+  for (int64_t r0 = 0; r0 < M; r0 += slab) {
+    const int rows = (int)(M - r0 < slab ? M - r0 : slab);
     const int tile = best_tile(rows, K, N);
     const NShape sh = kNShapes[tile];
     const int n_mt = (rows + sh.m - 1) / sh.m, n_nt = (N + sh.n - 1) / sh.n;
