@@ -23,7 +23,7 @@
 // conflicts.  Two workgroups fit on a compute unit, so the softmax VALU work
 // of one overlaps the MFMA work of the other.
 //
-// The reference point m of the state is only advanced when a tile's row max
+// The reference point m of the state (but for SPLIT, below) is only advanced when a tile's row max
 // exceeds it by more than kTau (in log2 units): (m, l, acc) with any common
 // reference gives the same O = acc / l, exponentials stay below 2^kTau, and
 // the rescale of acc (the correction step of the incremental form) is skipped
@@ -68,7 +68,10 @@ __device__ __forceinline__ void wait_vmem_all() {
 // turn for the same NW / 2 * 32 query rows; their states are merged through LDS at the end.  For
 // launches that leave compute units idle: twice the workgroups, half the key tiles in each.
 // SPLIT: a workgroup takes one of n_chunks runs of chunk_tiles key tiles and writes its state, [row][chunk] with the
-// maximum in log2 units, for attention_bf16_sum_kernel.
+// maximum in log2 units, for attention_bf16_sum_kernel.  Its reference follows the maximum at every tile, as in the few-row
+// kernel that would serve most of these calls in one launch: the probability of every new maximum is then 1, which
+// bf16 holds exactly.  (With kTau the error against 64 bits was up to 3 % above that kernel's, 2 x 8 heads of 242 x 7136
+// 2.31e-3 against 2.24e-3, now 2.18e-3; 21.5 -> 22.4 us.)
 template <int D, int NW, bool PAIRED, int KG = 1, bool SPLIT = false>
 __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
@@ -434,7 +437,7 @@ __global__ __launch_bounds__(NW * kWave, NW == 4 ? 2 : 1) void attention_bf16_ke
       tmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     }
     const float tmax2 = tmax * scale_log2e;  // log2 units; scale > 0 keeps the order
-    if (__builtin_amdgcn_ballot_w64(tmax2 > m_ref + kTau) != 0) {
+    if (__builtin_amdgcn_ballot_w64(tmax2 > m_ref + (SPLIT ? 0.f : kTau)) != 0) {
       const float m_new = fmaxf(m_ref, tmax2);
       const float corr = (m_new == -INFINITY) ? 1.0f : fast_exp2(m_ref - m_new);
       m_ref = m_new;
@@ -699,11 +702,11 @@ AttnRoute attention_bf16_route(const AttnShape& a, const Strides4& sk, const Str
 // Chunks of keys that a call with a workspace is cut into (64 rows and two key groups per workgroup, the states
 // added up by a second launch); 0 where one launch serves it better.  Few rows before a long context leave most
 // compute units idle, or have each of them walk all keys behind the latency of memory: us one launch / split, 2 x 8 heads
-// of 242 x 7136, d = 64, 43.0 / 21.1; 8 heads of 1 x 8192, d = 128, 73.5 / 13.3; 2 x 4 of 1506 x 7356, causal, d = 64,
-// 69.5 / 47.1; 3 x 2 of 3111 x 4823, causal, d = 128, 102.0 / 85.9; but 3 x 8 of 109 x 1115, causal, d = 128,
-// 14.9 / 16.0; 2 x 8 of 1097 x 2467, causal, d = 64, 28.5 / 29.3.  The figures are fitted to 422 cuts of 100 random
-// calls (4 % off on average, 19 % at most); of those, 39 are split by this rule, and are 2.0 times faster for it, the
-// least 1.2.  (3.5: what a second launch adds to a call that is waited for.)
+// of 242 x 7136, d = 64, 40.3 / 22.9; 8 heads of 1 x 8192, d = 128, 73.0 / 12.6; 2 x 4 of 1506 x 7356, causal, d = 64,
+// 66.1 / 52.4; but 3 x 8 of 109 x 1115, causal, d = 128, 14.9 / 16.0; 2 x 8 of 1097 x 2467, causal, d = 64, 28.5 / 29.3.
+// The figures are fitted to 422 cuts of 100 random calls (4 % off on average, 19 % at most; with a reference that lags
+// behind the rows' maxima: following them takes 1.2 % more, 4 % at most).  64 random calls that this rule splits
+// are 2.02 times faster for it, the least 1.17.  (3.5: what a second launch adds to a call that is waited for.)
 int attention_bf16_chunks(const AttnShape& a, const Strides4& sk, const Strides4& sv) {
   // (no shorter context had anything to gain, and small calls should not wait for the arithmetic below)
   if (a.Lk < 1024) return 0;
