@@ -381,16 +381,18 @@ struct MoeTile {
   static_assert(kStages == 4, "three tiles in flight: the waits below");
 };
 
-// NA sums for a tile's eight steps of 16 k in turn, added up pairwise at the end, with 8 after every 16 tiles too: no
-// chain is longer than those of four wavefronts that share a tile's steps over a third of the axis.  One chain over a
+// NA sums for a tile's eight steps of 16 k in turn, added up pairwise at the end, with 8 after every `fold_tiles` tiles too:
+// no chain is longer than those of four wavefronts that share a tile's steps over a third of the axis.  One chain over a
 // slice is 0.3 us faster and its error against 64 bits larger, 2048 x 4096 x 128 3.7e-7 (here 2.0e-7), 6000 x 8192 x 128
-// 16e-7 (2.2e-7).  (Adding up costs some 0.5 us each time, so short slices make do with 4 sums.)  LDS is handed over by
-// the launch: with its size known the compiler would keep the sums in registers that the vector ALU does not reach.
-constexpr int kMoeFoldTiles = 16;
+// 16e-7 (2.2e-7).  Adding up costs some 0.3 us each time, so slices of up to 8 tiles make do with 4 sums, but for three or
+// fewer of more than 4 tiles, which leave little else to add up; up to 24 tiles are folded in even parts of up to 8, longer
+// ones every 16.  (4 sums up to 8 tiles and a fold every 16: 4000 x 1920 x 128 2.0e-7, here 1.7e-7, 12.0 -> 12.3 us;
+// 5000 x 2304 x 128 2.1e-7, here 1.7e-7, 17.6 -> 17.8.)  LDS is handed over by the launch: with its size known the
+// compiler would keep the sums in registers that the vector ALU does not reach.
 template <int E, int NA>
 __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, float* __restrict__ part, int S,
-    int n_kblocks, int64_t ldx, int64_t ldw) {
+    int n_kblocks, int64_t ldx, int64_t ldw, int fold_tiles) {
   using T = MoeTile<E>;
   constexpr int PPR = E / 8;                // 16-byte pieces of a row of w
   constexpr int kXLoads = T::kXB / 4096, kWLoads = T::kWB / 4096;  // direct-to-LDS loads per wavefront and tile
@@ -472,14 +474,15 @@ __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
     for (int h = NA / 2; h >= 1; h /= 2)
 #pragma unroll
       for (int c = 0; c < h; ++c) acc[c] += acc[c + h];
-    sum += acc[0];
+    if constexpr (NA == 8) sum += acc[0];
+    else sum = acc[0];  // (once, at the end)
   };
 
   // NS - 1 tiles are in flight; the one that follows them goes to the stage that the tile before this one left.
 #pragma unroll
   for (int t = 0; t < NS - 1; ++t)
     if (t < nb) request(t, t);
-  int stage = 0;
+  int stage = 0, left = fold_tiles;
   for (int blk = 0; blk < nb; ++blk) {
     // this tile has landed (loads retire in order: the younger tiles' may be in flight), and the reads of the
     // tile before are back; then both hold for every wavefront
@@ -490,6 +493,7 @@ __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
     asm volatile("" ::: "memory");
     if (blk + NS - 1 < nb) request(blk + NS - 1, stage == 0 ? NS - 1 : stage - 1);
     const uint32_t at = stage * T::kStageB;
+    stage = stage == NS - 1 ? 0 : stage + 1;
     u32x4 bx[8];
     s16x4 bw[8][2];
 #pragma unroll
@@ -505,8 +509,8 @@ __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
       acc[kk % NA] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, bx[kk]), __builtin_bit_cast(bf16x8, b),
                                                         acc[kk % NA], 0, 0, 0);
     }
-    stage = stage == NS - 1 ? 0 : stage + 1;
-    if (NA == 8 && blk % kMoeFoldTiles == kMoeFoldTiles - 1) {
+    if (NA == 8 && --left == 0 && blk + 1 < nb) {
+      left = fold_tiles;
       fold();
 #pragma unroll
       for (int c = 0; c < NA; ++c) clear(acc[c]);
@@ -936,10 +940,12 @@ hipError_t launch_moe_routing(const void* x, const void* w, int S, int hd, int E
 #undef RF_MOE_FUSED
     return hipGetLastError();
   }
-  const bool long_slices = (n_kblocks + KS - 1) / KS > 8;
+  // (see moe_scores_kernel)
+  const int tiles = (n_kblocks + KS - 1) / KS, parts = (tiles + 7) / 8, fold_tiles = tiles <= 24 ? (tiles + parts - 1) / parts : 16;
+  const bool long_slices = tiles > (KS <= 3 ? 4 : 8);
 #define RF_MOE_SCORES_NA(EE, NA)                                                                                  \
   hipLaunchKernelGGL((moe_scores_kernel<EE, NA>), dim3((unsigned)((S + MoeTile<EE>::kTokens - 1) / MoeTile<EE>::kTokens), (unsigned)KS), \
-                     dim3(kMoeThreads), MoeTile<EE>::kStages * MoeTile<EE>::kStageB, s, xb, wb, part, S, n_kblocks, ldx, ldw)
+                     dim3(kMoeThreads), MoeTile<EE>::kStages * MoeTile<EE>::kStageB, s, xb, wb, part, S, n_kblocks, ldx, ldw, fold_tiles)
 #define RF_MOE_SCORES(EE)                    \
   if (long_slices) RF_MOE_SCORES_NA(EE, 8); \
   else RF_MOE_SCORES_NA(EE, 4)
