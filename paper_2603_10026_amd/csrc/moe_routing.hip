@@ -423,6 +423,9 @@ __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
     const int piece = (p % PPR) ^ fWm<PPR>(krow);
     w_off[e] = (uint32_t)(((int64_t)krow * ldw + 8 * piece) * 2);
   }
+  // Where a wavefront loads the rows of x that it multiplies (one column of experts), those past the end are left out with
+  // all that is done on them.  us: 1 x 1152 x 32 4.79 -> 4.69, 32 x 4096 x 32 5.99 -> 5.72.
+  const bool idle = T::kWaveE == 1 && row0 + 32 * wave >= S;
   auto request = [&](int blk, int stage) {  // tile b0 + blk
     const int b = b0 + blk;
     const char* xt = reinterpret_cast<const char*>(x) + (int64_t)b * kMoeKB * 2;
@@ -430,6 +433,7 @@ __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
 #pragma unroll
     for (int e = 0; e < kLoads; ++e) {
       const bool tok = e < kXLoads;
+      if (tok && idle) continue;
       const uint32_t dst = lds_base + stage * T::kStageB +
                            (tok ? (kXLoads * wave + e) * 1024 : T::kXB + (kWLoads * wave + e - kXLoads) * 1024);
       const uint32_t off = tok ? x_off[tok ? e : 0] : w_off[tok ? 0 : e - kXLoads];
@@ -486,14 +490,17 @@ __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
   for (int blk = 0; blk < nb; ++blk) {
     // this tile has landed (loads retire in order: the younger tiles' may be in flight), and the reads of the
     // tile before are back; then both hold for every wavefront
-    if (blk + 2 < nb) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads) : "memory");
-    else if (blk + 1 < nb) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kLoads) : "memory");
+    if (blk + 2 < nb && !idle) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kLoads) : "memory");
+    else if (blk + 2 < nb) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * kWLoads) : "memory");
+    else if (blk + 1 < nb && !idle) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kLoads) : "memory");
+    else if (blk + 1 < nb) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kWLoads) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (blk + NS - 1 < nb) request(blk + NS - 1, stage == 0 ? NS - 1 : stage - 1);
     const uint32_t at = stage * T::kStageB;
     stage = stage == NS - 1 ? 0 : stage + 1;
+    if (idle) continue;
     u32x4 bx[8];
     s16x4 bw[8][2];
 #pragma unroll
@@ -516,6 +523,7 @@ __global__ __launch_bounds__(kMoeThreads, 2) void moe_scores_kernel(
       for (int c = 0; c < NA; ++c) clear(acc[c]);
     }
   }
+  if (idle) return;
   fold();
 
   // A register is one token's 32 experts over 32 lanes: 128 contiguous bytes.

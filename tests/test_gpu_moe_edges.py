@@ -169,3 +169,22 @@ def test_moe_routing_error_of_a_few_slices(rf, S, hd, E, error):  # noqa: F811
         off.append(float((prob.double() - want).norm() / want.norm()))
     print(f"        {off}", flush=True)
     assert sum(off) / 3 <= error
+
+
+@pytest.mark.parametrize("hd", [1152, 3072, 4096, 8192])
+@pytest.mark.parametrize("S", [1, 31, 32, 33, 64, 65, 97, 128, 129, 225])
+def test_moe_routing_wavefronts_without_tokens(rf, S, hd):  # noqa: F811
+    """32 experts: a workgroup's four wavefronts take 32 tokens each, and those past the end take none; slices of one
+    and of several tiles.  Scores against fp64 (sums of hd products, 2^-24 each and a few), guard rows untouched."""
+    say(f"moe_routing 32 experts, S{S} hd{hd}")
+    x, w = I.moe_routing_inputs_device(11 + S, S, hd, 32, device=DEV)
+    ws = torch.full((rf.moe_routing_workspace_bytes(S, hd, 32) // 4 + 64,), float("nan"), device=DEV)
+    prob = torch.full((S + 1, 8), float("nan"), device=DEV)
+    idx = torch.full((S + 1, 8), -7, dtype=torch.int32, device=DEV)
+    rf.rf_moe_routing(x, w, 8, prob=prob[:S], idx=idx[:S], workspace=ws[:-64].view(torch.uint8))
+    torch.cuda.synchronize()
+    want = torch.softmax(x.double() @ w.double(), 1)
+    top = want.topk(8, 1).values
+    assert float((prob[:S].double() - top).abs().max()) <= 4e-6 * float(top.max())
+    assert float((want.gather(1, idx[:S].long()) - top).abs().max()) <= 4e-6 * float(top.max())
+    assert bool(torch.isnan(prob[S]).all()) and bool((idx[S] == -7).all()) and bool(torch.isnan(ws[-64:]).all())
